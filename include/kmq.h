@@ -317,7 +317,7 @@ kmq_status kmq_quantize_rows(const uint16_t* Wdense, int64_t N, int64_t K, int b
  *   Wdense    N x K bf16, row-major, 16-byte aligned for this call
  *   packed    N * K * bits / 32 words out; codebook 2^bits bf16 out; scales N x K/KMQ_BLOCK bf16 out
  *   workspace device memory of kmq_quantize_blockscaled_workspace_bytes() bytes, 8-byte aligned
- *             (partial sums of the clustering rounds; contents undefined before and after)
+ *             (25 MB: counters of the tensor's distinct values and their sums; contents undefined before and after)
  * K % KMQ_BLOCK != 0 -> KMQ_ERR_SHAPE; workspace NULL or too small -> KMQ_ERR_WORKSPACE. */
 size_t kmq_quantize_blockscaled_workspace_bytes(void);
 kmq_status kmq_quantize_blockscaled(const uint16_t* Wdense, int64_t N, int64_t K, int bits, int iters,

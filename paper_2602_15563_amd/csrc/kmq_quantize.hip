@@ -13,13 +13,14 @@
 //   * the stored codebook is the centroids rounded to bf16 (nearest even) and the indices
 //     are nearest STORED centroids.
 //
-// Sums of a cluster's members are formed per lane, then over a wave's lanes, then over
-// waves (and workgroups) in a fixed order: deterministic, and exact whenever the members'
-// exponents span fewer than 53 - log2(count) bits (always so for rows of bf16 weights of
-// one layer), in which case the result does not depend on the order at all.
+// Both quantisers replace "every element against every boundary, each round" by counts over the few distinct values
+// there are, taken once (the comments at the kernels).  Sums of members are deterministic, and exact whenever the
+// members' exponents span fewer than 53 - log2(count) bits (always so for rows of bf16 weights of one layer).
 //
 // Compiled with floating-point contraction off: the arithmetic is specified operation by
 // operation.
+#include <cstddef>
+
 #include "kmq_device.h"
 #include "kmq_launch.h"
 
@@ -143,6 +144,13 @@ typedef u32x4_t __attribute__((aligned(2))) u32x4_a2_t;
 typedef __attribute__((ext_vector_type(2))) unsigned short u16x2_t;
 typedef __attribute__((ext_vector_type(2))) short i16x2_t;
 
+// all ones in the halves that are negative (as assembly: the compiler takes vector shifts by 15 apart into compares)
+__device__ __forceinline__ uint32_t sign_masks(uint32_t v) {
+    uint32_t r;
+    asm("v_pk_ashrrev_i16 %0, 15, %1 op_sel_hi:[0,1]" : "=v"(r) : "v"(v));
+    return r;
+}
+
 __device__ __forceinline__ uint32_t udot2(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b), c, false);
 }
@@ -235,11 +243,9 @@ __global__ __launch_bounds__(256, NI == 4 ? 6 : 8) void quantize_rows_hist_kerne
     auto range_of = [&](const uint32_t (&v)[8]) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const i16x2_t h = __builtin_bit_cast(i16x2_t, v[i]);
             const u16x2_t mag = __builtin_bit_cast(u16x2_t, v[i] & 0x7FFF7FFFu);
             mn2 = __builtin_elementwise_min(mn2, static_cast<u16x2_t>(mag - u16x2_t{1, 1}));
-            const i16x2_t sg = h >> i16x2_t{15, 15};
-            const i16x2_t key = __builtin_bit_cast(i16x2_t, v[i] ^ (__builtin_bit_cast(uint32_t, sg) & 0x7FFF7FFFu));
+            const i16x2_t key = __builtin_bit_cast(i16x2_t, v[i] ^ (sign_masks(v[i]) & 0x7FFF7FFFu));
             lo2 = __builtin_elementwise_min(lo2, key);
             hi2 = __builtin_elementwise_max(hi2, key);
         }
@@ -597,110 +603,518 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __re
 }
 
 // ---- the paper's format: scale per 64-element block, one codebook per tensor -------------------------
-constexpr int kQuantPartials = 1024;   // workgroups of a clustering pass = partial sums per cluster
+// A normalised weight is w / scale, and the quotient of two bf16 values depends only on the scale's mantissa (128 of
+// them), the weight's mantissa, the distance of the exponents and the sign.  So the tensor's N*K quotients are counted
+// once, per scale mantissa, over the 32 octaves below the scale, in ascending order: 128 x 8192 counters, which carry
+// everything a Lloyd round asks for.  The steps:
+//   scales   largest magnitude of every block; blocks counted per scale mantissa
+//   group    block numbers sorted by scale mantissa (kept in the output's index words until those are written)
+//   count    a workgroup takes a run of that list, counts its elements in LDS and adds the counts to the tensor's
+//   prefix   per scale mantissa: number and sum of the members below every value
+//   rounds   one workgroup, all rounds: per (boundary, scale mantissa) one look-up in the prefix arrays
+//   assign   every element against its scale mantissa's boundaries, as 16-bit integers
+// A sum over members of one scale mantissa is a sum of weights (integers in the window's unit: exact in fp64 up to 2^53)
+// divided once by the scale's mantissa.  A boundary b stands for the exact test fl(w / scale) > b: where b * scale comes
+// within a few units in the last place of a weight, the division itself decides.
+// Elements more than 31 octaves below their scale ("far", next to none in any trained tensor) are counted apart per sign;
+// a round whose result could depend on their values looks them up in the tensor again.
+//
+// 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits: 149 / 166 / 182 / 221 us (8519 / 9344 / 10727 / 13475 with every element
+// divided by its scale and compared with every boundary in fp64, each round); 1024 x 1024: 74 / 90 / 100 / 131 (3212 ..
+// 3570).  At 8192 x 8192 and 4 bits: clear 5, scales 29 (4.6 TB/s), group 12, count 43 (blocks gathered 128 bytes at a
+// time, LDS atomics), prefix 11, rounds 80 (2.6 us each: one CU's issue and its scattered line fetches), assign 45 us.
+constexpr int kQuantMants = 128, kQuantBins = 2 * kHistMags, kQuantStride = kQuantBins + 1;
+constexpr double kFar = 4.656612873077393e-10;           // 2^-31: no far element reaches it
 
-struct QuantScratch {                  // layout of the caller's workspace
-    double cent[16];
-    double psum[kQuantPartials][16];
-    long long pcnt[kQuantPartials][16];
+struct BelowBin {                                        // what lies below a bin
+    double count;                                        // members (exact: at most 2^38)
+    double sum;                                          // ... and their sum, in units of 2^-31 / (128 + scale mantissa)
+};
+struct QuantScratch {                                    // layout of the caller's workspace; everything down to `exact_assign` starts as zeros
+    unsigned long long members[kQuantMants][kQuantBins];
+    unsigned long long blocks[kQuantMants];              // blocks per scale mantissa
+    unsigned long long cursor[kQuantMants];              // ... of them placed so far
+    unsigned long long zeros, far_neg, far_pos;
+    unsigned long long exact_assign;                     // a stored boundary lies among the far elements
+    BelowBin below[kQuantMants][kQuantStride];           // (side by side: a round's look-ups are scattered, a line each)
+    uint32_t above[kQuantMants][16];                     // per stored boundary: largest element key at or below it, in both halves
 };
 
-// scale = largest magnitude of the block (bf16 magnitudes order like their bit patterns); wave per block
+__global__ __launch_bounds__(256) void bs_clear_kernel(QuantScratch* q) {
+    typedef u32x4_t __attribute__((aligned(8))) u32x4_a8_t;
+    constexpr size_t n16 = offsetof(QuantScratch, below) / 16;
+    static_assert(offsetof(QuantScratch, below) % 16 == 0, "cleared in 16-byte pieces");
+    for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < n16; i += static_cast<size_t>(gridDim.x) * 256)
+        reinterpret_cast<u32x4_a8_t*>(q)[i] = u32x4_t{0, 0, 0, 0};
+}
+
+// Scales below 2^-95 put part of the window into bf16's subnormal range, where patterns are not spaced by exponents:
+// scale and weights are multiplied by 2^64 first (exact; the quotients stay the same).
+constexpr uint32_t kSmallScale = 32u << 7;
+__device__ __forceinline__ uint32_t lifted(uint32_t h) { return __float_as_uint(__uint_as_float(h << 16) * 1.8446744073709552e19f) >> 16; }
+__device__ __forceinline__ uint32_t scale_pattern(uint32_t scale) { return scale < kSmallScale ? lifted(scale) : scale; }
+__device__ __forceinline__ void lift_pairs(u32x4_t& v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = lifted(v[i] & 0xFFFFu) | (lifted(v[i] >> 16) << 16);
+}
+
+// Magnitude keys of two elements against the block's scale: 0 zero, 1 far, 2 + window position.
+__device__ __forceinline__ u16x2_t magnitude_keys(uint32_t pair, uint32_t scale_pat) {
+    const uint32_t base = (scale_pat & 0x7F80u) - ((kHistOctaves - 1) << 7);
+    const u16x2_t mag = __builtin_bit_cast(u16x2_t, pair & 0x7FFF7FFFu);
+    const u16x2_t k = __builtin_elementwise_max(mag, __builtin_bit_cast(u16x2_t, (base - 1) * 0x00010001u)) - __builtin_bit_cast(u16x2_t, (base - 2) * 0x00010001u);
+    return __builtin_elementwise_min(k, mag);
+}
+
+// largest magnitude of the block that eight neighbouring lanes hold (16 bytes each), in each of them
+__device__ __forceinline__ uint32_t block_scale(const u32x4_t& v) {
+    const auto mags = [](uint32_t d) { return __builtin_bit_cast(u16x2_t, d & 0x7FFF7FFFu); };
+    const u16x2_t m = __builtin_elementwise_max(__builtin_elementwise_max(mags(v[0]), mags(v[1])), __builtin_elementwise_max(mags(v[2]), mags(v[3])));
+    uint32_t s = m[0] > m[1] ? m[0] : m[1];
+    auto step = [&](uint32_t o) { s = o > s ? o : s; };
+    step(__builtin_amdgcn_update_dpp(0, s, 0xB1, 0xF, 0xF, true));         // quad_perm [1,0,3,2]
+    step(__builtin_amdgcn_update_dpp(0, s, 0x4E, 0xF, 0xF, true));         // quad_perm [2,3,0,1]
+    step(__builtin_amdgcn_update_dpp(0, s, 0x141, 0xF, 0xF, true));        // row_half_mirror
+    return s;
+}
+
 __global__ __launch_bounds__(256) void bs_scales_kernel(const uint16_t* __restrict__ W, int64_t nblocks,
-                                                        uint16_t* __restrict__ scales, QuantScratch* q, int C) {
-    const int lane = threadIdx.x & 63;
-    const int64_t blk = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    if (blockIdx.x == 0 && threadIdx.x < C) q->cent[threadIdx.x] = -1.0 + (2 * static_cast<int>(threadIdx.x) + 1) / static_cast<double>(C);
-    if (blk >= nblocks) return;
-    int mag = W[blk * KMQ_BLOCK + lane] & 0x7FFF;
+                                                        uint16_t* __restrict__ scales, QuantScratch* q) {
+    __shared__ uint32_t cnt[kQuantMants];
+    if (threadIdx.x < kQuantMants) cnt[threadIdx.x] = 0;
+    __syncthreads();
+    // eight lanes per block, four blocks of 32 per workgroup and turn
+    const int64_t step = static_cast<int64_t>(gridDim.x) * 128;
+    for (int64_t b0 = static_cast<int64_t>(blockIdx.x) * 128 + (threadIdx.x >> 3); b0 < nblocks; b0 += step) {
+        u32x4_t v[4];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const int o = __shfl_xor(mag, off, 64);
-        mag = o > mag ? o : mag;
-    }
-    if (lane == 0) scales[blk] = static_cast<uint16_t>(mag);
-}
-
-__device__ __forceinline__ double normalised(uint32_t w, uint32_t scale) {
-    const double s = bf16_to_f64(scale);
-    return s > 0.0 ? bf16_to_f64(w) / s : 0.0;
-}
-
-// one clustering round, first half: every workgroup sums the members of each cluster over its blocks
-template <int BITS>
-__global__ __launch_bounds__(256) void bs_lloyd_pass_kernel(const uint16_t* __restrict__ W,
-                                                            const uint16_t* __restrict__ scales, int64_t nblocks,
-                                                            QuantScratch* q) {
-    constexpr int C = 1 << BITS;
-    __shared__ double ps[4][C];
-    __shared__ long long pn[4][C];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    double c[C];
+        for (int i = 0; i < 4; ++i) {
+            const int64_t blk = b0 + i * 32 < nblocks ? b0 + i * 32 : nblocks - 1;
+            v[i] = *reinterpret_cast<const u32x4_t*>(W + blk * KMQ_BLOCK + (threadIdx.x & 7) * 8);
+        }
 #pragma unroll
-    for (int j = 0; j < C; ++j) c[j] = q->cent[j];
-    Clusters<C> cl;
-    cl.begin(c);
-    // a lane takes 8 consecutive elements (one 16-byte load; eight lanes share a block's scale), a wave 8 blocks
-    const int64_t nchunks = nblocks * (KMQ_BLOCK / 8);
-    for (int64_t c = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * kWave + lane; c < nchunks;
-         c += static_cast<int64_t>(gridDim.x) * 4 * kWave) {
-        const u32x4_t w8 = *reinterpret_cast<const u32x4_t*>(W + c * 8);
-        const uint32_t scale = scales[c >> 3];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            cl.add(normalised(w8[e] & 0xFFFFu, scale));
-            cl.add(normalised(w8[e] >> 16, scale));
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t s = block_scale(v[i]);
+            if ((threadIdx.x & 7) == 0 && b0 + i * 32 < nblocks) {
+                scales[b0 + i * 32] = static_cast<uint16_t>(s);
+                atomicAdd(&cnt[scale_pattern(s) & 127u], 1u);
+            }
         }
     }
+    __syncthreads();
+    if (threadIdx.x < kQuantMants && cnt[threadIdx.x]) atomicAdd(&q->blocks[threadIdx.x], static_cast<unsigned long long>(cnt[threadIdx.x]));
+}
+
+// First list position of every scale mantissa's blocks (start[128]: their number); by the workgroup's first wave,
+// valid behind the next barrier.
+__device__ __forceinline__ void list_starts(const QuantScratch* q, long long* start) {
+    if (threadIdx.x < 64) {
+        const int t = threadIdx.x;
+        const long long a = static_cast<long long>(q->blocks[2 * t]), b = static_cast<long long>(q->blocks[2 * t + 1]);
+        long long incl = a + b;
+        uint32_t unused = 0;
+        wave_scan(incl, unused);
+        start[2 * t] = incl - a - b;
+        start[2 * t + 1] = incl - b;
+        if (t == 63) start[kQuantMants] = incl;
+    }
+}
+
+constexpr int kGroupThreads = 1024, kGroupBlocks = 8192;   // blocks per workgroup of the grouping step (few: every one adds to 128 shared cursors)
+__global__ __launch_bounds__(kGroupThreads) void bs_group_kernel(const uint16_t* __restrict__ scales, int64_t nblocks, QuantScratch* q,
+                                                       uint32_t* __restrict__ list) {
+    __shared__ long long start[kQuantMants + 1];
+    __shared__ uint32_t cnt[kQuantMants];
+    __shared__ long long at[kQuantMants];
+    list_starts(q, start);
+    if (threadIdx.x < kQuantMants) cnt[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t b0 = static_cast<int64_t>(blockIdx.x) * kGroupBlocks + threadIdx.x;
+    uint32_t mant[kGroupBlocks / kGroupThreads], rank[kGroupBlocks / kGroupThreads];
 #pragma unroll
-    for (int j = 0; j < C; ++j) {
-        const double s = wave_sum(cl.s[j]);
-        const long long m = wave_sum(static_cast<long long>(cl.n[j]));
-        if (lane == 0) { ps[wave][j] = s; pn[wave][j] = m; }
+    for (int i = 0; i < kGroupBlocks / kGroupThreads; ++i)
+        if (b0 + i * kGroupThreads < nblocks) {
+            mant[i] = scale_pattern(scales[b0 + i * kGroupThreads]) & 127u;
+            rank[i] = atomicAdd(&cnt[mant[i]], 1u);
+        }
+    __syncthreads();
+    if (threadIdx.x < kQuantMants && cnt[threadIdx.x])
+        at[threadIdx.x] = start[threadIdx.x] + static_cast<long long>(atomicAdd(&q->cursor[threadIdx.x], static_cast<unsigned long long>(cnt[threadIdx.x])));
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kGroupBlocks / kGroupThreads; ++i)
+        if (b0 + i * kGroupThreads < nblocks) list[at[mant[i]] + rank[i]] = static_cast<uint32_t>(b0 + i * kGroupThreads);
+}
+
+// Every workgroup counts the elements of its run of the block list, in LDS: cell 2 * magnitude key + sign.
+constexpr int kCountThreads = 512, kCountCells = 2 * (kHistMags + 2);
+__global__ __launch_bounds__(kCountThreads) void bs_count_kernel(const uint16_t* __restrict__ W, const uint32_t* __restrict__ list,
+                                                                 int64_t nblocks, int64_t run, QuantScratch* q) {
+    __shared__ long long start[kQuantMants + 1];
+    __shared__ uint32_t cell[kCountCells];
+    const int tid = threadIdx.x;
+    list_starts(q, start);
+    for (int i = tid; i < kCountCells; i += kCountThreads) cell[i] = 0;
+    __syncthreads();
+    int64_t p = static_cast<int64_t>(blockIdx.x) * run;
+    const int64_t end = p + run < nblocks ? p + run : nblocks;
+    int mant = 0;
+    while (p < end) {
+        while (start[mant + 1] <= p) ++mant;              // (uniform; start[128] = nblocks > p)
+        const int64_t stop = start[mant + 1] < end ? start[mant + 1] : end;
+        // eight lanes per block, two blocks of 64 per turn in flight
+        for (int64_t t0 = p + (tid >> 3); t0 < stop; t0 += kCountThreads / 8 * 2) {
+            u32x4_t v[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int64_t t = t0 + i * (kCountThreads / 8);
+                v[i] = *reinterpret_cast<const u32x4_t*>(W + static_cast<int64_t>(list[t < stop ? t : t0]) * KMQ_BLOCK + (tid & 7) * 8);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                uint32_t s = block_scale(v[i]);
+                if (t0 + i * (kCountThreads / 8) >= stop) continue;
+                if (s < kSmallScale) { s = lifted(s); lift_pairs(v[i]); }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t d = v[i][j];           // (a vector element itself must not go into a bit cast: it reads element 0)
+                    const u16x2_t c = magnitude_keys(d, s) * u16x2_t{2, 2} + (__builtin_bit_cast(u16x2_t, d) >> u16x2_t{15, 15});
+                    atomicAdd(&cell[c[0]], 1u);
+                    atomicAdd(&cell[c[1]], 1u);
+                }
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < kCountCells; i += kCountThreads) {
+            const int sign = i >= kCountCells / 2, key = i - sign * (kCountCells / 2);      // neighbouring threads, neighbouring counters
+            const unsigned long long c = cell[2 * key + sign];
+            if (c == 0) continue;
+            cell[2 * key + sign] = 0;
+            unsigned long long* const to = key >= 2 ? &q->members[mant][sign ? kHistMags - 1 - (key - 2) : kHistMags + (key - 2)]
+                                         : key == 1 ? (sign ? &q->far_neg : &q->far_pos) : &q->zeros;
+            atomicAdd(to, c);
+        }
+        __syncthreads();
+        p = stop;
+    }
+}
+
+// counters -> members below (number and sum), one workgroup per scale mantissa, 8 bins per thread
+__global__ __launch_bounds__(1024) void bs_prefix_kernel(QuantScratch* q) {
+    constexpr int PER = kQuantBins / 1024;
+    __shared__ long long wn[16];
+    __shared__ double ws[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const unsigned long long* const n = q->members[blockIdx.x] + tid * PER;
+    BelowBin* const bin = q->below[blockIdx.x] + tid * PER;
+    const bool pos = tid >= 512;
+    const int mi0 = pos ? (tid - 512) * PER : kHistMags - 1 - tid * PER;             // magnitude of the first bin; then rising / falling
+    const double unit = static_cast<double>(1ull << (mi0 >> 7)) * (pos ? 1.0 : -1.0);
+    const int m0 = 128 + (mi0 & 127), dm = pos ? 1 : -1;
+    uint64_t c[PER];
+    long long tn = 0, tm = 0;                             // members, sum of their mantissas
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        c[i] = n[i];
+        tn += static_cast<long long>(c[i]);
+        tm += static_cast<long long>(c[i]) * (m0 + dm * i);
+    }
+    const double ts = static_cast<double>(tm) * unit;
+    long long in = tn;
+    double is = ts;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const long long pn = __shfl_up(in, off, 64);
+        const double ps = __shfl_up(is, off, 64);
+        if (lane >= off) { in += pn; is += ps; }
+    }
+    if (lane == 63) { wn[wave] = in; ws[wave] = is; }
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) { in += wn[w]; is += ws[w]; }
+    in -= tn;
+    is -= ts;
+    tm = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        bin[i] = BelowBin{static_cast<double>(in), is + static_cast<double>(tm) * unit};
+        in += static_cast<long long>(c[i]);
+        tm += static_cast<long long>(c[i]) * (m0 + dm * i);
+    }
+    if (tid == 1023) bin[PER] = BelowBin{static_cast<double>(in), is + static_cast<double>(tm) * unit};
+}
+
+// Window magnitudes g = mantissa * 2^octave (units of 2^-31 / (128 + scale mantissa)) with fl(g / scale) <= a (STRICT: < a).
+template <bool STRICT>
+__device__ __forceinline__ int magnitudes_within(double a, double scale) {
+    const double x = a * scale;                           // within one unit in the last place of the exact product
+    const uint64_t u = static_cast<uint64_t>(__double_as_longlong(x));
+    int mi = static_cast<int>(static_cast<uint32_t>(u >> 32) >> 13) - ((1023 + 7) << 7);   // largest magnitude <= x (below 0: none)
+    const uint64_t r = u + 8;
+    if ((static_cast<uint32_t>(r >> 32) & 0x1FFFu) == 0 && static_cast<uint32_t>(r) < 16) {
+        mi = static_cast<int>(static_cast<uint32_t>(r >> 32) >> 13) - ((1023 + 7) << 7);   // the magnitude that x is next to
+        if (mi >= 0 && mi < kHistMags) {
+            const double quot = static_cast<double>(static_cast<uint64_t>(128 + (mi & 127)) << (mi >> 7)) / scale;
+            if (!(STRICT ? quot < a : quot <= a)) --mi;
+        }
+    }
+    return mi < -1 ? 0 : mi >= kHistMags ? kHistMags : mi + 1;
+}
+
+// Sum over the wave, in every lane: DPP adds within and across rows of 16, then lane 63's value.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const uint64_t u = static_cast<uint64_t>(__double_as_longlong(v));
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<uint32_t>(u), CTRL, ROWS, 0xF, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<uint32_t>(u >> 32), CTRL, ROWS, 0xF, false);
+    return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
+}
+__device__ __forceinline__ double wave_total(double v) {
+    v += dpp_f64<0x111, 0xF>(v);
+    v += dpp_f64<0x112, 0xF>(v);
+    v += dpp_f64<0x114, 0xF>(v);
+    v += dpp_f64<0x118, 0xF>(v);
+    v += dpp_f64<0x142, 0xA>(v);
+    v += dpp_f64<0x143, 0xC>(v);
+    const uint64_t u = static_cast<uint64_t>(__double_as_longlong(v));
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(u), 63), hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(u >> 32), 63);
+    return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
+}
+// a value that is the same in every lane, for the scalar unit
+__device__ __forceinline__ double uniform(double v) {
+    const uint64_t u = static_cast<uint64_t>(__double_as_longlong(v));
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u)), hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u >> 32));
+    return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
+}
+
+// Number and sum of the far elements in (lo, hi], from the tensor; by the whole workgroup, in a fixed order.
+__device__ __forceinline__ void far_members(const uint16_t* W, const uint16_t* scales, int64_t nblocks, double lo, double hi,
+                                            double* ws, long long* wn, double* sum, long long* num) {
+    double s = 0.0;
+    long long n = 0;
+    for (int64_t blk = threadIdx.x >> 3; blk < nblocks; blk += blockDim.x >> 3) {
+        const double scale = bf16_to_f64(scales[blk]);
+        const uint32_t sp = scale_pattern(scales[blk]);
+        u32x4_t v = *reinterpret_cast<const u32x4_t*>(W + blk * KMQ_BLOCK + (threadIdx.x & 7) * 8), l = v;
+        if (scales[blk] < kSmallScale) lift_pairs(l);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const u16x2_t k = magnitude_keys(l[j], sp);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (k[h] != 1) continue;
+                const double quot = bf16_to_f64(h ? v[j] >> 16 : v[j] & 0xFFFFu) / scale;
+                if (quot > lo && quot <= hi) { s += quot; ++n; }
+            }
+        }
+    }
+    s = wave_sum(s);
+    n = wave_sum(n);
+    if ((threadIdx.x & 63) == 0) { ws[threadIdx.x >> 6] = s; wn[threadIdx.x >> 6] = n; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        s = 0.0;
+        n = 0;
+        for (unsigned w = 0; w < blockDim.x / 64; ++w) { s += ws[w]; n += wn[w]; }
+        *sum = s;
+        *num = n;
     }
     __syncthreads();
-    if (tid < C) {
-        q->psum[blockIdx.x][tid] = ((ps[0][tid] + ps[1][tid]) + ps[2][tid]) + ps[3][tid];
-        q->pcnt[blockIdx.x][tid] = pn[0][tid] + pn[1][tid] + pn[2][tid] + pn[3][tid];
+}
+
+// All rounds: wave i takes boundary i and cluster i, a lane scale mantissas `lane` and `lane + 64`.  Numbers of members
+// are kept as doubles (exact: at most 2^38).
+template <int BITS>
+__global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratch* q, const uint16_t* __restrict__ W,
+                                                                     const uint16_t* __restrict__ scales, int64_t nblocks, int iters,
+                                                                     uint16_t* __restrict__ codebook) {
+    constexpr int C = 1 << BITS;
+    __shared__ double cs[C];
+    __shared__ double bn[C][kQuantMants];                 // members below boundary i (i = C - 1: all), per scale mantissa
+    __shared__ double bsum[C][kQuantMants];
+    __shared__ double farsum[C], fw[C];
+    __shared__ long long farnum[C], fn[C];
+    __shared__ int moved, unsure;
+    const int i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const double far_neg = static_cast<double>(q->far_neg), far_pos = static_cast<double>(q->far_pos), zeros = static_cast<double>(q->zeros);
+    const bool any_far = far_neg + far_pos > 0.0;
+    double scale[2], inv[2];                              // of this lane's two mantissas, in the window's unit
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        scale[h] = static_cast<double>(static_cast<uint64_t>(128 + lane + 64 * h) << (kHistOctaves - 1));
+        inv[h] = 1.0 / scale[h];
+        const BelowBin all = q->below[lane + 64 * h][kQuantBins];
+        bn[C - 1][lane + 64 * h] = all.count;             // (every wave the same)
+        bsum[C - 1][lane + 64 * h] = all.sum;
+    }
+    if (threadIdx.x < C) cs[threadIdx.x] = -1.0 + (2 * static_cast<int>(threadIdx.x) + 1) / static_cast<double>(C);
+    if (threadIdx.x == 0) { moved = 0; unsure = 0; }
+    __syncthreads();
+    auto boundary = [&](int j) { return uniform(0.5 * (cs[j] + cs[j + 1])); };
+    auto below_of = [&](double b, int h) {
+        return b < 0.0 ? kHistMags - magnitudes_within<true>(-b, scale[h]) : kHistMags + magnitudes_within<false>(b, scale[h]);
+    };
+    auto far_below = [&](double b) { return b >= kFar ? far_neg + far_pos : b >= 0.0 ? far_neg : 0.0; };   // (b within +-kFar: see `unsure`)
+    auto zeros_below = [&](double b) { return b >= 0.0 ? zeros : 0.0; };
+    auto among_far = [&](double b) { return any_far && b != 0.0 && fabs(b) < kFar; };
+    int seen[2] = {-1, -1};
+    for (int t = 0; t < iters; ++t) {
+        const double b = i < C - 1 ? boundary(i) : 2.0, b0 = i > 0 ? boundary(i - 1) : -2.0;
+        if (i < C - 1) {
+            int now[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int below = below_of(b, h);
+                now[h] = below * 2 + (b < 0.0 ? 0 : 1);
+                if (now[h] != seen[h]) {                  // (a boundary soon moves past few of the bins: only those are fetched)
+                    const BelowBin at = q->below[lane + 64 * h][below];
+                    bn[i][lane + 64 * h] = at.count;
+                    bsum[i][lane + 64 * h] = at.sum;
+                }
+            }
+            if (now[0] != seen[0] || now[1] != seen[1] || among_far(b)) moved = 1;
+            if (among_far(b)) unsure = 1;
+            seen[0] = now[0];
+            seen[1] = now[1];
+        }
+        __syncthreads();
+        if (moved == 0) break;                            // every boundary where it was: a fixed point
+        double n = 0.0, s = 0.0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int m = lane + 64 * h;
+            n += bn[i][m] - (i > 0 ? bn[i - 1][m] : 0.0);
+            s += (bsum[i][m] - (i > 0 ? bsum[i - 1][m] : 0.0)) * inv[h];
+        }
+        n = wave_total(n);
+        s = wave_total(s);
+        const double nfar = far_below(b) - far_below(b0);
+        double nz = nfar + zeros_below(b) - zeros_below(b0);
+        if (any_far) {
+            if (lane == 0 && nfar > 0.0 && fabs(s) < nfar * 8192.0) unsure = 1;      // far members that would show in the mean
+            __syncthreads();
+            if (unsure) {                                 // (uniform; the far elements are looked up in the tensor)
+                for (int j = 0; j < C; ++j) {
+                    const double lo = j > 0 ? boundary(j - 1) : -2.0, hi = j < C - 1 ? boundary(j) : 2.0;
+                    if (lo < kFar && hi > -kFar) {
+                        far_members(W, scales, nblocks, lo, hi, fw, fn, &farsum[j], &farnum[j]);
+                    } else if (threadIdx.x == 0) {
+                        farsum[j] = 0.0;
+                        farnum[j] = 0;
+                    }
+                }
+                __syncthreads();
+                s += farsum[i];
+                nz += static_cast<double>(farnum[i]) - nfar;
+            }
+        }
+        n += nz;
+        const double c = s / n;
+        __syncthreads();                                  // boundaries and sums read by all before anything moves
+        if (lane == 0 && n > 0.0) cs[i] = c;
+        if (threadIdx.x == 0) { moved = 0; unsure = 0; }
+        __syncthreads();
+    }
+    __syncthreads();
+    if (threadIdx.x < C) {
+        const uint16_t hc = f64_to_bf16(cs[threadIdx.x]);
+        codebook[threadIdx.x] = hc;
+        cs[threadIdx.x] = bf16_to_f64(hc);
+    }
+    __syncthreads();
+    if (i < C - 1) {
+        const double b = boundary(i);
+        if (lane == 0 && among_far(b)) q->exact_assign = 1;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            // largest key (sign * magnitude key) at or below b: zero 0, far 1, window position + 2
+            const int below = below_of(b, h);
+            const int key = b < 0.0 ? -(kHistMags - below) - 2 : b == 0.0 ? 0 : below - kHistMags + 1;
+            q->above[lane + 64 * h][i] = (static_cast<uint32_t>(key) & 0xFFFFu) * 0x00010001u;
+        }
     }
 }
 
-// second half: partial sums added in workgroup order, centroids updated; on the last round the
-// codebook is written as well
-__global__ __launch_bounds__(64) void bs_lloyd_update_kernel(QuantScratch* q, int C, int partials, bool update,
-                                                             uint16_t* __restrict__ codebook) {
-    const int j = threadIdx.x;
-    if (j >= C) return;
-    if (update) {
-        double s = 0.0;
-        long long m = 0;
-        for (int p = 0; p < partials; ++p) { s += q->psum[p][j]; m += q->pcnt[p][j]; }
-        if (m > 0) q->cent[j] = s / static_cast<double>(m);
-    }
-    if (codebook) codebook[j] = f64_to_bf16(q->cent[j]);
-}
-
-// nearest stored centroid for every element, packed; one thread per 32 elements
+// Nearest stored centroid for every element, packed: a lane takes 16 elements (BITS half-words of the stream).
+// Two elements at a time, as 16-bit keys: a binary search over the boundaries with the sign masks of differences.
 template <int BITS>
 __global__ __launch_bounds__(256) void bs_assign_pack_kernel(const uint16_t* __restrict__ W,
                                                              const uint16_t* __restrict__ scales,
-                                                             const uint16_t* __restrict__ codebook, int64_t ngroups,
-                                                             uint32_t* __restrict__ packed) {
+                                                             const uint16_t* __restrict__ codebook, int64_t npieces,
+                                                             const QuantScratch* __restrict__ q, uint32_t* __restrict__ packed) {
     constexpr int C = 1 << BITS;
-    const int64_t g = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (g >= ngroups) return;
-    double c[C];
+    // rows of 4 dwords more than they hold: the 16 rows that a wave's lanes read start in different bank groups
+    __shared__ alignas(16) uint32_t above[kQuantMants][C < 4 ? 4 : C == 4 ? 4 : C + 4];
+    for (int i = threadIdx.x; i < kQuantMants * C; i += 256) above[i / C][i % C] = q->above[i / C][i % C];
+    const bool exact = q->exact_assign != 0;
+    __syncthreads();
+    for (int64_t piece = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; piece < npieces; piece += static_cast<int64_t>(gridDim.x) * 256) {
+        u32x4_t v[2];
+        v[0] = *reinterpret_cast<const u32x4_t*>(W + piece * 16);
+        v[1] = *reinterpret_cast<const u32x4_t*>(W + piece * 16 + 8);
+        const uint32_t scale = scales[piece >> 2];
+        uint64_t bits = 0;
+        if (exact) {                                      // boundaries among the far elements: in fp64
+            const double s = bf16_to_f64(scale);
 #pragma unroll
-    for (int j = 0; j < C; ++j) c[j] = bf16_to_f64(codebook[j]);
-    Clusters<C> cl;
-    cl.begin(c);
-    const uint32_t scale = scales[g >> 1];
-    const uint16_t* w = W + (g << 5);
-    GroupPacker<BITS> gp;
-    gp.clear();
-    pack_group<BITS>(gp, [&](int e) -> uint32_t { return static_cast<uint32_t>(cl.assign(normalised(w[e], scale))); });
+            for (int e = 0; e < 16; ++e) {
+                const uint32_t d = v[e >> 3][(e >> 1) & 3];
+                const double x = s > 0.0 ? bf16_to_f64(e & 1 ? d >> 16 : d & 0xFFFFu) / s : 0.0;
+                uint32_t a = 0;
+                for (int j = 0; j + 1 < C; ++j) a += x > 0.5 * (bf16_to_f64(codebook[j]) + bf16_to_f64(codebook[j + 1])) ? 1 : 0;
+                bits |= static_cast<uint64_t>(a) << (e * BITS);
+            }
+        } else {
+            uint32_t sp = scale;
+            if (scale < kSmallScale) { sp = lifted(scale); lift_pairs(v[0]); lift_pairs(v[1]); }
+            const uint32_t* row = above[sp & 127u];
+            uint32_t th[C < 4 ? 4 : C];
 #pragma unroll
-    for (int j = 0; j < BITS; ++j) packed[g * BITS + j] = gp.w[j];
+            for (int j = 0; j < (C < 4 ? 4 : C); j += 4) {
+                const u32x4_t r = *reinterpret_cast<const u32x4_t*>(row + j);
+                th[j] = r[0]; th[j + 1] = r[1]; th[j + 2] = r[2]; th[j + 3] = r[3];
+            }
+            uint32_t half[2] = {0, 0};
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) {
+                const uint32_t d = v[e >> 3][(e >> 1) & 3];
+                const uint32_t sg = sign_masks(d);
+                const i16x2_t key = __builtin_bit_cast(i16x2_t, __builtin_bit_cast(uint32_t, magnitude_keys(d, sp)) ^ sg) - __builtin_bit_cast(i16x2_t, sg);
+                auto greater = [&](uint32_t t) {          // all ones where the key lies above boundary key t
+                    return sign_masks(__builtin_bit_cast(uint32_t, static_cast<i16x2_t>(__builtin_bit_cast(i16x2_t, t) - key)));
+                };
+                auto pick = [](uint32_t m, uint32_t a, uint32_t b) { return (m & a) | (~m & b); };
+                uint32_t idx;                             // the two indices, in the two halves
+                const uint32_t m0 = greater(th[C / 2 - 1]);
+                idx = m0 & (0x00010001u << (BITS - 1));
+                if constexpr (BITS >= 2) {
+                    const uint32_t m1 = greater(pick(m0, th[C / 2 + C / 4 - 1], th[C / 4 - 1]));
+                    idx |= m1 & (0x00010001u << (BITS - 2));
+                    if constexpr (BITS >= 3) {
+                        const uint32_t m2 = greater(pick(m0, pick(m1, th[7 * C / 8 - 1], th[5 * C / 8 - 1]), pick(m1, th[3 * C / 8 - 1], th[C / 8 - 1])));
+                        idx |= m2 & (0x00010001u << (BITS - 3));
+                        if constexpr (BITS >= 4) {
+                            const uint32_t hi = pick(m1, pick(m2, th[14], th[12]), pick(m2, th[10], th[8]));
+                            const uint32_t lo = pick(m1, pick(m2, th[6], th[4]), pick(m2, th[2], th[0]));
+                            idx |= greater(pick(m0, hi, lo)) & 0x00010001u;
+                        }
+                    }
+                }
+                const uint32_t two = (idx | (idx >> (16 - BITS))) & ((1u << (2 * BITS)) - 1);
+                half[e >> 3] |= two << ((e & 7) * BITS);
+            }
+            bits = static_cast<uint64_t>(half[1]) << (8 * BITS) | half[0];
+        }
+        if constexpr (BITS == 2) {
+            packed[piece] = static_cast<uint32_t>(bits);
+        } else if constexpr (BITS == 4) {
+            typedef u32x2_t __attribute__((aligned(4))) u32x2_a4_t;
+            *reinterpret_cast<u32x2_a4_t*>(packed + piece * 2) = u32x2_t{static_cast<uint32_t>(bits), static_cast<uint32_t>(bits >> 32)};
+        } else {
+            uint16_t* out = reinterpret_cast<uint16_t*>(packed);
+#pragma unroll
+            for (int j = 0; j < BITS; ++j) out[piece * BITS + j] = static_cast<uint16_t>(bits >> (16 * j));
+        }
+    }
 }
 
 size_t quantize_blockscaled_workspace_bytes() { return sizeof(QuantScratch); }
@@ -737,20 +1151,20 @@ hipError_t launch_quantize_rows(const uint16_t* W, int64_t N, int64_t K, int bit
 template <int BITS>
 static hipError_t quantize_blockscaled_bits(const uint16_t* W, int64_t N, int64_t K, int iters, uint32_t* packed,
                                             uint16_t* codebook, uint16_t* scales, QuantScratch* q, hipStream_t s) {
-    constexpr int C = 1 << BITS;
-    const int64_t nblocks = N * (K / KMQ_BLOCK), ngroups = nblocks * 2;
-    const int64_t want = (nblocks + 31) / 32;          // a wave takes 8 blocks at a time
-    const int partials = static_cast<int>(want < kQuantPartials ? want : kQuantPartials);
-    hipLaunchKernelGGL(bs_scales_kernel, dim3(static_cast<unsigned>((nblocks + 3) / 4)), dim3(256), 0, s, W, nblocks, scales, q, C);
-    for (int t = 0; t < iters; ++t) {
-        hipLaunchKernelGGL((bs_lloyd_pass_kernel<BITS>), dim3(partials), dim3(256), 0, s, W, scales, nblocks, q);
-        hipLaunchKernelGGL(bs_lloyd_update_kernel, dim3(1), dim3(64), 0, s, q, C, partials, true,
-                           t + 1 == iters ? codebook : static_cast<uint16_t*>(nullptr));
-    }
-    if (iters == 0)
-        hipLaunchKernelGGL(bs_lloyd_update_kernel, dim3(1), dim3(64), 0, s, q, C, 0, false, codebook);
-    hipLaunchKernelGGL((bs_assign_pack_kernel<BITS>), dim3(static_cast<unsigned>((ngroups + 255) / 256)), dim3(256), 0, s, W,
-                       scales, codebook, ngroups, packed);
+    const int64_t nblocks = N * (K / KMQ_BLOCK), npieces = nblocks * 4;
+    auto grid = [](int64_t items, int64_t each, int64_t most) {
+        const int64_t g = (items + each - 1) / each;
+        return dim3(static_cast<unsigned>(g < most ? g : most));
+    };
+    hipLaunchKernelGGL(bs_clear_kernel, dim3(2048), dim3(256), 0, s, q);
+    hipLaunchKernelGGL(bs_scales_kernel, grid(nblocks, 128, 512), dim3(256), 0, s, W, nblocks, scales, q);
+    hipLaunchKernelGGL(bs_group_kernel, dim3(static_cast<unsigned>((nblocks + kGroupBlocks - 1) / kGroupBlocks)), dim3(kGroupThreads), 0, s, scales, nblocks, q, packed);
+    // four workgroups a CU; a run of at least 64 blocks, to spread the clearing and flushing of 4096 counters
+    const int64_t run = (nblocks + 1023) / 1024 < 64 ? 64 : (nblocks + 1023) / 1024;
+    hipLaunchKernelGGL(bs_count_kernel, dim3(static_cast<unsigned>((nblocks + run - 1) / run)), dim3(kCountThreads), 0, s, W, packed, nblocks, run, q);
+    hipLaunchKernelGGL(bs_prefix_kernel, dim3(kQuantMants), dim3(1024), 0, s, q);
+    hipLaunchKernelGGL((bs_rounds_kernel<BITS>), dim3(1), dim3((1 << BITS) * 64), 0, s, q, W, scales, nblocks, iters, codebook);
+    hipLaunchKernelGGL((bs_assign_pack_kernel<BITS>), grid(npieces, 256, 4096), dim3(256), 0, s, W, scales, codebook, npieces, q, packed);
     return hipGetLastError();
 }
 
