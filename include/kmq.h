@@ -167,8 +167,9 @@ kmq_status kmq_gemv(const uint32_t* W, const uint16_t* codebook, const uint16_t*
  * Every layout is accepted at every M.  KMQ_LAYOUT_TILED is the fast one for M >= 8
  * (matrix-core kernel: a weight is dequantised once for the whole batch);
  * KMQ_LAYOUT_ROWLANE serves M = 1..4 on the vector units, each weight dequantised once
- * (M > 4: one launch per four columns); on the canonical layout every batch column
- * looks the weights up again, in one launch. */
+ * (M > 4: one launch per four columns); on the canonical layout row lengths with a specialised
+ * table kernel look the weights up again for every column, in one launch, and everything else takes
+ * a matrix-core kernel as well. */
 kmq_status kmq_gemm_smallbatch(const uint32_t* W, const uint16_t* codebook, const uint16_t* X,
                                uint16_t* Y, int64_t N, int64_t K, int M, int bits, int layout,
                                void* workspace, size_t workspace_bytes, void* hip_stream);
@@ -325,7 +326,9 @@ kmq_status kmq_quantize_blockscaled(const uint16_t* Wdense, int64_t N, int64_t K
                                     void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /* Name of the kernel variant the launch heuristic picks for this problem
- * (static string, never NULL; "invalid" on bad arguments).  For reports. */
+ * (static string, never NULL; "invalid" on bad arguments).  For reports.  On the canonical layout it names
+ * the family that (N, K, bits) belongs to: "generic" and "blockscaled_generic" products of 1..4 bits, "lut_loop_b..."
+ * batches and most block-scaled batches run on the matrix cores (kmq_mfma_canon.hip), whatever the family. */
 const char* kmq_kernel_name(int64_t N, int64_t K, int bits, int M, int layout);
 
 const char* kmq_status_string(kmq_status s);

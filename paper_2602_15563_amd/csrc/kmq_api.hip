@@ -78,6 +78,33 @@ Plan make_plan(int64_t N, int64_t K, int bits, int M, int layout, bool scaled) {
     return Plan{kVariantGeneric, -1, 0, "generic"};
 }
 
+// Whether the matrix-core kernel of the canonical layout takes a product whose plan is `p`.  It decodes every weight once
+// for the whole batch, so it replaces the shape-agnostic kernels at every batch and the table kernels that would run one
+// workgroup per batch column.  Measured (us), before / with it:
+//   shape-agnostic, per row: 3-bit 5001 x 4101, batch 1 / 3 / 16: 41.0 / 111.0 / 567 -> 7.5 / 8.1 / 14.7; 1-bit 1024 x 1111:
+//     5.5 / 11.4 / 64.5 -> 3.1 / 3.1 / 5.6
+//   K in rounds, batch >= 2: 2-bit 4096 x 11008, batch 2 / 16: 8.5 / 45.3 -> 5.7 / 12.3; 4-bit 2048 x 1280: 3.9 / 12.7 -> 3.8 / 4.3
+//     (batch 1 stays: 1-bit 4096 x 11008 4.9 against 5.2, 3-bit 7.9 against 8.2)
+//   block-scaled, no table kernel: 4-bit 4096 x 2560, batch 1 / 16: 5.6 / 45.7 -> 5.7 / 6.7; 1-bit 5.1 / 45.5 -> 3.4 / 5.0
+//   block-scaled, table kernel: 4-bit 8192 x 8192, batch 3 / 16: 23.9 / 106 -> 14.0 / 20.0; 1-bit 11.3 / 48.5 -> 8.7 / 17.9; at
+//     batch 2 it loses about as often as it wins (2-bit 14336 x 4096 8.6 against 9.2, 4-bit 15.8 against 13.4), and small
+//     matrices start later with it (3-bit 2048 x 2048, batch 3 / 4 / 8: 3.7 / 3.8 / 4.8 against 4.1 / 4.2 / 4.5)
+// Table kernels specialised on K keep per-row batches: their columns are the batch-1 results bit for bit.
+static bool canon_takes(const GemmArgs& a, const Plan& p) {
+    if (a.layout != KMQ_LAYOUT_CANONICAL || a.bits > 4 || p.workspace_bytes > 0) return false;
+#ifdef KMQ_TUNING
+    static const char* const v = std::getenv("KMQ_CANON");
+    if (v) return v[0] == '1';
+#endif
+    switch (p.variant) {
+        case kVariantGeneric:
+        case kVariantBlockGeneric: return true;
+        case kVariantLutLoop: return a.M >= 2;
+        case kVariantPerColumn: return a.scales && a.M >= (a.N * a.K > (int64_t(1) << 23) ? 3 : 5);
+        default: return false;
+    }
+}
+
 // Text of the last HIP error a launch reported on this thread ("" if none).
 static thread_local const char* g_last_hip_error = "";
 
@@ -117,6 +144,7 @@ static kmq_status check_and_run(const GemmArgs& a_in, void* stream, bool library
     if (plan.workspace_bytes > 0 && (!a.workspace || a.workspace_bytes < plan.workspace_bytes)) return KMQ_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = hipSuccess;
+    if (canon_takes(a, plan)) return hip_status(launch_canon(a, s));
     switch (plan.variant) {
         case kVariantMfma: e = launch_mfma(a, s); break;
         case kVariantRowlane: e = launch_rowlane(a, s); break;

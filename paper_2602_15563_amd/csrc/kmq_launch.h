@@ -79,6 +79,9 @@ hipError_t launch_mfma_kslice(const GemmArgs& a, hipStream_t s);
 int mfma_waves_along_k(int64_t N, int64_t K, int bits);
 int mfma_row_blocks(int64_t N, int64_t K, int bits);
 
+// Matrix-core kernel on the canonical layout (any N and K, bits 1..4, per-row or block-scaled).
+hipError_t launch_canon(const GemmArgs& a, hipStream_t s);
+
 // Row-lane layout kernels (batch 1..4).
 bool rowlane_has_kernel(int64_t K, int bits, int M);
 bool rowlane_loops(int64_t K, int bits);              // K served by the kernel that walks K in rounds

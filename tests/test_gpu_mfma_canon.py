@@ -1,0 +1,76 @@
+"""The matrix-core kernel of the canonical layout at its edges, against the oracle through the C ABI: row lengths around its
+256-column tiles (a lone element, a partly filled tile alone and behind whole ones, tile counts below, at and above the
+waves of a workgroup), row counts around its blocks of 16, every group of batch rows it stages, both weight formats."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2602_15563_amd import kmq, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    from tests import gpu_util
+    return gpu_util
+
+
+PER_ROW = [(1, 1, 1), (3, 31, 2), (16, 255, 4), (17, 257, 5), (33, 515, 8), (15, 1023, 9), (250, 1025, 16), (40, 2047, 3),
+           (31, 2305, 1), (19, 4097, 16), (300, 4111, 6), (4100, 333, 2), (8209, 777, 7), (600, 5001, 1),
+           (1000, 2560, 4), (47, 24607, 16), (513, 24590, 1), (9000, 1056, 12)]
+
+
+@pytest.mark.parametrize("bits", (1, 2, 3, 4))
+@pytest.mark.parametrize("N,K,M", PER_ROW)
+def test_per_row_vs_oracle(gpu, bits, N, K, M):
+    if kmq.workspace_bytes(N, K, bits, M):
+        pytest.skip("few long rows: split over K")
+    seed = 7 * bits + N + K + M
+    idx, cb = synth.make_indices(seed, 0, N, K, bits), synth.make_codebook(seed, 0, N, bits, symmetric=(bits == 1))
+    X = synth.make_x(seed, 0, M, K)
+    p = oracle.pack(idx, bits)
+    Yg = gpu.run_gemm(gpu.dev(p), gpu.dev(cb), X, N, K, bits)
+    gpu.check_against_oracle(Yg, p, cb, X, K, bits, gpu.sample_ranges(N, seed), label=f"b{bits} {N}x{K} M{M}")
+
+
+SCALED = [(1, 64, 2), (16, 192, 4), (17, 256, 1), (33, 320, 5), (15, 1024 + 64, 16), (250, 2560, 1), (300, 2304, 9),
+          (40, 6400, 3), (4100, 640, 8), (8193, 384, 2), (520, 16448, 16), (4096, 4096, 3), (1100, 8192, 16)]
+
+
+@pytest.mark.parametrize("bits", (1, 2, 3, 4))
+@pytest.mark.parametrize("N,K,M", SCALED)
+def test_blockscaled_vs_oracle(gpu, bits, N, K, M):
+    seed = 5 * bits + N + K + M
+    idx, cb = synth.make_indices(seed, 0, N, K, bits), synth.make_shared_codebook(seed, 0, bits)
+    sc, X = synth.make_scales(seed, 0, N, K), synth.make_x(seed, 0, M, K)
+    p = oracle.pack(idx, bits)
+    Yg = gpu.run_gemm_blockscaled(gpu.dev(p), gpu.dev(cb), gpu.dev(sc), X, N, K, bits)
+    gpu.check_blockscaled_against_oracle(Yg, p, cb, sc, X, K, bits, row_ranges=gpu.sample_ranges(N, seed), label=f"b{bits} {N}x{K} M{M}")
+
+
+@pytest.mark.parametrize("bits", (2, 3, 4))
+def test_one_hot_columns_are_bit_exact(gpu, bits):
+    """Row m of X is e_k: a sum with one non-zero term is the weight itself, so every column of every tile position has to
+    meet its own weight (the operands' column order, the transposes, the tile behind the last whole one)."""
+    N, K = 35, 2 * 2048 + 77
+    seed = 40 + bits
+    idx, cb = synth.make_indices(seed, 0, N, K, bits), synth.make_codebook(seed, 0, N, bits)
+    p = oracle.pack(idx, bits)
+    Wd = oracle.dequant(p, cb, K, bits)
+    pd, cd = gpu.dev(p), gpu.dev(cb)
+    for k0 in list(range(0, 256, 16)) + [2040, 2048, 4080, 4096, K - 16]:
+        X = np.zeros((16, K), dtype=np.uint16)
+        X[np.arange(16), k0 + np.arange(16)] = 0x3F80
+        assert np.array_equal(gpu.run_gemm(pd, cd, X, N, K, bits), Wd[:, k0:k0 + 16].T), f"k0={k0}"
+
+
+@pytest.mark.parametrize("bits", (1, 2, 3, 4))
+def test_columns_do_not_depend_on_the_batch(gpu, bits):
+    """A column's sums run in the same order whatever the batch, as long as the waves split K the same way."""
+    N, K = 100, 3333
+    idx, cb, X = synth.make_indices(60, 0, N, K, bits), synth.make_codebook(60, 0, N, bits), synth.make_x(60, 0, 16, K)
+    pd, cd = gpu.dev(oracle.pack(idx, bits)), gpu.dev(cb)
+    full = gpu.run_gemm(pd, cd, X, N, K, bits)
+    assert np.array_equal(full, gpu.run_gemm(pd, cd, X, N, K, bits))
+    assert np.array_equal(full[:5], gpu.run_gemm(pd, cd, X[:5], N, K, bits))
