@@ -78,7 +78,8 @@ Plan make_plan(int64_t N, int64_t K, int bits, int M, int layout, bool scaled) {
     return Plan{kVariantGeneric, -1, 0, "generic"};
 }
 
-// Whether the matrix-core kernel of the canonical layout takes a product whose plan is `p`.  It decodes every weight once
+// Whether the matrix-core kernel for any row length (kmq_mfma_any.h) takes a product whose plan is `p`: on the tiled layout
+// where mfma_takes leaves it, on the canonical one as follows.  It decodes every weight once
 // for the whole batch, so it replaces the shape-agnostic kernels at every batch and the table kernels that would run one
 // workgroup per batch column.  Measured (us), before / with it:
 //   shape-agnostic, per row: 3-bit 5001 x 4101, batch 1 / 3 / 16: 41.0 / 111.0 / 567 -> 7.5 / 8.1 / 14.7; 1-bit 1024 x 1111:
@@ -91,15 +92,16 @@ Plan make_plan(int64_t N, int64_t K, int bits, int M, int layout, bool scaled) {
 //     matrices start later with it (3-bit 2048 x 2048, batch 3 / 4 / 8: 3.7 / 3.8 / 4.8 against 4.1 / 4.2 / 4.5)
 // Table kernels specialised on K keep per-row batches: their columns are the batch-1 results bit for bit.
 static bool canon_takes(const GemmArgs& a, const Plan& p) {
-    if (a.layout != KMQ_LAYOUT_CANONICAL || a.bits > 4 || p.workspace_bytes > 0) return false;
+    if (a.layout == KMQ_LAYOUT_ROWLANE || a.bits > 4 || p.workspace_bytes > 0) return false;
 #ifdef KMQ_TUNING
-    static const char* const v = std::getenv("KMQ_CANON");
-    if (v) return v[0] == '1';
+    const char* const v = std::getenv("KMQ_CANON");
+    if (v && v[0] != '2') return v[0] == '1';
 #endif
     switch (p.variant) {
         case kVariantGeneric:
         case kVariantBlockGeneric: return true;
         case kVariantLutLoop: return a.M >= 2;
+        case kVariantMfma: return !mfma_takes(a.N, a.K, a.bits, a.M, a.scales != nullptr);
         case kVariantPerColumn: return a.scales && a.M >= (a.N * a.K > (int64_t(1) << 23) ? 3 : 5);
         default: return false;
     }
@@ -144,7 +146,10 @@ static kmq_status check_and_run(const GemmArgs& a_in, void* stream, bool library
     if (plan.workspace_bytes > 0 && (!a.workspace || a.workspace_bytes < plan.workspace_bytes)) return KMQ_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = hipSuccess;
-    if (canon_takes(a, plan)) return hip_status(launch_canon(a, s));
+    if (canon_takes(a, plan)) {
+        static hipError_t (*const launch[4])(const GemmArgs&, hipStream_t) = {launch_canon_b1, launch_canon_b2, launch_canon_b3, launch_canon_b4};
+        return hip_status(launch[a.bits - 1](a, s));
+    }
     switch (plan.variant) {
         case kVariantMfma: e = launch_mfma(a, s); break;
         case kVariantRowlane: e = launch_rowlane(a, s); break;

@@ -71,16 +71,19 @@ size_t quantize_blockscaled_workspace_bytes();
 hipError_t launch_quantize_blockscaled(const uint16_t* W, int64_t N, int64_t K, int bits, int iters, uint32_t* packed,
                                        uint16_t* codebook, uint16_t* scales, void* workspace, hipStream_t s);
 
-// Matrix-core kernel (tiled layout only).
+// Matrix-core kernels of the tiled layout for rows that split evenly over the waves.
 hipError_t launch_mfma(const GemmArgs& a, hipStream_t s);
 // 2- and 3-bit rows of at most 4096 columns: every wave keeps its slice of the activations in registers
 bool mfma_kslice_has_kernel(int64_t N, int64_t K, int bits);
 hipError_t launch_mfma_kslice(const GemmArgs& a, hipStream_t s);
-int mfma_waves_along_k(int64_t N, int64_t K, int bits);
+bool mfma_takes(int64_t N, int64_t K, int bits, int M, bool scaled);   // else launch_canon_b*
 int mfma_row_blocks(int64_t N, int64_t K, int bits);
 
-// Matrix-core kernel on the canonical layout (any N and K, bits 1..4, per-row or block-scaled).
-hipError_t launch_canon(const GemmArgs& a, hipStream_t s);
+// Matrix-core kernel for any N and K, bits 1..4, canonical or tiled layout, per-row or block-scaled.
+hipError_t launch_canon_b1(const GemmArgs& a, hipStream_t s);
+hipError_t launch_canon_b2(const GemmArgs& a, hipStream_t s);
+hipError_t launch_canon_b3(const GemmArgs& a, hipStream_t s);
+hipError_t launch_canon_b4(const GemmArgs& a, hipStream_t s);
 
 // Row-lane layout kernels (batch 1..4).
 bool rowlane_has_kernel(int64_t K, int bits, int M);

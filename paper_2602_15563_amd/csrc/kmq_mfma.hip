@@ -501,14 +501,15 @@ static void launch_mfma_one(const GemmArgs& a, hipStream_t s) {
 }
 
 // Launch shapes (waves along K, row blocks per wave, super-blocks per wave) with a
-// compile-time K loop, and the (waves, row blocks) pairs that also exist with a runtime loop.
+// compile-time K loop, and the (waves, row blocks) pairs that also exist with a runtime loop
+// (fewer than four waves in such a loop leave the chip idle: other row lengths are kmq_mfma_any.h's).
 #define KMQ_MFMA_SHAPES(X) \
     X(8, 1, 1) X(8, 1, 2) X(8, 1, 4) X(4, 1, 3) X(4, 1, 4) X(2, 1, 3) \
     X(6, 1, 1) X(6, 1, 2) X(3, 1, 2) \
     X(4, 2, 2) X(4, 2, 4) X(4, 2, 8) X(6, 2, 1) X(8, 2, 2) X(8, 2, 4) X(8, 2, 8) X(8, 1, 8) \
     X(6, 3, 1) X(8, 3, 2)
 #define KMQ_MFMA_RT_SHAPES(X) \
-    X(8, 1) X(4, 1) X(2, 1) X(1, 1) X(8, 2) X(4, 2) X(2, 2) X(1, 2)
+    X(8, 1) X(4, 1) X(8, 2) X(4, 2)
 
 template <int BITS>
 static void launch_mfma_bits(const GemmArgs& a, int nwk, int rbw, int spw, hipStream_t s) {
@@ -520,7 +521,6 @@ static void launch_mfma_bits(const GemmArgs& a, int nwk, int rbw, int spw, hipSt
     if (nwk == NWK_ && rbw == RBW_) { launch_mfma_one<BITS, NWK_, RBW_, 0>(a, s); return; }
     KMQ_MFMA_RT_SHAPES(X)
 #undef X
-    launch_mfma_one<BITS, 1, 1, 0>(a, s);                  // any K the layout allows, one wave per row block
 }
 
 static bool mfma_has_shape(int nwk, int rbw, int spw) {
@@ -545,8 +545,8 @@ static int env_int(const char* name) {
 #endif
 }
 
-// Waves along K for `rbw` row blocks per wave: the largest of 8, 6, 4, 3, 2, 1 that divides
-// the number of super-blocks and has a kernel.  With two or more row blocks per wave and
+// Waves along K for `rbw` row blocks per wave: the largest of 8, 6, 4, 3, 2 that divides
+// the number of super-blocks and has a kernel, 0 if there is none.  With two or more row blocks per wave and
 // 2- or 3-bit decoding, more than 4 waves measured slower (registers); the 4-bit decode goes
 // through LDS lookups and wants every wave it can get (8192 x 8192, M = 16: 25.6 us with 4
 // waves, 20.8 with 8).
@@ -557,7 +557,7 @@ static int waves_along_k(int64_t K, int bits, int rbw) {
     static const int kChoices[] = {8, 6, 4, 3, 2};
     for (int w : kChoices)
         if (nsb % w == 0 && w <= cap && mfma_has_shape(w, rbw, nsb / w)) return w;
-    return 1;
+    return 0;
 }
 
 // Row blocks per wave.  Every workgroup reads all of X through the L1, so fewer, fatter
@@ -570,19 +570,36 @@ int mfma_row_blocks(int64_t N, int64_t K, int bits) {
     static const int forced = env_int("KMQ_MFMA_RBW");
     const int64_t nrb = (N + 15) / 16;
     const int max_rbw = bits == 1 ? 3 : 2;
-    int best = 1;
+    int best = 0;
     int64_t best_cost = 0;
     for (int r = 1; r <= max_rbw; ++r) {
         if (forced && r != forced) continue;
         const int w = waves_along_k(K, bits, r);
-        if (r > 1 && !mfma_has_shape(w, r, static_cast<int>(K / tiled_superblock_elems(bits) / w))) continue;
+        if (w == 0) continue;
         const int64_t wgs = (nrb + r - 1) / r, cost = ((wgs + 255) / 256) * r;
         if (best_cost == 0 || cost <= best_cost) { best = r; best_cost = cost; }
     }
     return best;
 }
 
-int mfma_waves_along_k(int64_t N, int64_t K, int bits) { return waves_along_k(K, bits, mfma_row_blocks(N, K, bits)); }
+// Whether the kernels of this file and of kmq_mfma_kslice.hip take a product on the tiled layout; the others are
+// kmq_mfma_any.h's.  Those here unroll K completely where it splits evenly over the waves and keep all 16 batch columns of X
+// moving; the other kernel takes any K and stages only the batch that is there.  Measured (us), this / the other, geometric
+// means over K = 1536 .. 14336 and 1100 .. 14336 rows, both formats:
+//   batch 1, 4: the other 18 to 34 % faster at every bit-width (4-bit scaled 8192 x 8192 and the like); only 1-bit matrices with
+//     three row blocks a wave stay (8192 x 9216: 9 to 15 %);
+//   batch 8: the other 9 to 13 % faster at 2 to 4 bits, but not on many short rows (3-bit 14336 x 4096: this 9 %), at 1 bit
+//     level (8192 x 9216 scaled: this 25 %, 1536 x 4096: the other 30 %);
+//   batch 16: this 1 to 11 % faster (2-bit 14336 x 4096: 34 %);
+//   K that does not split over at least four waves: the other (batch 1 / 16: 2-bit 2773 x 14592 48.6 / 6.7 at batch 1, 3-bit
+//     scaled 2688 x 15488 83.0 / 16.1 at batch 14).
+bool mfma_takes(int64_t N, int64_t K, int bits, int M, bool scaled) {
+    const int rbw = mfma_row_blocks(N, K, bits);
+    if (rbw == 0) return !scaled && M > 4 && mfma_kslice_has_kernel(N, K, bits);
+    if (M <= 4) return rbw == 3;
+    if (M <= 8) return bits == 1 || (K <= 4096 && N > 512 * 16) || (bits == 4 && K <= 2048 && !scaled);
+    return true;
+}
 
 hipError_t launch_mfma(const GemmArgs& a, hipStream_t s) {
     // short 2- and 3-bit rows: the kernel whose waves keep their slice of the activations in registers
