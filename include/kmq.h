@@ -170,7 +170,7 @@ kmq_status kmq_gemv(const uint32_t* W, const uint16_t* codebook, const uint16_t*
  * (matrix-core kernel: a weight is dequantised once for the whole batch);
  * KMQ_LAYOUT_ROWLANE serves M = 1..4 on the vector units, each weight dequantised once
  * (M > 4: one launch per four columns); on the canonical layout row lengths with a specialised
- * table kernel look the weights up again for every column, in one launch, and everything else takes
+ * table kernel look the weights up again for every column or pair of columns, in one launch, and everything else takes
  * a matrix-core kernel as well. */
 kmq_status kmq_gemm_smallbatch(const uint32_t* W, const uint16_t* codebook, const uint16_t* X,
                                uint16_t* Y, int64_t N, int64_t K, int M, int bits, int layout,

@@ -10,16 +10,13 @@
 namespace kmq {
 
 // On the canonical layout a batch above 1 runs the batch-1 table kernel, where the shape has one, over a
-// grid of (row group, column) workgroups in ONE launch: the workgroups that share rows of W sit next to
+// grid of (row group, column or pair of columns) workgroups in ONE launch: the workgroups that share rows of W sit next to
 // each other on one XCD, so W still comes from memory once and the other columns find it in that L2 (the
 // tiled layout with its matrix-core kernel remains the fastest route for batch > 1: it also decodes each
-// weight once).  Measured (us), every further column costs N*K / r with r = 20, 19, 14, 9.5 million
-// weights per us at 1, 2, 3, 4 bits -- decode time, every column looks every weight up again -- against
-// N*K / 9 for every column of the shape-agnostic kernel, which also starts later (about 5 us against 2.6
-// + bytes / 3.3e6 for the first column): the table kernel wins at every batch.  Table / shape-agnostic:
-// 9216x3072 1-bit, batch 4: 8.9 / 21.7; 14336x4096 2-bit, batch 16: 50.6 / 121; 8192x8192 block-scaled
-// 4-bit, batch 16: 111 / 237; 4096x4096 4-bit, batch 4: 10.0 / 12.8.  (Builds with -DKMQ_TUNING
-// read a cap on the batch from KMQ_PER_COLUMN_MAX in the environment, for sweeps.)
+// weight once).  Which batches pair their columns: lut_two_columns in kmq_lut.hip.  Measured (us), table kernel /
+// shape-agnostic: 9216x3072 1-bit, batch 4: 7.5 / 21.7; 14336x4096 2-bit, batch 16: 41 / 121; 4096x4096 4-bit,
+// batch 4: 8.2 / 12.8.  (Builds with -DKMQ_TUNING read a cap on the batch from KMQ_PER_COLUMN_MAX in the environment,
+// for sweeps.)
 static bool per_column_faster(int M) {
 #ifdef KMQ_TUNING
     static const char* const v = std::getenv("KMQ_PER_COLUMN_MAX");
