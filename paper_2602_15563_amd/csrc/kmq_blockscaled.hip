@@ -12,6 +12,8 @@
 
 namespace kmq {
 
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+
 // b-bit field `e` (0..63) of a 64-element block held in 2*BITS consecutive words
 // (64*BITS bits: a block starts and ends on a word boundary for every bit-width).
 template <int BITS>
@@ -82,43 +84,58 @@ __global__ __launch_bounds__(256) void gemm_blockscaled_kernel(
     }
 }
 
-// Dense weights of the format, Wd[n][k] = bf16( codebook[idx[n][k]] * scale[n][k / 64] ): one thread per
-// 8 consecutive elements, so that a wave's store is 1 KB of consecutive bytes.  The fp32 product of two
-// bf16 values is exact, so the result carries one rounding, to nearest even.
+// Dense weights of the format, Wd[n][k] = bf16( codebook[idx[n][k]] * scale[n][k / 64] ): a chunk is 8
+// consecutive elements, so that a wave's store is 1 KB of consecutive bytes; a thread takes four chunks, all loads first.
+// The fp32 product of two bf16 values is exact, so the result carries one rounding, to nearest even.  Bound by the store.
+// 8192 x 8192, 4 bits: 25.0 us (134 MB out and 38 in at 6.9 TB/s; a fill of the output 20.4); 29.3 with one chunk a thread, the
+// next word read although only 3-bit chunks reach into it, and the rounding in five vector instructions an element instead of
+// half a one.
+constexpr int kDequantChunks = 4;
 template <int BITS>
 __global__ __launch_bounds__(256) void dequant_blockscaled_kernel(const uint32_t* __restrict__ W,
                                                                   const uint16_t* __restrict__ codebook,
                                                                   const uint16_t* __restrict__ scales, int64_t nchunks,
                                                                   int64_t total_words, uint16_t* __restrict__ Wd) {
-    constexpr int C = 1 << BITS;
+    constexpr int C = 1 << BITS, U = kDequantChunks;
     constexpr uint32_t mask = C - 1;
     __shared__ float lut[C];
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * (256 * U) + threadIdx.x;
+    // K % 64 == 0: rows are whole words, so the matrix is one bit stream and chunk c8 starts at bit c8 * 8 * BITS
+    uint64_t v[U];
+    float s[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        int64_t c8 = first + u * 256;
+        c8 = c8 < nchunks ? c8 : nchunks - 1;
+        const int64_t bit0 = c8 * (8 * BITS);
+        const int64_t wi = bit0 >> 5;
+        uint64_t hi = 0;
+        if constexpr (32 % (8 * BITS) != 0) hi = W[wi + 1 < total_words ? wi + 1 : wi];      // the chunk may reach into the next word
+        v[u] = (W[wi] | (hi << 32)) >> static_cast<int>(bit0 & 31);
+        s[u] = bf16_to_f32(scales[c8 >> 3]);
+    }
     if (threadIdx.x < C) lut[threadIdx.x] = bf16_to_f32(codebook[threadIdx.x]);
     __syncthreads();
-    const int64_t c8 = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;   // chunk of 8 elements, row-major over N x K/8
-    if (c8 >= nchunks) return;
-    // K % 64 == 0: rows are whole words, so the matrix is one bit stream and chunk c8 starts at bit c8 * 8 * BITS
-    const int64_t bit0 = c8 * (8 * BITS);
-    const int64_t wi = bit0 >> 5;
-    const int sh = static_cast<int>(bit0 & 31);
-    const uint64_t lo = W[wi], hi = wi + 1 < total_words ? W[wi + 1] : 0u;
-    const uint64_t v = (lo | (hi << 32)) >> sh;
-    const float s = bf16_to_f32(scales[c8 >> 3]);
-    uint32_t out[4];
 #pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-        const uint32_t a = f32_to_bf16(lut[static_cast<uint32_t>(v >> (e * BITS)) & mask] * s);
-        const uint32_t b = f32_to_bf16(lut[static_cast<uint32_t>(v >> ((e + 1) * BITS)) & mask] * s);
-        out[e >> 1] = a | (b << 16);
+    for (int u = 0; u < U; ++u) {
+        const int64_t c8 = first + u * 256;
+        if (c8 >= nchunks) return;
+        uint32_t out[4];
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            const f32x2_t p{lut[static_cast<uint32_t>(v[u] >> (e * BITS)) & mask] * s[u],
+                            lut[static_cast<uint32_t>(v[u] >> ((e + 1) * BITS)) & mask] * s[u]};
+            out[e >> 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2_t));      // v_cvt_pk_bf16_f32
+        }
+        // written once and read by a later kernel: no reason to keep it in this kernel's caches
+        __builtin_nontemporal_store(u32x4_t{out[0], out[1], out[2], out[3]}, reinterpret_cast<u32x4_t*>(Wd + (c8 << 3)));
     }
-    // written once and read by a later kernel: no reason to keep it in this kernel's caches
-    __builtin_nontemporal_store(u32x4_t{out[0], out[1], out[2], out[3]}, reinterpret_cast<u32x4_t*>(Wd + (c8 << 3)));
 }
 
 hipError_t launch_dequant_blockscaled(const uint32_t* W, const uint16_t* codebook, const uint16_t* scales, uint16_t* Wd,
                                       int64_t N, int64_t K, int bits, hipStream_t s) {
     const int64_t nchunks = N * (K / 8), words = N * (K * bits / 32);
-    const dim3 grid(static_cast<unsigned>((nchunks + 255) / 256)), block(256);
+    const dim3 grid(static_cast<unsigned>((nchunks + 256 * kDequantChunks - 1) / (256 * kDequantChunks))), block(256);
 #define KMQ_DQ(B) hipLaunchKernelGGL(dequant_blockscaled_kernel<B>, grid, block, 0, s, W, codebook, scales, nchunks, words, Wd)
     switch (bits) {
         case 1: KMQ_DQ(1); break;

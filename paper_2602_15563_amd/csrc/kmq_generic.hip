@@ -239,7 +239,86 @@ __global__ __launch_bounds__(256) void dequant_kernel(
     }
 }
 
-// The same for the canonical layout with K % 8 == 0: one thread per 8 consecutive elements, one 16-byte
+// The canonical layout, bits 1..4, rows of at least kDequantWaveK columns of any length.  Bound by the store of the dense matrix.
+// A wave takes 64 * U chunks of eight columns of ONE row, so that the row's centroids become a table in the wave's own piece of
+// LDS (1 bit: four weights per entry, 2 and 3 bits: pairs, 4 bits: one; entries of one dword lie in different banks) and no thread
+// divides.  Chunks are cut at the 16-byte boundaries of Wd, not at the row's start: all but the row's first and last are whole
+// 16-byte stores whatever K and the address of Wd, 1 KB per wave and instruction, past the caches.
+// Measured (us), one thread per chunk and centroids through the caches (odd K: per 32 columns, 2-byte stores) / this kernel / a
+// fill of Wd: 8192 x 8192, 1 bit 23.9 / 22.2 / 20.4, 4 bits 41.3 / 25.0 / 20.4; 5001 x 4101, 3 bits 98.0 / 9.9 / 7.7.  From 512
+// columns on because a wave's segment is 1024: 100000 x 512 still gains (4 bits 31.7 / 18.9), shorter rows leave most lanes idle.
+constexpr int64_t kDequantWaveK = 512;
+template <int BITS, int U>
+__global__ __launch_bounds__(256) void dequant_wave_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict__ codebook,
+                                                           uint16_t* __restrict__ Wd, uint32_t N, int K, uint32_t segs) {
+    static_assert(BITS <= 4, "eight fields in one word");
+    constexpr int C = 1 << BITS;
+    __shared__ u32x2_t tab2[4][BITS == 1 ? 16 : 1];
+    __shared__ uint32_t tab[4][BITS == 3 ? 64 : 16];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const uint32_t id = blockIdx.x * 4u + wave, n = id / segs, seg = id % segs;
+    if (n >= N) return;                                  // (the waves of a workgroup share nothing)
+    const uint16_t* c = codebook + static_cast<int64_t>(n) * C;
+    const int wpr = static_cast<int>(words_per_row(BITS, K));
+    const uint32_t* row = W + static_cast<int64_t>(n) * wpr;
+    uint16_t* out = Wd + static_cast<int64_t>(n) * K;
+    const int head = static_cast<int>((0u - static_cast<uint32_t>(reinterpret_cast<uintptr_t>(out))) & 15u) >> 1;   // columns ahead of a 16-byte boundary
+    const int k0 = (head ? head - 8 : 0) + 8 * (static_cast<int>(seg) * (64 * U) + lane);
+
+    uint32_t v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int k = k0 + u * 512;
+        const int bit = (k > 0 ? k : 0) * BITS, wi = bit >> 5;
+        const uint32_t lo = row[wi < wpr ? wi : wpr - 1];
+        uint32_t hi = 0;
+        if (BITS == 3 || head) hi = row[wi + 1 < wpr ? wi + 1 : wpr - 1];
+        v[u] = __builtin_amdgcn_alignbit(hi, lo, bit & 31);
+        if (k < 0) v[u] <<= -k * BITS;                    // field e is column k + e
+    }
+    if constexpr (BITS == 1) {
+        if (lane < 16) {
+            const uint32_t a = c[0], b = c[1];
+            tab2[wave][lane] = u32x2_t{(lane & 1 ? b : a) | ((lane & 2 ? b : a) << 16), (lane & 4 ? b : a) | ((lane & 8 ? b : a) << 16)};
+        }
+    } else if constexpr (BITS == 4) {
+        if (lane < 16) tab[wave][lane] = c[lane];
+    } else {
+        if (lane < C * C) tab[wave][lane] = c[lane % C] | (static_cast<uint32_t>(c[lane / C]) << 16);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int k = k0 + u * 512;
+        if (k >= K) break;
+        u32x4_t o;
+        if constexpr (BITS == 1) {
+            const u32x2_t a = tab2[wave][v[u] & 15u], b = tab2[wave][(v[u] >> 4) & 15u];
+            o = u32x4_t{a[0], a[1], b[0], b[1]};
+        } else if constexpr (BITS == 4) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = tab[wave][(v[u] >> (8 * e)) & 15u] | (tab[wave][(v[u] >> (8 * e + 4)) & 15u] << 16);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = tab[wave][(v[u] >> (2 * BITS * e)) & (C * C - 1u)];
+        }
+        if (k >= 0 && k + 8 <= K) {
+            __builtin_nontemporal_store(o, reinterpret_cast<u32x4_t*>(out + k));
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (k + e >= 0 && k + e < K) out[k + e] = static_cast<uint16_t>(o[e >> 1] >> (16 * (e & 1)));
+        }
+    }
+}
+
+template <int BITS, int U>
+static void launch_dequant_wave(const uint32_t* W, const uint16_t* codebook, uint16_t* Wd, int64_t N, int64_t K, uint32_t segs, hipStream_t s) {
+    const dim3 grid(static_cast<unsigned>((N * segs + 3) / 4)), block(256);
+    hipLaunchKernelGGL((dequant_wave_kernel<BITS, U>), grid, block, 0, s, W, codebook, Wd, static_cast<uint32_t>(N), static_cast<int>(K), segs);
+}
+
+// The canonical layout with K % 8 == 0, short rows and 8 bits: one thread per 8 consecutive elements, one 16-byte
 // store per thread (a wave writes 1 KB of consecutive bytes, past the caches: the matrix is read by a later
 // kernel).  The row's centroids are read through the caches.
 template <int BITS>
@@ -315,6 +394,22 @@ hipError_t launch_generic(const GemmArgs& a, hipStream_t s) {
 
 hipError_t launch_dequant(const uint32_t* W, const uint16_t* codebook, uint16_t* Wd, int64_t N,
                           int64_t K, int bits, int layout, hipStream_t s) {
+    if (layout == KMQ_LAYOUT_CANONICAL && bits <= 4 && K >= kDequantWaveK) {
+        constexpr int U = 2;
+        const bool even = (K & 7) == 0 && (reinterpret_cast<uintptr_t>(Wd) & 15) == 0;
+        const int64_t chunks = even ? K >> 3 : (K + 14) >> 3;      // a first chunk of 1..8 columns, whole ones, a last one
+        const int64_t segs = (chunks + 64 * U - 1) / (64 * U);
+        if (N * segs < (int64_t(1) << 31)) {
+            const uint32_t sg = static_cast<uint32_t>(segs);
+            switch (bits) {
+                case 1: launch_dequant_wave<1, U>(W, codebook, Wd, N, K, sg, s); break;
+                case 2: launch_dequant_wave<2, U>(W, codebook, Wd, N, K, sg, s); break;
+                case 3: launch_dequant_wave<3, U>(W, codebook, Wd, N, K, sg, s); break;
+                default: launch_dequant_wave<4, U>(W, codebook, Wd, N, K, sg, s); break;
+            }
+            return hipGetLastError();
+        }
+    }
     if (layout == KMQ_LAYOUT_CANONICAL && (K & 7) == 0 && (reinterpret_cast<uintptr_t>(Wd) & 15) == 0 &&
         N * (K >> 3) <= (int64_t(1) << 38)) {                  // one workgroup per 256 chunks must fit the grid
         const int64_t chunks = N * (K >> 3);
