@@ -211,7 +211,7 @@ kmq_status kmq_gemv_swiglu(const uint32_t* Wgate, const uint16_t* codebook_gate,
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (rowlane) return kmq::hip_status(kmq::launch_rowlane_pair(a, s));
     const int l = kmq::lut_find(2 * N, K, bits, layout, false);
-    const hipError_t e = l >= 0 ? kmq::launch_lut_entry(l, a, s) : kmq::launch_pair_generic(a, s);
+    const hipError_t e = l >= 0 ? kmq::launch_lut_entry(l, a, s) : kmq::launch_fused_generic(a, s);
     return kmq::hip_status(e);
 }
 

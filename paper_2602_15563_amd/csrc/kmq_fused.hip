@@ -28,47 +28,137 @@ __device__ __forceinline__ uint32_t stream_field(const uint32_t* row, int64_t k)
     return v & mask;
 }
 
-// One wave per output element, four per workgroup; lanes stride over K.
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+
+// A workgroup computes four rows of one matrix (or two of a pair); its threads take the row's chunks of eight columns in turn.
+// Bound by its vector instructions and look-ups, not by memory, so both are spent once for as much as possible: x is read 16
+// bytes at a time, normalised and rounded once for the four rows; a chunk's indices are one word (8 bits: two); the tables in LDS
+// hold four weights per entry at 1 bit and two at 2 and 3.  The waves' sums are added in wave order.  The four launches of a decoder
+// layer (us), one row a wave and one column a lane and step / this kernel: hidden 2560, MLP 6912, 1 / 2 / 3 / 4 bits 64.3 / 75.5 / 101 /
+// 80.6 -> 26.9 / 27.6 / 33.1 / 32.4; 5120, 13824: 201 / 237 / 452 / 343 -> 54.6 / 57.5 / 80.6 / 77.5.  Eight rows a
+// workgroup were no faster but at 3 bits (5120, 13824: 56.6 / 57.0 / 69.1 / 78.2).
 template <int BITS, bool PAIR>
 __global__ __launch_bounds__(256) void gemv_fused_generic_kernel(
     const uint32_t* __restrict__ W, const uint16_t* __restrict__ codebook,
     const uint32_t* __restrict__ W2, const uint16_t* __restrict__ codebook2,
     const uint16_t* __restrict__ x, bool norm, const uint16_t* __restrict__ norm_w, float eps,
     const uint16_t* residual, uint16_t* y, int64_t N, int64_t K) {   // (may be one buffer: no __restrict__)
-    constexpr int C = 1 << BITS;
-    __shared__ float lut[4][2][C];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t n = static_cast<int64_t>(blockIdx.x) * 4 + wave;
-    const bool live = n < N;
-    if (live)
-        for (int e = lane; e < C; e += kWave) {
-            lut[wave][0][e] = bf16_to_f32(codebook[n * C + e]);
-            if constexpr (PAIR) lut[wave][1][e] = bf16_to_f32(codebook2[n * C + e]);
-        }
-    __syncthreads();
-    if (!live) return;
-
+    constexpr int C = 1 << BITS, ROWS = 4, OUT = PAIR ? 2 : 4;
+    constexpr int WE = BITS == 1 ? 4 : BITS <= 3 ? 2 : 1;             // weights per table entry
+    constexpr int T = WE == 1 ? C : BITS == 1 ? 16 : C * C;
+    constexpr int EW = BITS == 1 ? 2 : 1;                             // words per entry
+    __shared__ alignas(8) uint32_t tab[ROWS][T * EW];
+    __shared__ float red[4][ROWS + 1];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int64_t n0 = static_cast<int64_t>(blockIdx.x) * OUT;
     const int64_t wpr = words_per_row(BITS, K);
-    const uint32_t* r0 = W + n * wpr;
-    [[maybe_unused]] const uint32_t* r1 = PAIR ? W2 + n * wpr : nullptr;
-    float acc0 = 0.f, acc1 = 0.f, ss = 0.f;
-    for (int64_t k = lane; k < K; k += kWave) {
+    const uint32_t* row[ROWS];
+    const uint16_t* cb[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        int64_t n = n0 + (PAIR ? r >> 1 : r);
+        n = n < N ? n : N - 1;
+        row[r] = (PAIR && (r & 1) ? W2 : W) + n * wpr;
+        cb[r] = (PAIR && (r & 1) ? codebook2 : codebook) + n * C;
+#pragma unroll
+        for (int e = tid; e < T; e += 256) {
+            if constexpr (BITS == 1) {
+                const uint32_t a = cb[r][0], b = cb[r][1];
+                tab[r][2 * e] = (e & 1 ? b : a) | ((e & 2 ? b : a) << 16);
+                tab[r][2 * e + 1] = (e & 4 ? b : a) | ((e & 8 ? b : a) << 16);
+            } else if constexpr (WE == 2) {
+                tab[r][e] = cb[r][e % C] | (static_cast<uint32_t>(cb[r][e / C]) << 16);
+            } else {
+                tab[r][e] = static_cast<uint32_t>(cb[r][e]) << 16;    // as a float
+            }
+        }
+    }
+    __syncthreads();
+
+    float acc[ROWS] = {0.f, 0.f, 0.f, 0.f}, ss = 0.f;
+    auto pair_fma = [](uint32_t w, float x0, float x1, float a) {
+        return fmaf(__uint_as_float(w & 0xFFFF0000u), x1, fmaf(__uint_as_float(w << 16), x0, a));
+    };
+    const int chunks = static_cast<int>(K >> 3);
+#pragma unroll 2
+    for (int c = tid; c < chunks; c += 256) {
+        uint32_t v[ROWS];
+        [[maybe_unused]] uint32_t vh[ROWS];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const int bit = c * (8 * BITS), wi = bit >> 5;
+            const uint32_t lo = row[r][wi];
+            if constexpr (BITS == 3) v[r] = __builtin_amdgcn_alignbit(row[r][wi + 1 < wpr ? wi + 1 : wi], lo, bit & 31);
+            else v[r] = lo >> (bit & 31);
+            if constexpr (BITS == 8) vh[r] = row[r][wi + 1];
+        }
+        const u32x4_t xw = reinterpret_cast<const u32x4_t*>(x)[c];
+        float xv[8];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) { xv[2 * t] = __uint_as_float(xw[t] << 16); xv[2 * t + 1] = __uint_as_float(xw[t] & 0xFFFF0000u); }
+        if (norm) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ss = fmaf(xv[e], xv[e], ss);
+            if (norm_w) {
+                const u32x4_t gw = reinterpret_cast<const u32x4_t*>(norm_w)[c];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const f32x2_t p{xv[2 * t] * __uint_as_float(gw[t] << 16), xv[2 * t + 1] * __uint_as_float(gw[t] & 0xFFFF0000u)};
+                    const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2_t));
+                    xv[2 * t] = __uint_as_float(h << 16);
+                    xv[2 * t + 1] = __uint_as_float(h & 0xFFFF0000u);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            if constexpr (BITS == 1) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const u32x2_t w = *reinterpret_cast<const u32x2_t*>(&tab[r][2 * ((v[r] >> (4 * t)) & 15u)]);
+                    acc[r] = pair_fma(w[0], xv[4 * t], xv[4 * t + 1], acc[r]);
+                    acc[r] = pair_fma(w[1], xv[4 * t + 2], xv[4 * t + 3], acc[r]);
+                }
+            } else if constexpr (WE == 2) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    acc[r] = pair_fma(tab[r][(v[r] >> (2 * BITS * t)) & (T - 1u)], xv[2 * t], xv[2 * t + 1], acc[r]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    uint32_t f;
+                    if constexpr (BITS == 8) f = ((e < 4 ? v[r] : vh[r]) >> (8 * (e & 3))) & 255u;
+                    else f = (v[r] >> (4 * e)) & 15u;
+                    acc[r] = fmaf(__uint_as_float(tab[r][f]), xv[e], acc[r]);
+                }
+            }
+        }
+    }
+    if (tid < static_cast<int>(K & 7)) {                  // the columns past the last whole chunk, one per thread
+        const int64_t k = (K & ~int64_t(7)) + tid;
         float xv = bf16_to_f32(x[k]);
         if (norm) {
             ss = fmaf(xv, xv, ss);
             if (norm_w) xv = bf16_to_f32(f32_to_bf16(xv * bf16_to_f32(norm_w[k])));
         }
-        acc0 = fmaf(lut[wave][0][stream_field<BITS>(r0, k)], xv, acc0);
-        if constexpr (PAIR) acc1 = fmaf(lut[wave][1][stream_field<BITS>(r1, k)], xv, acc1);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) acc[r] = fmaf(bf16_to_f32(cb[r][stream_field<BITS>(row[r], k)]), xv, acc[r]);
     }
-    acc0 = group_sum<64>(acc0);
-    if constexpr (PAIR) acc1 = group_sum<64>(acc1);
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        acc[r] = group_sum<64>(acc[r]);
+        if (lane == 63) red[wave][r] = acc[r];
+    }
     ss = group_sum<64>(ss);
-    if (lane != 63) return;
-    const float r = norm ? 1.f / sqrtf(ss * (1.f / static_cast<float>(K)) + eps) : 1.f;
-    float out = acc0 * r;
+    if (lane == 63) red[wave][ROWS] = ss;
+    __syncthreads();
+    const int64_t n = n0 + tid;
+    if (tid >= OUT || n >= N) return;
+    auto total = [&](int r) { return ((red[0][r] + red[1][r]) + red[2][r]) + red[3][r]; };
+    const float s = norm ? 1.f / sqrtf(total(ROWS) * (1.f / static_cast<float>(K)) + eps) : 1.f;
+    float out = total(PAIR ? 2 * tid : tid) * s;
     if constexpr (PAIR) {
-        out = out / (1.f + __expf(-out)) * (acc1 * r);
+        out = out / (1.f + __expf(-out)) * (total(2 * tid + 1) * s);
     } else {
         if (residual) out += bf16_to_f32(residual[n]);
     }
@@ -77,12 +167,12 @@ __global__ __launch_bounds__(256) void gemv_fused_generic_kernel(
 
 template <int BITS>
 static hipError_t launch_fused_bits(const GemmArgs& a, hipStream_t s) {
-    const dim3 grid(static_cast<unsigned>((a.N + 3) / 4)), block(256);
+    const dim3 block(256);
     if (a.W2)
-        hipLaunchKernelGGL((gemv_fused_generic_kernel<BITS, true>), grid, block, 0, s, a.W, a.codebook, a.W2, a.codebook2, a.X,
+        hipLaunchKernelGGL((gemv_fused_generic_kernel<BITS, true>), dim3(static_cast<unsigned>((a.N + 1) / 2)), block, 0, s, a.W, a.codebook, a.W2, a.codebook2, a.X,
                            a.norm, a.norm_w, a.eps, static_cast<const uint16_t*>(nullptr), a.Y, a.N, a.K);
     else
-        hipLaunchKernelGGL((gemv_fused_generic_kernel<BITS, false>), grid, block, 0, s, a.W, a.codebook,
+        hipLaunchKernelGGL((gemv_fused_generic_kernel<BITS, false>), dim3(static_cast<unsigned>((a.N + 3) / 4)), block, 0, s, a.W, a.codebook,
                            static_cast<const uint32_t*>(nullptr), static_cast<const uint16_t*>(nullptr), a.X, a.norm, a.norm_w, a.eps,
                            a.residual, a.Y, a.N, a.K);
     return hipGetLastError();

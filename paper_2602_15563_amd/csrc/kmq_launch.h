@@ -53,8 +53,6 @@ int generic_splitk_slices(int64_t N, int64_t K, int layout);
 hipError_t noalloc_scratch(void** ptr);   // this GPU's KMQ_NOALLOC_SCRATCH_BYTES of library-owned scratch (kmq_gemm_smallbatch_noalloc)
 hipError_t launch_dequant(const uint32_t* W, const uint16_t* codebook, uint16_t* Wd, int64_t N,
                           int64_t K, int bits, int layout, hipStream_t s);
-
-hipError_t launch_pair_generic(const GemmArgs& a, hipStream_t s);
 hipError_t launch_fused_generic(const GemmArgs& a, hipStream_t s);   // batch 1, canonical layout, any shape; pair optional
 hipError_t launch_blockscaled_generic(const GemmArgs& a, hipStream_t s);
 hipError_t launch_dequant_blockscaled(const uint32_t* W, const uint16_t* codebook, const uint16_t* scales, uint16_t* Wd,
