@@ -330,7 +330,7 @@ kmq_status kmq_quantize_blockscaled(const uint16_t* Wdense, int64_t N, int64_t K
 /* Name of the kernel variant the launch heuristic picks for this problem
  * (static string, never NULL; "invalid" on bad arguments).  For reports.  On the canonical layout it names
  * the family that (N, K, bits) belongs to: "generic" and "blockscaled_generic" products of 1..4 bits, "lut_loop_b..."
- * batches and most block-scaled batches run on the matrix cores (kmq_mfma_canon.hip), whatever the family. */
+ * batches and most block-scaled batches run on the matrix cores (kmq_mfma_any.h), whatever the family. */
 const char* kmq_kernel_name(int64_t N, int64_t K, int bits, int M, int layout);
 
 const char* kmq_status_string(kmq_status s);
