@@ -10,7 +10,7 @@
 // words; tiled: the layout's granules, every eighth column 32j + 8q -- decodes eight weights at a time into the second operand
 // of v_mfma_f32_16x16x32_bf16 (k = the lanes' eight columns, X first), and requests the words of its next tile as soon as the
 // present ones are decoded.  D holds batch columns 4q..4q+3 of row n, so what belongs to a row (scales, centroids) is needed by
-// the lane that loads it.  The waves' partial tiles are added through LDS in wave order.  A last tile that K does not fill is one
+// the lane that loads it.  The waves' partial tiles are added through LDS, pairwise.  A last tile that K does not fill is one
 // wave's; columns past K are zeros in both operands, so that an infinite centroid meets no zero.
 //
 // Decode.  The columns of a matrix step may be any eight, as long as both operands agree:
@@ -99,11 +99,17 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
     constexpr int SVW = TC / 128;                         // words of scales per row and tile
     constexpr bool SPREAD = SC || TILED;                  // a step's columns lie in one 64-column block
     constexpr int TAB = BITS == 4 ? (SC ? 1 : RB) : 0;
+    // 1-bit canonical rows of whole words: sums of x as they are (nearly exact: no products), over the row's ones and over all
+    // columns, and the centroids in the epilogue, c0 * sum + (c1 - c0) * sum over the ones, as the table kernels do at batch 1.
+    // Rows with a non-finite centroid, and all rows where K is no multiple of 32, multiply by the centroids themselves.
+    constexpr bool SUMS = BITS == 1 && !SC && !TILED;
     static_assert(RB <= 4, "partial tiles reuse the staging memory");
     struct alignas(256) Smem {
         uint32_t ptab[TAB ? TAB : 1][TAB ? 16 : 1][64];   // 4-bit: centroid (in both halves) per entry and lane
         u32x2_t masks[16];                                // 1-bit: nibble -> four 16-bit masks
         u32x4_t xs[NW][R * 17];                           // per wave: R batch rows x 16 pieces of eight columns (+ 1 pad)
+        uint32_t cc[SUMS ? RB * 16 : 1];                  // the rows' centroids
+        float sx[SUMS ? NW : 1][16];                      // per wave: sum of its columns of X, per batch column
     };
     __shared__ Smem sm;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -112,6 +118,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
     const int64_t wpr = words_per_row(BITS, K), nblk = K / KMQ_BLOCK;
     [[maybe_unused]] const int64_t nsb = K / tiled_superblock_elems(BITS);
     const int full = static_cast<int>(K / TC), rest = static_cast<int>(K % TC);
+    [[maybe_unused]] const bool sums = SUMS && (K & 31) == 0;
+    auto finite = [](uint32_t cc) { return (cc & 0x7F80u) != 0x7F80u && (cc & 0x7F800000u) != 0x7F800000u; };
 
     // ---- what belongs to the lane's rows
     const uint32_t* wp[RB];
@@ -136,6 +144,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
             const uint32_t cc = cw[0];
             c0[r] = __builtin_amdgcn_perm(cc, cc, 0x01000100u);
             c1[r] = __builtin_amdgcn_perm(cc, cc, 0x03020302u);
+            if (sums && finite(cc)) { c0[r] = 0u; c1[r] = 0x3F803F80u; }
+            if (SUMS && wave == 0 && q == 0) sm.cc[r * 16 + n] = cc;
         } else if constexpr (BITS == 2 || BITS == 3) {
             lo0[r] = __builtin_amdgcn_perm(cw[1], cw[0], 0x06040200u);
             hi0[r] = __builtin_amdgcn_perm(cw[1], cw[0], 0x07050301u);
@@ -291,6 +301,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
     if constexpr (BITS == 1 || BITS == 4) __syncthreads();
 
     f32x4_t acc[RB];
+    [[maybe_unused]] float accx[MR] = {};                 // sums of X, batch rows 4i + q
 #pragma unroll
     for (int r = 0; r < RB; ++r) acc[r] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     [[maybe_unused]] uint32_t areg[8];                    // 4-bit: look-up addresses, byte 0 = lane * 4, byte 1 = index
@@ -443,9 +454,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
             }
             return a;
         };
+        // A tile's 256 columns are summed from zero in four chains, and their sums added to the running one: a chain over all of
+        // a wave's columns gathers more rounding than the short sums of 64 lanes do.  Results that are not the correctly rounded
+        // exact ones, of 4.7 million, one chain a wave / this / the vector kernels: 3-bit K = 4101 738 / 505 / 529, 2-bit 11008
+        // 823 / 497 / 500; batch 16.  Costs 0 to 5 % (3-bit 5001 x 4101, batch 3: 7.87 -> 7.98 us; 1-bit 4096 x 11008, batch 4, with the sums of X: 6.22 -> 6.49).
+        f32x4_t part[4];
         if constexpr (!SC) {
 #pragma unroll
-            for (int t = 0; t < 8; ++t) acc[r] = mfma(xf[t], weights(t), acc[r]);
+            for (int t = 0; t < 8; ++t) part[t >> 1] = mfma(xf[t], weights(t), t & 1 ? part[t >> 1] : f32x4_t{0.f, 0.f, 0.f, 0.f});
         } else {
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
@@ -454,9 +470,19 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
                 const uint32_t s2 = sv[r][2 * pair + (b >> 1)];
                 const float s = b & 1 ? __uint_as_float(s2 & 0xFFFF0000u) : __uint_as_float(s2 << 16);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[r][i] = fmaf(s, t[i], acc[r][i]);
+                for (int i = 0; i < 4; ++i) part[b][i] = b & 1 ? fmaf(s, t[i], part[b - 1][i]) : s * t[i];
             }
         }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[r][i] += SC ? part[1][i] + part[3][i] : (part[0][i] + part[1][i]) + (part[2][i] + part[3][i]);
+    };
+    auto sum_x = [&] {                                    // this lane's pieces of a tile
+#pragma unroll
+        for (int i = 0; i < MR; ++i)
+#pragma unroll
+            for (int hh = 0; hh < HALVES; ++hh)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) accx[i] = dot2_bf16(0x3F803F80u, xr[hh][i][j], accx[i]);
     };
 
     // one tile; `more`: another one follows, its operands are requested as their registers become free
@@ -471,6 +497,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
                 stage(2 * pair + 1);
                 fragments(xm, 1);
                 load_x_tail(full, false);
+            }
+            if constexpr (SUMS) {
+                if (sums) sum_x();
             }
             stage(2 * pair);
             fragments(xf, 0);
@@ -497,7 +526,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
         step(std::false_type{}, std::true_type{});
     }
 
-    // ---- the waves' partial tiles: [batch column][row, padded to 17 per block], added in wave order
+    // ---- the waves' partial tiles: [batch column][row, padded to 17 per block], added pairwise
     float* const part = reinterpret_cast<float*>(xs);
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
@@ -506,14 +535,36 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
             for (int j = 0; j < 4; ++j) part[(r * R + 4 * q + j) * 17 + n] = acc[r][j];
         }
     }
+    if constexpr (SUMS) {
+#pragma unroll
+        for (int i = 0; i < MR; ++i) {
+            const float t = group_sum<16>(accx[i]);
+            if (n == 15) sm.sx[wave][4 * i + q] = t;
+        }
+    }
     __syncthreads();
+    auto over_waves = [](auto&& of) {
+        float v[NW];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) v[k] = of(k);
+#pragma unroll
+        for (int w = 1; w < NW; w *= 2)
+#pragma unroll
+            for (int k = 0; k < NW; k += 2 * w) v[k] += v[k + w];
+        return v[0];
+    };
     for (int o = threadIdx.x; o < RB * R * 16; o += NW * 64) {
         const int m = o / (RB * 16), nl = o % (RB * 16);  // consecutive threads: consecutive rows
         const int64_t row = row0 + nl;
         if (m < M && row < N) {
-            float s = 0.f;
-#pragma unroll
-            for (int k = 0; k < NW; ++k) s += reinterpret_cast<const float*>(sm.xs[k])[((nl >> 4) * R + m) * 17 + (nl & 15)];
+            float s = over_waves([&](int k) { return reinterpret_cast<const float*>(sm.xs[k])[((nl >> 4) * R + m) * 17 + (nl & 15)]; });
+            if constexpr (SUMS) {
+                const uint32_t cc = sm.cc[nl];
+                if (sums && finite(cc)) {
+                    const float c0f = bf16_to_f32(cc & 0xFFFFu), d = bf16_to_f32(cc >> 16) - c0f;
+                    s = fmaf(d, s, c0f * over_waves([&](int k) { return sm.sx[k][m]; }));
+                }
+            }
             Y[static_cast<int64_t>(m) * N + row] = f32_to_bf16(s);
         }
     }
