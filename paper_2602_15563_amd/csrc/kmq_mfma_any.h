@@ -260,7 +260,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
 #pragma unroll
             for (int b = 0; b < 2 * SVW; ++b) {
                 const int64_t at = static_cast<int64_t>(tile) * (TC / KMQ_BLOCK) + b;
-                const uint32_t s = sp[r][at < nblk ? at : nblk - 1];
+                const uint32_t s = at < nblk ? sp[r][at] : 0u;      // (an infinity times a missing block's zero would be a NaN)
                 if (b & 1) sv[r][b >> 1] |= s << 16;
                 else sv[r][b >> 1] = s;
             }

@@ -86,3 +86,29 @@ def test_infinite_centroids(gpu, bits, layout, K, M):
     assert np.all(got[:, 8:] == 0x7F80)
     f = synth.bf16_to_f64
     assert np.all(np.abs(f(got[:, :8]) - f(want[:, :8])) <= 2.0 ** -7 * np.abs(f(want[:, :8])) + 1e-3)
+
+
+@pytest.mark.parametrize("layout,blocks", [(kmq.LAYOUT_CANONICAL, 1), (kmq.LAYOUT_CANONICAL, 5), (kmq.LAYOUT_CANONICAL, 38), (kmq.LAYOUT_CANONICAL, 39), (TILED, 6)])
+@pytest.mark.parametrize("bits", (1, 2, 3, 4))
+@pytest.mark.parametrize("M", (1, 9))
+def test_infinite_block_scale(gpu, bits, layout, blocks, M):
+    """The scale of a row's last block is an infinity, and the last tile has room for blocks that the row does not have: they
+    contribute nothing, so that rows of positive weights and x sum to that infinity and the others stay as they are."""
+    K = blocks * 64
+    if K % (SB[bits] if layout else 64):
+        pytest.skip("not a whole super-block")
+    N, seed = 33, 90 + bits
+    p, cb = oracle.pack(synth.make_indices(seed, 0, N, K, bits), bits), synth.make_shared_codebook(seed, 0, bits) & 0x7FFF
+    sc, X = synth.make_scales(seed, 0, N, K) & 0x7FFF, (synth.make_x(seed, 0, M, K) & 0x7FFF).astype(np.uint16) | 0x3000
+    stored = gpu.dev(kmq.repack(p, K, bits, TILED) if layout else p)
+
+    def product(scales):
+        Y = gpu.dev(np.zeros((M, N), np.uint16))
+        kmq.gemm_smallbatch_blockscaled(stored, gpu.dev(cb), gpu.dev(scales), gpu.dev(X), Y, N, K, M, bits, layout)
+        return gpu.host_u16(Y)
+
+    want = product(sc)
+    sc[3::2, -1] = 0x7F80
+    got = product(sc)
+    assert np.all(got[:, 3::2] == 0x7F80)
+    assert np.array_equal(got[:, [0, 1] + list(range(2, N, 2))], want[:, [0, 1] + list(range(2, N, 2))])
