@@ -485,6 +485,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
                 for (int j = 0; j < 4; ++j) accx[i] = dot2_bf16(0x3F803F80u, xr[hh][i][j], accx[i]);
     };
 
+    // The pieces pass between lanes of one wave, whose LDS instructions run in order: the compiler has to keep that order.
+    auto in_wave = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+    auto exchange = [&](u32x4_t (&f)[8], int hh, int piece) {
+        stage(piece);
+        in_wave();
+        fragments(f, hh);
+        in_wave();
+    };
     // one tile; `more`: another one follows, its operands are requested as their registers become free
     auto step = [&](auto more, auto tail) {
         const int next = tile + NW;
@@ -492,19 +500,15 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
         for (int pair = 0; pair < PAIRS; ++pair) {
             if constexpr (decltype(tail)::value) {
                 load_x_tail(full, true);
-                stage(2 * pair);
-                fragments(xm, 0);
-                stage(2 * pair + 1);
-                fragments(xm, 1);
+                exchange(xm, 0, 2 * pair);
+                exchange(xm, 1, 2 * pair + 1);
                 load_x_tail(full, false);
             }
             if constexpr (SUMS) {
                 if (sums) sum_x();
             }
-            stage(2 * pair);
-            fragments(xf, 0);
-            stage(2 * pair + 1);
-            fragments(xf, 1);
+            exchange(xf, 0, 2 * pair);
+            exchange(xf, 1, 2 * pair + 1);
             if constexpr (decltype(more)::value) {
                 if (pair == PAIRS - 1) load_x(next);
             }
