@@ -457,7 +457,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
         // A tile's 256 columns are summed from zero in four chains, and their sums added to the running one: a chain over all of
         // a wave's columns gathers more rounding than the short sums of 64 lanes do.  Results that are not the correctly rounded
         // exact ones, of 4.7 million, one chain a wave / this / the vector kernels: 3-bit K = 4101 738 / 505 / 529, 2-bit 11008
-        // 823 / 497 / 500; batch 16.  Costs 0 to 5 % (3-bit 5001 x 4101, batch 3: 7.87 -> 7.98 us; 1-bit 4096 x 11008, batch 4, with the sums of X: 6.22 -> 6.49).
+        // 823 / 497 / 500; batch 16.  Level in time (3-bit 5001 x 4101, batch 16: 11.6 / 11.7 us),
+        // 1-bit rows with the sums of X aside (4096 x 11008, batch 4: 6.2 / 6.5).
         f32x4_t part[4];
         if constexpr (!SC) {
 #pragma unroll
@@ -511,6 +512,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
             exchange(xf, 1, 2 * pair + 1);
             if constexpr (decltype(more)::value) {
                 if (pair == PAIRS - 1) load_x(next);
+                __builtin_amdgcn_sched_barrier(0);        // (the scheduler would put these loads behind the decoding)
             }
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
