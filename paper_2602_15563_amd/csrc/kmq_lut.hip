@@ -574,7 +574,8 @@ struct LutEntry {
 // the workgroups (2-bit 2048 x 6144, batch 2: 4.4 / 4.9; 2048 x 1536, batch 4: 3.1 / 3.2), and an odd batch pays for a column it does not
 // have: up to 5 that outweighs the gain for many shapes (3-bit 2048 x 14336: 16.3 / 18.0), at 7 it is even or better.  At 1 bit a
 // lookup brings four weights and 48 or 64 activation registers a column leave two or three waves (14336 x 8192, batch 4:
-// 22.0 / 24.0); the 8-byte loads of the 2-bit kernel for few rows do not gain either (9216 x 14336, batch 13: 121 / 131).  Four columns
+// 22.0 / 24.0); the 8-byte loads of the 2-bit kernel for few rows do not gain either (9216 x 14336, batch 13: 121 / 131), nor do the
+// three waves along K of the 4-bit one (1024 x 6144, batch 7: 8.6 / 10.0; 8192 x 6144: 50.0 / 54.3; even batches -2 % to +5 %).  Four columns
 // were slower than two nearly everywhere (2-bit 4096 x 14336, batch 4: 16.4): one workgroup a CU, whose loads nothing hides.
 static bool lut_two_columns(const GemmArgs& a) {
 #ifdef KMQ_TUNING
@@ -631,7 +632,7 @@ static void launch_lut(const GemmArgs& a, hipStream_t s) {
                                a.W, a.codebook, a.X, a.Y, a.N, a.scales, nullptr, nullptr, nullptr, 0.f, nullptr, a.M);
         };
         using std::integral_constant;
-        if constexpr (BITS > 1 && !(BITS == 2 && G == 2)) {
+        if constexpr (BITS > 1 && !(BITS == 2 && G == 2) && !(BITS == 4 && NWK == 3)) {
             constexpr int XR = G * (BITS == 4 ? 32 : 16) / BITS;      // activation registers of a column
             if (lut_two_columns(a)) {
                 launch(integral_constant<int, 2>{}, integral_constant<int, XR <= 24 ? 5 : 4>{});
