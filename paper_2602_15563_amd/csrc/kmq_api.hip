@@ -75,19 +75,56 @@ Plan make_plan(int64_t N, int64_t K, int bits, int M, int layout, bool scaled) {
     return Plan{kVariantGeneric, -1, 0, "generic"};
 }
 
-// Whether the matrix-core kernel for any row length (kmq_mfma_any.h) takes a product whose plan is `p`: on the tiled layout
-// where mfma_takes leaves it, on the canonical one as follows.  It decodes every weight once
-// for the whole batch, so it replaces the shape-agnostic kernels at every batch and the table kernels that would run one
-// workgroup per batch column.  Measured (us), before / with it:
-//   shape-agnostic, per row: 3-bit 5001 x 4101, batch 1 / 3 / 16: 41.0 / 111.0 / 567 -> 7.5 / 8.1 / 14.7; 1-bit 1024 x 1111:
-//     5.5 / 11.4 / 64.5 -> 3.1 / 3.1 / 5.6
-//   K in rounds, batch >= 2: 2-bit 4096 x 11008, batch 2 / 16: 8.5 / 45.3 -> 5.7 / 12.3; 4-bit 2048 x 1280: 3.9 / 12.7 -> 3.8 / 4.3
-//     (batch 1 stays: 1-bit 4096 x 11008 4.9 against 5.2, 3-bit 7.9 against 8.2)
-//   block-scaled, no table kernel: 4-bit 4096 x 2560, batch 1 / 16: 5.6 / 45.7 -> 5.7 / 6.7; 1-bit 5.1 / 45.5 -> 3.4 / 5.0
-//   block-scaled, table kernel: 4-bit 8192 x 8192, batch 3 / 16: 23.9 / 106 -> 14.0 / 20.0; 1-bit 11.3 / 48.5 -> 8.7 / 17.9; at
-//     batch 2 it loses about as often as it wins (2-bit 14336 x 4096 8.6 against 9.2, 4-bit 15.8 against 13.4), and small
-//     matrices start later with it (3-bit 2048 x 2048, batch 3 / 4 / 8: 3.7 / 3.8 / 4.8 against 4.1 / 4.2 / 4.5)
+// Where the matrix-core kernel for any row length (kmq_mfma_any.h) takes a product from the vector kernels of the canonical layout.
+// It decodes every weight once for the whole batch, so a shape-agnostic per-row product (K no multiple of 32, or a batch on few
+// long rows) is always its (3-bit 5001 x 4101, batch 1 / 3 / 16: 41.0 / 111.0 / 567 -> 7.6 / 8.0 / 11.8 us).  The other vector
+// kernels spread a product over more workgroups than one per 16 rows: with at most 256 blocks of 16 rows (one a CU) it takes a
+// time that K, the batch group and the bit-width set, whatever the number of rows, and theirs grows with N * K * M from
+// a floor.  Both are estimated from straight lines through measurements (us, vector / this):
+//   K in rounds, batch >= 2: 4-bit 13824 columns, batch 8: 64 rows 4.4 / 11.0, 512 14.4 / 11.9, 2048 28.7 / 12.5; 1-bit 6912
+//     columns, batch 4: 512 rows 4.1 / 5.0, 2048 7.7 / 4.9
+//   block-scaled, batch 1: 4-bit 3648 columns: 1024 rows 3.8 / 7.1, 4096 7.2 / 7.6; 1-bit 11008 columns: 1024 5.9 / 6.2, 4096
+//     13.2 / 6.8
+//   block-scaled with a table kernel, batch 8: 4-bit 8192 columns: 256 rows 5.0 / 10.3, 1024 10.0 / 10.4, 4096 29.9 / 11.0
+// With more rows it is always faster from batch 2 (K in rounds; 2-bit 4096 x 11008, batch 16: 45.3 -> 12.3), at every batch
+// (block-scaled without a table kernel) and from batch 3 on (with one; 4-bit 8192 x 8192, batch 3: 23.9 -> 14.0).
 // Table kernels specialised on K keep per-row batches: their columns are the batch-1 results bit for bit.
+constexpr int64_t kAnyOneRound = 256 * 16;
+struct AnyCost { double start, per_k[3]; };               // us; us per 1000 columns at batches up to 4, 8, 16
+static double any_length_us(int64_t K, int bits, int M, bool scaled) {
+    static const AnyCost cost[2][4] = {{{3.0, {0.30, 0.45, 0.72}}, {2.8, {0.26, 0.45, 0.75}}, {2.8, {0.45, 0.58, 0.85}}, {3.6, {0.53, 0.68, 0.95}}},
+                                       {{2.7, {0.38, 0.45, 0.62}}, {2.9, {0.45, 0.53, 0.68}}, {2.6, {0.65, 0.73, 0.90}}, {4.1, {0.70, 0.77, 0.90}}}};
+    static const double tail[3] = {0.8, 1.3, 2.5};        // a last tile that K does not fill
+    const int g = M <= 4 ? 0 : M <= 8 ? 1 : 2;
+    const AnyCost& c = cost[scaled ? 1 : 0][bits - 1];
+    return c.start + c.per_k[g] * 1e-3 * static_cast<double>(K) + (K % 256 ? tail[g] : 0.0);
+}
+static double from_floor(double floor, double start, double each, double work) {
+    const double t = start + each * work;
+    return t > floor ? t : floor;
+}
+static double millions(int64_t N, int64_t K, int M) { return 1e-6 * static_cast<double>(N) * static_cast<double>(K) * M; }
+// against the table kernel that walks K in rounds
+static bool any_beats_rounds(int64_t N, int64_t K, int bits, int M) {
+    static const double each[4] = {0.10, 0.105, 0.12, 0.19};
+    const int64_t k = K > 2048 ? K : 2048;                // (shorter rows cost it as much; large matrices get a better launch shape)
+    const double work = millions(N, k, M) * (N * K > (int64_t(24) << 20) ? 0.75 : 1.0);
+    return M >= 2 && (N > kAnyOneRound || any_length_us(K, bits, M, false) < from_floor(bits == 3 ? 4.3 : 4.0, 2.5, each[bits - 1], work));
+}
+// against the specialised table kernels, block-scaled
+static bool any_beats_scaled_table(int64_t N, int64_t K, int bits, int M) {
+    static const double each[4] = {0.045, 0.055, 0.07, 0.105};
+    return M >= 3 && (N > kAnyOneRound || any_length_us(K, bits, M, true) < from_floor(3.7, 2.0, each[bits - 1], millions(N, K, M)));
+}
+// against a wave per row and a lane per block (from batch 4 on its columns' latencies alone are longer)
+static bool any_beats_block_generic(int64_t N, int64_t K, int bits, int M) {
+    if (bits > 4) return false;
+    if (M >= 4 || N > kAnyOneRound) return true;
+    const double rounds = static_cast<double>((K / KMQ_BLOCK + 63) / 64);
+    const double latency = 2.6 + rounds * (M == 1 ? 0.9 : 2.6 + 0.9 * (M - 2));
+    return any_length_us(K, bits, M, true) < from_floor(latency, 1.9, 0.28 * (1 + 0.7 * (M - 1)), millions(N, K, 1));
+}
+// Whether it takes a product whose plan is `p` (tiled layout: where mfma_takes leaves it).
 static bool canon_takes(const GemmArgs& a, const Plan& p) {
     if (a.layout == KMQ_LAYOUT_ROWLANE || a.bits > 4 || p.workspace_bytes > 0) return false;
 #ifdef KMQ_TUNING
@@ -95,11 +132,11 @@ static bool canon_takes(const GemmArgs& a, const Plan& p) {
     if (v && v[0] != '2') return v[0] == '1';
 #endif
     switch (p.variant) {
-        case kVariantGeneric:
-        case kVariantBlockGeneric: return true;
-        case kVariantLutLoop: return a.M >= 2;
+        case kVariantGeneric: return true;
+        case kVariantLutLoop: return any_beats_rounds(a.N, a.K, a.bits, a.M);
+        case kVariantBlockGeneric: return any_beats_block_generic(a.N, a.K, a.bits, a.M);
         case kVariantMfma: return !mfma_takes(a.N, a.K, a.bits, a.M, a.scales != nullptr);
-        case kVariantPerColumn: return a.scales && a.M >= (a.N * a.K > (int64_t(1) << 23) ? 3 : 5);
+        case kVariantPerColumn: return a.scales && any_beats_scaled_table(a.N, a.K, a.bits, a.M);
         default: return false;
     }
 }

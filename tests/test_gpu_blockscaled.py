@@ -193,3 +193,14 @@ def test_dequant_blockscaled_errors(gpu):
         with pytest.raises(kmq.KmqError) as e:
             call()
         assert e.value.status == status
+
+
+@pytest.mark.parametrize("bits", (1, 2, 3, 4))
+@pytest.mark.parametrize("N,K", [(1, 320), (333, 2560), (70, 4160), (1000, 3648)])
+def test_single_columns_on_few_rows_take_a_lane_per_block(gpu, bits, N, K):
+    """Where a wave per row is the faster kernel.  Its sums start from the first block of a lane, so that a row with one
+    non-zero scale is that block's 64-element sum times the scale; and its K = 4160 gives lane 0 a second block."""
+    idx, cb, sc, X = _case(23 * bits + N + K, N, K, bits, 1)
+    p = oracle.pack(idx, bits)
+    Yg = gpu.run_gemm_blockscaled(gpu.dev(p), gpu.dev(cb), gpu.dev(sc), X, N, K, bits)
+    gpu.check_blockscaled_against_oracle(Yg, p, cb, sc, X, K, bits, label=f"b{bits} {N}x{K}")

@@ -91,3 +91,14 @@ def test_loop_kernel_is_deterministic(gpu):
     a = gpu.run_gemm(pd, cd, X, N, K, bits)
     for _ in range(3):
         assert np.array_equal(a, gpu.run_gemm(pd, cd, X, N, K, bits))
+
+
+@pytest.mark.parametrize("bits,N,K,M", [(1, 64, 6912, 8), (2, 122, 13088, 16), (3, 94, 5984, 6), (4, 77, 6240, 6), (4, 1024, 6912, 2)])
+def test_batches_on_few_rows_keep_the_loop_kernel(gpu, bits, N, K, M):
+    """Where it is the faster one: its columns are the batch-1 results bit for bit, the matrix cores' would not be."""
+    idx, cb, X = _case(9 * bits + N + K + M, N, K, bits, M)
+    pd, cd = gpu.dev(kmq.pack(idx, bits)), gpu.dev(cb)
+    Yg = gpu.run_gemm(pd, cd, X, N, K, bits)
+    gpu.check_against_oracle(Yg, oracle.pack(idx, bits), cb, X, K, bits, label=f"b{bits} {N}x{K} M{M}")
+    for m in range(M):
+        assert np.array_equal(Yg[m], gpu.run_gemm(pd, cd, X[m], N, K, bits)[0]), f"column {m}"
