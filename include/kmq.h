@@ -154,10 +154,9 @@ size_t kmq_workspace_bytes(int64_t N, int64_t K, int bits, int M, int layout);
  * Equivalent to kmq_gemm_smallbatch with M = 1.
  * Kernels on the canonical layout (kmq_kernel_name tells which one a shape gets): bits 1..4 with K one of
  * the row lengths the library has a fully unrolled table kernel for ("lut_b..."), any other K % 32 == 0 up
- * to 24576 through the table kernel that walks a row in rounds ("lut_loop_b..."), everything else (K not a
- * multiple of 32 or beyond 24576, bits = 8) through the shape-agnostic kernel ("generic", "generic_splitk").
- * The names are those of the launch plan: where it says "generic" or "blockscaled_generic" at 1..4 bits, "lut_loop_b..." at a
- * batch of two or more, or "mfma_b..." for rows that do not split evenly, the matrix-core kernel for any row length runs. */
+ * to 24576 through the table kernel that walks a row in rounds ("lut_loop_b..."), any other K through the matrix-core
+ * kernel for any row length ("mfma_any_b..."); 8 bits, and few long rows, through the shape-agnostic kernel ("generic",
+ * "generic_splitk"). */
 kmq_status kmq_gemv(const uint32_t* W, const uint16_t* codebook, const uint16_t* x, uint16_t* y,
                     int64_t N, int64_t K, int bits, int layout,
                     void* workspace, size_t workspace_bytes, void* hip_stream);
@@ -171,7 +170,9 @@ kmq_status kmq_gemv(const uint32_t* W, const uint16_t* codebook, const uint16_t*
  * KMQ_LAYOUT_ROWLANE serves M = 1..4 on the vector units, each weight dequantised once
  * (M > 4: one launch per four columns); on the canonical layout row lengths with a specialised
  * table kernel look the weights up again for every column or pair of columns, in one launch, and everything else takes
- * a matrix-core kernel as well. */
+ * a matrix-core kernel as well, but for few rows.  A column of a batch is summed in the order of its kernel, which may be
+ * another one at another M: where kmq_kernel_name gives the same "lut_..." name as at M = 1, it is the
+ * batch-1 result bit for bit.  Repeats of one call are. */
 kmq_status kmq_gemm_smallbatch(const uint32_t* W, const uint16_t* codebook, const uint16_t* X,
                                uint16_t* Y, int64_t N, int64_t K, int M, int bits, int layout,
                                void* workspace, size_t workspace_bytes, void* hip_stream);
@@ -328,9 +329,7 @@ kmq_status kmq_quantize_blockscaled(const uint16_t* Wdense, int64_t N, int64_t K
                                     void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /* Name of the kernel variant the launch heuristic picks for this problem
- * (static string, never NULL; "invalid" on bad arguments).  For reports.  On the canonical layout it names
- * the family that (N, K, bits) belongs to: "generic" and "blockscaled_generic" products of 1..4 bits, "lut_loop_b..."
- * batches and most block-scaled batches run on the matrix cores (kmq_mfma_any.h), whatever the family. */
+ * (static string, never NULL; "invalid" on bad arguments).  For reports. */
 const char* kmq_kernel_name(int64_t N, int64_t K, int bits, int M, int layout);
 
 const char* kmq_status_string(kmq_status s);

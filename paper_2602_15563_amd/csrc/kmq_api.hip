@@ -27,54 +27,6 @@ static bool per_column_faster(int M) {
     return M >= 2 && M <= cap;
 }
 
-// Launch-shape heuristic (the paper autotunes chunk shapes per problem, App. E
-// "Kernel implementations"; here the choice is a static function of the shape).
-Plan make_plan(int64_t N, int64_t K, int bits, int M, int layout, bool scaled) {
-    Plan p{kVariantInvalid, -1, 0, "invalid"};
-    if (!bits_valid(bits) || !dims_valid(N, K) || M < 1 || M > KMQ_MAX_BATCH) return p;
-    if (layout != KMQ_LAYOUT_CANONICAL && layout != KMQ_LAYOUT_TILED && layout != KMQ_LAYOUT_ROWLANE) return p;
-    if (layout == KMQ_LAYOUT_ROWLANE) {
-        if (scaled || !rowlane_valid(bits, K) || !rowlane_has_kernel(K, bits, M)) return p;
-        static const char* const names[2][2] = {{"rowlane_b1", "rowlane_b2"}, {"rowlane_loop_b1", "rowlane_loop_b2"}};
-        return Plan{kVariantRowlane, -1, 0, names[rowlane_loops(K, bits) ? 1 : 0][bits - 1]};
-    }
-    if (scaled) {
-        if (K % KMQ_BLOCK != 0) return p;
-        if (layout == KMQ_LAYOUT_TILED) {
-            // matrix-core kernel; its LDS holds the scales of at most 256 blocks of K per row
-            if (!tiled_valid(bits, K) || K > 256 * KMQ_BLOCK) return p;
-            static const char* const names[4] = {"mfma_sc_b1", "mfma_sc_b2", "mfma_sc_b3", "mfma_sc_b4"};
-            return Plan{kVariantMfma, -1, 0, names[bits - 1]};
-        }
-        if (M == 1 || per_column_faster(M)) {
-            const int l = lut_find(N, K, bits, layout, true);
-            if (l >= 0) return Plan{M == 1 ? kVariantLut : kVariantPerColumn, l, 0, lut_name(l)};
-        }
-        return Plan{kVariantBlockGeneric, -1, 0, "blockscaled_generic"};
-    }
-    if (layout == KMQ_LAYOUT_TILED && !tiled_valid(bits, K)) return p;
-    if (layout == KMQ_LAYOUT_TILED) {
-        static const char* const names[4] = {"mfma_b1", "mfma_b2", "mfma_b3", "mfma_b4"};
-        if (mfma_kslice_has_kernel(N, K, bits)) return Plan{kVariantMfma, -1, 0, bits == 2 ? "mfma_kslice_b2" : "mfma_kslice_b3"};
-        return Plan{kVariantMfma, -1, 0, names[bits - 1]};
-    }
-    bool use_loop = true, use_table = true;
-#ifdef KMQ_TUNING
-    static const char* const loop_env = std::getenv("KMQ_LOOP");      // sweeps only: 0 = never, 2 = instead of the specialised kernels
-    if (loop_env) { use_loop = loop_env[0] != '0'; use_table = loop_env[0] != '2'; }
-#endif
-    if (use_table && (M == 1 || per_column_faster(M))) {
-        const int l = lut_find(N, K, bits, layout);
-        if (l >= 0) return Plan{M == 1 ? kVariantLut : kVariantPerColumn, l, 0, lut_name(l)};
-    }
-    const int slices = generic_splitk_slices(N, K, layout);
-    if (slices > 1)
-        return Plan{kVariantGeneric, slices, static_cast<size_t>(slices) * M * N * sizeof(float), "generic_splitk"};
-    if (use_loop && (M == 1 || per_column_faster(M)) && lut_loop_has_kernel(N, K, bits, layout))
-        return Plan{kVariantLutLoop, -1, 0, lut_loop_name(bits)};
-    return Plan{kVariantGeneric, -1, 0, "generic"};
-}
-
 // Where the matrix-core kernel for any row length (kmq_mfma_any.h) takes a product from the vector kernels of the canonical layout.
 // It decodes every weight once for the whole batch, so a shape-agnostic per-row product (K no multiple of 32, or a batch on few
 // long rows) is always its (3-bit 5001 x 4101, batch 1 / 3 / 16: 41.0 / 111.0 / 567 -> 7.6 / 8.0 / 11.8 us).  The other vector
@@ -124,21 +76,62 @@ static bool any_beats_block_generic(int64_t N, int64_t K, int bits, int M) {
     const double latency = 2.6 + rounds * (M == 1 ? 0.9 : 2.6 + 0.9 * (M - 2));
     return any_length_us(K, bits, M, true) < from_floor(latency, 1.9, 0.28 * (1 + 0.7 * (M - 1)), millions(N, K, 1));
 }
-// Whether it takes a product whose plan is `p` (tiled layout: where mfma_takes leaves it).
-static bool canon_takes(const GemmArgs& a, const Plan& p) {
-    if (a.layout == KMQ_LAYOUT_ROWLANE || a.bits > 4 || p.workspace_bytes > 0) return false;
-#ifdef KMQ_TUNING
-    const char* const v = std::getenv("KMQ_CANON");
-    if (v && v[0] != '2') return v[0] == '1';
-#endif
-    switch (p.variant) {
-        case kVariantGeneric: return true;
-        case kVariantLutLoop: return any_beats_rounds(a.N, a.K, a.bits, a.M);
-        case kVariantBlockGeneric: return any_beats_block_generic(a.N, a.K, a.bits, a.M);
-        case kVariantMfma: return !mfma_takes(a.N, a.K, a.bits, a.M, a.scales != nullptr);
-        case kVariantPerColumn: return a.scales && any_beats_scaled_table(a.N, a.K, a.bits, a.M);
-        default: return false;
+static Plan any_length_plan(int bits, bool scaled) {
+    static const char* const names[2][4] = {{"mfma_any_b1", "mfma_any_b2", "mfma_any_b3", "mfma_any_b4"},
+                                            {"mfma_any_sc_b1", "mfma_any_sc_b2", "mfma_any_sc_b3", "mfma_any_sc_b4"}};
+    return Plan{kVariantMfmaAny, -1, 0, names[scaled ? 1 : 0][bits - 1]};
+}
+
+// Launch-shape heuristic (the paper autotunes chunk shapes per problem, App. E
+// "Kernel implementations"; here the choice is a static function of the shape).
+Plan make_plan(int64_t N, int64_t K, int bits, int M, int layout, bool scaled) {
+    Plan p{kVariantInvalid, -1, 0, "invalid"};
+    if (!bits_valid(bits) || !dims_valid(N, K) || M < 1 || M > KMQ_MAX_BATCH) return p;
+    if (layout != KMQ_LAYOUT_CANONICAL && layout != KMQ_LAYOUT_TILED && layout != KMQ_LAYOUT_ROWLANE) return p;
+    if (layout == KMQ_LAYOUT_ROWLANE) {
+        if (scaled || !rowlane_valid(bits, K) || !rowlane_has_kernel(K, bits, M)) return p;
+        static const char* const names[2][2] = {{"rowlane_b1", "rowlane_b2"}, {"rowlane_loop_b1", "rowlane_loop_b2"}};
+        return Plan{kVariantRowlane, -1, 0, names[rowlane_loops(K, bits) ? 1 : 0][bits - 1]};
     }
+    if (scaled) {
+        if (K % KMQ_BLOCK != 0) return p;
+        if (layout == KMQ_LAYOUT_TILED) {
+            // matrix-core kernel; its LDS holds the scales of at most 256 blocks of K per row
+            if (!tiled_valid(bits, K) || K > 256 * KMQ_BLOCK) return p;
+            static const char* const names[4] = {"mfma_sc_b1", "mfma_sc_b2", "mfma_sc_b3", "mfma_sc_b4"};
+            if (!mfma_takes(N, K, bits, M, true)) return any_length_plan(bits, true);
+            return Plan{kVariantMfma, -1, 0, names[bits - 1]};
+        }
+        if (M == 1 || per_column_faster(M)) {
+            const int l = lut_find(N, K, bits, layout, true);
+            if (l >= 0 && any_beats_scaled_table(N, K, bits, M)) return any_length_plan(bits, true);
+            if (l >= 0) return Plan{M == 1 ? kVariantLut : kVariantPerColumn, l, 0, lut_name(l)};
+        }
+        if (any_beats_block_generic(N, K, bits, M)) return any_length_plan(bits, true);
+        return Plan{kVariantBlockGeneric, -1, 0, "blockscaled_generic"};
+    }
+    if (layout == KMQ_LAYOUT_TILED && !tiled_valid(bits, K)) return p;
+    if (layout == KMQ_LAYOUT_TILED) {
+        static const char* const names[4] = {"mfma_b1", "mfma_b2", "mfma_b3", "mfma_b4"};
+        if (!mfma_takes(N, K, bits, M, false)) return any_length_plan(bits, false);
+        if (mfma_kslice_has_kernel(N, K, bits)) return Plan{kVariantMfma, -1, 0, bits == 2 ? "mfma_kslice_b2" : "mfma_kslice_b3"};
+        return Plan{kVariantMfma, -1, 0, names[bits - 1]};
+    }
+    bool use_loop = true, use_table = true;
+#ifdef KMQ_TUNING
+    static const char* const loop_env = std::getenv("KMQ_LOOP");      // sweeps only: 0 = never, 2 = instead of the specialised kernels
+    if (loop_env) { use_loop = loop_env[0] != '0'; use_table = loop_env[0] != '2'; }
+#endif
+    if (use_table && (M == 1 || per_column_faster(M))) {
+        const int l = lut_find(N, K, bits, layout);
+        if (l >= 0) return Plan{M == 1 ? kVariantLut : kVariantPerColumn, l, 0, lut_name(l)};
+    }
+    const int slices = generic_splitk_slices(N, K, layout);
+    if (slices > 1)
+        return Plan{kVariantGeneric, slices, static_cast<size_t>(slices) * M * N * sizeof(float), "generic_splitk"};
+    if (use_loop && (M == 1 || per_column_faster(M)) && lut_loop_has_kernel(N, K, bits, layout) && !any_beats_rounds(N, K, bits, M))
+        return Plan{kVariantLutLoop, -1, 0, lut_loop_name(bits)};
+    return bits <= 4 ? any_length_plan(bits, false) : Plan{kVariantGeneric, -1, 0, "generic"};
 }
 
 // Text of the last HIP error a launch reported on this thread ("" if none).
@@ -180,11 +173,12 @@ static kmq_status check_and_run(const GemmArgs& a_in, void* stream, bool library
     if (plan.workspace_bytes > 0 && (!a.workspace || a.workspace_bytes < plan.workspace_bytes)) return KMQ_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = hipSuccess;
-    if (canon_takes(a, plan)) {
-        static hipError_t (*const launch[4])(const GemmArgs&, hipStream_t) = {launch_canon_b1, launch_canon_b2, launch_canon_b3, launch_canon_b4};
-        return hip_status(launch[a.bits - 1](a, s));
-    }
     switch (plan.variant) {
+        case kVariantMfmaAny: {
+            static hipError_t (*const launch[4])(const GemmArgs&, hipStream_t) = {launch_canon_b1, launch_canon_b2, launch_canon_b3, launch_canon_b4};
+            e = launch[a.bits - 1](a, s);
+            break;
+        }
         case kVariantMfma: e = launch_mfma(a, s); break;
         case kVariantRowlane: e = launch_rowlane(a, s); break;
         case kVariantLut: e = launch_lut_entry(plan.table_index, a, s); break;

@@ -30,9 +30,10 @@ struct GemmArgs {
 // Kernel variants the heuristic can pick (kmq_kernel_name reports them).
 enum Variant {
     kVariantInvalid = 0,
-    kVariantGeneric,     // any shape: wave per row, fp32 codebook in LDS
+    kVariantGeneric,     // 8 bits, and few long rows (split over K): wave per row, fp32 codebook in LDS
     kVariantLut,         // batch 1, K from a table: hand-scheduled LDS-table kernel
-    kVariantMfma,        // tiled layout, batch 1..16: matrix-core kernel
+    kVariantMfma,        // tiled layout: matrix-core kernels for rows that split evenly over the waves
+    kVariantMfmaAny,     // canonical or tiled layout, 1..4 bits: matrix-core kernel for any row length
     kVariantBlockGeneric,  // block-scaled format, any shape with K % 64 == 0
     kVariantPerColumn,     // canonical layout, batch > 1, shape with a batch-1 table kernel: that kernel over a (row group, column) grid
     kVariantRowlane,       // row-lane layout, batch 1..4: lane-per-row table kernel, activations through DPP broadcasts

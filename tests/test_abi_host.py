@@ -228,8 +228,9 @@ def test_argument_errors_are_reported_before_any_launch():
     assert lib.kmq_gemv_blockscaled(W, cb, None, x, y, 4, 64, 2, 0, None, 0, None) == 1
     assert kmq.kernel_name_blockscaled(4, 96, 2, 1) == "invalid"
     assert kmq.kernel_name_blockscaled(8192, 8192, 4, 1).startswith("lut_sc_b4")
-    assert kmq.kernel_name_blockscaled(8192, 8192, 4, 16).startswith("lut_sc_b4")    # canonical batch: table kernel over (row group, column)
-    assert kmq.kernel_name_blockscaled(100, 8192 + 64, 4, 16) == "blockscaled_generic"
+    assert kmq.kernel_name_blockscaled(8192, 8192, 4, 16) == "mfma_any_sc_b4"        # canonical batch: matrix cores
+    assert kmq.kernel_name_blockscaled(100, 8192 + 64, 4, 16) == "mfma_any_sc_b4"
+    assert kmq.kernel_name_blockscaled(100, 8192 + 64, 8, 16) == "blockscaled_generic"
     assert lib.kmq_gemv_bf16(None, x, y, 4, 64, None) == 1 and lib.kmq_gemv_bf16(W, x, y, 4, 40000, None) == 3
     assert lib.kmq_gemv_bf16(W + 2, x, y, 4, 64, None) == 4 and lib.kmq_gemv_bf16(W, x, y, 0, 64, None) == 3
     for s in range(9):
@@ -242,15 +243,15 @@ def test_heuristic_names():
     assert kmq.kernel_name(4096, 14336, 2, 1).startswith("lut_b2")
     assert kmq.kernel_name(2048, 2048, 1, 1).startswith("lut_b1")
     assert kmq.kernel_name(4096, 4096, 3, 1).startswith("lut_b3")
-    assert kmq.kernel_name(4096, 1024, 3, 1) == "lut_loop_b3" and kmq.kernel_name(4096, 1000, 3, 1) == "generic"
+    assert kmq.kernel_name(4096, 1024, 3, 1) == "lut_loop_b3" and kmq.kernel_name(4096, 1000, 3, 1) == "mfma_any_b3"
     # no row length that is a multiple of 32 (up to 24576) falls to the shape-agnostic kernel on the canonical layout
     for bits in (1, 2, 3, 4):
         for K in range(32, 24576 + 1, 32):
             name = kmq.kernel_name(4096, K, bits, 1)
             assert name.startswith("lut_b") or name == f"lut_loop_b{bits}", (bits, K, name)
-    assert kmq.kernel_name(4096, 3072, 4, 1).startswith("lut_b4") and kmq.kernel_name(4096, 24576 + 32, 4, 1) == "generic"
-    assert kmq.kernel_name(4096, 11008, 4, 7) == "lut_loop_b4"                                # batches: grid rows
-    assert kmq.kernel_name(77, 515, 2, 1) == "generic"
+    assert kmq.kernel_name(4096, 3072, 4, 1).startswith("lut_b4") and kmq.kernel_name(4096, 24576 + 32, 4, 1) == "mfma_any_b4"
+    assert kmq.kernel_name(4096, 11008, 4, 7) == "mfma_any_b4" and kmq.kernel_name(77, 11008, 4, 7) == "lut_loop_b4"   # batches: by the number of rows
+    assert kmq.kernel_name(77, 515, 2, 1) == "mfma_any_b2" and kmq.kernel_name(77, 515, 8, 1) == "generic"
     assert kmq.kernel_name(4096, 4096, 3, 16, kmq.LAYOUT_TILED) == "mfma_b3"
     assert kmq.kernel_name(4096, 4000, 3, 16, kmq.LAYOUT_TILED) == "invalid"
     assert kmq.kernel_name(14336, 4096, 3, 16, kmq.LAYOUT_TILED) == "mfma_kslice_b3" and kmq.kernel_name(14336, 8192, 3, 16, kmq.LAYOUT_TILED) == "mfma_b3"
@@ -330,21 +331,40 @@ def test_batches_on_the_canonical_layout_take_the_table_kernels():
     assert kmq.kernel_name(14336, 4096, 2, 4).startswith("lut_b2") and kmq.kernel_name(14336, 4096, 2, 16).startswith("lut_b2")
     assert kmq.kernel_name(4096, 4096, 4, 2).startswith("lut_b4")
     assert kmq.kernel_name(4096, 4096, 4, 16).startswith("lut_b4") and kmq.kernel_name(2048, 2048, 1, 8).startswith("lut_b1")
-    assert kmq.kernel_name(100, 515, 2, 2) == "generic"                     # no table kernel for this K
-    assert kmq.kernel_name_blockscaled(8192, 8192, 4, 4).startswith("lut_sc_b4")
-    assert kmq.kernel_name_blockscaled(8192, 8192, 4, 16).startswith("lut_sc_b4")
+    assert kmq.kernel_name(100, 515, 2, 2) == "mfma_any_b2"                 # no table kernel for this K
+    assert kmq.kernel_name_blockscaled(8192, 8192, 4, 2).startswith("lut_sc_b4")
+
+
+def test_matrix_core_kernel_for_any_row_length():
+    """On the canonical layout it takes what has no vector kernel, and batches that the vector kernels would be slower at: those of
+    enough rows.  Every batch keeps its name's kernel on the tiled layout as well."""
+    for bits in (1, 2, 3, 4):
+        for M in range(1, 17):
+            assert kmq.kernel_name(5001, 4101, bits, M) == f"mfma_any_b{bits}"
+            assert kmq.kernel_name(20000, 2560, bits, M) == (f"lut_loop_b{bits}" if M == 1 else f"mfma_any_b{bits}")
+            assert kmq.kernel_name(64, 13824, bits, M) == f"lut_loop_b{bits}"
+            assert kmq.kernel_name_blockscaled(8192, 5120, bits, M) == f"mfma_any_sc_b{bits}"
+            assert kmq.kernel_name_blockscaled(1000, 3648, bits, M) == ("blockscaled_generic" if M == 1 else kmq.kernel_name_blockscaled(1000, 3648, bits, M))
+            sc = kmq.kernel_name_blockscaled(8192, 8192, bits, M)
+            assert sc.startswith(f"lut_sc_b{bits}") if M <= 2 else sc == f"mfma_any_sc_b{bits}"
+            assert kmq.kernel_name_blockscaled(256, 8192, bits, M).startswith(f"lut_sc_b{bits}")
+            tiled = kmq.kernel_name(4096, 512 * 11, bits, M, kmq.LAYOUT_TILED)
+            assert tiled == f"mfma_any_b{bits}" or (tiled == f"mfma_b{bits}" and M > 4), (bits, M, tiled)
+    assert kmq.kernel_name(64, 13824, 8, 3) == "generic"
 
 
 def test_matrix_core_kernel_choice():
     """The kernel whose waves keep their slice of the activations in registers is taken only where it was measured faster."""
     T = kmq.LAYOUT_TILED
-    assert kmq.kernel_name(4096, 4096, 3, 8, T) == "mfma_b3"             # one row block per workgroup: the general kernel
-    assert kmq.kernel_name(4800, 4096, 3, 8, T) == "mfma_b3"             # 300 row blocks: 150 workgroups would idle 106 CUs
-    assert kmq.kernel_name(14336, 8192, 3, 8, T) == "mfma_b3"            # a wave's slice of X would not fit in registers
-    assert kmq.kernel_name(14336, 2048, 3, 8, T) == "mfma_b3" and kmq.kernel_name(14336, 2048, 2, 8, T) == "mfma_b2"   # too little work per wave
-    assert kmq.kernel_name(14336, 4096, 1, 8, T) == "mfma_b1" and kmq.kernel_name(14336, 4096, 4, 8, T) == "mfma_b4"
-    assert kmq.kernel_name(70000, 4096, 3, 8, T) == "mfma_b3"            # more than four row blocks per workgroup
+    assert kmq.kernel_name(4096, 4096, 3, 16, T) == "mfma_b3"             # one row block per workgroup: the general kernel
+    assert kmq.kernel_name(4800, 4096, 3, 16, T) == "mfma_b3"             # 300 row blocks: 150 workgroups would idle 106 CUs
+    assert kmq.kernel_name(14336, 8192, 3, 16, T) == "mfma_b3"            # a wave's slice of X would not fit in registers
+    assert kmq.kernel_name(14336, 2048, 3, 16, T) == "mfma_b3" and kmq.kernel_name(14336, 2048, 2, 16, T) == "mfma_b2"   # too little work per wave
+    assert kmq.kernel_name(14336, 4096, 1, 16, T) == "mfma_b1" and kmq.kernel_name(14336, 4096, 4, 16, T) == "mfma_b4"
+    assert kmq.kernel_name(70000, 4096, 3, 16, T) == "mfma_b3"            # more than four row blocks per workgroup
     assert kmq.kernel_name(14336, 4096, 2, 16, T) == "mfma_kslice_b2"
+    assert kmq.kernel_name(12281, 4096, 3, 5, T) == "mfma_kslice_b3" and kmq.kernel_name(6144, 4096, 3, 8, T) == "mfma_any_b3"
+    assert kmq.kernel_name(14336, 4096, 3, 4, T) == "mfma_any_b3" and kmq.kernel_name(4096, 4096, 3, 8, T) == "mfma_any_b3"
 
 
 def test_the_built_library_is_not_an_instrumented_build():

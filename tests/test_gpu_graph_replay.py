@@ -150,10 +150,10 @@ def test_graph_replays_of_the_rowlane_and_kslice_calls(gpu):
     p3, c3, x3 = case(50, 256 * 19, 2, 2)              # rowlane_loop_b2
     p4, c4, x4 = case(64, 2048, 2, 1)                  # rowlane_pair_b2 (gate = up weights differ below)
     p4u, c4u, _ = case(64, 2048, 2, 1)
-    p5, c5, x5 = case(6144 + 3, 3072, 3, 8)            # mfma_kslice_b3
+    p5, c5, x5 = case(12281, 3072, 3, 8)               # mfma_kslice_b3
     p6, c6, x6 = case(40, 32768, 2, 2)                 # split over K: the static scratch of the no-allocation call
     p7, c7, x7 = case(1001, 2848, 3, 3)                # lut_loop_b3: rounds over K, a row that ends inside a round, batch as grid rows
-    assert kmq.kernel_name(6147, 3072, 3, 8, T) == "mfma_kslice_b3" and kmq.kernel_name(40, 32768, 2, 2) == "generic_splitk"
+    assert kmq.kernel_name(12281, 3072, 3, 8, T) == "mfma_kslice_b3" and kmq.kernel_name(40, 32768, 2, 2) == "generic_splitk"
     assert kmq.kernel_name(1001, 2848, 3, 3) == "lut_loop_b3"
     W1, W2, W3 = dev(kmq.repack(p1, 4096, 2, RL)), dev(kmq.repack(p2, 3072, 1, RL)), dev(kmq.repack(p3, 256 * 19, 2, RL))
     W4, W4u = dev(kmq.repack(p4, 2048, 2, RL)), dev(kmq.repack(p4u, 2048, 2, RL))
@@ -162,7 +162,7 @@ def test_graph_replays_of_the_rowlane_and_kslice_calls(gpu):
     Xd = [dev(x) for x in (x1, x2, x3, x4, x5, x6, x7)]
 
     def outputs():
-        shapes = ((1, 330), (7, 100), (2, 50), (1, 64), (8, 6147), (2, 40), (3, 1001))
+        shapes = ((1, 330), (7, 100), (2, 50), (1, 64), (8, 12281), (2, 40), (3, 1001))
         return [torch.full(s, 0x7FC1, dtype=torch.int16, device="cuda") for s in shapes]
 
     def run(Y):
@@ -170,7 +170,7 @@ def test_graph_replays_of_the_rowlane_and_kslice_calls(gpu):
         kmq.gemm_smallbatch(W2, C[1], Xd[1], Y[1], 100, 3072, 7, 1, RL)
         kmq.gemm_smallbatch(W3, C[2], Xd[2], Y[2], 50, 256 * 19, 2, 2, RL)
         kmq.gemv_swiglu(W4, C[3], W4u, C[4], Xd[3], Y[3], 64, 2048, 2, RL)
-        kmq.gemm_smallbatch(W5, C[5], Xd[4], Y[4], 6147, 3072, 8, 3, T)
+        kmq.gemm_smallbatch(W5, C[5], Xd[4], Y[4], 12281, 3072, 8, 3, T)
         kmq.gemm_smallbatch_noalloc(W6, C[6], Xd[5], Y[5], 40, 32768, 2, 2, 0)
         kmq.gemm_smallbatch(W7, C[7], Xd[6], Y[6], 1001, 2848, 3, 3, 0)
 

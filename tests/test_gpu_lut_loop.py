@@ -60,7 +60,7 @@ def test_loop_kernel_launch_shapes(gpu, bits, N, K):
                              label=f"lut_loop b{bits} {N}x{K}")
 
 
-@pytest.mark.parametrize("bits,N,K,M", [(3, 1000, 2560, 3), (4, 4099, 5120, 2), (2, 513, 7168, 16), (1, 2048, 1280, 5)])
+@pytest.mark.parametrize("bits,N,K,M", [(3, 200, 4000, 3), (4, 700, 5120, 2), (2, 130, 7168, 16), (1, 300, 12320, 5)])
 def test_loop_kernel_batches(gpu, bits, N, K, M):
     assert kmq.kernel_name(N, K, bits, M, kmq.LAYOUT_CANONICAL) == f"lut_loop_b{bits}"
     idx, cb, X = _case(7 * bits + N + K + M, N, K, bits, M)
@@ -96,6 +96,7 @@ def test_loop_kernel_is_deterministic(gpu):
 @pytest.mark.parametrize("bits,N,K,M", [(1, 64, 6912, 8), (2, 122, 13088, 16), (3, 94, 5984, 6), (4, 77, 6240, 6), (4, 1024, 6912, 2)])
 def test_batches_on_few_rows_keep_the_loop_kernel(gpu, bits, N, K, M):
     """Where it is the faster one: its columns are the batch-1 results bit for bit, the matrix cores' would not be."""
+    assert kmq.kernel_name(N, K, bits, M) == f"lut_loop_b{bits}"
     idx, cb, X = _case(9 * bits + N + K + M, N, K, bits, M)
     pd, cd = gpu.dev(kmq.pack(idx, bits)), gpu.dev(cb)
     Yg = gpu.run_gemm(pd, cd, X, N, K, bits)

@@ -30,6 +30,7 @@ def test_tiled_per_row_vs_oracle(gpu, bits, N, blocks, M):
     seed = 11 * bits + N + K + M
     idx, cb = synth.make_indices(seed, 0, N, K, bits), synth.make_codebook(seed, 0, N, bits, symmetric=(bits == 1))
     X, p = synth.make_x(seed, 0, M, K), oracle.pack(idx, bits)
+    assert M > 4 or kmq.kernel_name(N, K, bits, M, TILED) == f"mfma_any_b{bits}"
     Yg = gpu.run_gemm(gpu.dev(kmq.repack(p, K, bits, TILED)), gpu.dev(cb), X, N, K, bits, TILED)
     gpu.check_against_oracle(Yg, p, cb, X, K, bits, gpu.sample_ranges(N, seed, nblocks=3), label=f"b{bits} {N}x{K} M{M}")
 

@@ -1,7 +1,7 @@
 """GPU parity of the matrix-core kernel whose waves keep their slice of the activations in registers
 (tiled layout, 2 and 3 bits, K <= 4096, at least 6144 rows): through the C ABI against the CPU oracle on
-sampled row blocks -- two, three and four row blocks per workgroup, ragged last blocks, every batch size,
-every split of K over the waves, one-hot probes (bit-exact), determinism."""
+sampled row blocks -- two, three and four row blocks per workgroup, ragged last blocks, batches from 5 on,
+every split of K over the waves, one-hot probes (bit-exact), determinism.  (Smaller batches run the matrix-core kernel for any row length.)"""
 import numpy as np
 import pytest
 import torch
@@ -30,7 +30,7 @@ def _case(seed, N, K, bits, M):
 # rows: 6144 (384 row blocks: 2 per workgroup, 192 workgroups), 8190 (ragged, 2 x 256), 9216 (3 x 192),
 # 12281 (ragged, 3 x 256), 14336 (4 x 224), 16377 (ragged, 4 x 256)
 @pytest.mark.parametrize("bits,K", [(2, 3072), (2, 3584), (2, 4096), (3, 3072), (3, 3584), (3, 4096)])
-@pytest.mark.parametrize("N,M", [(6144, 8), (8190, 16), (9216, 1), (12281, 5), (14336, 16), (16377, 8)])
+@pytest.mark.parametrize("N,M", [(6144, 16), (8190, 16), (9216, 6), (12281, 5), (14336, 16), (16377, 8)])
 def test_kslice_vs_oracle(gpu, bits, K, N, M):
     idx, cb, X = _case(17 * bits + N + K + M, N, K, bits, M)
     p = kmq.pack(idx, bits)

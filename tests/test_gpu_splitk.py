@@ -80,7 +80,7 @@ def test_no_split_beyond_threshold(gpu, N, K, M):
     """Enough rows to fill the chip, or short rows: single pass, no workspace."""
     if slices_expected(N, K) == 1:
         name = kmq.kernel_name(N, K, 2, M)
-        assert kmq.workspace_bytes(N, K, 2, M) == 0 and (name == "generic" or name.startswith("lut_b2") or name == "lut_loop_b2"), name
+        assert kmq.workspace_bytes(N, K, 2, M) == 0 and (name == "mfma_any_b2" or name.startswith("lut_b2") or name == "lut_loop_b2"), name
     idx = synth.make_indices(9, 0, N, K, 2)
     cb = synth.make_codebook(9, 0, N, 2)
     X = synth.make_x(9, 0, M, K)
