@@ -616,8 +616,8 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __re
 // A sum over members of one scale mantissa is a sum of weights (integers in the window's unit: exact in fp64 up to 2^53)
 // divided once by the scale's mantissa.  A boundary b stands for the exact test fl(w / scale) > b: where b * scale comes
 // within a few units in the last place of a weight, the division itself decides.
-// Elements more than 31 octaves below their scale ("far", next to none in any trained tensor) are counted apart per sign;
-// a round whose result could depend on their values looks them up in the tensor again.
+// Elements more than 31 octaves below their scale ("far", next to none in most trained tensors) are counted apart per sign, and
+// their sums taken from the tensor (below).
 //
 // 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits: 149 / 166 / 182 / 221 us (8519 / 9344 / 10727 / 13475 with every element
 // divided by its scale and compared with every boundary in fp64, each round); 1024 x 1024: 74 / 90 / 100 / 131 (3212 ..
@@ -630,20 +630,33 @@ struct BelowBin {                                        // what lies below a bi
     double count;                                        // members (exact: at most 2^38)
     double sum;                                          // ... and their sum, in units of 2^-31 / (128 + scale mantissa)
 };
+constexpr int kFarChunks = 512;
+struct FarPart {
+    double sum;
+    long long num;
+};
+struct alignas(16) FarScratch {                          // starts as zeros
+    unsigned long long next;                             // search number << 32 | pieces claimed
+    unsigned long long done;                             // pieces done, over all searches
+    uint32_t arrived, finished;
+    double bounds[16];                                   // of the present search: changed only when all its pieces are done
+};
 struct QuantScratch {                                    // layout of the caller's workspace; everything down to `exact_assign` starts as zeros
+    FarScratch far;
     unsigned long long members[kQuantMants][kQuantBins];
     unsigned long long blocks[kQuantMants];              // blocks per scale mantissa
     unsigned long long cursor[kQuantMants];              // ... of them placed so far
     unsigned long long zeros, far_neg, far_pos;
     unsigned long long exact_assign;                     // a stored boundary lies among the far elements
+    FarPart far_part[kFarChunks][16];
     BelowBin below[kQuantMants][kQuantStride];           // (side by side: a round's look-ups are scattered, a line each)
     uint32_t above[kQuantMants][16];                     // per stored boundary: largest element key at or below it, in both halves
 };
 
 __global__ __launch_bounds__(256) void bs_clear_kernel(QuantScratch* q) {
     typedef u32x4_t __attribute__((aligned(8))) u32x4_a8_t;
-    constexpr size_t n16 = offsetof(QuantScratch, below) / 16;
-    static_assert(offsetof(QuantScratch, below) % 16 == 0, "cleared in 16-byte pieces");
+    constexpr size_t n16 = offsetof(QuantScratch, far_part) / 16;
+    static_assert(offsetof(QuantScratch, far_part) % 16 == 0, "cleared in 16-byte pieces");
     for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < n16; i += static_cast<size_t>(gridDim.x) * 256)
         reinterpret_cast<u32x4_a8_t*>(q)[i] = u32x4_t{0, 0, 0, 0};
 }
@@ -886,57 +899,151 @@ __device__ __forceinline__ double uniform(double v) {
     return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
 }
 
-// Number and sum of the far elements in (lo, hi], from the tensor; by the whole workgroup, in a fixed order.
-__device__ __forceinline__ void far_members(const uint16_t* W, const uint16_t* scales, int64_t nblocks, double lo, double hi,
-                                            double* ws, long long* wn, double* sum, long long* num) {
-    double s = 0.0;
-    long long n = 0;
-    for (int64_t blk = threadIdx.x >> 3; blk < nblocks; blk += blockDim.x >> 3) {
-        const double scale = bf16_to_f64(scales[blk]);
-        const uint32_t sp = scale_pattern(scales[blk]);
-        u32x4_t v = *reinterpret_cast<const u32x4_t*>(W + blk * KMQ_BLOCK + (threadIdx.x & 7) * 8), l = v;
-        if (scales[blk] < kSmallScale) lift_pairs(l);
+// ---- the far elements of the rounds
+// Their sums are not in the counters: they are taken from the tensor, once per sign, and again in every round that has a
+// boundary among them.  The whole grid does that: the first workgroup to arrive leads (it runs the rounds), the others wait
+// for work.  A search cuts the tensor into nchunks pieces; leader and helpers claim them from one counter until none is left,
+// and the leader then waits for the claimed ones to be done.  Whoever is waited for is running: nothing depends on how many
+// workgroups are resident or in which order they start, and the helpers end when the leader says so.  A piece's sums are
+// added in a fixed order, and the pieces' sums in theirs.
+// 8192 x 8192, 4 bits, 25 rounds: 223 us without far elements, 313 with 0.01 % of them (one search), 2.7 ms where all but the
+// scales are far (a search every round, 0.1 ms each); 133 and 423 ms with the rounds' workgroup searching alone.
+template <int C>
+struct FarShared {
+    double bounds[C];
+    double sum[C][C];                                    // per wave and cluster
+    int num[C][C];
+    uint32_t chunk;
+};
+constexpr uint32_t kNoChunk = ~0u, kFarEnd = ~0u - 1;
+
+// A piece of the present search for this workgroup, or kNoChunk.
+template <int C>
+__device__ __forceinline__ uint32_t far_claim(FarShared<C>& sh, FarScratch* f, uint32_t nchunks, bool helper) {
+    __syncthreads();                                      // (sh.chunk read by all)
+    if (threadIdx.x == 0) {
+        uint32_t c = kNoChunk;
+        const unsigned long long seen = __hip_atomic_load(&f->next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (seen >> 32 != 0 && static_cast<uint32_t>(seen) < nchunks) {         // (search 0: none has begun)
+            const uint32_t got = static_cast<uint32_t>(__hip_atomic_fetch_add(&f->next, 1ull, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT));
+            if (got < nchunks) c = got;
+        } else if (helper) {
+            // (no ordering asked for: an acquire would empty the caches that the leader's rounds live from, at every look)
+            if (__hip_atomic_load(&f->finished, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) c = kFarEnd;
+            else __builtin_amdgcn_s_sleep(32);
+        }
+        sh.chunk = c;
+    }
+    __syncthreads();
+    return sh.chunk;
+}
+
+template <int C>
+__device__ __forceinline__ void far_chunk(FarShared<C>& sh, QuantScratch* q, uint32_t chunk, uint32_t nchunks, const uint16_t* W,
+                                          const uint16_t* scales, int64_t nblocks) {
+    constexpr int T = C * 64, U = 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (threadIdx.x < C) sh.bounds[threadIdx.x] = q->far.bounds[threadIdx.x];
+    if (lane < C) { sh.sum[wave][lane] = 0.0; sh.num[wave][lane] = 0; }
+    __syncthreads();
+    const int64_t per = (nblocks + nchunks - 1) / nchunks, first = chunk * per, end = first + per < nblocks ? first + per : nblocks;
+    for (int64_t base = first + wave * 8; base < end; base += T / 8 * U) {      // (the whole wave together: eight lanes per block)
+        u32x4_t v[U];
+        uint32_t sc[U];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const u16x2_t k = magnitude_keys(l[j], sp);
+        for (int u = 0; u < U; ++u) {
+            const int64_t at = base + u * (T / 8) + (lane >> 3), blk = at < end ? at : end - 1;
+            v[u] = *reinterpret_cast<const u32x4_t*>(W + blk * KMQ_BLOCK + (lane & 7) * 8);
+            sc[u] = scales[blk];
+        }
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (k[h] != 1) continue;
-                const double quot = bf16_to_f64(h ? v[j] >> 16 : v[j] & 0xFFFFu) / scale;
-                if (quot > lo && quot <= hi) { s += quot; ++n; }
+        for (int u = 0; u < U; ++u) {
+            const bool live = base + u * (T / 8) + (lane >> 3) < end;
+            const uint32_t sp = scale_pattern(sc[u]);
+            u32x4_t l = v[u];
+            if (sc[u] < kSmallScale) lift_pairs(l);
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t d = l[j], raw = v[u][j];
+                const u16x2_t k = magnitude_keys(d, sp);
+                for (int h = 0; h < 2; ++h) {
+                    const bool far = live && k[h] == 1;
+                    uint64_t left = __ballot(far);
+                    if (left == 0) continue;
+                    const double quot = bf16_to_f64(h ? raw >> 16 : raw & 0xFFFFu) / bf16_to_f64(sc[u]);
+                    int a = 0;
+                    for (int e = 0; e + 1 < C; ++e) a += quot > sh.bounds[e] ? 1 : 0;
+                    do {                                  // one cluster after the other
+                        const int e = __builtin_amdgcn_readlane(a, __ffsll(static_cast<unsigned long long>(left)) - 1);
+                        const bool in = far && a == e;
+                        const uint64_t members = __ballot(in);
+                        const double t = wave_total(in ? quot : 0.0);
+                        if (lane == 0) { sh.sum[wave][e] += t; sh.num[wave][e] += __popcll(members); }
+                        left &= ~members;
+                    } while (left);
+                }
             }
         }
     }
-    s = wave_sum(s);
-    n = wave_sum(n);
-    if ((threadIdx.x & 63) == 0) { ws[threadIdx.x >> 6] = s; wn[threadIdx.x >> 6] = n; }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        s = 0.0;
-        n = 0;
-        for (unsigned w = 0; w < blockDim.x / 64; ++w) { s += ws[w]; n += wn[w]; }
-        *sum = s;
-        *num = n;
+    if (threadIdx.x < C) {
+        FarPart p{0.0, 0};
+        for (int w = 0; w < C; ++w) { p.sum += sh.sum[w][threadIdx.x]; p.num += sh.num[w][threadIdx.x]; }
+        q->far_part[chunk][threadIdx.x] = p;
     }
-    __syncthreads();
+    __syncthreads();                                      // the workgroup's stores ahead of the leader's sight of them
+    if (threadIdx.x == 0) __hip_atomic_fetch_add(&q->far.done, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // All rounds: wave i takes boundary i and cluster i, a lane scale mantissas `lane` and `lane + 64`.  Numbers of members
 // are kept as doubles (exact: at most 2^38).
 template <int BITS>
 __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratch* q, const uint16_t* __restrict__ W,
-                                                                     const uint16_t* __restrict__ scales, int64_t nblocks, int iters,
-                                                                     uint16_t* __restrict__ codebook) {
+                                                                     const uint16_t* __restrict__ scales, int64_t nblocks, uint32_t nchunks,
+                                                                     int iters, uint16_t* __restrict__ codebook) {
     constexpr int C = 1 << BITS;
     __shared__ double cs[C];
     __shared__ double bn[C][kQuantMants];                 // members below boundary i (i = C - 1: all), per scale mantissa
     __shared__ double bsum[C][kQuantMants];
-    __shared__ double farsum[C], fw[C];
-    __shared__ long long farnum[C], fn[C];
-    __shared__ int moved, unsure;
+    __shared__ FarShared<C> fs;
+    __shared__ int moved, search;
     const int i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const double far_neg = static_cast<double>(q->far_neg), far_pos = static_cast<double>(q->far_pos), zeros = static_cast<double>(q->zeros);
     const bool any_far = far_neg + far_pos > 0.0;
+    FarScratch* const f = &q->far;
+    if (!any_far) {
+        if (blockIdx.x != 0) return;
+    } else {
+        if (threadIdx.x == 0) fs.chunk = __hip_atomic_fetch_add(&f->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (fs.chunk != 0) {
+            for (;;) {
+                const uint32_t c = far_claim<C>(fs, f, nchunks, true);
+                if (c == kFarEnd) return;
+                if (c != kNoChunk) far_chunk<C>(fs, q, c, nchunks, W, scales, nblocks);
+            }
+        }
+    }
+    unsigned long long searches = 0;
+    // sum and number of this wave's cluster's far members, for the boundaries in f->bounds (written by the caller's threads)
+    auto far_search = [&](double& sum, double& num) {
+        ++searches;
+        __syncthreads();
+        if (threadIdx.x == 0) __hip_atomic_store(&f->next, searches << 32, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        for (;;) {
+            const uint32_t c = far_claim<C>(fs, f, nchunks, false);
+            if (c == kNoChunk) break;
+            far_chunk<C>(fs, q, c, nchunks, W, scales, nblocks);
+        }
+        if (threadIdx.x == 0) {
+            while (__hip_atomic_load(&f->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < searches * nchunks) __builtin_amdgcn_s_sleep(2);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        __syncthreads();
+        double s = 0.0, n = 0.0;
+        for (uint32_t c = lane; c < nchunks; c += 64) { s += q->far_part[c][i].sum; n += static_cast<double>(q->far_part[c][i].num); }
+        sum = wave_total(s);
+        num = wave_total(n);
+    };
     double scale[2], inv[2];                              // of this lane's two mantissas, in the window's unit
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -947,13 +1054,24 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
         bsum[C - 1][lane + 64 * h] = all.sum;
     }
     if (threadIdx.x < C) cs[threadIdx.x] = -1.0 + (2 * static_cast<int>(threadIdx.x) + 1) / static_cast<double>(C);
-    if (threadIdx.x == 0) { moved = 0; unsure = 0; }
+    if (threadIdx.x == 0) { moved = 0; search = 0; }
+    double neg_sum = 0.0, pos_sum = 0.0;
+    if (any_far && iters > 0) {                           // per sign: all boundaries 0, so the first cluster and the last
+        if (threadIdx.x < C) f->bounds[threadIdx.x] = 0.0;
+        double s, n;
+        far_search(s, n);
+        if (lane == 0) bsum[0][i] = s;                    // (free until the first round)
+        __syncthreads();
+        neg_sum = bsum[0][0];
+        pos_sum = bsum[0][C - 1];
+    }
     __syncthreads();
     auto boundary = [&](int j) { return uniform(0.5 * (cs[j] + cs[j + 1])); };
     auto below_of = [&](double b, int h) {
         return b < 0.0 ? kHistMags - magnitudes_within<true>(-b, scale[h]) : kHistMags + magnitudes_within<false>(b, scale[h]);
     };
-    auto far_below = [&](double b) { return b >= kFar ? far_neg + far_pos : b >= 0.0 ? far_neg : 0.0; };   // (b within +-kFar: see `unsure`)
+    // what lies below b of something with a negative and a positive part (b not among the far elements)
+    auto far_below = [&](double b, double neg, double pos) { return b >= kFar ? neg + pos : b >= 0.0 ? neg : 0.0; };
     auto zeros_below = [&](double b) { return b >= 0.0 ? zeros : 0.0; };
     auto among_far = [&](double b) { return any_far && b != 0.0 && fabs(b) < kFar; };
     int seen[2] = {-1, -1};
@@ -972,7 +1090,7 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
                 }
             }
             if (now[0] != seen[0] || now[1] != seen[1] || among_far(b)) moved = 1;
-            if (among_far(b)) unsure = 1;
+            if (among_far(b)) search = 1;
             seen[0] = now[0];
             seen[1] = now[1];
         }
@@ -987,34 +1105,27 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
         }
         n = wave_total(n);
         s = wave_total(s);
-        const double nfar = far_below(b) - far_below(b0);
-        double nz = nfar + zeros_below(b) - zeros_below(b0);
+        n += zeros_below(b) - zeros_below(b0);
         if (any_far) {
-            if (lane == 0 && nfar > 0.0 && fabs(s) < nfar * 8192.0) unsure = 1;      // far members that would show in the mean
-            __syncthreads();
-            if (unsure) {                                 // (uniform; the far elements are looked up in the tensor)
-                for (int j = 0; j < C; ++j) {
-                    const double lo = j > 0 ? boundary(j - 1) : -2.0, hi = j < C - 1 ? boundary(j) : 2.0;
-                    if (lo < kFar && hi > -kFar) {
-                        far_members(W, scales, nblocks, lo, hi, fw, fn, &farsum[j], &farnum[j]);
-                    } else if (threadIdx.x == 0) {
-                        farsum[j] = 0.0;
-                        farnum[j] = 0;
-                    }
-                }
-                __syncthreads();
-                s += farsum[i];
-                nz += static_cast<double>(farnum[i]) - nfar;
+            double fsum, fnum;
+            if (search) {                                 // (uniform)
+                if (lane == 0) f->bounds[i] = b;
+                far_search(fsum, fnum);
+            } else {
+                fsum = far_below(b, neg_sum, pos_sum) - far_below(b0, neg_sum, pos_sum);
+                fnum = far_below(b, far_neg, far_pos) - far_below(b0, far_neg, far_pos);
             }
+            s += fsum;
+            n += fnum;
         }
-        n += nz;
         const double c = s / n;
         __syncthreads();                                  // boundaries and sums read by all before anything moves
         if (lane == 0 && n > 0.0) cs[i] = c;
-        if (threadIdx.x == 0) { moved = 0; unsure = 0; }
+        if (threadIdx.x == 0) { moved = 0; search = 0; }
         __syncthreads();
     }
     __syncthreads();
+    if (any_far && threadIdx.x == 0) __hip_atomic_store(&f->finished, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     if (threadIdx.x < C) {
         const uint16_t hc = f64_to_bf16(cs[threadIdx.x]);
         codebook[threadIdx.x] = hc;
@@ -1163,7 +1274,10 @@ static hipError_t quantize_blockscaled_bits(const uint16_t* W, int64_t N, int64_
     const int64_t run = (nblocks + 1023) / 1024 < 64 ? 64 : (nblocks + 1023) / 1024;
     hipLaunchKernelGGL(bs_count_kernel, dim3(static_cast<unsigned>((nblocks + run - 1) / run)), dim3(kCountThreads), 0, s, W, packed, nblocks, run, q);
     hipLaunchKernelGGL(bs_prefix_kernel, dim3(kQuantMants), dim3(1024), 0, s, q);
-    hipLaunchKernelGGL((bs_rounds_kernel<BITS>), dim3(1), dim3((1 << BITS) * 64), 0, s, q, W, scales, nblocks, iters, codebook);
+    // one workgroup runs the rounds; the others, a few a CU, end at once unless there are far elements
+    const uint32_t nchunks = static_cast<uint32_t>(nblocks < 256 * kFarChunks ? (nblocks + 255) / 256 : kFarChunks);
+    hipLaunchKernelGGL((bs_rounds_kernel<BITS>), dim3(BITS <= 2 ? 512 : 256), dim3((1 << BITS) * 64), 0, s, q, W, scales, nblocks, nchunks,
+                       iters, codebook);
     hipLaunchKernelGGL((bs_assign_pack_kernel<BITS>), grid(npieces, 256, 4096), dim3(256), 0, s, W, scales, codebook, npieces, q, packed);
     return hipGetLastError();
 }

@@ -74,6 +74,72 @@ def test_far_elements(gpu, bits, share):
     check(gpu, W, bits, 8)
 
 
+def _with_tiny(W, share, seed):
+    """`share` of the elements (never a block's first) moved 40 to 60 octaves down."""
+    rng = np.random.default_rng(seed)
+    pick = rng.random(W.shape) < share
+    pick[:, ::64] = False
+    down = rng.integers(40, 61, size=W.shape) << 7
+    mag = np.where(pick, np.maximum((W & 0x7FFF).astype(np.int64) - down, 1), W & 0x7FFF)
+    out = ((W & 0x8000) | mag).astype(np.uint16)
+    first = out[:, ::64]
+    first[...] = np.maximum(first & 0x7FFF, 0x3C00)       # every block keeps an ordinary scale
+    return out
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("share", [0.0005, 0.3, 1.0])
+def test_far_elements_of_many_pieces(gpu, bits, share):
+    """More blocks than the tensor is cut into pieces: a few far elements, a third, all but the scales themselves."""
+    W = _with_tiny(synth.make_dense_weights(150, bits, 96, 2048), share, 8)
+    check(gpu, W, bits, 7)
+    a, b = (run_blockscaled(gpu, W, bits, 7) for _ in range(2))
+    assert all(np.array_equal(u, v) for u, v in zip(a, b))
+
+
+def test_far_member_decides_a_tie(gpu):
+    """16384 positive members, scales 1: without the far one their sum over their number is halfway between two bf16 values, with it
+    a little above (both sums are exact in 64 bits)."""
+    W = np.full((4, 4096), 0x3F40, np.uint16)             # 0.75
+    W[:, ::64] = 0x3F80                                    # 256 of 1, the scales
+    W[0, 1:64] = W[0, 65:127] = 0x3F00                     # 125 of 0.5
+    W[3, 4000] = 0x2F00                                    # 2^-33
+    v = synth.bf16_to_f64(W)
+    assert np.sum(v[v > 1e-9]) == 16384 * (0.75 + 2.0 ** -9)
+    idx, cb, _, _, _ = oracle.quantize_blockscaled(W, 1, 1)
+    assert list(cb) == [0xBF00, 0x3F41]
+    check(gpu, W, 1, 1)
+
+
+@pytest.mark.parametrize("bits", [1, 4])
+@pytest.mark.parametrize("share", [0.0001, 0.9])
+def test_far_elements_cost_no_more_than_a_reading_or_two_a_round(gpu, bits, share):
+    """The tensor is searched for them by the whole chip: once for a few of them, at most once a round where they fill clusters of
+    their own.  One workgroup's search took 50 to 700 times the call without them."""
+    import torch
+    N, K, iters = 2048, 4096, 8
+    W = synth.make_dense_weights(160, bits, N, K)
+    times = []
+    for w in (W, _with_tiny(W, share, 9)):
+        Wd = gpu.dev(w)
+        packed = torch.empty((N, K * bits // 32), dtype=torch.int32, device="cuda")
+        cb, sc = torch.empty(1 << bits, dtype=torch.int16, device="cuda"), torch.empty((N, K // 64), dtype=torch.int16, device="cuda")
+        ws = torch.empty(kmq.quantize_blockscaled_workspace_bytes(), dtype=torch.uint8, device="cuda")
+        run = lambda: kmq.quantize_blockscaled(Wd, N, K, bits, iters, packed, cb, sc, ws)
+        run()
+        took = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            run()
+            b.record()
+            torch.cuda.synchronize()
+            took.append(a.elapsed_time(b))
+        times.append(sorted(took)[2])
+    print(f"b{bits} share {share}: {times[0] * 1e3:.0f} us without, {times[1] * 1e3:.0f} us with far elements")
+    assert times[1] < (3 if share < 0.5 else 3 + iters) * times[0]
+
+
 def test_list_reuse_of_the_output(gpu):
     """The index words hold the sorted block list for a while: nothing of it may be left, and repeats give the same bits."""
     W = synth.make_dense_weights(140, 0, 96, 4096)
