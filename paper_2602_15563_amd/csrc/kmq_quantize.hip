@@ -14,8 +14,9 @@
 //     are nearest STORED centroids.
 //
 // Both quantisers replace "every element against every boundary, each round" by counts over the few distinct values
-// there are, taken once (the comments at the kernels).  Sums of members are deterministic, and exact whenever the
-// members' exponents span fewer than 53 - log2(count) bits (always so for rows of bf16 weights of one layer).
+// there are, taken once (the comments at the kernels).  Sums of members are deterministic.  A row's are exact whenever its
+// exponents span fewer than 53 - log2(count) bits (always so for rows of bf16 weights of one layer); a tensor's are exact per
+// scale mantissa, and rounded to 64 bits where those are scaled and added up.
 //
 // Compiled with floating-point contraction off: the arithmetic is specified operation by
 // operation.
@@ -59,7 +60,7 @@ template <int C>
 struct Clusters {
     double b[C > 1 ? C - 1 : 1];   // boundaries
     double s[C];
-    int n[C];                      // per lane: at most a few thousand members, widened when lanes are added up
+    int n[C];                      // per lane: at most 2^16 members (K <= 2^24), widened when lanes are added up
     __device__ __forceinline__ void begin(const double* c) {
 #pragma unroll
         for (int i = 0; i + 1 < C; ++i) b[i] = 0.5 * (c[i] + c[i + 1]);
@@ -613,8 +614,8 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __re
 //   prefix   per scale mantissa: number and sum of the members below every value
 //   rounds   one workgroup, all rounds: per (boundary, scale mantissa) one look-up in the prefix arrays
 //   assign   every element against its scale mantissa's boundaries, as 16-bit integers
-// A sum over members of one scale mantissa is a sum of weights (integers in the window's unit: exact in fp64 up to 2^53)
-// divided once by the scale's mantissa.  A boundary b stands for the exact test fl(w / scale) > b: where b * scale comes
+// A sum over members of one scale mantissa is a sum of weights (integers in the window's unit: exact) times the
+// reciprocal of the scale's mantissa.  A boundary b stands for the exact test fl(w / scale) > b: where b * scale comes
 // within a few units in the last place of a weight, the division itself decides.
 // Elements more than 31 octaves below their scale ("far", next to none in most trained tensors) are counted apart per sign, and
 // their sums taken from the tensor (below).
@@ -626,19 +627,34 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __re
 constexpr int kQuantMants = 128, kQuantBins = 2 * kHistMags, kQuantStride = kQuantBins + 1;
 constexpr double kFar = 4.656612873077393e-10;           // 2^-31: no far element reaches it
 
-struct BelowBin {                                        // what lies below a bin
-    double count;                                        // members (exact: at most 2^38)
-    double sum;                                          // ... and their sum, in units of 2^-31 / (128 + scale mantissa)
+// What lies below a bin: 40 bits of members (at most 2^38) above 88 bits of their sum, in units of 2^-31 / (128 + scale mantissa)
+// (at most 2^38 members of 2^39 units).  Integers, so that a cluster's sum, the difference of two of them, is exact however
+// much lies below it.
+struct BelowBin {
+    unsigned long long lo, hi;
 };
+typedef __int128 int128_t;
+__device__ __forceinline__ BelowBin below_bin(long long count, int128_t sum) {
+    return BelowBin{static_cast<unsigned long long>(sum), static_cast<unsigned long long>(count) << 24 | (static_cast<unsigned long long>(sum >> 64) & 0xFFFFFFu)};
+}
+__device__ __forceinline__ double below_count(unsigned long long hi) { return static_cast<double>(hi >> 24); }
+__device__ __forceinline__ int128_t below_sum(unsigned long long lo, unsigned long long hi) {
+    return static_cast<int128_t>(static_cast<long long>(hi << 40) >> 40) << 64 | lo;
+}
+__device__ __forceinline__ double sum_to_f64(int128_t v) {   // |v| < 2^88: the high part is exact
+    const unsigned __int128 m = v < 0 ? -static_cast<unsigned __int128>(v) : static_cast<unsigned __int128>(v);
+    const double d = static_cast<double>(static_cast<unsigned long long>(m >> 64)) * 18446744073709551616.0 + static_cast<double>(static_cast<unsigned long long>(m));
+    return v < 0 ? -d : d;
+}
 constexpr int kFarChunks = 512;
 struct FarPart {
     double sum;
     long long num;
 };
-struct alignas(16) FarScratch {                          // starts as zeros
+struct FarScratch {                                      // starts as zeros
     unsigned long long next;                             // search number << 32 | pieces claimed
     unsigned long long done;                             // pieces done, over all searches
-    uint32_t arrived, finished;
+    uint32_t arrived, finished, unused[2];
     double bounds[16];                                   // of the present search: changed only when all its pieces are done
 };
 struct QuantScratch {                                    // layout of the caller's workspace; everything down to `exact_assign` starts as zeros
@@ -656,7 +672,7 @@ struct QuantScratch {                                    // layout of the caller
 __global__ __launch_bounds__(256) void bs_clear_kernel(QuantScratch* q) {
     typedef u32x4_t __attribute__((aligned(8))) u32x4_a8_t;
     constexpr size_t n16 = offsetof(QuantScratch, far_part) / 16;
-    static_assert(offsetof(QuantScratch, far_part) % 16 == 0, "cleared in 16-byte pieces");
+    static_assert(alignof(QuantScratch) == 8 && offsetof(QuantScratch, far_part) % 16 == 0, "cleared in 16-byte pieces");
     for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < n16; i += static_cast<size_t>(gridDim.x) * 256)
         reinterpret_cast<u32x4_a8_t*>(q)[i] = u32x4_t{0, 0, 0, 0};
 }
@@ -816,14 +832,14 @@ __global__ __launch_bounds__(kCountThreads) void bs_count_kernel(const uint16_t*
 __global__ __launch_bounds__(1024) void bs_prefix_kernel(QuantScratch* q) {
     constexpr int PER = kQuantBins / 1024;
     __shared__ long long wn[16];
-    __shared__ double ws[16];
+    __shared__ int128_t ws[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const unsigned long long* const n = q->members[blockIdx.x] + tid * PER;
     BelowBin* const bin = q->below[blockIdx.x] + tid * PER;
     const bool pos = tid >= 512;
     const int mi0 = pos ? (tid - 512) * PER : kHistMags - 1 - tid * PER;             // magnitude of the first bin; then rising / falling
-    const double unit = static_cast<double>(1ull << (mi0 >> 7)) * (pos ? 1.0 : -1.0);
-    const int m0 = 128 + (mi0 & 127), dm = pos ? 1 : -1;
+    const int octave = mi0 >> 7, m0 = 128 + (mi0 & 127), dm = pos ? 1 : -1;
+    auto in_units = [&](long long mantissas) { return static_cast<int128_t>(pos ? mantissas : -mantissas) << octave; };
     uint64_t c[PER];
     long long tn = 0, tm = 0;                             // members, sum of their mantissas
 #pragma unroll
@@ -832,14 +848,15 @@ __global__ __launch_bounds__(1024) void bs_prefix_kernel(QuantScratch* q) {
         tn += static_cast<long long>(c[i]);
         tm += static_cast<long long>(c[i]) * (m0 + dm * i);
     }
-    const double ts = static_cast<double>(tm) * unit;
+    const int128_t ts = in_units(tm);
     long long in = tn;
-    double is = ts;
+    int128_t is = ts;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const long long pn = __shfl_up(in, off, 64);
-        const double ps = __shfl_up(is, off, 64);
-        if (lane >= off) { in += pn; is += ps; }
+        const unsigned long long lo = __shfl_up(static_cast<unsigned long long>(is), off, 64);
+        const long long hi = __shfl_up(static_cast<long long>(is >> 64), off, 64);
+        if (lane >= off) { in += pn; is += static_cast<int128_t>(hi) << 64 | lo; }
     }
     if (lane == 63) { wn[wave] = in; ws[wave] = is; }
     __syncthreads();
@@ -849,11 +866,11 @@ __global__ __launch_bounds__(1024) void bs_prefix_kernel(QuantScratch* q) {
     tm = 0;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        bin[i] = BelowBin{static_cast<double>(in), is + static_cast<double>(tm) * unit};
+        bin[i] = below_bin(in, is + in_units(tm));
         in += static_cast<long long>(c[i]);
         tm += static_cast<long long>(c[i]) * (m0 + dm * i);
     }
-    if (tid == 1023) bin[PER] = BelowBin{static_cast<double>(in), is + static_cast<double>(tm) * unit};
+    if (tid == 1023) bin[PER] = below_bin(in, is + in_units(tm));
 }
 
 // Window magnitudes g = mantissa * 2^octave (units of 2^-31 / (128 + scale mantissa)) with fl(g / scale) <= a (STRICT: < a).
@@ -1002,8 +1019,8 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
                                                                      int iters, uint16_t* __restrict__ codebook) {
     constexpr int C = 1 << BITS;
     __shared__ double cs[C];
-    __shared__ double bn[C][kQuantMants];                 // members below boundary i (i = C - 1: all), per scale mantissa
-    __shared__ double bsum[C][kQuantMants];
+    __shared__ BelowBin bb[C][kQuantMants];               // what lies below boundary i (i = C - 1: all), per scale mantissa
+    __shared__ double fsum_of[C];
     __shared__ FarShared<C> fs;
     __shared__ int moved, search;
     const int i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -1049,9 +1066,7 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
     for (int h = 0; h < 2; ++h) {
         scale[h] = static_cast<double>(static_cast<uint64_t>(128 + lane + 64 * h) << (kHistOctaves - 1));
         inv[h] = 1.0 / scale[h];
-        const BelowBin all = q->below[lane + 64 * h][kQuantBins];
-        bn[C - 1][lane + 64 * h] = all.count;             // (every wave the same)
-        bsum[C - 1][lane + 64 * h] = all.sum;
+        bb[C - 1][lane + 64 * h] = q->below[lane + 64 * h][kQuantBins];      // (every wave the same)
     }
     if (threadIdx.x < C) cs[threadIdx.x] = -1.0 + (2 * static_cast<int>(threadIdx.x) + 1) / static_cast<double>(C);
     if (threadIdx.x == 0) { moved = 0; search = 0; }
@@ -1060,10 +1075,10 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
         if (threadIdx.x < C) f->bounds[threadIdx.x] = 0.0;
         double s, n;
         far_search(s, n);
-        if (lane == 0) bsum[0][i] = s;                    // (free until the first round)
+        if (lane == 0) fsum_of[i] = s;
         __syncthreads();
-        neg_sum = bsum[0][0];
-        pos_sum = bsum[0][C - 1];
+        neg_sum = fsum_of[0];
+        pos_sum = fsum_of[C - 1];
     }
     __syncthreads();
     auto boundary = [&](int j) { return uniform(0.5 * (cs[j] + cs[j + 1])); };
@@ -1084,9 +1099,7 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
                 const int below = below_of(b, h);
                 now[h] = below * 2 + (b < 0.0 ? 0 : 1);
                 if (now[h] != seen[h]) {                  // (a boundary soon moves past few of the bins: only those are fetched)
-                    const BelowBin at = q->below[lane + 64 * h][below];
-                    bn[i][lane + 64 * h] = at.count;
-                    bsum[i][lane + 64 * h] = at.sum;
+                    bb[i][lane + 64 * h] = q->below[lane + 64 * h][below];
                 }
             }
             if (now[0] != seen[0] || now[1] != seen[1] || among_far(b)) moved = 1;
@@ -1100,8 +1113,9 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int m = lane + 64 * h;
-            n += bn[i][m] - (i > 0 ? bn[i - 1][m] : 0.0);
-            s += (bsum[i][m] - (i > 0 ? bsum[i - 1][m] : 0.0)) * inv[h];
+            const BelowBin hi = bb[i][m], lo = i > 0 ? bb[i - 1][m] : BelowBin{0, 0};
+            n += below_count(hi.hi) - below_count(lo.hi);
+            s += sum_to_f64(below_sum(hi.lo, hi.hi) - below_sum(lo.lo, lo.hi)) * inv[h];
         }
         n = wave_total(n);
         s = wave_total(s);
@@ -1270,7 +1284,7 @@ static hipError_t quantize_blockscaled_bits(const uint16_t* W, int64_t N, int64_
     hipLaunchKernelGGL(bs_clear_kernel, dim3(2048), dim3(256), 0, s, q);
     hipLaunchKernelGGL(bs_scales_kernel, grid(nblocks, 128, 512), dim3(256), 0, s, W, nblocks, scales, q);
     hipLaunchKernelGGL(bs_group_kernel, dim3(static_cast<unsigned>((nblocks + kGroupBlocks - 1) / kGroupBlocks)), dim3(kGroupThreads), 0, s, scales, nblocks, q, packed);
-    // four workgroups a CU; a run of at least 64 blocks, to spread the clearing and flushing of 4096 counters
+    // four workgroups a CU; a run of at least 64 blocks, to spread the clearing and flushing of 8196 counters
     const int64_t run = (nblocks + 1023) / 1024 < 64 ? 64 : (nblocks + 1023) / 1024;
     hipLaunchKernelGGL(bs_count_kernel, dim3(static_cast<unsigned>((nblocks + run - 1) / run)), dim3(kCountThreads), 0, s, W, packed, nblocks, run, q);
     hipLaunchKernelGGL(bs_prefix_kernel, dim3(kQuantMants), dim3(1024), 0, s, q);

@@ -97,17 +97,30 @@ def test_far_elements_of_many_pieces(gpu, bits, share):
     assert all(np.array_equal(u, v) for u, v in zip(a, b))
 
 
-def test_far_member_decides_a_tie(gpu):
-    """16384 positive members, scales 1: without the far one their sum over their number is halfway between two bf16 values, with it
-    a little above (both sums are exact in 64 bits)."""
+def _halfway():
+    """16384 positive members, scales 1, without the last one's value halfway between two bf16 values in the mean."""
     W = np.full((4, 4096), 0x3F40, np.uint16)             # 0.75
     W[:, ::64] = 0x3F80                                    # 256 of 1, the scales
     W[0, 1:64] = W[0, 65:127] = 0x3F00                     # 125 of 0.5
+    W[3, 4000] = 0
+    assert np.sum(synth.bf16_to_f64(W)) == 16384 * (0.75 + 2.0 ** -9)
+    return W
+
+
+def test_far_member_decides_a_tie(gpu):
+    """With the far one the mean lies a little above halfway (both sums are exact in 64 bits)."""
+    W = _halfway()
     W[3, 4000] = 0x2F00                                    # 2^-33
-    v = synth.bf16_to_f64(W)
-    assert np.sum(v[v > 1e-9]) == 16384 * (0.75 + 2.0 ** -9)
-    idx, cb, _, _, _ = oracle.quantize_blockscaled(W, 1, 1)
-    assert list(cb) == [0xBF00, 0x3F41]
+    assert list(oracle.quantize_blockscaled(W, 1, 1)[1]) == [0xBF00, 0x3F41]
+    check(gpu, W, 1, 1)
+
+
+def test_small_member_decides_a_tie_above_many_others(gpu):
+    """The same with a member of 2^-31 and 2^24 members of -1 in the cluster below: a cluster's sum owes nothing to those."""
+    W = np.full((4100, 4096), 0xBF80, np.uint16)
+    W[:4] = _halfway()
+    W[3, 4000] = 0x3000                                    # 2^-31
+    assert list(oracle.quantize_blockscaled(W, 1, 1)[1]) == [0xBF80, 0x3F41]
     check(gpu, W, 1, 1)
 
 
