@@ -309,7 +309,7 @@ kmq_status kmq_dequant_blockscaled(const uint32_t* W, const uint16_t* codebook, 
 /* One codebook per row, no scales (the format kmq_gemv takes): row n of Wdense (N x K bf16,
  * row-major, 2-byte aligned) is clustered on its own, lo / hi = the row's min / max.
  *   packed    N * kmq_words_per_row(bits, K) words out (4-byte aligned), pad bits zero
- *   codebook  N x 2^bits bf16 out, ascending per row
+ *   codebook  N x 2^bits bf16 out, ascending per row (of a row with a non-finite weight: some values)
  * Errors: KMQ_ERR_NULL, KMQ_ERR_BITS, KMQ_ERR_SHAPE (N, K < 1, iters < 0), KMQ_ERR_ALIGN. */
 kmq_status kmq_quantize_rows(const uint16_t* Wdense, int64_t N, int64_t K, int bits, int iters,
                              uint32_t* packed, uint16_t* codebook, void* hip_stream);
@@ -320,6 +320,8 @@ kmq_status kmq_quantize_rows(const uint16_t* Wdense, int64_t N, int64_t K, int b
  * N*K normalised weights with lo = -1, hi = 1.
  *   Wdense    N x K bf16, row-major, 16-byte aligned for this call
  *   packed    N * K * bits / 32 words out; codebook 2^bits bf16 out; scales N x K/KMQ_BLOCK bf16 out
+ * Weights are finite; if one is not, every entry of the codebook is a NaN (and so are products with it), the
+ * indices are some, and its block's scale is the largest of the block's bit patterns without sign.
  *   workspace device memory of kmq_quantize_blockscaled_workspace_bytes() bytes, 8-byte aligned
  *             (25 MB: counters of the tensor's distinct values and their sums; contents undefined before and after)
  * K % KMQ_BLOCK != 0 -> KMQ_ERR_SHAPE; workspace NULL or too small -> KMQ_ERR_WORKSPACE. */

@@ -617,6 +617,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __re
 // A sum over members of one scale mantissa is a sum of weights (integers in the window's unit: exact) times the
 // reciprocal of the scale's mantissa.  A boundary b stands for the exact test fl(w / scale) > b: where b * scale comes
 // within a few units in the last place of a weight, the division itself decides.
+// Infinities and NaNs count as the magnitudes that their patterns continue (in range everywhere); the codebook says NaN then.
 // Elements more than 31 octaves below their scale ("far", next to none in most trained tensors) are counted apart per sign, and
 // their sums taken from the tensor (below).
 //
@@ -663,7 +664,8 @@ struct QuantScratch {                                    // layout of the caller
     unsigned long long blocks[kQuantMants];              // blocks per scale mantissa
     unsigned long long cursor[kQuantMants];              // ... of them placed so far
     unsigned long long zeros, far_neg, far_pos;
-    unsigned long long exact_assign;                     // a stored boundary lies among the far elements
+    uint32_t exact_assign;                               // a stored boundary lies among the far elements
+    uint32_t nonfinite;                                  // a weight is an infinity or a NaN
     FarPart far_part[kFarChunks][16];
     BelowBin below[kQuantMants][kQuantStride];           // (side by side: a round's look-ups are scattered, a line each)
     uint32_t above[kQuantMants][16];                     // per stored boundary: largest element key at or below it, in both halves
@@ -727,6 +729,7 @@ __global__ __launch_bounds__(256) void bs_scales_kernel(const uint16_t* __restri
             if ((threadIdx.x & 7) == 0 && b0 + i * 32 < nblocks) {
                 scales[b0 + i * 32] = static_cast<uint16_t>(s);
                 atomicAdd(&cnt[scale_pattern(s) & 127u], 1u);
+                if (s >= 0x7F80u) q->nonfinite = 1;
             }
         }
     }
@@ -1142,7 +1145,7 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
     if (any_far && threadIdx.x == 0) __hip_atomic_store(&f->finished, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     if (threadIdx.x < C) {
         const uint16_t hc = f64_to_bf16(cs[threadIdx.x]);
-        codebook[threadIdx.x] = hc;
+        codebook[threadIdx.x] = q->nonfinite ? 0x7FC0 : hc;
         cs[threadIdx.x] = bf16_to_f64(hc);
     }
     __syncthreads();

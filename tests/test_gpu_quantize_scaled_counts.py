@@ -153,6 +153,20 @@ def test_far_elements_cost_no_more_than_a_reading_or_two_a_round(gpu, bits, shar
     assert times[1] < (3 if share < 0.5 else 3 + iters) * times[0]
 
 
+@pytest.mark.parametrize("bits", [1, 4])
+@pytest.mark.parametrize("pattern", [0x7F80, 0xFF80, 0x7FC1, 0xFFFF])
+def test_non_finite_weight(gpu, bits, pattern):
+    """One infinity or NaN in the tensor shows in every centroid; the other blocks keep their scales."""
+    for N, iters in ((40, 5), (4, 3)):
+        W = synth.make_dense_weights(170, bits, N, 1024)
+        sc = run_blockscaled(gpu, W, bits, iters)[2]
+        W[3, 700] = pattern
+        _, cg, sg = run_blockscaled(gpu, W, bits, iters)
+        assert np.all((cg & 0x7FFF) > 0x7F80)
+        sc[3, 700 // 64] = pattern & 0x7FFF
+        assert np.array_equal(sg, sc)
+
+
 def test_list_reuse_of_the_output(gpu):
     """The index words hold the sorted block list for a while: nothing of it may be left, and repeats give the same bits."""
     W = synth.make_dense_weights(140, 0, 96, 4096)
