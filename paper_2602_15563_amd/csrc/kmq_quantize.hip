@@ -658,23 +658,23 @@ struct FarScratch {                                      // starts as zeros
     uint32_t arrived, finished, unused[2];
     double bounds[16];                                   // of the present search: changed only when all its pieces are done
 };
-struct QuantScratch {                                    // layout of the caller's workspace; everything down to `exact_assign` starts as zeros
+struct QuantScratch {                                    // layout of the caller's workspace; everything down to `members` starts as zeros
     FarScratch far;
-    unsigned long long members[kQuantMants][kQuantBins];
     unsigned long long blocks[kQuantMants];              // blocks per scale mantissa
     unsigned long long cursor[kQuantMants];              // ... of them placed so far
     unsigned long long zeros, far_neg, far_pos;
     uint32_t exact_assign;                               // a stored boundary lies among the far elements
     uint32_t nonfinite;                                  // a weight is an infinity or a NaN
+    unsigned long long members[kQuantMants][kQuantBins];
     FarPart far_part[kFarChunks][16];
     BelowBin below[kQuantMants][kQuantStride];           // (side by side: a round's look-ups are scattered, a line each)
     uint32_t above[kQuantMants][16];                     // per stored boundary: largest element key at or below it, in both halves
 };
 
-__global__ __launch_bounds__(256) void bs_clear_kernel(QuantScratch* q) {
+constexpr size_t kClearAll = offsetof(QuantScratch, far_part) / 16, kClearSmall = offsetof(QuantScratch, members) / 16;
+__global__ __launch_bounds__(256) void bs_clear_kernel(QuantScratch* q, size_t n16) {
     typedef u32x4_t __attribute__((aligned(8))) u32x4_a8_t;
-    constexpr size_t n16 = offsetof(QuantScratch, far_part) / 16;
-    static_assert(alignof(QuantScratch) == 8 && offsetof(QuantScratch, far_part) % 16 == 0, "cleared in 16-byte pieces");
+    static_assert(alignof(QuantScratch) == 8 && offsetof(QuantScratch, far_part) % 16 == 0 && offsetof(QuantScratch, members) % 16 == 0, "cleared in 16-byte pieces");
     for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < n16; i += static_cast<size_t>(gridDim.x) * 256)
         reinterpret_cast<u32x4_a8_t*>(q)[i] = u32x4_t{0, 0, 0, 0};
 }
@@ -1245,6 +1245,84 @@ __global__ __launch_bounds__(256) void bs_assign_pack_kernel(const uint16_t* __r
     }
 }
 
+// All of it in one workgroup, every element against every boundary: a few rounds on a small tensor, which the counters' fixed
+// cost of about 40 us outweighs.  64 x 64, 1 round, 1 / 4 bits: 17 / 19 us (counts: 42 / 46); 4 rounds: 17 / 45 (46 / 56).
+constexpr int kSmallChunks = 4;                          // of eight elements per thread
+constexpr int64_t kSmallBlocks = 256 * kSmallChunks / 8;
+constexpr int kSmallRounds = 4;
+template <int BITS>
+__global__ __launch_bounds__(256) void bs_small_kernel(const uint16_t* __restrict__ W, int nblocks, int iters, uint32_t* __restrict__ packed,
+                                                       uint16_t* __restrict__ codebook, uint16_t* __restrict__ scales) {
+    constexpr int C = 1 << BITS, U = kSmallChunks;
+    __shared__ double cs[C];
+    __shared__ double ps[4][C];
+    __shared__ int pn[4][C];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nchunks = nblocks * 8;
+    double v[U][8];
+    bool nonfinite = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {                         // eight lanes per block
+        const int c = tid + u * 256;
+        const u32x4_t w = *reinterpret_cast<const u32x4_t*>(W + (c < nchunks ? c : nchunks - 8 + (tid & 7)) * 8);
+        const uint32_t s = block_scale(w);
+        if ((tid & 7) == 0 && c < nchunks) scales[c >> 3] = static_cast<uint16_t>(s);
+        nonfinite |= s >= 0x7F80u;
+        const double scale = bf16_to_f64(s);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t d = w[e >> 1];
+            v[u][e] = s != 0 ? bf16_to_f64(e & 1 ? d >> 16 : d & 0xFFFFu) / scale : 0.0;
+        }
+    }
+    if (tid < C) cs[tid] = -1.0 + (2 * tid + 1) / static_cast<double>(C);
+    nonfinite = __syncthreads_or(nonfinite ? 1 : 0) != 0;
+    Clusters<C> cl;
+    double c[C];
+    for (int t = 0; t < iters; ++t) {
+#pragma unroll
+        for (int j = 0; j < C; ++j) c[j] = cs[j];
+        cl.begin(c);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (tid + u * 256 < nchunks) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) cl.add(v[u][e]);
+            }
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            const double s = wave_sum(cl.s[j]);
+            const int m = static_cast<int>(wave_sum(static_cast<long long>(cl.n[j])));
+            if (lane == 0) { ps[wave][j] = s; pn[wave][j] = m; }
+        }
+        __syncthreads();
+        if (tid < C) {
+            const double s = ((ps[0][tid] + ps[1][tid]) + ps[2][tid]) + ps[3][tid];
+            const int m = pn[0][tid] + pn[1][tid] + pn[2][tid] + pn[3][tid];
+            if (m > 0) cs[tid] = s / static_cast<double>(m);
+        }
+        __syncthreads();
+    }
+    if (tid < C) {
+        const uint16_t h = f64_to_bf16(cs[tid]);
+        codebook[tid] = nonfinite ? 0x7FC0 : h;
+        cs[tid] = bf16_to_f64(h);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < C; ++j) c[j] = cs[j];
+    cl.begin(c);
+    uint8_t* const out = reinterpret_cast<uint8_t*>(packed);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (tid + u * 256 >= nchunks) break;
+        uint32_t bits = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bits |= static_cast<uint32_t>(cl.assign(v[u][e])) << (e * BITS);
+#pragma unroll
+        for (int i = 0; i < BITS; ++i) out[(tid + u * 256) * BITS + i] = static_cast<uint8_t>(bits >> (8 * i));
+    }
+}
+
 size_t quantize_blockscaled_workspace_bytes() { return sizeof(QuantScratch); }
 
 template <int BITS>
@@ -1284,16 +1362,25 @@ static hipError_t quantize_blockscaled_bits(const uint16_t* W, int64_t N, int64_
         const int64_t g = (items + each - 1) / each;
         return dim3(static_cast<unsigned>(g < most ? g : most));
     };
-    hipLaunchKernelGGL(bs_clear_kernel, dim3(2048), dim3(256), 0, s, q);
+    if (nblocks <= kSmallBlocks && iters <= kSmallRounds) {
+        hipLaunchKernelGGL((bs_small_kernel<BITS>), dim3(1), dim3(256), 0, s, W, static_cast<int>(nblocks), iters, packed, codebook, scales);
+        return hipGetLastError();
+    }
+    const size_t clear = iters ? kClearAll : kClearSmall;
+    hipLaunchKernelGGL(bs_clear_kernel, grid(static_cast<int64_t>(clear), 256, 2048), dim3(256), 0, s, q, clear);
     hipLaunchKernelGGL(bs_scales_kernel, grid(nblocks, 128, 512), dim3(256), 0, s, W, nblocks, scales, q);
-    hipLaunchKernelGGL(bs_group_kernel, dim3(static_cast<unsigned>((nblocks + kGroupBlocks - 1) / kGroupBlocks)), dim3(kGroupThreads), 0, s, scales, nblocks, q, packed);
-    // four workgroups a CU; a run of at least 64 blocks, to spread the clearing and flushing of 8196 counters
-    const int64_t run = (nblocks + 1023) / 1024 < 64 ? 64 : (nblocks + 1023) / 1024;
-    hipLaunchKernelGGL(bs_count_kernel, dim3(static_cast<unsigned>((nblocks + run - 1) / run)), dim3(kCountThreads), 0, s, W, packed, nblocks, run, q);
-    hipLaunchKernelGGL(bs_prefix_kernel, dim3(kQuantMants), dim3(1024), 0, s, q);
+    if (iters) {                                          // (without rounds nothing is counted)
+        hipLaunchKernelGGL(bs_group_kernel, dim3(static_cast<unsigned>((nblocks + kGroupBlocks - 1) / kGroupBlocks)), dim3(kGroupThreads), 0, s, scales, nblocks, q, packed);
+        // Four workgroups a CU, of at least 64 blocks each to spread the clearing and flushing of 8196 counters (1024 x 1024: 6 us more
+        // with 16), but at least one workgroup a CU: it flushes once per scale mantissa among its blocks (64 x 64: 171 us in one
+        // workgroup, 49 with a block each; 25 rounds, 1 bit).
+        const int64_t least = nblocks < 64 * 256 ? (nblocks + 255) / 256 : 64, run = (nblocks + 1023) / 1024 < least ? least : (nblocks + 1023) / 1024;
+        hipLaunchKernelGGL(bs_count_kernel, dim3(static_cast<unsigned>((nblocks + run - 1) / run)), dim3(kCountThreads), 0, s, W, packed, nblocks, run, q);
+        hipLaunchKernelGGL(bs_prefix_kernel, dim3(kQuantMants), dim3(1024), 0, s, q);
+    }
     // one workgroup runs the rounds; the others, a few a CU, end at once unless there are far elements
     const uint32_t nchunks = static_cast<uint32_t>(nblocks < 256 * kFarChunks ? (nblocks + 255) / 256 : kFarChunks);
-    hipLaunchKernelGGL((bs_rounds_kernel<BITS>), dim3(BITS <= 2 ? 512 : 256), dim3((1 << BITS) * 64), 0, s, q, W, scales, nblocks, nchunks,
+    hipLaunchKernelGGL((bs_rounds_kernel<BITS>), dim3(iters == 0 ? 1 : BITS <= 2 ? 512 : 256), dim3((1 << BITS) * 64), 0, s, q, W, scales, nblocks, nchunks,
                        iters, codebook);
     hipLaunchKernelGGL((bs_assign_pack_kernel<BITS>), grid(npieces, 256, 4096), dim3(256), 0, s, W, scales, codebook, npieces, q, packed);
     return hipGetLastError();

@@ -34,6 +34,21 @@ def test_sizes(gpu, N, K, bits):
 
 
 @pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("N,K", [(1, 64), (3, 64), (31, 64), (2, 64 * 64), (1, 64 * 129), (64, 64), (640, 64)])
+@pytest.mark.parametrize("iters", [0, 1, 4, 5])
+def test_few_rounds_of_small_tensors(gpu, N, K, bits, iters):
+    """Up to 128 blocks and 4 rounds one workgroup does everything; around those limits, with zeros, a block of zeros, subnormal
+    scales and far elements."""
+    W = synth.make_dense_weights(115 + bits, N + iters, N, K)
+    W[0, 5::7] &= 0x8000
+    if N > 2:
+        W[1] = 0
+        W[2, 1::3] = (W[2, 1::3] & 0x807F) | (40 << 7)
+        W[N // 2] = W[N // 2] & 0x803F
+    check(gpu, W, bits, iters)
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
 @pytest.mark.parametrize("iters", [0, 1, 40])
 def test_rounds_and_exact_boundaries(gpu, bits, iters):
     """Weights on a coarse grid: many quotients coincide with the evenly spaced starting boundaries."""
