@@ -494,8 +494,23 @@ __global__ __launch_bounds__(256, NI == 4 ? 6 : 8) void quantize_rows_hist_kerne
 
 // ---- one codebook per row: any data ----------------------------------------------------------------
 // One workgroup of four waves per row; the row is re-read from the caches each round.  MARKED: only the rows that
-// quantize_rows_hist_kernel left (their codebook starts with kRowMark), kMarkedRows rows looked at per workgroup.
-constexpr int kMarkedRows = 4;
+// quantize_rows_hist_kernel left (their codebook starts with kRowMark).  Where all rows are left, 8 rounds, 1 bit / 4 bits: 256 x 4096
+// 30 / 112 us, 4096 x 4096 118 / 834 (without the histogram kernel in front 32 / 104 and 116 / 818; with four rows one after the other
+// per workgroup, of which none are left as a rule, 114 / 398 and 190 / 1003; the look at the marks costs 1 us at 14336 rows).
+template <int BITS, typename F>
+__device__ __forceinline__ void row_elements(const uint16_t* w, int64_t K, F&& f) {      // a thread's elements, ascending
+    int64_t k = threadIdx.x;
+    if constexpr (BITS == 1) {                            // eight in flight (wider: the registers of the clusters' sums are needed)
+        for (; k + 7 * 256 < K; k += 8 * 256) {
+            uint16_t h[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) h[i] = w[k + i * 256];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) f(bf16_to_f64(h[i]));
+        }
+    }
+    for (; k < K; k += 256) f(bf16_to_f64(w[k]));
+}
 template <int BITS>
 struct RowShared {
     double cs[1 << BITS];
@@ -516,11 +531,10 @@ __device__ __forceinline__ void quantize_row(RowShared<BITS>& sh, const uint16_t
     const uint16_t* w = W + n * K;
 
     double lo = __builtin_huge_val(), hi = -__builtin_huge_val();
-    for (int64_t k = tid; k < K; k += 256) {
-        const double v = bf16_to_f64(w[k]);
+    row_elements<BITS>(w, K, [&](double v) {
         lo = v < lo ? v : lo;
         hi = v > hi ? v : hi;
-    }
+    });
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         const double l2 = __shfl_xor(lo, off, 64), h2 = __shfl_xor(hi, off, 64);
@@ -543,7 +557,7 @@ __device__ __forceinline__ void quantize_row(RowShared<BITS>& sh, const uint16_t
 #pragma unroll
         for (int j = 0; j < C; ++j) c[j] = cs[j];
         cl.begin(c);
-        for (int64_t k = tid; k < K; k += 256) cl.add(bf16_to_f64(w[k]));
+        row_elements<BITS>(w, K, [&](double v) { cl.add(v); });
 #pragma unroll
         for (int j = 0; j < C; ++j) {
             const double s = wave_sum(cl.s[j]);
@@ -583,24 +597,15 @@ __device__ __forceinline__ void quantize_row(RowShared<BITS>& sh, const uint16_t
 }
 
 template <int BITS, bool MARKED>
-__global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __restrict__ W, int64_t N, int64_t K, int iters,
+__global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __restrict__ W, int64_t K, int iters,
                                                             uint32_t* __restrict__ packed, uint16_t* codebook) {
     constexpr int C = 1 << BITS;
     __shared__ RowShared<BITS> sh;
-    if constexpr (!MARKED) {
-        quantize_row<BITS>(sh, W, blockIdx.x, K, iters, packed, codebook);
-    } else {
-        const int64_t n0 = static_cast<int64_t>(blockIdx.x) * kMarkedRows;
-        uint32_t marks = 0;                                 // bit i: row n0 + i is to be done (the same in every thread)
-#pragma unroll
-        for (int i = 0; i < kMarkedRows; ++i)
-            marks |= n0 + i < N && codebook[(n0 + i) * C] == kRowMark ? 1u << i : 0u;
-        if (marks == 0) return;
-        for (int i = 0; i < kMarkedRows; ++i) {
-            __syncthreads();                                // marks read by all before the first is overwritten; shared arrays free
-            if (marks >> i & 1u) quantize_row<BITS>(sh, W, n0 + i, K, iters, packed, codebook);
-        }
+    const int64_t n = blockIdx.x;
+    if constexpr (MARKED) {
+        if (codebook[n * C] != kRowMark) return;          // (the same for every thread; overwritten behind the first barrier only)
     }
+    quantize_row<BITS>(sh, W, n, K, iters, packed, codebook);
 }
 
 // ---- the paper's format: scale per 64-element block, one codebook per tensor -------------------------
@@ -1329,8 +1334,10 @@ template <int BITS>
 static hipError_t quantize_rows_bits(const uint16_t* W, int64_t N, int64_t K, int iters, uint32_t* packed,
                                      uint16_t* codebook, hipStream_t s) {
     const dim3 rows(static_cast<unsigned>(N)), block(256);
-    if (K > kHistMaxK) {
-        hipLaunchKernelGGL((quantize_rows_kernel<BITS, false>), rows, block, 0, s, W, N, K, iters, packed, codebook);
+    // without rounds a short row does not repay its histogram (100000 x 64, 1 / 2 / 3 / 4 bits: 258 / 276 / 303 / 339 us with it,
+    // 148 / 158 / 237 / 413 without)
+    if (K > kHistMaxK || (iters == 0 && K <= 512 && BITS <= 3)) {
+        hipLaunchKernelGGL((quantize_rows_kernel<BITS, false>), rows, block, 0, s, W, K, iters, packed, codebook);
         return hipGetLastError();
     }
 #define KMQ_HIST(NI) hipLaunchKernelGGL((quantize_rows_hist_kernel<BITS, NI>), rows, block, 0, s, W, K, iters, packed, codebook)
@@ -1339,8 +1346,7 @@ static hipError_t quantize_rows_bits(const uint16_t* W, int64_t N, int64_t K, in
     else if (K <= 16384) KMQ_HIST(4);
     else KMQ_HIST(0);
 #undef KMQ_HIST
-    hipLaunchKernelGGL((quantize_rows_kernel<BITS, true>), dim3(static_cast<unsigned>((N + kMarkedRows - 1) / kMarkedRows)), block, 0, s,
-                       W, N, K, iters, packed, codebook);
+    hipLaunchKernelGGL((quantize_rows_kernel<BITS, true>), rows, block, 0, s, W, K, iters, packed, codebook);
     return hipGetLastError();
 }
 

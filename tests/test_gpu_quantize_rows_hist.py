@@ -53,3 +53,33 @@ def test_rows_not_aligned(gpu):
     """Odd row lengths start rows on odd half-words."""
     check(gpu, synth.make_dense_weights(95, 0, 37, 1111), 3, 9)
     check(gpu, synth.make_dense_weights(95, 1, 37, 4095), 4, 25)
+
+
+def test_rows_left_over_run_side_by_side(gpu):
+    """Neighbouring rows outside the histogram's window take about as long as one of them."""
+    import torch
+    from paper_2602_15563_amd import kmq
+    bits, N, K, iters = 4, 256, 4096, 8
+    times = []
+    for rows in (1, 4):
+        W = synth.make_dense_weights(97, 0, N, K)
+        W[8:8 + rows, 3::500] = (W[8:8 + rows, 3::500] & 0x807F) | (60 << 7)
+        Wd = gpu.dev(W)
+        packed, cb = torch.empty((N, K * bits // 32), dtype=torch.int32, device="cuda"), torch.empty((N, 1 << bits), dtype=torch.int16, device="cuda")
+        took = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            kmq.quantize_rows(Wd, N, K, bits, iters, packed, cb)
+            b.record()
+            torch.cuda.synchronize()
+            took.append(a.elapsed_time(b))
+        times.append(sorted(took)[3])
+    print(f"one row left over {times[0] * 1e3:.0f} us, four {times[1] * 1e3:.0f} us")
+    assert times[1] < 2 * times[0]
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("K", [17, 511, 512, 513])
+def test_no_rounds(gpu, bits, K):
+    check(gpu, synth.make_dense_weights(98, bits, 9, K), bits, 0)
