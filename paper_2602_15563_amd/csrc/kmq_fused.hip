@@ -37,8 +37,11 @@ typedef __attribute__((ext_vector_type(2))) float f32x2_t;
 // layer (us), one row a wave and one column a lane and step / this kernel: hidden 2560, MLP 6912, 1 / 2 / 3 / 4 bits 64.3 / 75.5 / 101 /
 // 80.6 -> 26.9 / 27.6 / 33.1 / 32.4; 5120, 13824: 201 / 237 / 452 / 343 -> 54.6 / 57.5 / 80.6 / 77.5.  Eight rows a
 // workgroup were no faster but at 3 bits (5120, 13824: 56.6 / 57.0 / 69.1 / 78.2).
-template <int BITS, bool PAIR>
-__global__ __launch_bounds__(256) void gemv_fused_generic_kernel(
+// Rows of at most 512 columns are one wave's (NW = 1), as a second one would have no chunk: 20000 x 72 with gains and residual, 1 / 2 /
+// 3 / 4 / 8 bits 8.5 / 8.1 / 10.1 / 9.2 / 15.0 -> 5.4 / 5.3 / 5.4 / 5.4 / 10.0 us.  The tables of 8 bits want all four waves to fill them where
+// there are few workgroups (300 x 512: 4.0 against 5.0).
+template <int BITS, bool PAIR, int NW>
+__global__ __launch_bounds__(NW * 64) void gemv_fused_generic_kernel(
     const uint32_t* __restrict__ W, const uint16_t* __restrict__ codebook,
     const uint32_t* __restrict__ W2, const uint16_t* __restrict__ codebook2,
     const uint16_t* __restrict__ x, bool norm, const uint16_t* __restrict__ norm_w, float eps,
@@ -48,7 +51,7 @@ __global__ __launch_bounds__(256) void gemv_fused_generic_kernel(
     constexpr int T = WE == 1 ? C : BITS == 1 ? 16 : C * C;
     constexpr int EW = BITS == 1 ? 2 : 1;                             // words per entry
     __shared__ alignas(8) uint32_t tab[ROWS][T * EW];
-    __shared__ float red[4][ROWS + 1];
+    __shared__ float red[NW][ROWS + 1];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int64_t n0 = static_cast<int64_t>(blockIdx.x) * OUT;
     const int64_t wpr = words_per_row(BITS, K);
@@ -61,7 +64,7 @@ __global__ __launch_bounds__(256) void gemv_fused_generic_kernel(
         row[r] = (PAIR && (r & 1) ? W2 : W) + n * wpr;
         cb[r] = (PAIR && (r & 1) ? codebook2 : codebook) + n * C;
 #pragma unroll
-        for (int e = tid; e < T; e += 256) {
+        for (int e = tid; e < T; e += NW * 64) {
             if constexpr (BITS == 1) {
                 const uint32_t a = cb[r][0], b = cb[r][1];
                 tab[r][2 * e] = (e & 1 ? b : a) | ((e & 2 ? b : a) << 16);
@@ -81,7 +84,7 @@ __global__ __launch_bounds__(256) void gemv_fused_generic_kernel(
     };
     const int chunks = static_cast<int>(K >> 3);
 #pragma unroll 2
-    for (int c = tid; c < chunks; c += 256) {
+    for (int c = tid; c < chunks; c += NW * 64) {
         uint32_t v[ROWS];
         [[maybe_unused]] uint32_t vh[ROWS];
 #pragma unroll
@@ -154,7 +157,12 @@ __global__ __launch_bounds__(256) void gemv_fused_generic_kernel(
     __syncthreads();
     const int64_t n = n0 + tid;
     if (tid >= OUT || n >= N) return;
-    auto total = [&](int r) { return ((red[0][r] + red[1][r]) + red[2][r]) + red[3][r]; };
+    auto total = [&](int r) {
+        float t = red[0][r];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t += red[w][r];
+        return t;
+    };
     const float s = norm ? 1.f / sqrtf(total(ROWS) * (1.f / static_cast<float>(K)) + eps) : 1.f;
     float out = total(PAIR ? 2 * tid : tid) * s;
     if constexpr (PAIR) {
@@ -165,16 +173,22 @@ __global__ __launch_bounds__(256) void gemv_fused_generic_kernel(
     y[n] = f32_to_bf16(out);
 }
 
-template <int BITS>
-static hipError_t launch_fused_bits(const GemmArgs& a, hipStream_t s) {
-    const dim3 block(256);
+template <int BITS, int NW>
+static void launch_fused_waves(const GemmArgs& a, hipStream_t s) {
+    const dim3 block(NW * 64);
     if (a.W2)
-        hipLaunchKernelGGL((gemv_fused_generic_kernel<BITS, true>), dim3(static_cast<unsigned>((a.N + 1) / 2)), block, 0, s, a.W, a.codebook, a.W2, a.codebook2, a.X,
+        hipLaunchKernelGGL((gemv_fused_generic_kernel<BITS, true, NW>), dim3(static_cast<unsigned>((a.N + 1) / 2)), block, 0, s, a.W, a.codebook, a.W2, a.codebook2, a.X,
                            a.norm, a.norm_w, a.eps, static_cast<const uint16_t*>(nullptr), a.Y, a.N, a.K);
     else
-        hipLaunchKernelGGL((gemv_fused_generic_kernel<BITS, false>), dim3(static_cast<unsigned>((a.N + 3) / 4)), block, 0, s, a.W, a.codebook,
+        hipLaunchKernelGGL((gemv_fused_generic_kernel<BITS, false, NW>), dim3(static_cast<unsigned>((a.N + 3) / 4)), block, 0, s, a.W, a.codebook,
                            static_cast<const uint32_t*>(nullptr), static_cast<const uint16_t*>(nullptr), a.X, a.norm, a.norm_w, a.eps,
                            a.residual, a.Y, a.N, a.K);
+}
+
+template <int BITS>
+static hipError_t launch_fused_bits(const GemmArgs& a, hipStream_t s) {
+    if (a.K <= 512 && (BITS <= 4 || a.N >= 4096)) launch_fused_waves<BITS, 1>(a, s);
+    else launch_fused_waves<BITS, 4>(a, s);
     return hipGetLastError();
 }
 

@@ -14,8 +14,9 @@ def gpu():
     return gpu_util
 
 
-@pytest.mark.parametrize("bits", [1, 2, 3, 4])
-@pytest.mark.parametrize("N,K", [(1, 8), (5, 2047), (3, 2049), (9, 2056), (6, 4109), (2, 8200), (4097, 519), (2049, 1032)])
+@pytest.mark.parametrize("bits", [1, 2, 3, 4, 8])
+@pytest.mark.parametrize("N,K", [(1, 8), (5, 2047), (3, 2049), (9, 2056), (6, 4109), (2, 8200), (4097, 519), (2049, 1032),
+                                 (1, 7), (9, 72), (5, 504), (3, 511), (6, 512), (4099, 100), (5, 513)])      # rows of one wave, and just above
 def test_edges(gpu, bits, N, K):
     idx, cb, x, g, res = _inputs(40 * bits + N + K, bits, N, K)
     _check(gpu, _run(gpu, idx, cb, x, bits, g, res), idx, cb, x, bits, g, res, f"b{bits} {N}x{K}")
