@@ -5,8 +5,9 @@
 //     Y[m][n] = sum_g scale[n][g] * sum_{k in block g} codebook[idx[n][k]] * X[m][k]
 //
 // i.e. the appendix's deferred-scaling variant, with the block sums and the sum
-// over blocks in fp32.  Canonical layout, any N, any K that is a multiple of 64,
-// batch 1..16.  The shape-specialised batch-1 kernels live in kmq_lut.hip.
+// over blocks in fp32.  Canonical layout, any N, any K that is a multiple of 64: 8 bits at
+// batch 1..16, 1..4 bits at batch 1..3 on few rows.  The kernels specialised on K live in kmq_lut.hip,
+// the matrix-core kernel of the other products in kmq_mfma_any.h.
 #include "kmq_device.h"
 #include "kmq_launch.h"
 
@@ -153,10 +154,16 @@ static hipError_t launch_blockscaled_bits(const GemmArgs& a, hipStream_t s) {
     const dim3 grid(static_cast<unsigned>((a.N + 3) / 4)), block(256);
 #define KMQ_BS_LAUNCH(MT) \
     hipLaunchKernelGGL((gemm_blockscaled_kernel<BITS, MT>), grid, block, 0, s, a.W, a.codebook, a.scales, a.X, a.Y, a.N, a.K, a.M)
-    if (a.M == 1) KMQ_BS_LAUNCH(1);
-    else if (a.M <= 4) KMQ_BS_LAUNCH(4);
-    else if (a.M <= 8) KMQ_BS_LAUNCH(8);
-    else KMQ_BS_LAUNCH(16);
+    if (a.M == 1) {
+        KMQ_BS_LAUNCH(1);
+    } else if (a.M <= 4) {
+        KMQ_BS_LAUNCH(4);
+    } else if constexpr (BITS == 8) {                     // (up to 4 bits batches of 4 and more are the matrix cores')
+        if (a.M <= 8) KMQ_BS_LAUNCH(8);
+        else KMQ_BS_LAUNCH(16);
+    } else {
+        return hipErrorInvalidValue;
+    }
 #undef KMQ_BS_LAUNCH
     return hipGetLastError();
 }

@@ -1,6 +1,6 @@
-// Shape-agnostic kernels: any K >= 1, any bit-width, both layouts, batch 1..16.
-// They are the fallback behind the shape-specialised kernels and the
-// bit-exact dequantiser.  Operation: paper App. E, "Kernel implementations"
+// Shape-agnostic kernels: products of the canonical layout, any K >= 1, any bit-width, batch 1..16 -- for 8 bits
+// and for few long rows, split over K; the rest has faster kernels -- and the
+// bit-exact dequantiser of both layouts.  Operation: paper App. E, "Kernel implementations"
 // (lookup, then multiply-accumulate), per-row codebooks, fp32 accumulation.
 #include <mutex>
 
@@ -62,7 +62,7 @@ template <int BITS, int MT>
 __global__ __launch_bounds__(256) void gemm_generic_kernel(
     const uint32_t* __restrict__ W, const uint16_t* __restrict__ codebook,
     const uint16_t* __restrict__ X, uint16_t* __restrict__ Y,
-    int64_t N, int64_t K, int M, int layout, float* __restrict__ partial) {
+    int64_t N, int64_t K, int M, float* __restrict__ partial) {
     constexpr int C = 1 << BITS;
     __shared__ float lut[4][C];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -86,18 +86,14 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(
         const int64_t k0 = g << 5;
         const bool full = k0 + 32 <= K;
         float wt[32];
-        if (layout == KMQ_LAYOUT_CANONICAL) {
-            uint32_t w[BITS];
+        uint32_t w[BITS];
 #pragma unroll
-            for (int j = 0; j < BITS; ++j) {
-                const int64_t wi = g * BITS + j;
-                w[j] = wi < wpr ? W[n * wpr + wi] : 0u;
-            }
-#pragma unroll
-            for (int e = 0; e < 32; ++e) wt[e] = lut[wave][group_field<BITS>(w, e)];
-        } else {
-            for (int e = 0; e < 32; ++e) wt[e] = lut[wave][tiled_fetch_index(W, BITS, K, n, k0 + e)];   // K % 128 == 0 here
+        for (int j = 0; j < BITS; ++j) {
+            const int64_t wi = g * BITS + j;
+            w[j] = wi < wpr ? W[n * wpr + wi] : 0u;
         }
+#pragma unroll
+        for (int e = 0; e < 32; ++e) wt[e] = lut[wave][group_field<BITS>(w, e)];
         if (full && vec_x) {
 #pragma unroll
             for (int m = 0; m < MT; ++m) {
@@ -301,7 +297,7 @@ static hipError_t launch_generic_bits(const GemmArgs& a, int slices, hipStream_t
     const dim3 grid(static_cast<unsigned>((a.N + 3) / 4), static_cast<unsigned>(slices)), block(256);
     float* partial = slices > 1 ? static_cast<float*>(a.workspace) : nullptr;
 #define KMQ_GEN_LAUNCH(MT) \
-    hipLaunchKernelGGL((gemm_generic_kernel<BITS, MT>), grid, block, 0, s, a.W, a.codebook, a.X, a.Y, a.N, a.K, a.M, a.layout, partial)
+    hipLaunchKernelGGL((gemm_generic_kernel<BITS, MT>), grid, block, 0, s, a.W, a.codebook, a.X, a.Y, a.N, a.K, a.M, partial)
     if (a.M == 1) KMQ_GEN_LAUNCH(1);
     else if (a.M <= 4) KMQ_GEN_LAUNCH(4);
     else if (a.M <= 8) KMQ_GEN_LAUNCH(8);
