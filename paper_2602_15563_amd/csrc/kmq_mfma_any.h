@@ -86,9 +86,19 @@ __device__ __forceinline__ void canon_index_to_byte1(uint32_t& a, uint32_t src, 
         asm("v_and_b32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:DWORD" : "+v"(a) : "v"(src), "v"(mask));
 }
 
+// Waves a SIMD that the registers have to leave room for: what an instance keeps without spilling.  Left alone the compiler spends
+// up to a third more of them, and a SIMD loses a wave or two (1-bit 18624 x 2843, batch 1: 10.3 us against 7.4).
+template <int BITS, bool SC, bool TILED, int MR, int RB>
+constexpr int canon_waves() {
+    if (BITS == 1 && TILED) return RB == 1 && MR <= 2 ? 4 : MR == 1 ? 3 : 2;             // (tiles of 512 columns)
+    if (RB == 2) return MR == 1 ? 4 : MR == 2 ? (BITS == 4 && SC ? 3 : 4) : 3;
+    if (BITS == 4) return MR == 1 ? 5 : MR == 2 ? 4 : SC ? 3 : 4;
+    return MR <= 2 ? 5 : 4;
+}
+
 // TILED: the matrix-core layout instead of the canonical one.  MR: groups of four batch rows that are staged (M <= 4 * MR).
 template <int BITS, bool SC, bool TILED, int MR, int RB, int NW>
-__global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict__ codebook,
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(canon_waves<BITS, SC, TILED, MR, RB>()))) void gemm_canon_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict__ codebook,
                                                              const uint16_t* __restrict__ X, uint16_t* __restrict__ Y,
                                                              int64_t N, int64_t K, int M, const uint16_t* __restrict__ scales) {
     constexpr int C = 1 << BITS, R = 4 * MR;
@@ -459,23 +469,23 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
         // exact ones, of 4.7 million, one chain a wave / this / the vector kernels: 3-bit K = 4101 738 / 505 / 529, 2-bit 11008
         // 823 / 497 / 500; batch 16.  Level in time (3-bit 5001 x 4101, batch 16: 11.6 / 11.7 us),
         // 1-bit rows with the sums of X aside (4096 x 11008, batch 4: 6.2 / 6.5).
-        f32x4_t part[4];
-        if constexpr (!SC) {
+        f32x4_t tile_sum;
 #pragma unroll
-            for (int t = 0; t < 8; ++t) part[t >> 1] = mfma(xf[t], weights(t), t & 1 ? part[t >> 1] : f32x4_t{0.f, 0.f, 0.f, 0.f});
-        } else {
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                f32x4_t t = mfma(xf[2 * b], weights(2 * b), f32x4_t{0.f, 0.f, 0.f, 0.f});
-                t = mfma(xf[2 * b + 1], weights(2 * b + 1), t);
+        for (int b = 0; b < 4; ++b) {
+            f32x4_t t = mfma(xf[2 * b], weights(2 * b), f32x4_t{0.f, 0.f, 0.f, 0.f});
+            t = mfma(xf[2 * b + 1], weights(2 * b + 1), t);
+            if constexpr (SC) {
                 const uint32_t s2 = sv[r][2 * pair + (b >> 1)];
                 const float s = b & 1 ? __uint_as_float(s2 & 0xFFFF0000u) : __uint_as_float(s2 << 16);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) part[b][i] = b & 1 ? fmaf(s, t[i], part[b - 1][i]) : s * t[i];
+                for (int i = 0; i < 4; ++i) tile_sum[i] = b ? fmaf(s, t[i], tile_sum[i]) : s * t[i];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) tile_sum[i] = b ? tile_sum[i] + t[i] : t[i];
             }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[r][i] += SC ? part[1][i] + part[3][i] : (part[0][i] + part[1][i]) + (part[2][i] + part[3][i]);
+        for (int i = 0; i < 4; ++i) acc[r][i] += tile_sum[i];
     };
     auto sum_x = [&] {                                    // this lane's pieces of a tile
 #pragma unroll
@@ -489,10 +499,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
     // The pieces pass between lanes of one wave, whose LDS instructions run in order: the compiler has to keep that order.
     auto in_wave = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
     auto exchange = [&](u32x4_t (&f)[8], int hh, int piece) {
+        in_wave();
         stage(piece);
         in_wave();
         fragments(f, hh);
-        in_wave();
     };
     // one tile; `more`: another one follows, its operands are requested as their registers become free
     auto step = [&](auto more, auto tail) {
@@ -512,7 +522,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_canon_kernel(const uint32_t* __r
             exchange(xf, 1, 2 * pair + 1);
             if constexpr (decltype(more)::value) {
                 if (pair == PAIRS - 1) load_x(next);
-                __builtin_amdgcn_sched_barrier(0);        // (the scheduler would put these loads behind the decoding)
+                __builtin_amdgcn_sched_barrier(0x100);    // (the scheduler would put these loads behind the decoding; LDS reads may move)
             }
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
