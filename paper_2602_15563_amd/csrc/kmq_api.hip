@@ -68,12 +68,13 @@ static bool any_beats_scaled_table(int64_t N, int64_t K, int bits, int M) {
     static const double each[4] = {0.045, 0.055, 0.07, 0.105};
     return M >= 3 && (N > kAnyOneRound || any_length_us(K, bits, M, true) < from_floor(3.7, 2.0, each[bits - 1], millions(N, K, M)));
 }
-// against a wave per row and a lane per block (from batch 4 on its columns' latencies alone are longer)
+// against a wave per row and a lane per block (from batch 4 on its columns' latencies alone are longer, and from batch 2 on where
+// they do not fit the first-level cache: 4-bit 1088 x 7808, batch 3: 14.2 against 10.4)
 static bool any_beats_block_generic(int64_t N, int64_t K, int bits, int M) {
     if (bits > 4) return false;
-    if (M >= 4 || N > kAnyOneRound) return true;
+    if (M >= 4 || N > kAnyOneRound || (M >= 2 && K > 4096)) return true;
     const double rounds = static_cast<double>((K / KMQ_BLOCK + 63) / 64);
-    const double latency = 2.6 + rounds * (M == 1 ? 0.9 : 2.6 + 0.9 * (M - 2));
+    const double latency = 2.6 + (M == 1 ? 0.9 : 2.6 + 0.9 * (M - 2)) * rounds;
     return any_length_us(K, bits, M, true) < from_floor(latency, 1.9, 0.28 * (1 + 0.7 * (M - 1)), millions(N, K, 1));
 }
 static Plan any_length_plan(int bits, bool scaled) {
