@@ -626,10 +626,10 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __re
 // Elements more than 31 octaves below their scale ("far", next to none in most trained tensors) are counted apart per sign, and
 // their sums taken from the tensor (below).
 //
-// 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits: 149 / 166 / 182 / 221 us (8519 / 9344 / 10727 / 13475 with every element
-// divided by its scale and compared with every boundary in fp64, each round); 1024 x 1024: 74 / 90 / 100 / 131 (3212 ..
-// 3570).  At 8192 x 8192 and 4 bits: clear 5, scales 29 (4.6 TB/s), group 12, count 43 (blocks gathered 128 bytes at a
-// time, LDS atomics), prefix 11, rounds 80 (2.6 us each: one CU's issue and its scattered line fetches), assign 45 us.
+// 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits: 157 / 177 / 193 / 224 us (8519 / 9344 / 10727 / 13475 with every element
+// divided by its scale and compared with every boundary in fp64, each round); 1024 x 1024, 4 bits: 127 (3570).  At 8192 x 8192
+// and 4 bits: clear 5, scales 33 (4.1 TB/s), group 13, count 43 (blocks gathered 128 bytes at a time, LDS atomics), prefix 12,
+// rounds 77 (3 us each: one CU's issue and its scattered line fetches), assign 45 us (vector issue).
 constexpr int kQuantMants = 128, kQuantBins = 2 * kHistMags, kQuantStride = kQuantBins + 1;
 constexpr double kFar = 4.656612873077393e-10;           // 2^-31: no far element reaches it
 
@@ -1076,6 +1076,9 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
         inv[h] = 1.0 / scale[h];
         bb[C - 1][lane + 64 * h] = q->below[lane + 64 * h][kQuantBins];      // (every wave the same)
     }
+    // fewer than 2^24 members of every scale mantissa, each of less than 2^39 units: their sums fit 64 bits (8192 x 8192, 4 bits:
+    // 234 -> 224 us)
+    const bool narrow = __all(below_count(bb[C - 1][lane].hi) < 16777216.0 && below_count(bb[C - 1][lane + 64].hi) < 16777216.0);
     if (threadIdx.x < C) cs[threadIdx.x] = -1.0 + (2 * static_cast<int>(threadIdx.x) + 1) / static_cast<double>(C);
     if (threadIdx.x == 0) { moved = 0; search = 0; }
     double neg_sum = 0.0, pos_sum = 0.0;
@@ -1122,8 +1125,13 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
         for (int h = 0; h < 2; ++h) {
             const int m = lane + 64 * h;
             const BelowBin hi = bb[i][m], lo = i > 0 ? bb[i - 1][m] : BelowBin{0, 0};
-            n += below_count(hi.hi) - below_count(lo.hi);
-            s += sum_to_f64(below_sum(hi.lo, hi.hi) - below_sum(lo.lo, lo.hi)) * inv[h];
+            if (narrow) {
+                n += static_cast<double>(static_cast<uint32_t>(hi.hi >> 24) - static_cast<uint32_t>(lo.hi >> 24));
+                s += static_cast<double>(static_cast<long long>(hi.lo - lo.lo)) * inv[h];
+            } else {
+                n += below_count(hi.hi) - below_count(lo.hi);
+                s += sum_to_f64(below_sum(hi.lo, hi.hi) - below_sum(lo.lo, lo.hi)) * inv[h];
+            }
         }
         n = wave_total(n);
         s = wave_total(s);
