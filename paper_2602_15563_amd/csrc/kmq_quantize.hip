@@ -629,7 +629,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __re
 // 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits: 157 / 177 / 193 / 224 us (8519 / 9344 / 10727 / 13475 with every element
 // divided by its scale and compared with every boundary in fp64, each round); 1024 x 1024, 4 bits: 127 (3570).  At 8192 x 8192
 // and 4 bits: clear 5, scales 33 (4.1 TB/s), group 13, count 43 (blocks gathered 128 bytes at a time, LDS atomics), prefix 12,
-// rounds 77 (3 us each: one CU's issue and its scattered line fetches), assign 45 us (vector issue).
+// rounds 80 (3 us each: one CU's issue and its scattered line fetches), assign 45 us (vector issue).
 constexpr int kQuantMants = 128, kQuantBins = 2 * kHistMags, kQuantStride = kQuantBins + 1;
 constexpr double kFar = 4.656612873077393e-10;           // 2^-31: no far element reaches it
 
@@ -931,7 +931,7 @@ __device__ __forceinline__ double uniform(double v) {
 // and the leader then waits for the claimed ones to be done.  Whoever is waited for is running: nothing depends on how many
 // workgroups are resident or in which order they start, and the helpers end when the leader says so.  A piece's sums are
 // added in a fixed order, and the pieces' sums in theirs.
-// 8192 x 8192, 4 bits, 25 rounds: 223 us without far elements, 313 with 0.01 % of them (one search), 2.7 ms where all but the
+// 8192 x 8192, 4 bits, 25 rounds: 228 us without far elements, 314 with 0.01 % of them (one search), 2.7 ms where all but the
 // scales are far (a search every round, 0.1 ms each); 133 and 423 ms with the rounds' workgroup searching alone.
 template <int C>
 struct FarShared {
