@@ -169,7 +169,7 @@ kmq_status kmq_gemv(const uint32_t* W, const uint16_t* codebook, const uint16_t*
  * (matrix-core kernel: a weight is dequantised once for the whole batch);
  * KMQ_LAYOUT_ROWLANE serves M = 1..4 on the vector units, each weight dequantised once
  * (M > 4: one launch per four columns); on the canonical layout row lengths with a specialised
- * table kernel look the weights up again for every column or pair of columns, in one launch, and everything else takes
+ * table kernel look the weights up again for every group of up to four columns, in one launch, and everything else takes
  * a matrix-core kernel as well, but for few rows.  A column of a batch is summed in the order of its kernel, which may be
  * another one at another M: where kmq_kernel_name gives the same "lut_..." name as at M = 1, it is the
  * batch-1 result bit for bit.  Repeats of one call are. */

@@ -10,12 +10,12 @@
 namespace kmq {
 
 // On the canonical layout a batch above 1 runs the batch-1 table kernel, where the shape has one, over a
-// grid of (row group, column or pair of columns) workgroups in ONE launch: the workgroups that share rows of W sit next to
+// grid of (row group, group of up to four columns) workgroups in ONE launch: the workgroups that share rows of W sit next to
 // each other on one XCD, so W still comes from memory once and the other columns find it in that L2 (the
 // tiled layout with its matrix-core kernel remains the fastest route for batch > 1: it also decodes each
-// weight once).  Which batches pair their columns: lut_two_columns in kmq_lut.hip.  Measured (us), table kernel /
-// shape-agnostic: 9216x3072 1-bit, batch 4: 7.5 / 21.7; 14336x4096 2-bit, batch 16: 41 / 121; 4096x4096 4-bit,
-// batch 4: 8.2 / 12.8.  (Builds with -DKMQ_TUNING read a cap on the batch from KMQ_PER_COLUMN_MAX in the environment,
+// weight once).  Which batches take several columns a workgroup: kmq_lut_columns.hip.  Measured (us), table kernel /
+// shape-agnostic: 9216x3072 1-bit, batch 4: 6.4 / 21.7; 14336x4096 2-bit, batch 16: 27.4 / 121; 4096x4096 4-bit,
+// batch 4: 6.6 / 12.8.  (Builds with -DKMQ_TUNING read a cap on the batch from KMQ_PER_COLUMN_MAX in the environment,
 // for sweeps.)
 static bool per_column_faster(int M) {
 #ifdef KMQ_TUNING

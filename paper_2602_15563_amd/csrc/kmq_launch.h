@@ -96,6 +96,7 @@ int lut_find(int64_t N, int64_t K, int bits, int layout, bool scaled = false);
 const char* lut_name(int table_index);
 bool lut_has_fusions(int table_index);   // RMSNorm in front / residual behind (GemmArgs::norm_w, residual)
 hipError_t launch_lut_entry(int table_index, const GemmArgs& a, hipStream_t s);
+bool launch_lut_columns(int table_index, const GemmArgs& a, hipStream_t s);   // batches: several columns a workgroup; false: too little work for that
 
 // The table kernel that walks K in rounds (canonical layout, K % 32 == 0, K <= 24576, batches in one launch).
 bool lut_loop_has_kernel(int64_t N, int64_t K, int bits, int layout);

@@ -40,6 +40,7 @@
 #include "kmq_device.h"
 #include "kmq_launch.h"
 #include "kmq_lut_blocks.h"
+#include "kmq_lut_shapes.h"
 
 namespace kmq {
 
@@ -63,9 +64,7 @@ namespace kmq {
 //   bit 2  RMSNorm with unit gains (gains folded into the weights before quantisation): only the
 //          scalar, taken from the activations the workgroup stages anyway -- no second vector to
 //          fetch per workgroup, which is what bit 0 costs.
-// MC: batch columns a workgroup computes (batch calls; 1 otherwise).  A column's sums are those of MC = 1 in the same order,
-// so its results are the batch-1 results bit for bit; what the columns share is the words, the lookups and the tables.
-template <int BITS, int G, int LPR, int NWK, int NWR, int RS, int WPE, bool SC, bool PAIR, int FUSE, int MC = 1>
+template <int BITS, int G, int LPR, int NWK, int NWR, int RS, int WPE, bool SC, bool PAIR, int FUSE>
 __global__ __launch_bounds__(NWK * NWR * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict__ codebook,
                      const uint16_t* __restrict__ x, uint16_t* y, int64_t N,
@@ -77,7 +76,6 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
     static_assert(FUSE == 0 || !SC, "decoder fusions are offered for the per-row-codebook format");
     static_assert(!(PAIR && (FUSE & 2)), "the fused pair has no residual input");
     static_assert((FUSE & 5) != 5, "gains or unit gains");
-    static_assert(MC == 1 || (!PAIR && FUSE == 0), "batch columns: plain products");
     constexpr bool NORM_G = (FUSE & 1) != 0, NORM = (FUSE & 5) != 0, RES = (FUSE & 2) != 0;
     static_assert(BITS >= 1 && BITS <= 4, "bit-width");
     static_assert(BITS != 3 || G % 3 == 0, "3-bit: lane slices are whole groups of three words");
@@ -119,9 +117,9 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
         // staged activations, padded per lane slice; threads past the end of x (the
         // thread count need not divide the chunk count) write clamped data into the tail,
         // so that staging has no branch for the loads to be sunk into
-        u32x4_t xs[MC][(XSLOTS + C16 - 1) / C16 * XSTR];
-        float part[MC][NWK][ROWS_WG];              // per-slice partial sums
-        float sxp[MC][NWK * NWR];                  // 1-bit: per-wave sum of the x the wave staged
+        u32x4_t xs[(XSLOTS + C16 - 1) / C16 * XSTR];
+        float part[NWK][ROWS_WG];                  // per-slice partial sums
+        float sxp[NWK * NWR];                      // 1-bit: per-wave sum of the x the wave staged
         float ssq[NWK * NWR];                      // RMSNorm: per-wave sum of x^2 over the chunks the wave staged
     };
     __shared__ Smem sm;
@@ -130,7 +128,7 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int wk = wave % NWK, wr = wave / NWK;
     const int sub = lane / LPR, pos = lane % LPR;
-    // mcols > 1: a batch of mcols activation rows in one launch, every workgroup MC columns (x and y are
+    // mcols > 1: a batch of mcols activation rows in one launch, every workgroup one column (x and y are
     // K and N elements apart per column).  Workgroup ids go round-robin over the 8 XCDs, each with its own L2;
     // the id is cut so that the workgroups that read the same rows of W sit on one XCD, one after the
     // other: the first fetches those rows from memory, the others find them in that L2.
@@ -138,13 +136,10 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
     // comparisons on 64-bit values cost two to three vector instructions each, ahead of the first load.
     const int Nr = static_cast<int>(N);
     int wg = blockIdx.x;
-    [[maybe_unused]] int live = 1;                           // columns of this workgroup; those past the batch repeat the last one
     if (mcols > 1) {
-        const int t = wg >> 3, cgroups = (mcols + MC - 1) / MC;
-        const int col = t % cgroups * MC;
-        wg = (t / cgroups) * 8 + (wg & 7);
+        const int t = wg >> 3, col = t % mcols;
+        wg = (t / mcols) * 8 + (wg & 7);
         if (wg * ROWS_WG >= Nr) return;                      // the grid is padded to a multiple of 8 row groups
-        live = mcols - col;
         x += static_cast<int64_t>(col) * K;
         y += static_cast<int64_t>(col) * (PAIR ? N / 2 : N);
     }
@@ -179,16 +174,14 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
     static_assert(XPT == 1 || XPT == 2 || XPT == 4, "x chunks per thread");
     typedef __attribute__((ext_vector_type(4 * XPT))) uint32_t xwide_t;
     static_assert(XCHUNKS % XPT == 0, "a thread's chunks are all inside x or all past its end");
-    xwide_t xt[MC];
+    xwide_t xt;
     [[maybe_unused]] xwide_t gt;                   // RMSNorm weights of the same elements
     [[maybe_unused]] uint16_t resv[2];             // residual of the two rows this thread stores
     [[maybe_unused]] uint32_t ccv[2];              // 1-bit: centroid pair of the two rows this thread stores
     {
         int c = threadIdx.x * XPT;
         c = c < XCHUNKS ? c : XCHUNKS - XPT;
-        xt[0] = *reinterpret_cast<const xwide_t*>(x + c * 8);
-#pragma unroll
-        for (int m = 1; m < MC; ++m) xt[m] = *reinterpret_cast<const xwide_t*>(x + static_cast<int64_t>(m < live ? m : live - 1) * K + c * 8);
+        xt = *reinterpret_cast<const xwide_t*>(x + c * 8);
         if constexpr (NORM_G) gt = *reinterpret_cast<const xwide_t*>(norm_w + c * 8);
         if constexpr (RES) {
 #pragma unroll
@@ -278,15 +271,15 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
         float ss = 0.f;
 #pragma unroll
         for (int i = 0; i < 4 * XPT; ++i) {
-            ss = dot2_bf16(xt[0][i], xt[0][i], ss);
+            ss = dot2_bf16(xt[i], xt[i], ss);
             if constexpr (NORM_G) {
-                const float x0 = __uint_as_float(xt[0][i] << 16), x1 = __uint_as_float(xt[0][i] & 0xFFFF0000u);
+                const float x0 = __uint_as_float(xt[i] << 16), x1 = __uint_as_float(xt[i] & 0xFFFF0000u);
                 const float g0 = __uint_as_float(gt[i] << 16), g1 = __uint_as_float(gt[i] & 0xFFFF0000u);
                 // a product of two bf16 values is exact in fp32: one rounding (to nearest even, the
                 // hardware's packed conversion), to the bf16 activation
                 typedef __attribute__((ext_vector_type(2))) float f32x2_t;
                 const f32x2_t p = {x0 * g0, x1 * g1};
-                xt[0][i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2_t));
+                xt[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2_t));
             }
         }
         ss = threadIdx.x * XPT < XCHUNKS ? ss : 0.f;       // threads past the end restaged a neighbour's chunks
@@ -296,23 +289,18 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
     if constexpr (BITS == 1 && !SC) {
         // sum of the activations for the two-centroid closed form, taken here from the chunks every thread stages anyway
         // (4 * XPT dots per thread) rather than from each wave's activation registers behind the lookups
+        float sxl = 0.f;
 #pragma unroll
-        for (int m = 0; m < MC; ++m) {
-            float sxl = 0.f;
-#pragma unroll
-            for (int i = 0; i < 4 * XPT; ++i) sxl = dot2_bf16(0x3F803F80u, xt[m][i], sxl);
-            sxl = threadIdx.x * XPT < XCHUNKS ? sxl : 0.f; // threads past the end restaged a neighbour's chunks
-            sxl = group_sum<64>(sxl);
-            if (lane == 63) sm.sxp[m][wave] = sxl;
-        }
+        for (int i = 0; i < 4 * XPT; ++i) sxl = dot2_bf16(0x3F803F80u, xt[i], sxl);
+        sxl = threadIdx.x * XPT < XCHUNKS ? sxl : 0.f;     // threads past the end restaged a neighbour's chunks
+        sxl = group_sum<64>(sxl);
+        if (lane == 63) sm.sxp[wave] = sxl;
     }
 #pragma unroll
     for (int h = 0; h < XPT; ++h) {
         const int c = threadIdx.x * XPT + h;
         const int sl = c / C16, q = c % C16;
-#pragma unroll
-        for (int m = 0; m < MC; ++m)
-            sm.xs[m][sl * XSTR + q] = u32x4_t{xt[m][4 * h], xt[m][4 * h + 1], xt[m][4 * h + 2], xt[m][4 * h + 3]};
+        sm.xs[sl * XSTR + q] = u32x4_t{xt[4 * h], xt[4 * h + 1], xt[4 * h + 2], xt[4 * h + 3]};
     }
     if constexpr (BITS == 1) {
         if (threadIdx.x < 16) {
@@ -326,36 +314,29 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
     __syncthreads();
 
     // ---- 4. this lane's activations into registers ---------------------------------------------
-    uint32_t xr[MC][XR];
+    uint32_t xr[XR];
 #pragma unroll
-    for (int m = 0; m < MC; ++m) {
+    for (int q = 0; q < C16; ++q) {
+        const u32x4_t v = sm.xs[xbase + q];
 #pragma unroll
-        for (int q = 0; q < C16; ++q) {
-            const u32x4_t v = sm.xs[m][xbase + q];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if constexpr (BITS == 4) {
-                    xr[m][q * 8 + 2 * j] = v[j] << 16;
-                    xr[m][q * 8 + 2 * j + 1] = v[j] & 0xFFFF0000u;
-                } else {
-                    xr[m][q * 4 + j] = v[j];
-                }
+        for (int j = 0; j < 4; ++j) {
+            if constexpr (BITS == 4) {
+                xr[q * 8 + 2 * j] = v[j] << 16;
+                xr[q * 8 + 2 * j + 1] = v[j] & 0xFFFF0000u;
+            } else {
+                xr[q * 4 + j] = v[j];
             }
         }
     }
 
     // 1-bit block-scaled: the sums of x over this lane's two blocks, taken now, while the index words are still in
     // flight, rather than behind the lookups
-    [[maybe_unused]] float sx0[MC], sx1[MC];
+    [[maybe_unused]] float sx0 = 0.f, sx1 = 0.f;
     if constexpr (SC && BITS == 1) {
 #pragma unroll
-        for (int m = 0; m < MC; ++m) {
-            sx0[m] = sx1[m] = 0.f;
-#pragma unroll
-            for (int i = 0; i < XR / 2; ++i) {
-                sx0[m] = dot2_bf16(0x3F803F80u, xr[m][i], sx0[m]);
-                sx1[m] = dot2_bf16(0x3F803F80u, xr[m][XR / 2 + i], sx1[m]);
-            }
+        for (int i = 0; i < XR / 2; ++i) {
+            sx0 = dot2_bf16(0x3F803F80u, xr[i], sx0);
+            sx1 = dot2_bf16(0x3F803F80u, xr[XR / 2 + i], sx1);
         }
     }
 
@@ -404,19 +385,14 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
     if constexpr (SC && BITS == 1) cpair = *reinterpret_cast<const uint32_t*>(codebook);
     asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(cpair) : : "memory");
     const uint32_t mask = BITS == 1 ? 0x78u : BITS == 3 ? 0xFCu : 0x3Cu;
-    float acc[MC][RS];
-    [[maybe_unused]] float accb[MC][RS];           // 1-bit with scales: the first block's sum
-    float a0[MC], a1[MC];
-#pragma unroll
-    for (int m = 0; m < MC; ++m) a0[m] = a1[m] = 0.f;
-    auto take = [&](float (&out)[MC][RS], int t) {
-#pragma unroll
-        for (int m = 0; m < MC; ++m) {
-            settle_dot(a0[m], a1[m]);
-            out[m][t] = a0[m] + a1[m];
-            a0[m] = 0.f;
-            a1[m] = 0.f;
-        }
+    float acc[RS];
+    [[maybe_unused]] float accb[RS];               // 1-bit with scales: the first block's sum
+    float a0 = 0.f, a1 = 0.f;
+    auto take = [&](float (&out)[RS], int t) {
+        settle_dot(a0, a1);
+        out[t] = a0 + a1;
+        a0 = 0.f;
+        a1 = 0.f;
     };
     constexpr int NU = RS * U;
     if constexpr (BITS == 1) {
@@ -431,8 +407,7 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
                 constexpr int t1 = (n + 1) / U, u1 = (n + 1) % U;
                 issue4_b64<u1 % 2>(w[t1][u1 / 2], re, ro, ar, vv[(n + 1) & 1], mask);
             }
-#pragma unroll
-            for (int m = 0; m < MC; ++m) consume4_b64<more ? 4 : 0>(vv[n & 1], &xr[m][u * 8], a0[m], a1[m]);
+            consume4_b64<more ? 4 : 0>(vv[n & 1], &xr[u * 8], a0, a1);
             if constexpr (SC && u == U / 2 - 1) take(accb, t);
             if constexpr (u == U - 1) take(acc, t);
         });
@@ -450,14 +425,11 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
             }
         };
         // PENDING: see the blocks
-        auto consume = [&](auto pc, int m, const uint32_t (&vd)[8], int u) {
-            if constexpr (BITS != 4) consume8_dot2<decltype(pc)::value>(vd, &xr[m][u * 8], a0[m], a1[m]);
-            else consume8_fma<decltype(pc)::value>(vd, &xr[m][u * 8], a0[m], a1[m]);
+        auto consume = [&](auto pc, const uint32_t (&vd)[8], int u) {
+            if constexpr (BITS != 4) consume8_dot2<decltype(pc)::value>(vd, &xr[u * 8], a0, a1);
+            else consume8_fma<decltype(pc)::value>(vd, &xr[u * 8], a0, a1);
         };
         using std::integral_constant;
-        // the first columns of a unit stand between the two halves of the next one's lookups, the others behind them: there
-        // the unit's own values are already in registers (at most the next unit's eight reads are outstanding)
-        constexpr int MF = (MC + 1) / 2;
         issue_half(integral_constant<int, 0>{}, integral_constant<int, 0>{}, integral_constant<int, 0>{}, v[0]);
         issue_half(integral_constant<int, 0>{}, integral_constant<int, 0>{}, integral_constant<int, 1>{}, v[0]);
         static_for<0, NU>([&](auto ic) {
@@ -466,14 +438,10 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
             if constexpr (n + 1 < NU) {
                 constexpr int t1 = (n + 1) / U, u1 = (n + 1) % U;
                 issue_half(integral_constant<int, t1>{}, integral_constant<int, u1>{}, integral_constant<int, 0>{}, v[(n + 1) & 1]);
-#pragma unroll
-                for (int m = 0; m < MF; ++m) consume(integral_constant<int, 4>{}, m, v[n & 1], u);
+                consume(integral_constant<int, 4>{}, v[n & 1], u);
                 issue_half(integral_constant<int, t1>{}, integral_constant<int, u1>{}, integral_constant<int, 1>{}, v[(n + 1) & 1]);
-#pragma unroll
-                for (int m = MF; m < MC; ++m) consume(integral_constant<int, 8>{}, m, v[n & 1], u);
             } else {
-#pragma unroll
-                for (int m = 0; m < MC; ++m) consume(integral_constant<int, 0>{}, m, v[n & 1], u);
+                consume(integral_constant<int, 0>{}, v[n & 1], u);
             }
             if constexpr (u == U - 1) take(acc, t);
         });
@@ -483,31 +451,25 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
     // (nothing of what follows may be scheduled into the hand-counted pipeline above)
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (SC) {
+        if constexpr (BITS == 1) {
+            // two blocks per lane: s0*(c0*X0 + d*S0) + s1*(c0*X1 + d*S1), X = the block's sum of x
+            const float c0 = bf16_to_f32(cpair & 0xFFFFu), d = bf16_to_f32(cpair >> 16) - c0;
 #pragma unroll
-        for (int m = 0; m < MC; ++m) {
-            if constexpr (BITS == 1) {
-                // two blocks per lane: s0*(c0*X0 + d*S0) + s1*(c0*X1 + d*S1), X = the block's sum of x
-                const float c0 = bf16_to_f32(cpair & 0xFFFFu), d = bf16_to_f32(cpair >> 16) - c0;
+            for (int t = 0; t < RS; ++t)
+                acc[t] = bf16_to_f32(sv[t][0]) * fmaf(d, accb[t], c0 * sx0) + bf16_to_f32(sv[t][1]) * fmaf(d, acc[t], c0 * sx1);
+        } else {
 #pragma unroll
-                for (int t = 0; t < RS; ++t)
-                    acc[m][t] = bf16_to_f32(sv[t][0]) * fmaf(d, accb[m][t], c0 * sx0[m]) + bf16_to_f32(sv[t][1]) * fmaf(d, acc[m][t], c0 * sx1[m]);
-            } else {
-#pragma unroll
-                for (int t = 0; t < RS; ++t) acc[m][t] *= bf16_to_f32(sv[t][0]);
-            }
+            for (int t = 0; t < RS; ++t) acc[t] *= bf16_to_f32(sv[t][0]);
         }
     }
 #pragma unroll
-    for (int m = 0; m < MC; ++m) {
-#pragma unroll
-        for (int t = 0; t < RS; ++t) {
-            const float s = group_sum<LPR>(acc[m][t]);
-            if (pos == LPR - 1) sm.part[m][wk][wr * ROWS_WAVE + t * RPL + sub] = s;
-        }
+    for (int t = 0; t < RS; ++t) {
+        const float s = group_sum<LPR>(acc[t]);
+        if (pos == LPR - 1) sm.part[wk][wr * ROWS_WAVE + t * RPL + sub] = s;
     }
     __syncthreads();
 
-    // ---- 7. epilogue: two rows per thread, one coalesced store per workgroup and column ----------
+    // ---- 7. epilogue: two rows per thread, one coalesced store per workgroup --------------------
     if (threadIdx.x < ROWS_WG / 2) {
         [[maybe_unused]] float rnorm = 1.f;
         if constexpr (NORM) {
@@ -517,41 +479,36 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
             rnorm = 1.f / sqrtf(ss * (1.f / K) + eps);
         }
         const int r2 = wg_row0 + threadIdx.x * 2;
+        float out[2];
 #pragma unroll
-        for (int m = 0; m < MC; ++m) {
-            if (MC > 1 && m >= live) break;
-            float out[2];
+        for (int h = 0; h < 2; ++h) {
+            const int rl = threadIdx.x * 2 + h;
+            float s = 0.f;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int rl = threadIdx.x * 2 + h;
-                float s = 0.f;
+            for (int k = 0; k < NWK; ++k) s += sm.part[k][rl];
+            if constexpr (BITS == 1 && !SC) {
+                float sx = 0.f;
 #pragma unroll
-                for (int k = 0; k < NWK; ++k) s += sm.part[m][k][rl];
-                if constexpr (BITS == 1 && !SC) {
-                    float sx = 0.f;
-#pragma unroll
-                    for (int k = 0; k < NWK * NWR; ++k) sx += sm.sxp[m][k];
-                    const uint32_t cc = ccv[h];
-                    const float c0 = bf16_to_f32(cc & 0xFFFFu), c1 = bf16_to_f32(cc >> 16);
-                    s = fmaf(c1 - c0, s, c0 * sx);
-                }
-                if constexpr (NORM) s *= rnorm;
-                if constexpr (RES) s += bf16_to_f32(resv[h]);
-                out[h] = s;
+                for (int k = 0; k < NWK * NWR; ++k) sx += sm.sxp[k];
+                const uint32_t cc = ccv[h];
+                const float c0 = bf16_to_f32(cc & 0xFFFFu), c1 = bf16_to_f32(cc >> 16);
+                s = fmaf(c1 - c0, s, c0 * sx);
             }
-            if constexpr (PAIR) {
-                // out[0] = gate, out[1] = up of output element r2 / 2: silu(gate) * up in fp32
-                if (r2 < Nr) y[r2 >> 1] = f32_to_bf16(out[0] / (1.f + __expf(-out[0])) * out[1]);
-                return;
-            }
-            uint16_t* const ym = y + static_cast<int64_t>(m) * N;
-            const uint32_t packed = static_cast<uint32_t>(f32_to_bf16(out[0])) | (static_cast<uint32_t>(f32_to_bf16(out[1])) << 16);
-            if (r2 + 1 < Nr && (reinterpret_cast<uintptr_t>(ym) & 3u) == 0) {
-                *reinterpret_cast<uint32_t*>(ym + r2) = packed;
-            } else {
-                if (r2 < Nr) ym[r2] = static_cast<uint16_t>(packed);
-                if (r2 + 1 < Nr) ym[r2 + 1] = static_cast<uint16_t>(packed >> 16);
-            }
+            if constexpr (NORM) s *= rnorm;
+            if constexpr (RES) s += bf16_to_f32(resv[h]);
+            out[h] = s;
+        }
+        if constexpr (PAIR) {
+            // out[0] = gate, out[1] = up of output element r2 / 2: silu(gate) * up in fp32
+            if (r2 < Nr) y[r2 >> 1] = f32_to_bf16(out[0] / (1.f + __expf(-out[0])) * out[1]);
+            return;
+        }
+        const uint32_t packed = static_cast<uint32_t>(f32_to_bf16(out[0])) | (static_cast<uint32_t>(f32_to_bf16(out[1])) << 16);
+        if (r2 + 1 < Nr && (reinterpret_cast<uintptr_t>(y) & 3u) == 0) {
+            *reinterpret_cast<uint32_t*>(y + r2) = packed;
+        } else {
+            if (r2 < Nr) y[r2] = static_cast<uint16_t>(packed);
+            if (r2 + 1 < Nr) y[r2 + 1] = static_cast<uint16_t>(packed >> 16);
         }
     }
 }
@@ -566,23 +523,6 @@ struct LutEntry {
     const char* name;
     void (*launch)(const GemmArgs&, hipStream_t);
 };
-
-// Whether a workgroup of a batch call takes two columns.  They share the address arithmetic and the table reads, which at
-// one column are two thirds of the instructions; they cost registers, so fewer waves hide the first loads.  Measured (us), one
-// column / two: 2-bit 4096 x 14336, batch 2 / 4 / 16: 10.4 / 8.5, 19.6 / 13.7, 63.3 / 47.9; 3-bit 14336 x 4096, batch 4: 20.1 / 14.9;
-// 4-bit 9216 x 3072: 14.9 / 11.9; scaled 4-bit 9216 x 14336, batch 2: 40.2 / 29.3.  Small products do not fill the chip with half
-// the workgroups (2-bit 2048 x 6144, batch 2: 4.4 / 4.9; 2048 x 1536, batch 4: 3.1 / 3.2), and an odd batch pays for a column it does not
-// have: up to 5 that outweighs the gain for many shapes (3-bit 2048 x 14336: 16.3 / 18.0), at 7 it is even or better.  At 1 bit a
-// lookup brings four weights and 48 or 64 activation registers a column leave two or three waves (14336 x 8192, batch 4:
-// 22.0 / 24.0); the 8-byte loads of the 2-bit kernel for few rows do not gain either (9216 x 14336, batch 13: 121 / 131), nor do the
-// three waves along K of the 4-bit one (1024 x 6144, batch 7: 8.6 / 10.0; 8192 x 6144: 50.0 / 54.3; even batches -2 % to +5 %).  Four columns
-// were slower than two nearly everywhere (2-bit 4096 x 14336, batch 4: 16.4): one workgroup a CU, whose loads nothing hides.
-static bool lut_two_columns(const GemmArgs& a) {
-#ifdef KMQ_TUNING
-    if (const char* const v = std::getenv("KMQ_LUT_MC")) return v[0] == '2';
-#endif
-    return (a.M % 2 == 0 || a.M >= 7) && a.N * a.K * a.M > (int64_t(24) << 20);
-}
 
 template <int BITS, int G, int LPR, int NWK, int NWR, int RS, int WPE, bool SC>
 static void launch_lut(const GemmArgs& a, hipStream_t s) {
@@ -623,104 +563,20 @@ static void launch_lut(const GemmArgs& a, hipStream_t s) {
         }
 #undef KMQ_LUT_FUSED
     }
-    if (a.M > 1) {                                            // batch: one workgroup per (row group, group of columns)
-        const int64_t groups = (a.N + rows_wg - 1) / rows_wg;
-        auto launch = [&](auto mc, auto wpe) {
-            constexpr int MC = decltype(mc)::value;
-            const dim3 grid_m(static_cast<unsigned>((groups + 7) / 8 * 8 * ((a.M + MC - 1) / MC)));
-            hipLaunchKernelGGL((gemv_lut_kernel<BITS, G, LPR, NWK, NWR, RS, decltype(wpe)::value, SC, false, 0, MC>), grid_m, block, 0, s,
-                               a.W, a.codebook, a.X, a.Y, a.N, a.scales, nullptr, nullptr, nullptr, 0.f, nullptr, a.M);
-        };
-        using std::integral_constant;
-        if constexpr (BITS > 1 && !(BITS == 2 && G == 2) && !(BITS == 4 && NWK == 3)) {
-            constexpr int XR = G * (BITS == 4 ? 32 : 16) / BITS;      // activation registers of a column
-            if (lut_two_columns(a)) {
-                launch(integral_constant<int, 2>{}, integral_constant<int, XR <= 24 ? 5 : 4>{});
-                return;
-            }
-        }
-        launch(integral_constant<int, 1>{}, integral_constant<int, WPE>{});
-        return;
-    }
-    hipLaunchKernelGGL((gemv_lut_kernel<BITS, G, LPR, NWK, NWR, RS, WPE, SC, false, 0>), grid, block, 0, s,
-                       a.W, a.codebook, a.X, a.Y, a.N, a.scales, nullptr, nullptr, nullptr, 0.f, nullptr, 1);
+    const int64_t groups = (a.N + rows_wg - 1) / rows_wg;     // a batch: one workgroup per (row group, column)
+    const dim3 grid_m(static_cast<unsigned>((groups + 7) / 8 * 8 * a.M));
+    hipLaunchKernelGGL((gemv_lut_kernel<BITS, G, LPR, NWK, NWR, RS, WPE, SC, false, 0>), a.M > 1 ? grid_m : grid, block, 0, s,
+                       a.W, a.codebook, a.X, a.Y, a.N, a.scales, nullptr, nullptr, nullptr, 0.f, nullptr, a.M);
 }
 
 #define KMQ_LUT(BITS, G, LPR, NWK, NWR, RS, WPE) \
     { BITS, int64_t(NWK) * LPR * (G * 32 / BITS), NWR * (64 / LPR) * RS, false, \
-      "lut_b" #BITS "_g" #G "_l" #LPR "_k" #NWK "_r" #NWR "x" #RS, &launch_lut<BITS, G, LPR, NWK, NWR, RS, WPE, false> }
+      "lut_b" #BITS "_g" #G "_l" #LPR "_k" #NWK "_r" #NWR "x" #RS, &launch_lut<BITS, G, LPR, NWK, NWR, RS, WPE, false> },
 #define KMQ_LUT_SC(BITS, G, LPR, NWK, NWR, RS, WPE) \
     { BITS, int64_t(NWK) * LPR * (G * 32 / BITS), NWR * (64 / LPR) * RS, true, \
-      "lut_sc_b" #BITS "_g" #G "_l" #LPR "_k" #NWK "_r" #NWR "x" #RS, &launch_lut<BITS, G, LPR, NWK, NWR, RS, WPE, true> }
+      "lut_sc_b" #BITS "_g" #G "_l" #LPR "_k" #NWK "_r" #NWR "x" #RS, &launch_lut<BITS, G, LPR, NWK, NWR, RS, WPE, true> },
 
-static const LutEntry kLut[] = {
-    // Several shapes may serve one (bits, K): lut_find takes the one whose grid comes out
-    // most even over the CUs for the given N; the first listed wins ties.
-    // 1-bit
-    KMQ_LUT(1, 3, 16, 1, 4, 1, 4),   // K = 1536, 16 rows per workgroup
-    KMQ_LUT(1, 4, 16, 1, 4, 1, 4),   // K = 2048, 16 rows per workgroup
-    KMQ_LUT(1, 4, 16, 1, 2, 1, 4),   //            8
-    KMQ_LUT(1, 3, 32, 1, 4, 2, 4),   // K = 3072, 16
-    KMQ_LUT(1, 3, 32, 1, 3, 3, 4),   //           18
-    KMQ_LUT(1, 3, 32, 1, 3, 2, 4),   //           12
-    KMQ_LUT(1, 4, 32, 1, 4, 2, 4),   // K = 4096
-    KMQ_LUT(1, 3, 64, 1, 6, 2, 4),   // K = 6144, 12
-    KMQ_LUT(1, 4, 64, 1, 4, 2, 4),   // K = 8192,  8
-    KMQ_LUT(1, 4, 64, 1, 4, 3, 4),   //           12
-    // 2-bit
-    KMQ_LUT(2, 3, 32, 1, 4, 2, 6),   // K = 1536
-    KMQ_LUT(2, 4, 32, 1, 4, 2, 6),   // K = 2048
-    KMQ_LUT(2, 3, 64, 1, 4, 2, 6),   // K = 3072
-    KMQ_LUT(2, 4, 64, 1, 4, 2, 7),   // K = 4096
-    KMQ_LUT(2, 3, 64, 2, 3, 2, 6),   // K = 6144: two slices of 12-byte loads, 6 rows per workgroup
-    KMQ_LUT(2, 4, 64, 2, 2, 4, 4),   // K = 8192: 16 rows per workgroup (x, staged once per workgroup, is 16 KB here)
-    KMQ_LUT(2, 4, 64, 2, 2, 2, 7),   //            8
-    KMQ_LUT(2, 4, 32, 7, 1, 4, 4),   // K = 14336: 16-byte loads, 8 rows per workgroup (6.6 us on 4096 rows; 7.1 with 3 or 8 rows per wave)
-    KMQ_LUT(2, 2, 64, 7, 1, 4, 7),   //            8-byte loads, 4 rows per workgroup (7.05 us; taken for few rows)
-    // 3-bit (lane slices are whole groups of three words = 32 elements)
-    KMQ_LUT(3, 3, 16, 3, 1, 2, 6),   // K = 1536: three slices of 12-byte loads, 8 rows per workgroup
-    KMQ_LUT(3, 6, 32, 1, 4, 2, 6),   // K = 2048
-    KMQ_LUT(3, 3, 32, 3, 1, 4, 6),   // K = 3072: three slices of 12-byte loads (9216 rows: 5.2 us; 6.1 with one slice of 36-byte loads)
-    KMQ_LUT(3, 6, 64, 1, 4, 2, 7),   // K = 4096 (14336 rows: 7.7 us; 8.0 with 4 rows per wave)
-    KMQ_LUT(3, 3, 64, 3, 2, 4, 6),   // K = 6144: three slices of 12-byte loads, 8 rows per workgroup
-    KMQ_LUT(3, 6, 64, 2, 2, 4, 4),   // K = 8192: 16 rows per workgroup
-    KMQ_LUT(3, 6, 64, 2, 2, 2, 6),   //            8
-    KMQ_LUT(3, 3, 64, 7, 1, 4, 6),   // K = 14336: 12-byte loads, 4 rows per workgroup (4096 rows: 8.7 us; 9.0-9.2 with 24-byte loads)
-    // 4-bit
-    KMQ_LUT(4, 3, 64, 1, 4, 2, 6),   // K = 1536: 12-byte loads
-    KMQ_LUT(4, 4, 64, 1, 4, 2, 6),   // K = 2048
-    KMQ_LUT(4, 3, 64, 2, 2, 2, 6),   // K = 3072: two slices of 12-byte loads
-    KMQ_LUT(4, 4, 64, 2, 2, 2, 6),   // K = 4096
-    KMQ_LUT(4, 4, 64, 3, 2, 2, 6),   // K = 6144
-    KMQ_LUT(4, 4, 64, 4, 1, 4, 4),   // K = 8192: 4 rows per workgroup (4096 rows: 6.6 us; 7.0 with 2 or 6)
-    KMQ_LUT(4, 4, 64, 4, 1, 2, 6),   //           2
-    KMQ_LUT(4, 4, 64, 7, 1, 4, 4),   // K = 14336: 4 rows per workgroup (4096 rows: 10.5 us; 12.2 with 2, 10.9 with 6)
-    KMQ_LUT(4, 4, 64, 7, 1, 2, 6),   //            2
-    // block-scaled format (lane slices of 32, 64 or 128 elements only)
-    KMQ_LUT_SC(1, 4, 16, 1, 4, 1, 4),   // K = 2048
-    KMQ_LUT_SC(1, 4, 16, 1, 2, 1, 4),
-    KMQ_LUT_SC(1, 4, 32, 1, 4, 2, 4),   // K = 4096
-    KMQ_LUT_SC(1, 4, 64, 1, 4, 2, 4),   // K = 8192
-    KMQ_LUT_SC(1, 4, 64, 1, 4, 3, 4),
-    KMQ_LUT_SC(2, 4, 32, 1, 4, 2, 6),   // K = 2048
-    KMQ_LUT_SC(2, 4, 64, 1, 4, 2, 7),   // K = 4096
-    KMQ_LUT_SC(2, 4, 64, 2, 2, 4, 4),   // K = 8192
-    KMQ_LUT_SC(2, 4, 64, 2, 2, 2, 7),
-    KMQ_LUT_SC(2, 4, 32, 7, 1, 4, 4),   // K = 14336
-    KMQ_LUT_SC(2, 2, 64, 7, 1, 4, 7),
-    KMQ_LUT_SC(3, 6, 32, 1, 4, 2, 6),   // K = 2048
-    KMQ_LUT_SC(3, 6, 64, 1, 4, 2, 7),   // K = 4096
-    KMQ_LUT_SC(3, 6, 64, 2, 2, 4, 4),   // K = 8192
-    KMQ_LUT_SC(3, 6, 64, 2, 2, 2, 6),
-    KMQ_LUT_SC(3, 6, 32, 7, 1, 4, 4),   // K = 14336 (lane slices of 64 elements: one block)
-    KMQ_LUT_SC(4, 4, 64, 1, 4, 2, 6),   // K = 2048
-    KMQ_LUT_SC(4, 4, 64, 2, 2, 2, 6),   // K = 4096
-    KMQ_LUT_SC(4, 4, 64, 4, 2, 4, 4),   // K = 8192: 8 rows per workgroup (8192 rows: 10.8 us; 11.3 with 4 rows, 12.8 with 16 rows and 16 waves)
-    KMQ_LUT_SC(4, 4, 64, 4, 1, 4, 4),   //           4
-    KMQ_LUT_SC(4, 4, 64, 4, 1, 2, 6),
-    KMQ_LUT_SC(4, 4, 64, 7, 1, 4, 4),   // K = 14336
-    KMQ_LUT_SC(4, 4, 64, 7, 1, 2, 6),
-};
+static const LutEntry kLut[] = {KMQ_LUT_SHAPES(KMQ_LUT, KMQ_LUT_SC)};
 constexpr int kLutCount = sizeof(kLut) / sizeof(kLut[0]);
 
 // Cost of a shape for N rows: the most rows any CU gets when the workgroups are dealt
@@ -752,7 +608,7 @@ const char* lut_name(int i) { return kLut[i].name; }
 bool lut_has_fusions(int i) { return !kLut[i].scaled; }
 
 hipError_t launch_lut_entry(int i, const GemmArgs& a, hipStream_t s) {
-    kLut[i].launch(a, s);
+    if (a.M == 1 || !launch_lut_columns(i, a, s)) kLut[i].launch(a, s);
     return hipGetLastError();
 }
 
