@@ -118,6 +118,7 @@ __device__ __forceinline__ void pack_group(GroupPacker<BITS>& g, F&& index_of) {
 // same bits.  A row outside that (or with non-finite or subnormal-sized data) is marked in its codebook and left to
 // quantize_rows_kernel, in a second launch.
 //
+// For few rows, long ones, and what the kernel of four rows a workgroup (below) leaves.
 // What bounds it: vector issue.  25 rounds at 14336 x 4096, 1 / 2 / 3 / 4 bits: 107 / 132 / 150 / 169 us (61 - 68 without
 // the rounds; every element against every boundary in fp64, each round, took 1033 / 1864 / 3767 / 8470 us); 4096 x 14336:
 // 65 / 74 / 77 / 82.  One row per workgroup and 20 KB of LDS put eight rows on a CU; a round is about 110 instructions and
@@ -127,18 +128,17 @@ constexpr int kHistOctaves = 32;
 constexpr int64_t kHistMaxK = 65535;       // 16-bit counters
 constexpr uint16_t kRowMark = 0x7FFF;      // a NaN: no codebook entry of a row with finite weights
 
-// Number of values <= b in the window's ascending order (0..2 * kHistMags; zeros not counted): negative values by
+// Number of values <= b in the ascending order of a window of MAGS magnitudes (0..2 * MAGS; zeros not counted): negative values by
 // falling magnitude, then positive ones by rising magnitude.
+template <int MAGS = kHistMags>
 __device__ __forceinline__ int hist_below(double b, int base) {
     const uint64_t u = static_cast<uint64_t>(__double_as_longlong(b));
-    const uint32_t top = static_cast<uint32_t>(u >> 45);                                  // sign, exponent, seven mantissa bits
-    const int mag = static_cast<int>(top & 0x3FFFFu) - ((1023 - 127) << 7);               // bf16 magnitude, towards zero (below the normal range: negative)
-    if (b < 0.0) {
-        const int mi = mag + ((u & ((1ull << 45) - 1)) != 0 ? 1 : 0) - base;              // smallest magnitude not above b
-        return kHistMags - (mi < 0 ? 0 : mi > kHistMags ? kHistMags : mi);
-    }
-    const int mi = mag - base + 1;
-    return kHistMags + (mi < 0 ? 0 : mi > kHistMags ? kHistMags : mi);
+    const uint32_t hi = static_cast<uint32_t>(u >> 32);
+    const int mag = static_cast<int>((hi & 0x7FFFFFFFu) >> 13) - ((1023 - 127) << 7) - base;   // bf16 magnitude, towards zero (below the normal range: negative)
+    const bool neg = b < 0.0, more = (static_cast<uint32_t>(u) | (hi & 0x1FFFu)) != 0;
+    const int mi = mag + ((neg ? more : true) ? 1 : 0);                                        // negative: smallest magnitude not above b
+    const int in = mi < 0 ? 0 : mi > MAGS ? MAGS : mi;
+    return neg ? MAGS - in : MAGS + in;
 }
 
 typedef u32x4_t __attribute__((aligned(2))) u32x4_a2_t;
@@ -155,6 +155,8 @@ __device__ __forceinline__ uint32_t sign_masks(uint32_t v) {
 __device__ __forceinline__ uint32_t udot2(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b), c, false);
 }
+
+__device__ __forceinline__ uint32_t udot4(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_udot4(a, b, c, false); }
 
 // Sum over groups of LANES (4, 8, 16) consecutive lanes, in every lane of the group.
 template <int LANES>
@@ -211,29 +213,29 @@ __device__ __forceinline__ void load16(const uint16_t* w, int k0, int K, uint32_
     }
 }
 
+struct alignas(16) HistShared {
+    uint32_t cells[4 + kHistMags];                          // the histogram from cell 4 on; cell 3 counts the zeros
+    long long psum[kHistBuckets + 1];                       // sum of the members below bucket i, in units
+    uint32_t pcnt[kHistBuckets + 1];                        // ... and their number
+    long long wsum[4];
+    uint32_t wcnt[4];
+    int wlo[4], whi[4], wmin[4];
+    int thr[16];                                            // values at or below each boundary of the stored codebook
+    int zero_cluster;
+};
+
+// One row by a workgroup of four waves; false (for all of them): not a row for this.
 // NI > 0: the row is at most NI * 4096 elements and a thread keeps its NI pieces of 16 in registers; 0: re-read.
 template <int BITS, int NI>
-__global__ __launch_bounds__(256, NI == 4 ? 6 : 8) void quantize_rows_hist_kernel(const uint16_t* __restrict__ W, int64_t rowlen, int iters,
-                                                                                 uint32_t* __restrict__ packed,
-                                                                                 uint16_t* __restrict__ codebook) {
+__device__ __forceinline__ bool quantize_row_hist(HistShared& sm, const uint16_t* W, int64_t n, int64_t rowlen, int iters, uint32_t* packed, uint16_t* codebook) {
     constexpr int C = 1 << BITS;
     constexpr int LG = C <= 4 ? 16 : 64 / C;                // lanes per boundary in the clustering wave
     constexpr int DW = kHistBucket / LG;                    // histogram dwords (of a bucket's 32) per lane
     constexpr int H = kHistMags;
-    struct alignas(16) Smem {
-        uint32_t cells[4 + H];                              // the histogram from cell 4 on; cell 3 counts the zeros
-        long long psum[kHistBuckets + 1];                   // sum of the members below bucket i, in units
-        uint32_t pcnt[kHistBuckets + 1];                    // ... and their number
-        long long wsum[4];
-        uint32_t wcnt[4];
-        int wlo[4], whi[4], wmin[4];
-        int thr[16];                                        // values at or below each boundary of the stored codebook
-        int zero_cluster;
-    };
-    __shared__ Smem sm;
     uint32_t* const hist = sm.cells + 4;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t n = blockIdx.x;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                           // (one row after the other: nothing derived from it is kept over the rows, in registers that this needs)
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint16_t* w = W + n * rowlen;
     const int K = static_cast<int>(rowlen), pieces = (K + 15) >> 4;
 
@@ -289,10 +291,7 @@ __global__ __launch_bounds__(256, NI == 4 ? 6 : 8) void quantize_rows_hist_kerne
     const bool all_zero = maxmag == 0;
     const int emax = all_zero ? 127 : maxmag >> 7, emin = all_zero ? 127 : ((mn + 1) >> 7 > 0 ? (mn + 1) >> 7 : 1);
     const int log2k = 32 - __clz(K - 1);                    // K <= 2^log2k (K = 1: 0)
-    if (maxmag >= 0x7F80 || emax <= kHistOctaves || emax - emin >= kHistOctaves || emax - emin + 8 + log2k > 53) {
-        if (tid == 0) codebook[n * C] = kRowMark;           // the same for every thread: the whole workgroup leaves
-        return;
-    }
+    if (maxmag >= 0x7F80 || emax <= kHistOctaves || emax - emin >= kHistOctaves || emax - emin + 8 + log2k > 53) return false;   // (uniform)
     const int base = __builtin_amdgcn_readfirstlane((emax - (kHistOctaves - 1)) << 7);
 
     // ---- 2. histogram: dword `magnitude - base`, low half for positive values, high half for negative ones.  From here on
@@ -490,11 +489,430 @@ __global__ __launch_bounds__(256, NI == 4 ? 6 : 8) void quantize_rows_hist_kerne
     // the half-words behind the last piece that the row's last word still has (16 * BITS bits per piece)
     if (tid == 0)
         for (int i = pieces * BITS; i < 2 * wpr; ++i) out[i] = 0;
+    return true;
+}
+
+template <int BITS, int NI>
+__global__ __launch_bounds__(256, NI == 4 ? 6 : 8) void quantize_rows_hist_kernel(const uint16_t* __restrict__ W, int64_t rowlen, int iters,
+                                                                                 uint32_t* __restrict__ packed,
+                                                                                 uint16_t* __restrict__ codebook) {
+    __shared__ HistShared sm;
+    if (!quantize_row_hist<BITS, NI>(sm, W, blockIdx.x, rowlen, iters, packed, codebook) && threadIdx.x == 0) codebook[static_cast<int64_t>(blockIdx.x) << BITS] = kRowMark;
+}
+
+// ---- one codebook per row: four rows a workgroup --------------------------------------------------
+// The same rounds for many rows.  What bounds them is the instructions of the rounds (a wave for one row's
+// few boundaries: 25 rounds are two thirds of all instructions at 4096 elements), so here one wave runs the rounds of four rows
+// at once, 16 lanes a row, and everything else is done by the row's own WPR waves (one per 4096 elements).  A round is a chain of
+// 1400 clocks that only other rows hide, so a row has to be small in LDS: counters of a byte over a window of 15 octaves below the
+// row's largest magnitude, prefix sums over buckets of 16 with number and sum in one 64-bit integer; 24 rows a CU.  A few elements
+// below the window ("tiny": one row in three of 4096 normal weights has one) are kept in a list and met one by one where a boundary
+// lies among them; rows with more, or with more than 255 of one value other than zero, are left to the kernel above.
+// The sums are the same integers, exact in fp64, so the results are the same bits.
+// 25 rounds, 14336 x 4096, 1 / 2 / 3 / 4 bits, a workgroup a row / this (us): 104 / 132 / 150 / 170 -> 73 / 86 / 93 / 104; 8192 x 8192,
+// 2 / 4 bits: 98 / 115 -> 90 / 104; 100000 x 64, 2 bits, 10 rounds: 401 -> 160.  Vector issue: two thirds of the busy time.
+// Where every row is left over, the look at it comes on top (4096 x 4096, 2 / 4 bits, elements spread evenly over 22 octaves: 43 / 60 ->
+// 66 / 82).
+constexpr int kWinOctaves = 15, kWinMags = kWinOctaves * 128, kWinBucket = 16, kWinBuckets = 2 * kWinMags / kWinBucket;
+constexpr int kWinRows = 4, kWinTiny = 16, kWinCountBits = 17;
+// Cells of a byte, a plane of 2048 for either sign: the window's magnitudes from 16 on, tiny elements at 15, zeros at 1940 (alone in their
+// four bytes: a count of 32 bits)
+constexpr int kWinPlane = 2048, kWinFirst = 16, kWinTinyKey = 15, kWinZeroKey = 1940;
+static_assert(kWinFirst + kWinMags <= kWinZeroKey && kWinZeroKey % 4 == 0, "planes");
+
+typedef uint32_t WinCells[2 * kWinPlane / 4];               // (a power of two: a row's base can be or-ed into an address)
+typedef __attribute__((address_space(3))) uint32_t lds_u32_t;
+typedef __attribute__((address_space(3))) uint8_t lds_u8_t;
+struct alignas(16) WinRow {
+    long long below[kWinBuckets + 2];                       // below bucket i: sum in units << 17, plus number
+    double lo, hi;
+    int base, valid, ntiny, exact;
+    uint32_t nzero;
+    uint16_t tiny[kWinTiny];
+    int thr[16];
+    double bound[16];                                       // boundaries of the stored codebook
+    uint32_t ext[3][4];                                     // of the row's waves
+};
+
+__device__ __forceinline__ uint32_t pk_max_u(uint32_t a, uint32_t b) { return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b))); }
+__device__ __forceinline__ uint32_t pk_min_u(uint32_t a, uint32_t b) { return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b))); }
+__device__ __forceinline__ uint32_t pk_max_i(uint32_t a, uint32_t b) { return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2_t, a), __builtin_bit_cast(i16x2_t, b))); }
+
+// a value of the lane N below (SHR) or above in the same row of 16 (0 outside)
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<uint32_t>(v), CTRL, 0xF, 0xF, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<uint32_t>(v >> 32), CTRL, 0xF, 0xF, true);
+    return static_cast<uint64_t>(hi) << 32 | lo;
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_row_f64(double v) {
+    return __longlong_as_double(static_cast<long long>(dpp_u64<CTRL>(static_cast<uint64_t>(__double_as_longlong(v)))));
+}
+
+// WPR: 1 (rows of at most 4096 elements) or 2 (8192)
+template <int BITS, int WPR>
+__global__ __launch_bounds__(kWinRows * WPR * 64, WPR == 1 && BITS == 4 ? 5 : 6) void quantize_rows_window_kernel(const uint16_t* __restrict__ W, int64_t N, int K, int iters,
+                                                                                  uint32_t* __restrict__ packed, uint16_t* __restrict__ codebook) {
+    constexpr int C = 1 << BITS, NI = 4, H = kWinMags;
+    __shared__ alignas(sizeof(WinCells)) WinCells all_cells[kWinRows];
+    __shared__ WinRow rows[kWinRows];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = wave % WPR, at = part * 64 + lane;     // this thread among the row's
+    constexpr int T = WPR * 64;
+    WinRow& sm = rows[wave / WPR];
+    uint32_t* const cells = all_cells[wave / WPR];
+    uint32_t cells_at = static_cast<uint32_t>(reinterpret_cast<size_t>((lds_u32_t*)cells));
+    asm volatile("" : "+v"(cells_at));                      // (in a vector register: v_and_or_b32 takes one scalar, the mask)
+    const int64_t n = static_cast<int64_t>(blockIdx.x) * kWinRows + wave / WPR;
+    const bool there = n < N;                               // (uniform over the wave)
+    const uint16_t* const w = W + (there ? n : 0) * K;
+    const int pieces = there ? (K + 15) >> 4 : 0;
+    // a row's waves wait for each other; a lone wave's LDS instructions run in order
+    auto row_sync = [] {
+        if constexpr (WPR > 1) __syncthreads();
+        else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+
+    // ---- 1. the row and its range.  As patterns: the largest unsigned one is the most negative value, if there is a negative one, the
+    // largest signed one the largest value, if there is a positive one; else the smallest unsigned one is that
+    uint32_t reg[NI][8];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+        if (at + i * T < pieces) load16(w, (at + i * T) << 4, K, reg[i]);
+    for (int i = at; i < 2 * kWinPlane / 16; i += T) reinterpret_cast<u32x4_t*>(cells)[i] = u32x4_t{0, 0, 0, 0};
+    uint32_t umax = 0, umin = 0xFFFFFFFFu, smax = 0x80008000u;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+        if (at + i * T < pieces) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { umax = pk_max_u(umax, reg[i][j]); umin = pk_min_u(umin, reg[i][j]); smax = pk_max_i(smax, reg[i][j]); }
+        }
+    const auto halves = [](uint32_t v, bool is_signed, int h) { return is_signed ? static_cast<int>(static_cast<int16_t>(h ? v >> 16 : v)) : static_cast<int>(h ? v >> 16 : v & 0xFFFFu); };
+    const auto of_wave = [](int v) { return __builtin_amdgcn_readlane(v, 63); };
+    int um = max(halves(umax, false, 0), halves(umax, false, 1)), un = min(halves(umin, false, 0), halves(umin, false, 1)), sx = max(halves(smax, true, 0), halves(smax, true, 1));
+    um = of_wave(wave_extreme<true>(um));
+    un = of_wave(wave_extreme<false>(un));
+    sx = of_wave(wave_extreme<true>(sx));
+    if constexpr (WPR > 1) {
+        if (lane == 0) { sm.ext[0][part] = um; sm.ext[1][part] = un; sm.ext[2][part] = sx; }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < WPR; ++q) {
+            um = max(um, static_cast<int>(sm.ext[0][q]));
+            un = min(un, static_cast<int>(sm.ext[1][q]));
+            sx = max(sx, static_cast<int>(sm.ext[2][q]));
+        }
+        um = __builtin_amdgcn_readfirstlane(um);
+        un = __builtin_amdgcn_readfirstlane(un);
+        sx = __builtin_amdgcn_readfirstlane(sx);
+    }
+    const uint32_t lo_h = static_cast<uint32_t>(um >= 0x8000 ? um : un), hi_h = static_cast<uint32_t>(sx >= 0 ? sx : un);
+    const int maxmag = max(static_cast<int>(lo_h & 0x7FFFu), static_cast<int>(hi_h & 0x7FFFu));
+    const int emax = maxmag == 0 ? 127 : maxmag >> 7;
+    bool valid = there && maxmag < 0x7F80 && emax > kWinOctaves;
+    const int base = (emax - (kWinOctaves - 1)) << 7;
+    row_sync();                                             // cells cleared
+
+    // ---- 2. histogram.  From here on an element is the number of its cell (place in the plane, bit 11 the sign) times 8: the low
+    // five bits are the shift that puts a one into the cell's byte
+    const auto code_of = [](const uint32_t (&v)[8], int e) { return e & 1 ? v[e >> 1] >> 16 : v[e >> 1] & 0xFFFFu; };
+    if (valid) {
+        const uint32_t floor2 = static_cast<uint32_t>(base - 2) * 0x00010001u, base2 = static_cast<uint32_t>(base - 2 - kWinTinyKey) * 0x00010001u;
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+            if (at + i * T < pieces) {
+                uint32_t (&v)[8] = reg[i];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const uint32_t d = v[j];
+                    const u16x2_t less = __builtin_bit_cast(u16x2_t, d & 0x7FFF7FFFu) - u16x2_t{1, 1};      // (zeros: 65535)
+                    const u16x2_t k = __builtin_bit_cast(u16x2_t, pk_max_u(__builtin_bit_cast(uint32_t, less), floor2)) - __builtin_bit_cast(u16x2_t, base2);
+                    const uint32_t key = pk_min_u(__builtin_bit_cast(uint32_t, k), kWinZeroKey * 0x00010001u);
+                    v[j] = (key << 3) | ((d >> 1) & 0x40004000u);
+                }
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const uint32_t d = code_of(v, e);
+                    lds_u32_t* const cell = reinterpret_cast<lds_u32_t*>(static_cast<size_t>(((d >> 3) & (2 * kWinPlane - 4)) | cells_at));
+                    __hip_atomic_fetch_add(cell, 1u << (d & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                const int extra = ((at + i * T) << 4) + 16 - K;   // repeats of the first element in the row's last piece
+                if (extra > 0) atomicSub(&cells[code_of(v, 0) >> 5], static_cast<uint32_t>(extra) << (v[0] & 31u));
+            }
+    }
+    row_sync();
+    const int ntiny = __builtin_amdgcn_readfirstlane(static_cast<int>((cells[kWinTinyKey / 4] >> 24) + (cells[(kWinPlane + kWinTinyKey) / 4] >> 24)));
+    if (ntiny > kWinTiny) valid = false;
+    if (valid && ntiny > 0) {                               // the tiny elements themselves
+        if (at == 0) sm.ntiny = 0;
+        row_sync();
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+            if (at + i * T < pieces) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int k = ((at + i * T) << 4) + e;
+                    if (((code_of(reg[i], e) >> 3) & (kWinPlane - 1)) == kWinTinyKey && k < K) {
+                        const int slot = atomicAdd(&sm.ntiny, 1);
+                        if (slot < kWinTiny) sm.tiny[slot] = w[k];
+                    }
+                }
+            }
+    } else if constexpr (WPR > 1) {
+        __syncthreads();
+    }
+    row_sync();
+    // (the sums have to fit 53 bits down to the smallest element's unit; a counter of more than 255 has lost them)
+    if (valid && ntiny > 0) {
+        const int log2k = 32 - __clz(K - 1);
+        int emin = emax;
+        for (int i = 0; i < ntiny; ++i) emin = min(emin, max((sm.tiny[i] & 0x7FFF) >> 7, 1));
+        if (emax - emin + 8 + log2k > 53 || sm.ntiny != ntiny) valid = false;
+        valid = __builtin_amdgcn_readfirstlane(valid);
+    }
+
+    // ---- 3. buckets of 16 magnitudes (a thread each), then prefix sums over them in ascending order of the values
+    if (valid) {
+        for (int bucket = at; bucket < kWinBuckets / 2; bucket += T) {
+            uint32_t cp = 0, cn = 0, sp = 0, sn = 0;        // members and place sums of positive / negative ones
+            const u32x4_t dp = reinterpret_cast<const u32x4_t*>(cells)[kWinFirst / 16 + bucket], dn = reinterpret_cast<const u32x4_t*>(cells)[(kWinPlane + kWinFirst) / 16 + bucket];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t places = 0x03020100u + j * 0x04040404u;
+                cp = udot4(dp[j], 0x01010101u, cp);
+                sp = udot4(dp[j], places, sp);
+                cn = udot4(dn[j], 0x01010101u, cn);
+                sn = udot4(dn[j], places, sn);
+            }
+            const uint32_t m0 = 128u + static_cast<uint32_t>((bucket * kWinBucket) & 127);
+            const long long vp = static_cast<long long>(static_cast<uint64_t>(m0 * cp + sp) << (bucket >> 3));
+            const long long vn = static_cast<long long>(static_cast<uint64_t>(m0 * cn + sn) << (bucket >> 3));
+            sm.below[kWinBuckets / 2 + bucket + 1] = (vp << kWinCountBits) + cp;
+            sm.below[kWinBuckets / 2 - 1 - bucket + 1] = cn - (vn << kWinCountBits);
+        }
+    }
+    row_sync();
+    if (valid && part == 0) {
+        constexpr int PER = 4;
+        static_assert(kWinBuckets <= PER * 64, "buckets per lane");
+        long long v[PER];
+        long long mine = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            v[i] = lane * PER + i < kWinBuckets ? sm.below[lane * PER + i + 1] : 0;
+            mine += v[i];
+        }
+        long long run = mine;
+        uint32_t unused = 0;
+        wave_scan(run, unused);
+        run -= mine;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            run += v[i];
+            if (lane * PER + i < kWinBuckets) sm.below[lane * PER + i + 1] = run;
+        }
+        const uint32_t counted = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<uint32_t>(run), 63)) & ((1u << kWinCountBits) - 1);
+        const uint32_t nzero = cells[kWinZeroKey / 4] + cells[(kWinPlane + kWinZeroKey) / 4];
+        if (__builtin_amdgcn_readfirstlane(counted + nzero) + ntiny != static_cast<uint32_t>(K)) valid = false;      // a counter ran over
+        if (lane == 0) {
+            sm.below[0] = 0;
+            sm.lo = bf16_to_f64(lo_h);
+            sm.hi = bf16_to_f64(hi_h);
+            sm.base = base;
+            sm.ntiny = ntiny;
+            sm.nzero = nzero;
+        }
+    }
+    if (part == 0 && lane == 0) sm.valid = valid ? 1 : 0;
+    __syncthreads();
+    valid = __builtin_amdgcn_readfirstlane(sm.valid) != 0;
+
+    // ---- 4. the rounds, one wave: 16 lanes a row, LG of them per cluster and for the boundary above it.  Waves of one number
+    // share a SIMD: neighbouring workgroups of a CU take different ones
+    if (wave == static_cast<int>((blockIdx.x >> 8) & 3)) {
+        constexpr int LG = 16 / C, DPL = LG < 4 ? 4 / LG : 1;   // dwords of a bucket's 16 cells per lane (1 bit: half of the lanes have none)
+        WinRow& r = rows[lane >> 4];
+        const uint32_t* const rcells = all_cells[lane >> 4];
+        const int G = (lane & 15) / LG, p = lane % LG;
+        const bool live = r.valid != 0;
+        const int rbase = live ? r.base : 128;
+        const uint32_t nzero = live ? r.nzero : 0u;
+        const int rtiny = live ? r.ntiny : 0;
+        const bool any_tiny = __any(rtiny > 0);
+        const double l = live ? r.lo : 0.0, h = live ? r.hi : 0.0;
+        const double unit = __longlong_as_double(static_cast<long long>((rbase >> 7) - 127 - 7 + 1023) << 52);
+        const double floor_mag = __longlong_as_double(static_cast<long long>((rbase >> 7) - 127 + 1023) << 52);   // the window's smallest magnitude
+        double tiny_sum = 0.0;
+        for (int i = 0; i < rtiny; ++i) tiny_sum += bf16_to_f64(r.tiny[i]);
+        const bool top = G >= C - 1;                        // no boundary above the last cluster: everything is below
+        double c = l + (G + 0.5) * (h - l) / C;
+        int seen = -1;
+        for (int t = 0; t < iters; ++t) {
+            const double b = 0.5 * (c + dpp_row_f64<0x100 + LG>(c));
+            const int below = top ? 2 * H : hist_below<H>(b, rbase);
+            const bool middle = top || !(b < 0.0);          // zeros are below
+            const bool among = rtiny > 0 && !top && b != 0.0 && fabs(b) < floor_mag;
+            const int now = below * 2 + (middle ? 1 : 0);
+            if (__all((now == seen && !among) || !live)) break;   // the members of every cluster as in the round before: a fixed point
+            seen = among ? -1 : now;
+            const int bucket = below >> 4, rest = below & 15;
+            const bool pos = bucket >= kWinBuckets / 2;
+            const int mb0 = pos ? bucket - kWinBuckets / 2 : kWinBuckets / 2 - 1 - bucket;   // bucket of magnitudes
+            const int mb = mb0 < kWinBuckets / 2 ? mb0 : kWinBuckets / 2 - 1;                 // (all below: none of the last one's cells, rest = 0)
+            // the bucket's magnitudes below: positive, the first `rest`; negative, all but the first 16 - rest
+            const int head = pos ? rest : kWinBucket - rest, plane = pos ? 0 : kWinPlane;
+            const uint32_t* const cell = rcells + (plane + kWinFirst + mb * kWinBucket) / 4;
+            uint32_t cnt = 0, si = 0;
+#pragma unroll
+            for (int j = 0; j < DPL; ++j) {
+                const int q = p * DPL + j, bytes = head - 4 * q;
+                const uint32_t first = bytes <= 0 ? 0u : 0xFFFFFFFFu >> (bytes < 4 ? 32 - 8 * bytes : 0);
+                uint32_t d = cell[LG > 4 ? q & 3 : q] & (pos ? first : ~first);
+                if (LG > 4) d = q < 4 ? d : 0u;
+                cnt = udot4(d, 0x01010101u, cnt);
+                si = udot4(d, 0x03020100u + j * 0x04040404u, si);
+            }
+            if constexpr (LG > 1) {
+                si += cnt * static_cast<uint32_t>(p * DPL * 4);
+                auto lanes = [](uint32_t v) {
+                    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);
+                    if (LG >= 4) v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);
+                    if (LG >= 8) v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true);
+                    return v;
+                };
+                cnt = lanes(cnt);
+                si = lanes(si);
+            }
+            const uint32_t m0 = 128u + static_cast<uint32_t>((mb * kWinBucket) & 127);
+            const long long ds = static_cast<long long>(static_cast<uint64_t>(m0 * cnt + si) << ((mb >> 3) + kWinCountBits));
+            long long P = r.below[bucket] + (pos ? ds : -ds) + cnt + (middle ? nzero : 0u);
+            double Tt = 0.0;
+            if (any_tiny) {
+                uint32_t tc = 0;
+                if (__any(among)) {
+                    for (int i = 0; i < kWinTiny; ++i) {
+                        if (__all(i >= rtiny)) break;
+                        const double v = bf16_to_f64(r.tiny[i < rtiny ? i : 0]);
+                        if (i < rtiny && (top || v <= b)) { Tt += v; ++tc; }
+                    }
+                } else {                                    // (b = 0: the negative ones; among them only if there is no other case)
+                    const bool zero = b == 0.0 && !top;
+                    if (__any(zero)) {
+                        for (int i = 0; i < rtiny; ++i) {
+                            const double v = bf16_to_f64(r.tiny[i]);
+                            if (top || v <= b) { Tt += v; ++tc; }
+                        }
+                    } else if (top || b > 0.0) {
+                        Tt = tiny_sum;
+                        tc = static_cast<uint32_t>(rtiny);
+                    }
+                }
+                P += tc;
+            }
+            const long long P0 = static_cast<long long>(dpp_u64<0x110 + LG>(static_cast<uint64_t>(P)));      // (the first cluster's: 0)
+            const long long D = P - P0;
+            const uint32_t M = static_cast<uint32_t>(D) & ((1u << kWinCountBits) - 1);
+            double S = static_cast<double>(D >> kWinCountBits) * unit;
+            if (any_tiny) S += Tt - dpp_row_f64<0x110 + LG>(Tt);
+            if (M > 0) c = S / static_cast<double>(M);
+        }
+        const uint16_t hc = f64_to_bf16(c);
+        const int64_t rn = static_cast<int64_t>(blockIdx.x) * kWinRows + (lane >> 4);
+        if (p == 0 && G < C && rn < N) {
+            if (live) codebook[rn * C + G] = hc;
+            else if (G == 0) codebook[rn * C] = kRowMark;
+        }
+        c = bf16_to_f64(hc);
+        const double b = 0.5 * (c + dpp_row_f64<0x100 + LG>(c));
+        if (p == 0 && G < C - 1) { r.thr[G] = hist_below<H>(b, rbase); r.bound[G] = b; }
+        // a boundary among the tiny elements: such a row's elements are compared one by one
+        const uint64_t odd = __ballot(G < C - 1 && rtiny > 0 && b != 0.0 && fabs(b) < floor_mag);
+        if ((lane & 15) == 0) r.exact = ((odd >> (lane & 48)) & 0xFFFFu) != 0 ? 1 : 0;
+    }
+    __syncthreads();
+
+    // ---- 5. cluster of every value, over the histogram
+    const int wpr = static_cast<int>(words_per_row(BITS, K));
+    uint8_t* const table = reinterpret_cast<uint8_t*>(cells);
+    if (valid) {
+        for (int g = at; g < H / 16; g += T) {
+            const int m = g * 16;                           // this thread's magnitudes m..m + 15, all like the first of them (of +m and -(m + 15) ...
+            int p0 = 0, n1 = 0;                             // ... upwards, that is)
+#pragma unroll
+            for (int i = 0; i < C - 1; ++i) {
+                const int th = sm.thr[i];
+                p0 += th <= H + m ? 1 : 0;
+                n1 += th <= H - 1 - (m + 15) ? 1 : 0;
+            }
+            const uint32_t fp = static_cast<uint32_t>(p0) * 0x01010101u, fn = static_cast<uint32_t>(n1) * 0x01010101u;
+            reinterpret_cast<u32x4_t*>(table + kWinFirst)[g] = u32x4_t{fp, fp, fp, fp};
+            reinterpret_cast<u32x4_t*>(table + kWinPlane + kWinFirst)[g] = u32x4_t{fn, fn, fn, fn};
+        }
+        row_sync();
+        for (int task = at; task < (C - 1) * 16; task += T) {   // ... and one by one where a boundary lies among them
+            const int th = sm.thr[task >> 4], e = task & 15;    // values in ascending order, 0..2H - 1: the 16 around the boundary
+            const int v = (th & ~15) + e;
+            int z = 0;
+#pragma unroll
+            for (int i = 0; i < C - 1; ++i) z += sm.thr[i] <= v ? 1 : 0;
+            if (v < 2 * H) table[v >= H ? kWinFirst + (v - H) : kWinPlane + kWinFirst + (H - 1 - v)] = static_cast<uint8_t>(z);
+        }
+        if (at < 4) {                                       // tiny elements and zeros of either sign: no boundary lies among them (or `exact`)
+            int z = 0;
+#pragma unroll
+            for (int i = 0; i < C - 1; ++i) z += sm.bound[i] < 0.0 || (sm.bound[i] == 0.0 && at == 0) ? 1 : 0;
+            table[(at & 1 ? kWinPlane : 0) + (at < 2 ? kWinTinyKey : kWinZeroKey)] = static_cast<uint8_t>(z);
+        }
+    }
+    row_sync();
+
+    // ---- 6. indices, 16 elements (BITS half-words of the stream) per thread and piece
+    if (!valid) return;
+    uint16_t* const out = reinterpret_cast<uint16_t*>(packed + n * wpr);
+    const bool exact = __builtin_amdgcn_readfirstlane(sm.exact) != 0;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int piece = at + i * T;
+        if (piece >= pieces) continue;
+        uint32_t half[2] = {0, 0};                          // eight elements each: 8 * BITS bits
+        if (exact) {
+#pragma unroll 1
+            for (int e = 0; e < 16; ++e) {
+                const int k = (piece << 4) + e;
+                const double v = bf16_to_f64(w[k < K ? k : K - 1]);
+                uint32_t a = 0;
+                for (int j = 0; j < C - 1; ++j) a += v > sm.bound[j] ? 1u : 0u;
+                half[e >> 3] |= a << ((e & 7) * BITS);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const uint32_t two = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2_t, reg[i][e >> 1]) >> u16x2_t{3, 3});
+                const lds_u8_t* const entry = reinterpret_cast<const lds_u8_t*>(static_cast<size_t>((e & 1 ? two >> 16 : two & 0xFFFFu) + cells_at));   // (the halves picked by the addition itself)
+                half[e >> 3] |= static_cast<uint32_t>(*entry) << ((e & 7) * BITS);
+            }
+        }
+        uint64_t bits = static_cast<uint64_t>(half[1]) << (8 * BITS) | half[0];
+        const int last = K - (piece << 4);
+        if (last < 16) bits &= (uint64_t(1) << (last * BITS)) - 1;
+        if constexpr (BITS == 2 || BITS == 4) {
+            uint32_t* o32 = reinterpret_cast<uint32_t*>(out);
+#pragma unroll
+            for (int j = 0; j < BITS / 2; ++j)
+                if (piece * (BITS / 2) + j < wpr) o32[piece * (BITS / 2) + j] = static_cast<uint32_t>(bits >> (32 * j));
+        } else {
+#pragma unroll
+            for (int j = 0; j < BITS; ++j)
+                if (piece * BITS + j < 2 * wpr) out[piece * BITS + j] = static_cast<uint16_t>(bits >> (16 * j));
+        }
+    }
+    if (at == 0)
+        for (int i = pieces * BITS; i < 2 * wpr; ++i) out[i] = 0;
 }
 
 // ---- one codebook per row: any data ----------------------------------------------------------------
-// One workgroup of four waves per row; the row is re-read from the caches each round.  MARKED: only the rows that
-// quantize_rows_hist_kernel left (their codebook starts with kRowMark).  Where all rows are left, 8 rounds, 1 bit / 4 bits: 256 x 4096
+// One workgroup of four waves per row; the row is re-read from the caches each round.  Where all rows are left by the histogram, 8 rounds, 1 bit / 4 bits: 256 x 4096
 // 30 / 112 us, 4096 x 4096 118 / 834 (without the histogram kernel in front 32 / 104 and 116 / 818; with four rows one after the other
 // per workgroup, of which none are left as a rule, 114 / 398 and 190 / 1003; the look at the marks costs 1 us at 14336 rows).
 template <int BITS, typename F>
@@ -596,16 +1014,38 @@ __device__ __forceinline__ void quantize_row(RowShared<BITS>& sh, const uint16_t
     }
 }
 
-template <int BITS, bool MARKED>
+template <int BITS>
 __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __restrict__ W, int64_t K, int iters,
                                                             uint32_t* __restrict__ packed, uint16_t* codebook) {
-    constexpr int C = 1 << BITS;
     __shared__ RowShared<BITS> sh;
-    const int64_t n = blockIdx.x;
-    if constexpr (MARKED) {
-        if (codebook[n * C] != kRowMark) return;          // (the same for every thread; overwritten behind the first barrier only)
+    quantize_row<BITS>(sh, W, blockIdx.x, K, iters, packed, codebook);
+}
+
+// The rows that a kernel before left (their codebook starts with kRowMark).  64 rows at a time: a mark per lane, the same for all waves
+// (a row's codebook is overwritten behind a barrier only); rows next to each other fall to different workgroups.
+constexpr int kMarkedGroups = 2048;
+template <int C, typename F>
+__device__ __forceinline__ void marked_rows(int64_t N, const uint16_t* codebook, F&& f) {
+    for (int64_t n0 = blockIdx.x; n0 < N; n0 += static_cast<int64_t>(gridDim.x) * 64) {
+        const int64_t mine = n0 + static_cast<int64_t>(threadIdx.x & 63) * gridDim.x;
+        uint64_t left = __ballot(mine < N && codebook[(mine < N ? mine : n0) * C] == kRowMark);
+        for (; left; left &= left - 1) {
+            f(n0 + static_cast<int64_t>(__builtin_ctzll(left)) * gridDim.x);
+            __syncthreads();
+        }
     }
-    quantize_row<BITS>(sh, W, n, K, iters, packed, codebook);
+}
+template <int BITS, int NI>
+__global__ __launch_bounds__(256, 8) void quantize_marked_rows_hist_kernel(const uint16_t* __restrict__ W, int64_t N, int64_t K, int iters,
+                                                                           uint32_t* __restrict__ packed, uint16_t* codebook) {
+    __shared__ HistShared sm;
+    marked_rows<1 << BITS>(N, codebook, [&](int64_t n) { quantize_row_hist<BITS, NI>(sm, W, n, K, iters, packed, codebook); });
+}
+template <int BITS>
+__global__ __launch_bounds__(256) void quantize_marked_rows_kernel(const uint16_t* __restrict__ W, int64_t N, int64_t K, int iters,
+                                                                   uint32_t* __restrict__ packed, uint16_t* codebook) {
+    __shared__ RowShared<BITS> sh;
+    marked_rows<1 << BITS>(N, codebook, [&](int64_t n) { quantize_row<BITS>(sh, W, n, K, iters, packed, codebook); });
 }
 
 // ---- the paper's format: scale per 64-element block, one codebook per tensor -------------------------
@@ -1336,6 +1776,10 @@ __global__ __launch_bounds__(256) void bs_small_kernel(const uint16_t* __restric
     }
 }
 
+// Four rows a workgroup need many rows (us, a workgroup a row / four rows; 2 bits, 25 rounds): 1024 x 4096 19.3 / 22.8, 2048 27.3 / 28.5,
+// 3072 38.4 / 32.5; 4096 x 8192 58 / 56; and short ones: with four waves a row a CU holds four rows (4096 x 14336: 74 / 115).
+constexpr int64_t kWinLeastRows = 2560, kWinMostK = 8192;
+
 size_t quantize_blockscaled_workspace_bytes() { return sizeof(QuantScratch); }
 
 template <int BITS>
@@ -1345,7 +1789,19 @@ static hipError_t quantize_rows_bits(const uint16_t* W, int64_t N, int64_t K, in
     // without rounds a short row does not repay its histogram (100000 x 64, 1 / 2 / 3 / 4 bits: 258 / 276 / 303 / 339 us with it,
     // 148 / 158 / 237 / 413 without)
     if (K > kHistMaxK || (iters == 0 && K <= 512 && BITS <= 3)) {
-        hipLaunchKernelGGL((quantize_rows_kernel<BITS, false>), rows, block, 0, s, W, K, iters, packed, codebook);
+        hipLaunchKernelGGL((quantize_rows_kernel<BITS>), rows, block, 0, s, W, K, iters, packed, codebook);
+        return hipGetLastError();
+    }
+    const dim3 marked(static_cast<unsigned>(N < kMarkedGroups ? N : kMarkedGroups));
+    if (K <= kWinMostK && N >= kWinLeastRows) {
+        const dim3 fours(static_cast<unsigned>((N + kWinRows - 1) / kWinRows));
+#define KMQ_WIN(WPR) hipLaunchKernelGGL((quantize_rows_window_kernel<BITS, WPR>), fours, dim3(kWinRows * WPR * 64), 0, s, W, N, static_cast<int>(K), iters, packed, codebook)
+        if (K <= 4096) KMQ_WIN(1);
+        else KMQ_WIN(2);
+#undef KMQ_WIN
+        if (K <= 4096) hipLaunchKernelGGL((quantize_marked_rows_hist_kernel<BITS, 1>), marked, block, 0, s, W, N, K, iters, packed, codebook);
+        else hipLaunchKernelGGL((quantize_marked_rows_hist_kernel<BITS, 2>), marked, block, 0, s, W, N, K, iters, packed, codebook);
+        hipLaunchKernelGGL((quantize_marked_rows_kernel<BITS>), marked, block, 0, s, W, N, K, iters, packed, codebook);
         return hipGetLastError();
     }
 #define KMQ_HIST(NI) hipLaunchKernelGGL((quantize_rows_hist_kernel<BITS, NI>), rows, block, 0, s, W, K, iters, packed, codebook)
@@ -1354,7 +1810,7 @@ static hipError_t quantize_rows_bits(const uint16_t* W, int64_t N, int64_t K, in
     else if (K <= 16384) KMQ_HIST(4);
     else KMQ_HIST(0);
 #undef KMQ_HIST
-    hipLaunchKernelGGL((quantize_rows_kernel<BITS, true>), rows, block, 0, s, W, K, iters, packed, codebook);
+    hipLaunchKernelGGL((quantize_marked_rows_kernel<BITS>), marked, block, 0, s, W, N, K, iters, packed, codebook);
     return hipGetLastError();
 }
 
