@@ -1066,9 +1066,9 @@ __global__ __launch_bounds__(256) void quantize_marked_rows_kernel(const uint16_
 // Elements more than 31 octaves below their scale ("far", next to none in most trained tensors) are counted apart per sign, and
 // their sums taken from the tensor (below).
 //
-// 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits: 157 / 177 / 193 / 224 us (8519 / 9344 / 10727 / 13475 with every element
-// divided by its scale and compared with every boundary in fp64, each round); 1024 x 1024, 4 bits: 127 (3570).  At 8192 x 8192
-// and 4 bits: clear 5, scales 33 (4.1 TB/s), group 13, count 43 (blocks gathered 128 bytes at a time, LDS atomics), prefix 12,
+// 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits: 134 / 149 / 170 / 202 us (8519 / 9344 / 10727 / 13475 with every element
+// divided by its scale and compared with every boundary in fp64, each round); 1024 x 1024, 4 bits: 126 (3570).  At 8192 x 8192
+// and 4 bits: clear 5, scales 21 (6.5 TB/s), group 13, count 34 (blocks gathered 128 bytes at a time, LDS atomics, 16 for the adding up), prefix 12,
 // rounds 80 (3 us each: one CU's issue and its scattered line fetches), assign 45 us (vector issue).
 constexpr int kQuantMants = 128, kQuantBins = 2 * kHistMags, kQuantStride = kQuantBins + 1;
 constexpr double kFar = 4.656612873077393e-10;           // 2^-31: no far element reaches it
@@ -1092,7 +1092,7 @@ __device__ __forceinline__ double sum_to_f64(int128_t v) {   // |v| < 2^88: the 
     const double d = static_cast<double>(static_cast<unsigned long long>(m >> 64)) * 18446744073709551616.0 + static_cast<double>(static_cast<unsigned long long>(m));
     return v < 0 ? -d : d;
 }
-constexpr int kFarChunks = 512;
+constexpr int kFarChunks = 512, kBlockCounters = 16;
 struct FarPart {
     double sum;
     long long num;
@@ -1105,18 +1105,21 @@ struct FarScratch {                                      // starts as zeros
 };
 struct QuantScratch {                                    // layout of the caller's workspace; everything down to `members` starts as zeros
     FarScratch far;
-    unsigned long long blocks[kQuantMants];              // blocks per scale mantissa
-    unsigned long long cursor[kQuantMants];              // ... of them placed so far
+    unsigned long long cursor[kQuantMants];              // blocks of a scale mantissa placed so far
     unsigned long long zeros, far_neg, far_pos;
     uint32_t exact_assign;                               // a stored boundary lies among the far elements
     uint32_t nonfinite;                                  // a weight is an infinity or a NaN
     unsigned long long members[kQuantMants][kQuantBins];
-    FarPart far_part[kFarChunks][16];
+    union {                                              // (until the rounds begin, when nobody asks for the blocks any more)
+        FarPart far_part[kFarChunks][16];
+        // blocks per scale mantissa, starting as zeros: a workgroup adds to one of sixteen (all to one: 33 us instead of 20 at 8192 x 8192)
+        unsigned long long blocks[kBlockCounters][kQuantMants];
+    };
     BelowBin below[kQuantMants][kQuantStride];           // (side by side: a round's look-ups are scattered, a line each)
     uint32_t above[kQuantMants][16];                     // per stored boundary: largest element key at or below it, in both halves
 };
 
-constexpr size_t kClearAll = offsetof(QuantScratch, far_part) / 16, kClearSmall = offsetof(QuantScratch, members) / 16;
+constexpr size_t kClearAll = (offsetof(QuantScratch, blocks) + sizeof(QuantScratch::blocks)) / 16, kClearSmall = offsetof(QuantScratch, members) / 16;
 __global__ __launch_bounds__(256) void bs_clear_kernel(QuantScratch* q, size_t n16) {
     typedef u32x4_t __attribute__((aligned(8))) u32x4_a8_t;
     static_assert(alignof(QuantScratch) == 8 && offsetof(QuantScratch, far_part) % 16 == 0 && offsetof(QuantScratch, members) % 16 == 0, "cleared in 16-byte pieces");
@@ -1154,22 +1157,24 @@ __device__ __forceinline__ uint32_t block_scale(const u32x4_t& v) {
     return s;
 }
 
+constexpr int kScaleTurn = 128;                          // blocks per workgroup and turn
 __global__ __launch_bounds__(256) void bs_scales_kernel(const uint16_t* __restrict__ W, int64_t nblocks,
                                                         uint16_t* __restrict__ scales, QuantScratch* q) {
     __shared__ uint32_t cnt[kQuantMants];
     if (threadIdx.x < kQuantMants) cnt[threadIdx.x] = 0;
     __syncthreads();
-    // eight lanes per block, four blocks of 32 per workgroup and turn
-    const int64_t step = static_cast<int64_t>(gridDim.x) * 128;
-    for (int64_t b0 = static_cast<int64_t>(blockIdx.x) * 128 + (threadIdx.x >> 3); b0 < nblocks; b0 += step) {
-        u32x4_t v[4];
+    // eight lanes per block, kScaleTurn / 32 blocks in flight per lane
+    constexpr int U = kScaleTurn / 32;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kScaleTurn;
+    for (int64_t b0 = static_cast<int64_t>(blockIdx.x) * kScaleTurn + (threadIdx.x >> 3); b0 < nblocks; b0 += step) {
+        u32x4_t v[U];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < U; ++i) {
             const int64_t blk = b0 + i * 32 < nblocks ? b0 + i * 32 : nblocks - 1;
             v[i] = *reinterpret_cast<const u32x4_t*>(W + blk * KMQ_BLOCK + (threadIdx.x & 7) * 8);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < U; ++i) {
             const uint32_t s = block_scale(v[i]);
             if ((threadIdx.x & 7) == 0 && b0 + i * 32 < nblocks) {
                 scales[b0 + i * 32] = static_cast<uint16_t>(s);
@@ -1179,7 +1184,7 @@ __global__ __launch_bounds__(256) void bs_scales_kernel(const uint16_t* __restri
         }
     }
     __syncthreads();
-    if (threadIdx.x < kQuantMants && cnt[threadIdx.x]) atomicAdd(&q->blocks[threadIdx.x], static_cast<unsigned long long>(cnt[threadIdx.x]));
+    if (threadIdx.x < kQuantMants && cnt[threadIdx.x]) atomicAdd(&q->blocks[blockIdx.x % kBlockCounters][threadIdx.x], static_cast<unsigned long long>(cnt[threadIdx.x]));
 }
 
 // First list position of every scale mantissa's blocks (start[128]: their number); by the workgroup's first wave,
@@ -1187,7 +1192,12 @@ __global__ __launch_bounds__(256) void bs_scales_kernel(const uint16_t* __restri
 __device__ __forceinline__ void list_starts(const QuantScratch* q, long long* start) {
     if (threadIdx.x < 64) {
         const int t = threadIdx.x;
-        const long long a = static_cast<long long>(q->blocks[2 * t]), b = static_cast<long long>(q->blocks[2 * t + 1]);
+        long long a = 0, b = 0;
+#pragma unroll
+        for (int i = 0; i < kBlockCounters; ++i) {
+            a += static_cast<long long>(q->blocks[i][2 * t]);
+            b += static_cast<long long>(q->blocks[i][2 * t + 1]);
+        }
         long long incl = a + b;
         uint32_t unused = 0;
         wave_scan(incl, unused);
@@ -1224,7 +1234,7 @@ __global__ __launch_bounds__(kGroupThreads) void bs_group_kernel(const uint16_t*
 }
 
 // Every workgroup counts the elements of its run of the block list, in LDS: cell 2 * magnitude key + sign.
-constexpr int kCountThreads = 512, kCountCells = 2 * (kHistMags + 2);
+constexpr int kCountThreads = 1024, kCountCells = 2 * (kHistMags + 2);
 __global__ __launch_bounds__(kCountThreads) void bs_count_kernel(const uint16_t* __restrict__ W, const uint32_t* __restrict__ list,
                                                                  int64_t nblocks, int64_t run, QuantScratch* q) {
     __shared__ long long start[kQuantMants + 1];
@@ -1239,14 +1249,20 @@ __global__ __launch_bounds__(kCountThreads) void bs_count_kernel(const uint16_t*
     while (p < end) {
         while (start[mant + 1] <= p) ++mant;              // (uniform; start[128] = nblocks > p)
         const int64_t stop = start[mant + 1] < end ? start[mant + 1] : end;
-        // eight lanes per block, two blocks of 64 per turn in flight
-        for (int64_t t0 = p + (tid >> 3); t0 < stop; t0 += kCountThreads / 8 * 2) {
-            u32x4_t v[2];
+        // eight lanes per block, two blocks of 64 per turn; the next turn's are requested ahead of the present one's counting
+        constexpr int kTurn = kCountThreads / 8 * 2;
+        auto request = [&](int64_t t0, u32x4_t (&v)[2]) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const int64_t t = t0 + i * (kCountThreads / 8);
-                v[i] = *reinterpret_cast<const u32x4_t*>(W + static_cast<int64_t>(list[t < stop ? t : t0]) * KMQ_BLOCK + (tid & 7) * 8);
+                v[i] = *reinterpret_cast<const u32x4_t*>(W + static_cast<int64_t>(list[t < stop ? t : stop - 1]) * KMQ_BLOCK + (tid & 7) * 8);
             }
+        };
+        u32x4_t ahead[2];
+        request(p + (tid >> 3), ahead);
+        for (int64_t t0 = p + (tid >> 3); t0 < stop; t0 += kTurn) {
+            u32x4_t v[2] = {ahead[0], ahead[1]};
+            request(t0 + kTurn, ahead);
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 uint32_t s = block_scale(v[i]);
@@ -1838,13 +1854,13 @@ static hipError_t quantize_blockscaled_bits(const uint16_t* W, int64_t N, int64_
     }
     const size_t clear = iters ? kClearAll : kClearSmall;
     hipLaunchKernelGGL(bs_clear_kernel, grid(static_cast<int64_t>(clear), 256, 2048), dim3(256), 0, s, q, clear);
-    hipLaunchKernelGGL(bs_scales_kernel, grid(nblocks, 128, 512), dim3(256), 0, s, W, nblocks, scales, q);
+    hipLaunchKernelGGL(bs_scales_kernel, grid(nblocks, kScaleTurn, 1024), dim3(256), 0, s, W, nblocks, scales, q);
     if (iters) {                                          // (without rounds nothing is counted)
         hipLaunchKernelGGL(bs_group_kernel, dim3(static_cast<unsigned>((nblocks + kGroupBlocks - 1) / kGroupBlocks)), dim3(kGroupThreads), 0, s, scales, nblocks, q, packed);
-        // Four workgroups a CU, of at least 64 blocks each to spread the clearing and flushing of 8196 counters (1024 x 1024: 6 us more
-        // with 16), but at least one workgroup a CU: it flushes once per scale mantissa among its blocks (64 x 64: 171 us in one
+        // Two workgroups of 16 waves a CU, of at least 64 blocks each to spread the clearing and flushing of 8196 counters (1024 x 1024: 6 us more
+        // with 16; 8192 x 8192: 44 us in all with four workgroups of eight waves, 34 with two), but at least one workgroup a CU: it flushes once per scale mantissa among its blocks (64 x 64: 171 us in one
         // workgroup, 49 with a block each; 25 rounds, 1 bit).
-        const int64_t least = nblocks < 64 * 256 ? (nblocks + 255) / 256 : 64, run = (nblocks + 1023) / 1024 < least ? least : (nblocks + 1023) / 1024;
+        const int64_t least = nblocks < 64 * 256 ? (nblocks + 255) / 256 : 64, run = (nblocks + 511) / 512 < least ? least : (nblocks + 511) / 512;
         hipLaunchKernelGGL(bs_count_kernel, dim3(static_cast<unsigned>((nblocks + run - 1) / run)), dim3(kCountThreads), 0, s, W, packed, nblocks, run, q);
         hipLaunchKernelGGL(bs_prefix_kernel, dim3(kQuantMants), dim3(1024), 0, s, q);
     }
