@@ -1066,10 +1066,10 @@ __global__ __launch_bounds__(256) void quantize_marked_rows_kernel(const uint16_
 // Elements more than 31 octaves below their scale ("far", next to none in most trained tensors) are counted apart per sign, and
 // their sums taken from the tensor (below).
 //
-// 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits: 134 / 149 / 170 / 202 us (8519 / 9344 / 10727 / 13475 with every element
-// divided by its scale and compared with every boundary in fp64, each round); 1024 x 1024, 4 bits: 126 (3570).  At 8192 x 8192
-// and 4 bits: clear 5, scales 21 (6.5 TB/s), group 13, count 34 (blocks gathered 128 bytes at a time, LDS atomics, 16 for the adding up), prefix 12,
-// rounds 80 (3 us each: one CU's issue and its scattered line fetches), assign 45 us (vector issue).
+// 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits: 127 / 145 / 163 / 198 us (8519 / 9344 / 10727 / 13475 with every element
+// divided by its scale and compared with every boundary in fp64, each round); 1024 x 1024, 4 bits: 122 (3570).  At 8192 x 8192
+// and 4 bits: clear 5, scales 21 (6.5 TB/s), group 13, count 34 (blocks gathered 128 bytes at a time, LDS atomics, 16 for the adding up), prefix 9,
+// rounds 78 (3 us each: one CU's issue and its scattered line fetches), assign 45 us (vector issue).
 constexpr int kQuantMants = 128, kQuantBins = 2 * kHistMags, kQuantStride = kQuantBins + 1;
 constexpr double kFar = 4.656612873077393e-10;           // 2^-31: no far element reaches it
 
@@ -1299,7 +1299,10 @@ __global__ __launch_bounds__(1024) void bs_prefix_kernel(QuantScratch* q) {
     __shared__ int128_t ws[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const unsigned long long* const n = q->members[blockIdx.x] + tid * PER;
-    BelowBin* const bin = q->below[blockIdx.x] + tid * PER;
+    // (a thread's bins go through LDS, nine places for eight, so that a wave writes whole lines: 12 -> 9 us)
+    __shared__ BelowBin out[1024 * (PER + 1)];
+    BelowBin* const bin = out + tid * (PER + 1);
+    BelowBin* const below = q->below[blockIdx.x];
     const bool pos = tid >= 512;
     const int mi0 = pos ? (tid - 512) * PER : kHistMags - 1 - tid * PER;             // magnitude of the first bin; then rising / falling
     const int octave = mi0 >> 7, m0 = 128 + (mi0 & 127), dm = pos ? 1 : -1;
@@ -1334,7 +1337,13 @@ __global__ __launch_bounds__(1024) void bs_prefix_kernel(QuantScratch* q) {
         in += static_cast<long long>(c[i]);
         tm += static_cast<long long>(c[i]) * (m0 + dm * i);
     }
-    if (tid == 1023) bin[PER] = below_bin(in, is + in_units(tm));
+    if (tid == 1023) below[kQuantBins] = below_bin(in, is + in_units(tm));
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int b = i * 1024 + tid;
+        below[b] = out[b / PER * (PER + 1) + b % PER];
+    }
 }
 
 // Window magnitudes g = mantissa * 2^octave (units of 2^-31 / (128 + scale mantissa)) with fl(g / scale) <= a (STRICT: < a).
@@ -1372,6 +1381,15 @@ __device__ __forceinline__ double wave_total(double v) {
     const uint64_t u = static_cast<uint64_t>(__double_as_longlong(v));
     const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(u), 63), hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(u >> 32), 63);
     return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
+}
+__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return __builtin_amdgcn_readlane(v, 63);
 }
 // a value that is the same in every lane, for the scalar unit
 __device__ __forceinline__ double uniform(double v) {
@@ -1482,11 +1500,11 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
                                                                      const uint16_t* __restrict__ scales, int64_t nblocks, uint32_t nchunks,
                                                                      int iters, uint16_t* __restrict__ codebook) {
     constexpr int C = 1 << BITS;
-    __shared__ double cs[C];
+    __shared__ double cs2[2][C];                          // the centroids of a round and of the next one
     __shared__ BelowBin bb[C][kQuantMants];               // what lies below boundary i (i = C - 1: all), per scale mantissa
     __shared__ double fsum_of[C];
     __shared__ FarShared<C> fs;
-    __shared__ int moved, search;
+    __shared__ int moved, search;                         // last round (from 1) in which a boundary passed a member, or lay among the far ones
     const int i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const double far_neg = static_cast<double>(q->far_neg), far_pos = static_cast<double>(q->far_pos), zeros = static_cast<double>(q->zeros);
     const bool any_far = far_neg + far_pos > 0.0;
@@ -1535,7 +1553,7 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
     // fewer than 2^24 members of every scale mantissa, each of less than 2^39 units: their sums fit 64 bits (8192 x 8192, 4 bits:
     // 234 -> 224 us)
     const bool narrow = __all(below_count(bb[C - 1][lane].hi) < 16777216.0 && below_count(bb[C - 1][lane + 64].hi) < 16777216.0);
-    if (threadIdx.x < C) cs[threadIdx.x] = -1.0 + (2 * static_cast<int>(threadIdx.x) + 1) / static_cast<double>(C);
+    if (threadIdx.x < C) cs2[0][threadIdx.x] = -1.0 + (2 * static_cast<int>(threadIdx.x) + 1) / static_cast<double>(C);
     if (threadIdx.x == 0) { moved = 0; search = 0; }
     double neg_sum = 0.0, pos_sum = 0.0;
     if (any_far && iters > 0) {                           // per sign: all boundaries 0, so the first cluster and the last
@@ -1548,6 +1566,7 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
         pos_sum = fsum_of[C - 1];
     }
     __syncthreads();
+    double* cs = cs2[0];
     auto boundary = [&](int j) { return uniform(0.5 * (cs[j] + cs[j + 1])); };
     auto below_of = [&](double b, int h) {
         return b < 0.0 ? kHistMags - magnitudes_within<true>(-b, scale[h]) : kHistMags + magnitudes_within<false>(b, scale[h]);
@@ -1569,32 +1588,33 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
                     bb[i][lane + 64 * h] = q->below[lane + 64 * h][below];
                 }
             }
-            if (now[0] != seen[0] || now[1] != seen[1] || among_far(b)) moved = 1;
-            if (among_far(b)) search = 1;
+            if (now[0] != seen[0] || now[1] != seen[1] || among_far(b)) moved = t + 1;
+            if (among_far(b)) search = t + 1;
             seen[0] = now[0];
             seen[1] = now[1];
         }
         __syncthreads();
-        if (moved == 0) break;                            // every boundary where it was: a fixed point
+        if (moved != t + 1) break;                         // every boundary where it was: a fixed point
         double n = 0.0, s = 0.0;
+        uint32_t n32 = 0;                                 // (narrow: at most 2^31)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int m = lane + 64 * h;
             const BelowBin hi = bb[i][m], lo = i > 0 ? bb[i - 1][m] : BelowBin{0, 0};
             if (narrow) {
-                n += static_cast<double>(static_cast<uint32_t>(hi.hi >> 24) - static_cast<uint32_t>(lo.hi >> 24));
+                n32 += static_cast<uint32_t>(hi.hi >> 24) - static_cast<uint32_t>(lo.hi >> 24);
                 s += static_cast<double>(static_cast<long long>(hi.lo - lo.lo)) * inv[h];
             } else {
                 n += below_count(hi.hi) - below_count(lo.hi);
                 s += sum_to_f64(below_sum(hi.lo, hi.hi) - below_sum(lo.lo, lo.hi)) * inv[h];
             }
         }
-        n = wave_total(n);
+        n = narrow ? static_cast<double>(wave_total(n32)) : wave_total(n);
         s = wave_total(s);
         n += zeros_below(b) - zeros_below(b0);
         if (any_far) {
             double fsum, fnum;
-            if (search) {                                 // (uniform)
+            if (search == t + 1) {                        // (uniform)
                 if (lane == 0) f->bounds[i] = b;
                 far_search(fsum, fnum);
             } else {
@@ -1605,10 +1625,10 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
             n += fnum;
         }
         const double c = s / n;
-        __syncthreads();                                  // boundaries and sums read by all before anything moves
-        if (lane == 0 && n > 0.0) cs[i] = c;
-        if (threadIdx.x == 0) { moved = 0; search = 0; }
-        __syncthreads();
+        double* const next = cs2[(t + 1) & 1];
+        if (lane == 0) next[i] = n > 0.0 ? c : cs[i];
+        cs = next;
+        __syncthreads();                                  // (this round's values have been read by all)
     }
     __syncthreads();
     if (any_far && threadIdx.x == 0) __hip_atomic_store(&f->finished, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
