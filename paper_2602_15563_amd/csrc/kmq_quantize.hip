@@ -568,7 +568,7 @@ __global__ __launch_bounds__(kWinRows * WPR * 64, WPR == 1 && BITS == 4 ? 5 : 6)
     const bool there = n < N;                               // (uniform over the wave)
     const uint16_t* const w = W + (there ? n : 0) * K;
     const int pieces = there ? (K + 15) >> 4 : 0;
-    // a row's waves wait for each other; a lone wave's LDS instructions run in order
+    // a row's waves wait for each other (and for the workgroup's others: every wave calls this as often); a lone wave's LDS instructions run in order
     auto row_sync = [] {
         if constexpr (WPR > 1) __syncthreads();
         else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -644,9 +644,9 @@ __global__ __launch_bounds__(kWinRows * WPR * 64, WPR == 1 && BITS == 4 ? 5 : 6)
     row_sync();
     const int ntiny = __builtin_amdgcn_readfirstlane(static_cast<int>((cells[kWinTinyKey / 4] >> 24) + (cells[(kWinPlane + kWinTinyKey) / 4] >> 24)));
     if (ntiny > kWinTiny) valid = false;
+    if (valid && ntiny > 0 && at == 0) sm.ntiny = 0;
+    row_sync();
     if (valid && ntiny > 0) {                               // the tiny elements themselves
-        if (at == 0) sm.ntiny = 0;
-        row_sync();
 #pragma unroll
         for (int i = 0; i < NI; ++i)
             if (at + i * T < pieces) {
@@ -659,8 +659,6 @@ __global__ __launch_bounds__(kWinRows * WPR * 64, WPR == 1 && BITS == 4 ? 5 : 6)
                     }
                 }
             }
-    } else if constexpr (WPR > 1) {
-        __syncthreads();
     }
     row_sync();
     // (the sums have to fit 53 bits down to the smallest element's unit; a counter of more than 255 has lost them)
@@ -849,7 +847,9 @@ __global__ __launch_bounds__(kWinRows * WPR * 64, WPR == 1 && BITS == 4 ? 5 : 6)
             reinterpret_cast<u32x4_t*>(table + kWinFirst)[g] = u32x4_t{fp, fp, fp, fp};
             reinterpret_cast<u32x4_t*>(table + kWinPlane + kWinFirst)[g] = u32x4_t{fn, fn, fn, fn};
         }
-        row_sync();
+    }
+    row_sync();
+    if (valid) {
         for (int task = at; task < (C - 1) * 16; task += T) {   // ... and one by one where a boundary lies among them
             const int th = sm.thr[task >> 4], e = task & 15;    // values in ascending order, 0..2H - 1: the 16 around the boundary
             const int v = (th & ~15) + e;
