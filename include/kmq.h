@@ -155,8 +155,8 @@ size_t kmq_workspace_bytes(int64_t N, int64_t K, int bits, int M, int layout);
  * Kernels on the canonical layout (kmq_kernel_name tells which one a shape gets): bits 1..4 with K one of
  * the row lengths the library has a fully unrolled table kernel for ("lut_b..."), any other K % 32 == 0 up
  * to 24576 through the table kernel that walks a row in rounds ("lut_loop_b..."), any other K through the matrix-core
- * kernel for any row length ("mfma_any_b..."); 8 bits, and few long rows, through the shape-agnostic kernel ("generic",
- * "generic_splitk"). */
+ * kernel for any row length ("mfma_any_b..."); 8 bits through a matrix-core kernel of their own ("mfma_b8"), few rows of
+ * them, and few long rows, through the shape-agnostic kernel ("generic", "generic_splitk"). */
 kmq_status kmq_gemv(const uint32_t* W, const uint16_t* codebook, const uint16_t* x, uint16_t* y,
                     int64_t N, int64_t K, int bits, int layout,
                     void* workspace, size_t workspace_bytes, void* hip_stream);

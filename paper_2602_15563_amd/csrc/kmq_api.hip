@@ -132,7 +132,9 @@ Plan make_plan(int64_t N, int64_t K, int bits, int M, int layout, bool scaled) {
         return Plan{kVariantGeneric, slices, static_cast<size_t>(slices) * M * N * sizeof(float), "generic_splitk"};
     if (use_loop && (M == 1 || per_column_faster(M)) && lut_loop_has_kernel(N, K, bits, layout) && !any_beats_rounds(N, K, bits, M))
         return Plan{kVariantLutLoop, -1, 0, lut_loop_name(bits)};
-    return bits <= 4 ? any_length_plan(bits, false) : Plan{kVariantGeneric, -1, 0, "generic"};
+    if (bits <= 4) return any_length_plan(bits, false);
+    if (mfma_b8_takes(N, K, M)) return Plan{kVariantMfmaB8, -1, 0, "mfma_b8"};
+    return Plan{kVariantGeneric, -1, 0, "generic"};
 }
 
 // Text of the last HIP error a launch reported on this thread ("" if none).
@@ -181,6 +183,7 @@ static kmq_status check_and_run(const GemmArgs& a_in, void* stream, bool library
             break;
         }
         case kVariantMfma: e = launch_mfma(a, s); break;
+        case kVariantMfmaB8: e = launch_mfma_b8(a, s); break;
         case kVariantRowlane: e = launch_rowlane(a, s); break;
         case kVariantLut: e = launch_lut_entry(plan.table_index, a, s); break;
         case kVariantPerColumn:                               // one launch, a workgroup per (row group, column)

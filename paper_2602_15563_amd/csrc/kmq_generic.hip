@@ -1,4 +1,4 @@
-// Shape-agnostic kernels: products of the canonical layout, any K >= 1, any bit-width, batch 1..16 -- for 8 bits
+// Shape-agnostic kernels: products of the canonical layout, any K >= 1, any bit-width, batch 1..16 -- for few rows of 8 bits
 // and for few long rows, split over K; the rest has faster kernels -- and the
 // bit-exact dequantiser of both layouts.  Operation: paper App. E, "Kernel implementations"
 // (lookup, then multiply-accumulate), per-row codebooks, fp32 accumulation.

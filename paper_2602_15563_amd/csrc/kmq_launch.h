@@ -30,10 +30,11 @@ struct GemmArgs {
 // Kernel variants the heuristic can pick (kmq_kernel_name reports them).
 enum Variant {
     kVariantInvalid = 0,
-    kVariantGeneric,     // 8 bits, and few long rows (split over K): wave per row, fp32 codebook in LDS
+    kVariantGeneric,     // few rows of 8 bits, and few long rows (split over K): wave per row, fp32 codebook in LDS
     kVariantLut,         // batch 1, K from a table: hand-scheduled LDS-table kernel
     kVariantMfma,        // tiled layout: matrix-core kernels for rows that split evenly over the waves
     kVariantMfmaAny,     // canonical or tiled layout, 1..4 bits: matrix-core kernel for any row length
+    kVariantMfmaB8,      // canonical layout, 8 bits: matrix-core kernel
     kVariantBlockGeneric,  // block-scaled format, any shape with K % 64 == 0
     kVariantPerColumn,     // canonical layout, batch > 1, shape with a batch-1 table kernel: that kernel over a (row group, column) grid
     kVariantRowlane,       // row-lane layout, batch 1..4: lane-per-row table kernel, activations through DPP broadcasts
@@ -83,6 +84,10 @@ hipError_t launch_canon_b1(const GemmArgs& a, hipStream_t s);
 hipError_t launch_canon_b2(const GemmArgs& a, hipStream_t s);
 hipError_t launch_canon_b3(const GemmArgs& a, hipStream_t s);
 hipError_t launch_canon_b4(const GemmArgs& a, hipStream_t s);
+
+// Matrix-core kernel of 8-bit products (canonical layout).
+bool mfma_b8_takes(int64_t N, int64_t K, int M);      // else launch_generic
+hipError_t launch_mfma_b8(const GemmArgs& a, hipStream_t s);
 
 // Row-lane layout kernels (batch 1..4).
 bool rowlane_has_kernel(int64_t K, int bits, int M);
