@@ -133,12 +133,23 @@ constexpr uint16_t kRowMark = 0x7FFF;      // a NaN: no codebook entry of a row 
 template <int MAGS = kHistMags>
 __device__ __forceinline__ int hist_below(double b, int base) {
     const uint64_t u = static_cast<uint64_t>(__double_as_longlong(b));
-    const uint32_t hi = static_cast<uint32_t>(u >> 32);
-    const int mag = static_cast<int>((hi & 0x7FFFFFFFu) >> 13) - ((1023 - 127) << 7) - base;   // bf16 magnitude, towards zero (below the normal range: negative)
-    const bool neg = b < 0.0, more = (static_cast<uint32_t>(u) | (hi & 0x1FFFu)) != 0;
-    const int mi = mag + ((neg ? more : true) ? 1 : 0);                                        // negative: smallest magnitude not above b
-    const int in = mi < 0 ? 0 : mi > MAGS ? MAGS : mi;
-    return neg ? MAGS - in : MAGS + in;
+    if constexpr (MAGS == kHistMags) {                                                        // (a wave's boundaries of one row: the branch is the faster one)
+        const uint32_t top = static_cast<uint32_t>(u >> 45);                                  // sign, exponent, seven mantissa bits
+        const int mag = static_cast<int>(top & 0x3FFFFu) - ((1023 - 127) << 7);               // bf16 magnitude, towards zero (below the normal range: negative)
+        if (b < 0.0) {
+            const int mi = mag + ((u & ((1ull << 45) - 1)) != 0 ? 1 : 0) - base;              // smallest magnitude not above b
+            return MAGS - (mi < 0 ? 0 : mi > MAGS ? MAGS : mi);
+        }
+        const int mi = mag - base + 1;
+        return MAGS + (mi < 0 ? 0 : mi > MAGS ? MAGS : mi);
+    } else {                                                                                  // (boundaries of four rows in a wave)
+        const uint32_t hi = static_cast<uint32_t>(u >> 32);
+        const int mag = static_cast<int>((hi & 0x7FFFFFFFu) >> 13) - ((1023 - 127) << 7) - base;
+        const bool neg = b < 0.0, more = (static_cast<uint32_t>(u) | (hi & 0x1FFFu)) != 0;
+        const int mi = mag + ((neg ? more : true) ? 1 : 0);
+        const int in = mi < 0 ? 0 : mi > MAGS ? MAGS : mi;
+        return neg ? MAGS - in : MAGS + in;
+    }
 }
 
 typedef u32x4_t __attribute__((aligned(2))) u32x4_a2_t;
@@ -213,29 +224,32 @@ __device__ __forceinline__ void load16(const uint16_t* w, int k0, int K, uint32_
     }
 }
 
-struct alignas(16) HistShared {
-    uint32_t cells[4 + kHistMags];                          // the histogram from cell 4 on; cell 3 counts the zeros
-    long long psum[kHistBuckets + 1];                       // sum of the members below bucket i, in units
-    uint32_t pcnt[kHistBuckets + 1];                        // ... and their number
-    long long wsum[4];
-    uint32_t wcnt[4];
-    int wlo[4], whi[4], wmin[4];
-    int thr[16];                                            // values at or below each boundary of the stored codebook
-    int zero_cluster;
-};
-
-// One row by a workgroup of four waves; false (for all of them): not a row for this.
-// NI > 0: the row is at most NI * 4096 elements and a thread keeps its NI pieces of 16 in registers; 0: re-read.
-template <int BITS, int NI>
-__device__ __forceinline__ bool quantize_row_hist(HistShared& sm, const uint16_t* W, int64_t n, int64_t rowlen, int iters, uint32_t* packed, uint16_t* codebook) {
+// NI > 0: the row is at most NI * 4096 elements and a thread keeps its NI pieces of 16 in registers; 0: re-read.  MARKED: only the rows that the kernel of four rows a workgroup left.
+template <int BITS, int NI, bool MARKED>
+__global__ __launch_bounds__(256, NI == 4 ? 6 : 8) void quantize_rows_hist_kernel(const uint16_t* __restrict__ W, int64_t rowlen, int iters,
+                                                                                 uint32_t* __restrict__ packed,
+                                                                                 uint16_t* codebook) {
     constexpr int C = 1 << BITS;
     constexpr int LG = C <= 4 ? 16 : 64 / C;                // lanes per boundary in the clustering wave
     constexpr int DW = kHistBucket / LG;                    // histogram dwords (of a bucket's 32) per lane
     constexpr int H = kHistMags;
+    struct alignas(16) Smem {
+        uint32_t cells[4 + H];                              // the histogram from cell 4 on; cell 3 counts the zeros
+        long long psum[kHistBuckets + 1];                   // sum of the members below bucket i, in units
+        uint32_t pcnt[kHistBuckets + 1];                    // ... and their number
+        long long wsum[4];
+        uint32_t wcnt[4];
+        int wlo[4], whi[4], wmin[4];
+        int thr[16];                                        // values at or below each boundary of the stored codebook
+        int zero_cluster;
+    };
+    __shared__ Smem sm;
     uint32_t* const hist = sm.cells + 4;
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));                           // (one row after the other: nothing derived from it is kept over the rows, in registers that this needs)
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t n = blockIdx.x;
+    if constexpr (MARKED) {
+        if (codebook[n * C] != kRowMark) return;          // (the same for every thread; overwritten behind the first barrier only)
+    }
     const uint16_t* w = W + n * rowlen;
     const int K = static_cast<int>(rowlen), pieces = (K + 15) >> 4;
 
@@ -291,7 +305,10 @@ __device__ __forceinline__ bool quantize_row_hist(HistShared& sm, const uint16_t
     const bool all_zero = maxmag == 0;
     const int emax = all_zero ? 127 : maxmag >> 7, emin = all_zero ? 127 : ((mn + 1) >> 7 > 0 ? (mn + 1) >> 7 : 1);
     const int log2k = 32 - __clz(K - 1);                    // K <= 2^log2k (K = 1: 0)
-    if (maxmag >= 0x7F80 || emax <= kHistOctaves || emax - emin >= kHistOctaves || emax - emin + 8 + log2k > 53) return false;   // (uniform)
+    if (maxmag >= 0x7F80 || emax <= kHistOctaves || emax - emin >= kHistOctaves || emax - emin + 8 + log2k > 53) {
+        if (tid == 0) codebook[n * C] = kRowMark;           // the same for every thread: the whole workgroup leaves
+        return;
+    }
     const int base = __builtin_amdgcn_readfirstlane((emax - (kHistOctaves - 1)) << 7);
 
     // ---- 2. histogram: dword `magnitude - base`, low half for positive values, high half for negative ones.  From here on
@@ -489,28 +506,19 @@ __device__ __forceinline__ bool quantize_row_hist(HistShared& sm, const uint16_t
     // the half-words behind the last piece that the row's last word still has (16 * BITS bits per piece)
     if (tid == 0)
         for (int i = pieces * BITS; i < 2 * wpr; ++i) out[i] = 0;
-    return true;
-}
-
-template <int BITS, int NI>
-__global__ __launch_bounds__(256, NI == 4 ? 6 : 8) void quantize_rows_hist_kernel(const uint16_t* __restrict__ W, int64_t rowlen, int iters,
-                                                                                 uint32_t* __restrict__ packed,
-                                                                                 uint16_t* __restrict__ codebook) {
-    __shared__ HistShared sm;
-    if (!quantize_row_hist<BITS, NI>(sm, W, blockIdx.x, rowlen, iters, packed, codebook) && threadIdx.x == 0) codebook[static_cast<int64_t>(blockIdx.x) << BITS] = kRowMark;
 }
 
 // ---- one codebook per row: four rows a workgroup --------------------------------------------------
 // The same rounds for many rows.  What bounds them is the instructions of the rounds (a wave for one row's
 // few boundaries: 25 rounds are two thirds of all instructions at 4096 elements), so here one wave runs the rounds of four rows
-// at once, 16 lanes a row, and everything else is done by the row's own WPR waves (one per 4096 elements).  A round is a chain of
+// at once, 16 lanes a row, and everything else is done by the row's own wave.  A round is a chain of
 // 1400 clocks that only other rows hide, so a row has to be small in LDS: counters of a byte over a window of 15 octaves below the
 // row's largest magnitude, prefix sums over buckets of 16 with number and sum in one 64-bit integer; 24 rows a CU.  A few elements
 // below the window ("tiny": one row in three of 4096 normal weights has one) are kept in a list and met one by one where a boundary
 // lies among them; rows with more, or with more than 255 of one value other than zero, are left to the kernel above.
 // The sums are the same integers, exact in fp64, so the results are the same bits.
-// 25 rounds, 14336 x 4096, 1 / 2 / 3 / 4 bits, a workgroup a row / this (us): 104 / 132 / 150 / 170 -> 73 / 86 / 93 / 104; 8192 x 8192,
-// 2 / 4 bits: 98 / 115 -> 90 / 104; 100000 x 64, 2 bits, 10 rounds: 401 -> 160.  Vector issue: two thirds of the busy time.
+// 25 rounds, 14336 x 4096, 1 / 2 / 3 / 4 bits, a workgroup a row / this (us): 104 / 132 / 150 / 170 -> 78 / 89 / 96 / 109;
+// 100000 x 64, 2 bits, 10 rounds: 401 -> 160.  Vector issue: two thirds of the busy time.
 // Where every row is left over, the look at it comes on top (4096 x 4096, 2 / 4 bits, elements spread evenly over 22 octaves: 43 / 60 ->
 // 66 / 82).
 constexpr int kWinOctaves = 15, kWinMags = kWinOctaves * 128, kWinBucket = 16, kWinBuckets = 2 * kWinMags / kWinBucket;
@@ -531,7 +539,6 @@ struct alignas(16) WinRow {
     uint16_t tiny[kWinTiny];
     int thr[16];
     double bound[16];                                       // boundaries of the stored codebook
-    uint32_t ext[3][4];                                     // of the row's waves
 };
 
 __device__ __forceinline__ uint32_t pk_max_u(uint32_t a, uint32_t b) { return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b))); }
@@ -550,29 +557,24 @@ __device__ __forceinline__ double dpp_row_f64(double v) {
     return __longlong_as_double(static_cast<long long>(dpp_u64<CTRL>(static_cast<uint64_t>(__double_as_longlong(v)))));
 }
 
-// WPR: 1 (rows of at most 4096 elements) or 2 (8192)
-template <int BITS, int WPR>
-__global__ __launch_bounds__(kWinRows * WPR * 64, WPR == 1 && BITS == 4 ? 5 : 6) void quantize_rows_window_kernel(const uint16_t* __restrict__ W, int64_t N, int K, int iters,
+template <int BITS>
+__global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_rows_window_kernel(const uint16_t* __restrict__ W, int64_t N, int K, int iters,
                                                                                   uint32_t* __restrict__ packed, uint16_t* __restrict__ codebook) {
     constexpr int C = 1 << BITS, NI = 4, H = kWinMags;
     __shared__ alignas(sizeof(WinCells)) WinCells all_cells[kWinRows];
     __shared__ WinRow rows[kWinRows];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int part = wave % WPR, at = part * 64 + lane;     // this thread among the row's
-    constexpr int T = WPR * 64;
-    WinRow& sm = rows[wave / WPR];
-    uint32_t* const cells = all_cells[wave / WPR];
+    const int at = lane;                                    // (a wave a row)
+    constexpr int T = 64;
+    WinRow& sm = rows[wave];
+    uint32_t* const cells = all_cells[wave];
     uint32_t cells_at = static_cast<uint32_t>(reinterpret_cast<size_t>((lds_u32_t*)cells));
     asm volatile("" : "+v"(cells_at));                      // (in a vector register: v_and_or_b32 takes one scalar, the mask)
-    const int64_t n = static_cast<int64_t>(blockIdx.x) * kWinRows + wave / WPR;
+    const int64_t n = static_cast<int64_t>(blockIdx.x) * kWinRows + wave;
     const bool there = n < N;                               // (uniform over the wave)
     const uint16_t* const w = W + (there ? n : 0) * K;
     const int pieces = there ? (K + 15) >> 4 : 0;
-    // a row's waves wait for each other (and for the workgroup's others: every wave calls this as often); a lone wave's LDS instructions run in order
-    auto row_sync = [] {
-        if constexpr (WPR > 1) __syncthreads();
-        else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    };
+    auto row_sync = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };      // a lone wave's LDS instructions run in order
 
     // ---- 1. the row and its range.  As patterns: the largest unsigned one is the most negative value, if there is a negative one, the
     // largest signed one the largest value, if there is a positive one; else the smallest unsigned one is that
@@ -594,19 +596,6 @@ __global__ __launch_bounds__(kWinRows * WPR * 64, WPR == 1 && BITS == 4 ? 5 : 6)
     um = of_wave(wave_extreme<true>(um));
     un = of_wave(wave_extreme<false>(un));
     sx = of_wave(wave_extreme<true>(sx));
-    if constexpr (WPR > 1) {
-        if (lane == 0) { sm.ext[0][part] = um; sm.ext[1][part] = un; sm.ext[2][part] = sx; }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < WPR; ++q) {
-            um = max(um, static_cast<int>(sm.ext[0][q]));
-            un = min(un, static_cast<int>(sm.ext[1][q]));
-            sx = max(sx, static_cast<int>(sm.ext[2][q]));
-        }
-        um = __builtin_amdgcn_readfirstlane(um);
-        un = __builtin_amdgcn_readfirstlane(un);
-        sx = __builtin_amdgcn_readfirstlane(sx);
-    }
     const uint32_t lo_h = static_cast<uint32_t>(um >= 0x8000 ? um : un), hi_h = static_cast<uint32_t>(sx >= 0 ? sx : un);
     const int maxmag = max(static_cast<int>(lo_h & 0x7FFFu), static_cast<int>(hi_h & 0x7FFFu));
     const int emax = maxmag == 0 ? 127 : maxmag >> 7;
@@ -691,7 +680,7 @@ __global__ __launch_bounds__(kWinRows * WPR * 64, WPR == 1 && BITS == 4 ? 5 : 6)
         }
     }
     row_sync();
-    if (valid && part == 0) {
+    if (valid) {
         constexpr int PER = 4;
         static_assert(kWinBuckets <= PER * 64, "buckets per lane");
         long long v[PER];
@@ -722,7 +711,7 @@ __global__ __launch_bounds__(kWinRows * WPR * 64, WPR == 1 && BITS == 4 ? 5 : 6)
             sm.nzero = nzero;
         }
     }
-    if (part == 0 && lane == 0) sm.valid = valid ? 1 : 0;
+    if (lane == 0) sm.valid = valid ? 1 : 0;
     __syncthreads();
     valid = __builtin_amdgcn_readfirstlane(sm.valid) != 0;
 
@@ -1014,38 +1003,16 @@ __device__ __forceinline__ void quantize_row(RowShared<BITS>& sh, const uint16_t
     }
 }
 
-template <int BITS>
+template <int BITS, bool MARKED>
 __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __restrict__ W, int64_t K, int iters,
                                                             uint32_t* __restrict__ packed, uint16_t* codebook) {
+    constexpr int C = 1 << BITS;
     __shared__ RowShared<BITS> sh;
-    quantize_row<BITS>(sh, W, blockIdx.x, K, iters, packed, codebook);
-}
-
-// The rows that a kernel before left (their codebook starts with kRowMark).  64 rows at a time: a mark per lane, the same for all waves
-// (a row's codebook is overwritten behind a barrier only); rows next to each other fall to different workgroups.
-constexpr int kMarkedGroups = 2048;
-template <int C, typename F>
-__device__ __forceinline__ void marked_rows(int64_t N, const uint16_t* codebook, F&& f) {
-    for (int64_t n0 = blockIdx.x; n0 < N; n0 += static_cast<int64_t>(gridDim.x) * 64) {
-        const int64_t mine = n0 + static_cast<int64_t>(threadIdx.x & 63) * gridDim.x;
-        uint64_t left = __ballot(mine < N && codebook[(mine < N ? mine : n0) * C] == kRowMark);
-        for (; left; left &= left - 1) {
-            f(n0 + static_cast<int64_t>(__builtin_ctzll(left)) * gridDim.x);
-            __syncthreads();
-        }
+    const int64_t n = blockIdx.x;
+    if constexpr (MARKED) {
+        if (codebook[n * C] != kRowMark) return;          // (the same for every thread; overwritten behind the first barrier only)
     }
-}
-template <int BITS, int NI>
-__global__ __launch_bounds__(256, 8) void quantize_marked_rows_hist_kernel(const uint16_t* __restrict__ W, int64_t N, int64_t K, int iters,
-                                                                           uint32_t* __restrict__ packed, uint16_t* codebook) {
-    __shared__ HistShared sm;
-    marked_rows<1 << BITS>(N, codebook, [&](int64_t n) { quantize_row_hist<BITS, NI>(sm, W, n, K, iters, packed, codebook); });
-}
-template <int BITS>
-__global__ __launch_bounds__(256) void quantize_marked_rows_kernel(const uint16_t* __restrict__ W, int64_t N, int64_t K, int iters,
-                                                                   uint32_t* __restrict__ packed, uint16_t* codebook) {
-    __shared__ RowShared<BITS> sh;
-    marked_rows<1 << BITS>(N, codebook, [&](int64_t n) { quantize_row<BITS>(sh, W, n, K, iters, packed, codebook); });
+    quantize_row<BITS>(sh, W, n, K, iters, packed, codebook);
 }
 
 // ---- the paper's format: scale per 64-element block, one codebook per tensor -------------------------
@@ -1812,9 +1779,10 @@ __global__ __launch_bounds__(256) void bs_small_kernel(const uint16_t* __restric
     }
 }
 
-// Four rows a workgroup need many rows (us, a workgroup a row / four rows; 2 bits, 25 rounds): 1024 x 4096 19.3 / 22.8, 2048 27.3 / 28.5,
-// 3072 38.4 / 32.5; 4096 x 8192 58 / 56; and short ones: with four waves a row a CU holds four rows (4096 x 14336: 74 / 115).
-constexpr int64_t kWinLeastRows = 2560, kWinMostK = 8192;
+// Four rows a workgroup need many rows (us, a workgroup a row / four rows; 8 and 25 rounds): 2 bits, 2560 x 4096 21.8 / 23.0 and 35.4 / 31.9, 3000 x
+// 4096 24.5 / 23.4 and 38.1 / 32.2, 2560 x 1024 19.6 / 16.7 and 29.4 / 25.4; and short ones: with two waves a row a CU holds half as many
+// (1 / 2 / 4 bits, 3584 x 6400: 33 / 34 / 39 -> 40 / 39 / 44 and 42 / 51 / 59 -> 49 / 53 / 60).
+constexpr int64_t kWinLeastRows = 3000, kWinLeastShort = 2560, kWinMostK = 4096;
 
 size_t quantize_blockscaled_workspace_bytes() { return sizeof(QuantScratch); }
 
@@ -1825,28 +1793,23 @@ static hipError_t quantize_rows_bits(const uint16_t* W, int64_t N, int64_t K, in
     // without rounds a short row does not repay its histogram (100000 x 64, 1 / 2 / 3 / 4 bits: 258 / 276 / 303 / 339 us with it,
     // 148 / 158 / 237 / 413 without)
     if (K > kHistMaxK || (iters == 0 && K <= 512 && BITS <= 3)) {
-        hipLaunchKernelGGL((quantize_rows_kernel<BITS>), rows, block, 0, s, W, K, iters, packed, codebook);
+        hipLaunchKernelGGL((quantize_rows_kernel<BITS, false>), rows, block, 0, s, W, K, iters, packed, codebook);
         return hipGetLastError();
     }
-    const dim3 marked(static_cast<unsigned>(N < kMarkedGroups ? N : kMarkedGroups));
-    if (K <= kWinMostK && N >= kWinLeastRows) {
-        const dim3 fours(static_cast<unsigned>((N + kWinRows - 1) / kWinRows));
-#define KMQ_WIN(WPR) hipLaunchKernelGGL((quantize_rows_window_kernel<BITS, WPR>), fours, dim3(kWinRows * WPR * 64), 0, s, W, N, static_cast<int>(K), iters, packed, codebook)
-        if (K <= 4096) KMQ_WIN(1);
-        else KMQ_WIN(2);
-#undef KMQ_WIN
-        if (K <= 4096) hipLaunchKernelGGL((quantize_marked_rows_hist_kernel<BITS, 1>), marked, block, 0, s, W, N, K, iters, packed, codebook);
-        else hipLaunchKernelGGL((quantize_marked_rows_hist_kernel<BITS, 2>), marked, block, 0, s, W, N, K, iters, packed, codebook);
-        hipLaunchKernelGGL((quantize_marked_rows_kernel<BITS>), marked, block, 0, s, W, N, K, iters, packed, codebook);
+    if (K <= kWinMostK && N >= (K <= 2048 ? kWinLeastShort : kWinLeastRows)) {
+        hipLaunchKernelGGL((quantize_rows_window_kernel<BITS>), dim3(static_cast<unsigned>((N + kWinRows - 1) / kWinRows)), dim3(kWinRows * 64), 0, s,
+                           W, N, static_cast<int>(K), iters, packed, codebook);
+        hipLaunchKernelGGL((quantize_rows_hist_kernel<BITS, 1, true>), rows, block, 0, s, W, K, iters, packed, codebook);
+        hipLaunchKernelGGL((quantize_rows_kernel<BITS, true>), rows, block, 0, s, W, K, iters, packed, codebook);
         return hipGetLastError();
     }
-#define KMQ_HIST(NI) hipLaunchKernelGGL((quantize_rows_hist_kernel<BITS, NI>), rows, block, 0, s, W, K, iters, packed, codebook)
+#define KMQ_HIST(NI) hipLaunchKernelGGL((quantize_rows_hist_kernel<BITS, NI, false>), rows, block, 0, s, W, K, iters, packed, codebook)
     if (K <= 4096) KMQ_HIST(1);
     else if (K <= 8192) KMQ_HIST(2);
     else if (K <= 16384) KMQ_HIST(4);
     else KMQ_HIST(0);
 #undef KMQ_HIST
-    hipLaunchKernelGGL((quantize_marked_rows_kernel<BITS>), marked, block, 0, s, W, N, K, iters, packed, codebook);
+    hipLaunchKernelGGL((quantize_rows_kernel<BITS, true>), rows, block, 0, s, W, K, iters, packed, codebook);
     return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-"""The row quantiser's kernel of four rows a workgroup (2560 rows and more, at most 8192 elements) at its edges, bit for bit against
+"""The row quantiser's kernel of four rows a workgroup (2560 rows and more, from 2049 elements on 3000, at most 4096 elements) at its edges, bit for bit against
 the fp64 oracle: row lengths around a thread's piece and a wave's share, row counts that leave a workgroup partly empty, and rows
 side by side that go its several ways: elements below its window (a few, sixteen, seventeen), boundaries among those, counters at
 and over 255, zeros of both signs, one value only, infinities' neighbours."""
@@ -33,7 +33,7 @@ def check(gpu, W, bits, iters, rows):
 
 
 @pytest.mark.parametrize("bits", [1, 2, 3, 4])
-@pytest.mark.parametrize("N,K", [(2560, 1), (2561, 15), (2562, 16), (2563, 17), (2560, 33), (2561, 1023), (2562, 1041), (2563, 4095), (2560, 4096), (2561, 4097),
+@pytest.mark.parametrize("N,K", [(2560, 1), (2561, 15), (2562, 16), (2563, 17), (2560, 33), (2561, 1023), (2562, 1041), (3003, 2049), (3003, 4095), (3000, 4096), (3001, 4097),
                                  (2562, 6001), (2563, 8191), (2560, 8192)])
 def test_sizes(gpu, N, K, bits):
     W = synth.make_dense_weights(120 + bits, K, N, K)
@@ -78,7 +78,7 @@ def special_rows(K, rng):
 def test_rows_of_every_kind(gpu, K, bits, iters):
     rng = np.random.default_rng(K + bits)
     special = special_rows(K, rng)
-    W = synth.make_dense_weights(130 + bits, K, 2561, K)
-    at = rng.permutation(2561)[:len(special)]                  # side by side with ordinary rows, any place in a workgroup
+    W = synth.make_dense_weights(130 + bits, K, 3001, K)
+    at = rng.permutation(3001)[:len(special)]                  # side by side with ordinary rows, any place in a workgroup
     W[at] = special
     check(gpu, W, bits, iters, at)
