@@ -517,7 +517,7 @@ __global__ __launch_bounds__(256, NI == 4 ? 6 : 8) void quantize_rows_hist_kerne
 // below the window ("tiny": one row in three of 4096 normal weights has one) are kept in a list and met one by one where a boundary
 // lies among them; rows with more, or with more than 255 of one value other than zero, are left to the kernel above.
 // The sums are the same integers, exact in fp64, so the results are the same bits.
-// 25 rounds, 14336 x 4096, 1 / 2 / 3 / 4 bits, a workgroup a row / this (us): 104 / 132 / 150 / 170 -> 78 / 89 / 96 / 109;
+// 25 rounds, 14336 x 4096, 1 / 2 / 4 bits, a workgroup a row / this (us): 104 / 132 / 170 -> 78 / 89 / 109;
 // 100000 x 64, 2 bits, 10 rounds: 401 -> 160.  Vector issue: two thirds of the busy time.
 // Where every row is left over, the look at it comes on top (4096 x 4096, 2 / 4 bits, elements spread evenly over 22 octaves: 43 / 60 ->
 // 66 / 82).
