@@ -18,7 +18,8 @@ typedef __attribute__((address_space(3))) const uint32_t lds_cu32_t;
 // The LGKM counter of a wave has 4 bits: at most 15 LDS/scalar-memory operations
 // may be outstanding, or s_waitcnt lgkmcnt(n) stops meaning what it says.  The
 // pipeline below therefore issues lookups in groups of four and never has more
-// than 12 in flight.
+// than 12 in flight; where a kernel lets the compiler read LDS between them
+// (kmq_lut_columns.hip), at most 15 of both.
 
 // 2-bit / 4-bit: four 4-byte lookups, nibbles 4H..4H+3 of `word` (H = 0, 1), into
 // v[4H..4H+3]; v[2i] belongs to nibble 2i (even).  re/ro are the rotated words,

@@ -245,9 +245,6 @@ void gemm_lut_columns_kernel(const uint32_t* __restrict__ W, const uint16_t* __r
     uint32_t ar[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) ar[i] = lut_base;
-    // the compiler's own scalar loads must have landed: they share the counter of the hand-counted reads and return out of
-    // order with them (its LDS reads return in order: waits of either side only become longer by the other's)
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     const uint32_t mask = BITS == 1 ? 0x78u : BITS == 3 ? 0xFCu : 0x3Cu;
     float a0[MC][RS], a1[MC][RS];
 #pragma unroll
@@ -275,6 +272,14 @@ void gemm_lut_columns_kernel(const uint32_t* __restrict__ W, const uint16_t* __r
     using std::integral_constant;
 #pragma unroll
     for (int m = 0; m < MC; ++m) load_x(integral_constant<int, 0>{}, m);
+    // the compiler's own scalar loads must have landed: they share the counter of the hand-counted reads and return out of
+    // order with them (its LDS reads return in order: waits of either side only become longer by the other's).  The first unit's
+    // x, too (up to eight reads, tied to the wait): with the twelve lookups ahead of the first counted wait they were up to 20 in
+    // flight, more than the counter's four bits tell apart; later reads of x come between lookups, at most 15 in all
+#pragma unroll
+    for (int m = 0; m < MC; ++m)
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(xu[m][0]), "+v"(xu[m][1]), "+v"(xu[m][2]), "+v"(xu[m][3]),
+                                              "+v"(xu[m][4]), "+v"(xu[m][5]), "+v"(xu[m][6]), "+v"(xu[m][7]) : : "memory");
     constexpr int NS = U * RS;                               // steps: unit by unit, the rows of each
     if constexpr (BITS == 1) {
         u32x2_t vv[2][4];
