@@ -40,17 +40,26 @@ __device__ __forceinline__ float dpp_move(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xF, true));
 }
 
-// Sum over groups of LANES consecutive lanes (16, 32 or 64) with DPP adds.
+// Sum over groups of LANES consecutive lanes (16, 32 or 64) with DPP adds, from sums of neighbouring pairs.
 // The result is valid in the LAST lane of each group.
 template <int LANES>
-__device__ __forceinline__ float group_sum(float v) {
-    v += dpp_move<0xB1>(v);    // quad_perm [1,0,3,2]
+__device__ __forceinline__ float group_sum_of_pairs(float v) {
     v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]
     v += dpp_move<0x141>(v);   // row_half_mirror
     v += dpp_move<0x140>(v);   // row_mirror: every lane of a 16-lane row holds the row sum
     if (LANES >= 32) v += dpp_move<0x142, 0xA>(v);   // row_bcast15 into rows 1 and 3
     if (LANES >= 64) v += dpp_move<0x143, 0xC>(v);   // row_bcast31 into rows 2 and 3
     return v;
+}
+template <int LANES>
+__device__ __forceinline__ float group_sum(float v) {
+    return group_sum_of_pairs<LANES>(v + dpp_move<0xB1>(v));    // quad_perm [1,0,3,2]
+}
+// Sum of v * scale.  A lane adds its own product unrounded: written out, so that kernels which promise each other's bits do not
+// rest on which multiplications the compiler fuses.
+template <int LANES>
+__device__ __forceinline__ float group_sum_scaled(float v, float scale) {
+    return group_sum_of_pairs<LANES>(fmaf(v, scale, dpp_move<0xB1>(v * scale)));
 }
 
 // Index of element k of row n read from the tiled stream (slow path: used by the

@@ -450,21 +450,18 @@ void gemv_lut_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict_
     // ---- 6. K-reduction: lanes of the group, then slices through LDS ------------------------------
     // (nothing of what follows may be scheduled into the hand-counted pipeline above)
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (SC) {
-        if constexpr (BITS == 1) {
-            // two blocks per lane: s0*(c0*X0 + d*S0) + s1*(c0*X1 + d*S1), X = the block's sum of x
-            const float c0 = bf16_to_f32(cpair & 0xFFFFu), d = bf16_to_f32(cpair >> 16) - c0;
+    if constexpr (SC && BITS == 1) {
+        // two blocks per lane: s0*(c0*X0 + d*S0) + s1*(c0*X1 + d*S1), X = the block's sum of x
+        const float c0 = bf16_to_f32(cpair & 0xFFFFu), d = bf16_to_f32(cpair >> 16) - c0;
 #pragma unroll
-            for (int t = 0; t < RS; ++t)
-                acc[t] = bf16_to_f32(sv[t][0]) * fmaf(d, accb[t], c0 * sx0) + bf16_to_f32(sv[t][1]) * fmaf(d, acc[t], c0 * sx1);
-        } else {
-#pragma unroll
-            for (int t = 0; t < RS; ++t) acc[t] *= bf16_to_f32(sv[t][0]);
-        }
+        for (int t = 0; t < RS; ++t)
+            acc[t] = bf16_to_f32(sv[t][0]) * fmaf(d, accb[t], c0 * sx0) + bf16_to_f32(sv[t][1]) * fmaf(d, acc[t], c0 * sx1);
     }
 #pragma unroll
     for (int t = 0; t < RS; ++t) {
-        const float s = group_sum<LPR>(acc[t]);
+        float s;
+        if constexpr (SC && BITS != 1) s = group_sum_scaled<LPR>(acc[t], bf16_to_f32(sv[t][0]));
+        else s = group_sum<LPR>(acc[t]);
         if (pos == LPR - 1) sm.part[wk][wr * ROWS_WAVE + t * RPL + sub] = s;
     }
     __syncthreads();

@@ -334,21 +334,19 @@ void gemm_lut_columns_kernel(const uint32_t* __restrict__ W, const uint16_t* __r
 
     // ---- K-reduction: lanes of the group, then slices through LDS
     __builtin_amdgcn_sched_barrier(0);
-    // (with scales the first level of group_sum is a fused multiply-add whose rounding differs between the two lanes: only
-    // the same code gives the same bits)
+    // (with scales the first level of the sum is a fused multiply-add, whose rounding differs between its two lanes: the batch-1
+    // kernel's own sum, lane for lane)
     float sums[MC * RS];
 #pragma unroll
     for (int m = 0; m < MC; ++m) {
 #pragma unroll
         for (int t = 0; t < RS; ++t) {
             settle_dot(a0[m][t], a1[m][t]);
-            float s = a0[m][t] + a1[m][t];
+            sums[m * RS + t] = a0[m][t] + a1[m][t];
             if constexpr (SC) {
-                s *= bf16_to_f32(sv[t]);
-                s = group_sum<LPR>(s);
+                const float s = group_sum_scaled<LPR>(sums[m * RS + t], bf16_to_f32(sv[t]));
                 if (pos == LPR - 1) sm.part[m][wk][wr * ROWS_WAVE + t * RPL + sub] = s;
             }
-            sums[m * RS + t] = s;
         }
     }
     if constexpr (!SC) {
