@@ -191,6 +191,15 @@ def _stream():
     return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice())
 
 
+def _forget_torch():
+    """In a forked child the parent's streams are not usable: torch is asked again, and refuses."""
+    global _torch_c
+    _torch_c = None
+
+
+os.register_at_fork(after_in_child=_forget_torch)
+
+
 def _ptr(t):
     return t.data_ptr() if t is not None else None
 
