@@ -564,8 +564,6 @@ __global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_row
     __shared__ alignas(sizeof(WinCells)) WinCells all_cells[kWinRows];
     __shared__ WinRow rows[kWinRows];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int at = lane;                                    // (a wave a row)
-    constexpr int T = 64;
     WinRow& sm = rows[wave];
     uint32_t* const cells = all_cells[wave];
     uint32_t cells_at = static_cast<uint32_t>(reinterpret_cast<size_t>((lds_u32_t*)cells));
@@ -581,12 +579,12 @@ __global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_row
     uint32_t reg[NI][8];
 #pragma unroll
     for (int i = 0; i < NI; ++i)
-        if (at + i * T < pieces) load16(w, (at + i * T) << 4, K, reg[i]);
-    for (int i = at; i < 2 * kWinPlane / 16; i += T) reinterpret_cast<u32x4_t*>(cells)[i] = u32x4_t{0, 0, 0, 0};
+        if (lane + i * 64 < pieces) load16(w, (lane + i * 64) << 4, K, reg[i]);
+    for (int i = lane; i < 2 * kWinPlane / 16; i += 64) reinterpret_cast<u32x4_t*>(cells)[i] = u32x4_t{0, 0, 0, 0};
     uint32_t umax = 0, umin = 0xFFFFFFFFu, smax = 0x80008000u;
 #pragma unroll
     for (int i = 0; i < NI; ++i)
-        if (at + i * T < pieces) {
+        if (lane + i * 64 < pieces) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) { umax = pk_max_u(umax, reg[i][j]); umin = pk_min_u(umin, reg[i][j]); smax = pk_max_i(smax, reg[i][j]); }
         }
@@ -610,7 +608,7 @@ __global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_row
         const uint32_t floor2 = static_cast<uint32_t>(base - 2) * 0x00010001u, base2 = static_cast<uint32_t>(base - 2 - kWinTinyKey) * 0x00010001u;
 #pragma unroll
         for (int i = 0; i < NI; ++i)
-            if (at + i * T < pieces) {
+            if (lane + i * 64 < pieces) {
                 uint32_t (&v)[8] = reg[i];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
@@ -626,22 +624,22 @@ __global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_row
                     lds_u32_t* const cell = reinterpret_cast<lds_u32_t*>(static_cast<size_t>(((d >> 3) & (2 * kWinPlane - 4)) | cells_at));
                     __hip_atomic_fetch_add(cell, 1u << (d & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
-                const int extra = ((at + i * T) << 4) + 16 - K;   // repeats of the first element in the row's last piece
+                const int extra = ((lane + i * 64) << 4) + 16 - K;   // repeats of the first element in the row's last piece
                 if (extra > 0) atomicSub(&cells[code_of(v, 0) >> 5], static_cast<uint32_t>(extra) << (v[0] & 31u));
             }
     }
     row_sync();
     const int ntiny = __builtin_amdgcn_readfirstlane(static_cast<int>((cells[kWinTinyKey / 4] >> 24) + (cells[(kWinPlane + kWinTinyKey) / 4] >> 24)));
     if (ntiny > kWinTiny) valid = false;
-    if (valid && ntiny > 0 && at == 0) sm.ntiny = 0;
+    if (valid && ntiny > 0 && lane == 0) sm.ntiny = 0;
     row_sync();
     if (valid && ntiny > 0) {                               // the tiny elements themselves
 #pragma unroll
         for (int i = 0; i < NI; ++i)
-            if (at + i * T < pieces) {
+            if (lane + i * 64 < pieces) {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    const int k = ((at + i * T) << 4) + e;
+                    const int k = ((lane + i * 64) << 4) + e;
                     if (((code_of(reg[i], e) >> 3) & (kWinPlane - 1)) == kWinTinyKey && k < K) {
                         const int slot = atomicAdd(&sm.ntiny, 1);
                         if (slot < kWinTiny) sm.tiny[slot] = w[k];
@@ -661,7 +659,7 @@ __global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_row
 
     // ---- 3. buckets of 16 magnitudes (a thread each), then prefix sums over them in ascending order of the values
     if (valid) {
-        for (int bucket = at; bucket < kWinBuckets / 2; bucket += T) {
+        for (int bucket = lane; bucket < kWinBuckets / 2; bucket += 64) {
             uint32_t cp = 0, cn = 0, sp = 0, sn = 0;        // members and place sums of positive / negative ones
             const u32x4_t dp = reinterpret_cast<const u32x4_t*>(cells)[kWinFirst / 16 + bucket], dn = reinterpret_cast<const u32x4_t*>(cells)[(kWinPlane + kWinFirst) / 16 + bucket];
 #pragma unroll
@@ -711,9 +709,9 @@ __global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_row
             sm.nzero = nzero;
         }
     }
+    valid = __builtin_amdgcn_readfirstlane(valid) != 0;     // (the same in every lane; for the scalar unit)
     if (lane == 0) sm.valid = valid ? 1 : 0;
     __syncthreads();
-    valid = __builtin_amdgcn_readfirstlane(sm.valid) != 0;
 
     // ---- 4. the rounds, one wave: 16 lanes a row, LG of them per cluster and for the boundary above it.  Waves of one number
     // share a SIMD: neighbouring workgroups of a CU take different ones
@@ -823,7 +821,7 @@ __global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_row
     const int wpr = static_cast<int>(words_per_row(BITS, K));
     uint8_t* const table = reinterpret_cast<uint8_t*>(cells);
     if (valid) {
-        for (int g = at; g < H / 16; g += T) {
+        for (int g = lane; g < H / 16; g += 64) {
             const int m = g * 16;                           // this thread's magnitudes m..m + 15, all like the first of them (of +m and -(m + 15) ...
             int p0 = 0, n1 = 0;                             // ... upwards, that is)
 #pragma unroll
@@ -839,7 +837,7 @@ __global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_row
     }
     row_sync();
     if (valid) {
-        for (int task = at; task < (C - 1) * 16; task += T) {   // ... and one by one where a boundary lies among them
+        for (int task = lane; task < (C - 1) * 16; task += 64) {   // ... and one by one where a boundary lies among them
             const int th = sm.thr[task >> 4], e = task & 15;    // values in ascending order, 0..2H - 1: the 16 around the boundary
             const int v = (th & ~15) + e;
             int z = 0;
@@ -847,11 +845,11 @@ __global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_row
             for (int i = 0; i < C - 1; ++i) z += sm.thr[i] <= v ? 1 : 0;
             if (v < 2 * H) table[v >= H ? kWinFirst + (v - H) : kWinPlane + kWinFirst + (H - 1 - v)] = static_cast<uint8_t>(z);
         }
-        if (at < 4) {                                       // tiny elements and zeros of either sign: no boundary lies among them (or `exact`)
+        if (lane < 4) {                                       // tiny elements and zeros of either sign: no boundary lies among them (or `exact`)
             int z = 0;
 #pragma unroll
-            for (int i = 0; i < C - 1; ++i) z += sm.bound[i] < 0.0 || (sm.bound[i] == 0.0 && at == 0) ? 1 : 0;
-            table[(at & 1 ? kWinPlane : 0) + (at < 2 ? kWinTinyKey : kWinZeroKey)] = static_cast<uint8_t>(z);
+            for (int i = 0; i < C - 1; ++i) z += sm.bound[i] < 0.0 || (sm.bound[i] == 0.0 && lane == 0) ? 1 : 0;
+            table[(lane & 1 ? kWinPlane : 0) + (lane < 2 ? kWinTinyKey : kWinZeroKey)] = static_cast<uint8_t>(z);
         }
     }
     row_sync();
@@ -862,7 +860,7 @@ __global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_row
     const bool exact = __builtin_amdgcn_readfirstlane(sm.exact) != 0;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-        const int piece = at + i * T;
+        const int piece = lane + i * 64;
         if (piece >= pieces) continue;
         uint32_t half[2] = {0, 0};                          // eight elements each: 8 * BITS bits
         if (exact) {
@@ -896,7 +894,7 @@ __global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_row
                 if (piece * BITS + j < 2 * wpr) out[piece * BITS + j] = static_cast<uint16_t>(bits >> (16 * j));
         }
     }
-    if (at == 0)
+    if (lane == 0)
         for (int i = pieces * BITS; i < 2 * wpr; ++i) out[i] = 0;
 }
 
