@@ -519,8 +519,10 @@ __global__ __launch_bounds__(256, NI == 4 ? 6 : 8) void quantize_rows_hist_kerne
 // The sums are the same integers, exact in fp64, so the results are the same bits.
 // 25 rounds, 14336 x 4096, 1 / 2 / 4 bits, a workgroup a row / this (us): 104 / 132 / 170 -> 78 / 89 / 109;
 // 100000 x 64, 2 bits, 10 rounds: 401 -> 160.  Vector issue: two thirds of the busy time.
-// Where every row is left over, the look at it comes on top (4096 x 4096, 2 / 4 bits, elements spread evenly over 22 octaves: 43 / 60 ->
-// 66 / 82).
+// Where every row is left over, the look at it comes on top: rows of more than 1024 elements are left once a part of their first 1024 has
+// shown it.  25 rounds, 2 / 4 bits, a workgroup a row / a look at the whole row / this (us): 4096 x 4096, elements spread evenly over 22
+// octaves 42 / 69 / 51 and 59 / 86 / 68; a grid of 15 values (4-bit integers times a scale) 48 / 80 / 61 and 50 / 82 / 63; 14336 x 4096, that
+// grid 150 / 245 / 180 and 156 / 251 / 187.  (The look costs ordinary rows 0 to 0.6 %.)
 constexpr int kWinOctaves = 15, kWinMags = kWinOctaves * 128, kWinBucket = 16, kWinBuckets = 2 * kWinMags / kWinBucket;
 constexpr int kWinRows = 4, kWinTiny = 16, kWinCountBits = 17;
 // Cells of a byte, a plane of 2048 for either sign: the window's magnitudes from 16 on, tiny elements at 15, zeros at 1940 (alone in their
@@ -604,28 +606,53 @@ __global__ __launch_bounds__(kWinRows * 64, BITS == 4 ? 5 : 6) void quantize_row
     // ---- 2. histogram.  From here on an element is the number of its cell (place in the plane, bit 11 the sign) times 8: the low
     // five bits are the shift that puts a one into the cell's byte
     const auto code_of = [](const uint32_t (&v)[8], int e) { return e & 1 ? v[e >> 1] >> 16 : v[e >> 1] & 0xFFFFu; };
+    const uint32_t floor2 = static_cast<uint32_t>(base - 2) * 0x00010001u, base2 = static_cast<uint32_t>(base - 2 - kWinTinyKey) * 0x00010001u;
+    const auto to_cells = [&](uint32_t (&v)[8]) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t d = v[j];
+            const u16x2_t less = __builtin_bit_cast(u16x2_t, d & 0x7FFF7FFFu) - u16x2_t{1, 1};      // (zeros: 65535)
+            const u16x2_t k = __builtin_bit_cast(u16x2_t, pk_max_u(__builtin_bit_cast(uint32_t, less), floor2)) - __builtin_bit_cast(u16x2_t, base2);
+            const uint32_t key = pk_min_u(__builtin_bit_cast(uint32_t, k), kWinZeroKey * 0x00010001u);
+            v[j] = (key << 3) | ((d >> 1) & 0x40004000u);
+        }
+    };
+    const auto count = [&](const uint32_t (&v)[8], auto first) {     // elements first .. first + 7 of a piece
+#pragma unroll
+        for (int e = decltype(first)::value; e < decltype(first)::value + 8; ++e) {
+            const uint32_t d = code_of(v, e);
+            lds_u32_t* const cell = reinterpret_cast<lds_u32_t*>(static_cast<size_t>(((d >> 3) & (2 * kWinPlane - 4)) | cells_at));
+            __hip_atomic_fetch_add(cell, 1u << (d & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    };
+    using std::integral_constant;
     if (valid) {
-        const uint32_t floor2 = static_cast<uint32_t>(base - 2) * 0x00010001u, base2 = static_cast<uint32_t>(base - 2 - kWinTinyKey) * 0x00010001u;
+        if (lane < pieces) {
+            to_cells(reg[0]);
+            count(reg[0], integral_constant<int, 0>{});
+        }
+        // A row that will be left over shows it in half of its first pieces: a lane's first element lies below the window and too many
+        // others do, or it is one of more equal ones than the share that 255 of the row are.  (A row of one piece a lane has little to leave.)
+        if (pieces > 64) {
+            row_sync();
+            const uint32_t place = code_of(reg[0], 0) >> 3, key = place & (kWinPlane - 1);
+            const int alike = *reinterpret_cast<const lds_u8_t*>(static_cast<size_t>(place | cells_at));
+            count(reg[0], integral_constant<int, 8>{});              // (while it is on its way)
+            const int most = key == kWinTinyKey ? kWinTiny * K : key == kWinZeroKey ? 255 * K : 255 * 8 * 64;
+            valid = !__any(alike * K > most);
+        }
+    }
+    if (valid) {
 #pragma unroll
         for (int i = 0; i < NI; ++i)
             if (lane + i * 64 < pieces) {
-                uint32_t (&v)[8] = reg[i];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint32_t d = v[j];
-                    const u16x2_t less = __builtin_bit_cast(u16x2_t, d & 0x7FFF7FFFu) - u16x2_t{1, 1};      // (zeros: 65535)
-                    const u16x2_t k = __builtin_bit_cast(u16x2_t, pk_max_u(__builtin_bit_cast(uint32_t, less), floor2)) - __builtin_bit_cast(u16x2_t, base2);
-                    const uint32_t key = pk_min_u(__builtin_bit_cast(uint32_t, k), kWinZeroKey * 0x00010001u);
-                    v[j] = (key << 3) | ((d >> 1) & 0x40004000u);
+                if (i > 0) {
+                    to_cells(reg[i]);
+                    count(reg[i], integral_constant<int, 0>{});
                 }
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const uint32_t d = code_of(v, e);
-                    lds_u32_t* const cell = reinterpret_cast<lds_u32_t*>(static_cast<size_t>(((d >> 3) & (2 * kWinPlane - 4)) | cells_at));
-                    __hip_atomic_fetch_add(cell, 1u << (d & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                }
+                if (i > 0 || pieces <= 64) count(reg[i], integral_constant<int, 8>{});
                 const int extra = ((lane + i * 64) << 4) + 16 - K;   // repeats of the first element in the row's last piece
-                if (extra > 0) atomicSub(&cells[code_of(v, 0) >> 5], static_cast<uint32_t>(extra) << (v[0] & 31u));
+                if (extra > 0) atomicSub(&cells[code_of(reg[i], 0) >> 5], static_cast<uint32_t>(extra) << (reg[i][0] & 31u));
             }
     }
     row_sync();

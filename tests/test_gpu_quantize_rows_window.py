@@ -82,3 +82,33 @@ def test_rows_of_every_kind(gpu, K, bits, iters):
     at = rng.permutation(3001)[:len(special)]                  # side by side with ordinary rows, any place in a workgroup
     W[at] = special
     check(gpu, W, bits, iters, at)
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("K", [1025, 1041, 3001, 4096])
+def test_rows_left_early(gpu, K, bits):
+    """The look after half of the first pieces (eight of every sixteen elements, the first 1024): equal values and elements below the
+    window around what it lets pass, all inside that half or all outside; rows that are left there and rows that are not give the same bits."""
+    rng = np.random.default_rng(7 * K + bits)
+    inside = np.flatnonzero((np.arange(K) < 1024) & (np.arange(K) % 16 < 8))
+    outside = np.setdiff1d(np.arange(K), inside)
+    rows = []
+    for places in (inside, outside):
+        share = 255 * 8 * 64 // K                               # of the half: as many as 255 of the row
+        for n in (share - 1, share, share + 1, 254, 255, 256, 257, len(places)):
+            r = rng.standard_normal(K) * 0.02
+            r[rng.permutation(places)[:n]] = rng.choice([0.0123, -0.0123])
+            rows.append(r)
+        for n in (1, 16, 17, 40, 256, 300):
+            r = rng.standard_normal(K) * 0.02
+            at = rng.permutation(places)[:n]
+            r[at] = rng.choice([-1, 1], len(at)) * 2.0 ** rng.uniform(-30, -16, len(at)) * 0.06
+            rows.append(r)
+        for zero in (0.0, -0.0):
+            r = rng.standard_normal(K) * 0.02
+            r[places] = zero
+            rows.append(r)
+    W = synth.make_dense_weights(150 + bits, K, 3001, K)
+    at = rng.permutation(3001)[:len(rows)]
+    W[at] = bf16(np.array(rows))
+    check(gpu, W, bits, 12, at)
