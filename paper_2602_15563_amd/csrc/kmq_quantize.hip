@@ -1804,10 +1804,16 @@ __global__ __launch_bounds__(256) void bs_small_kernel(const uint16_t* __restric
     }
 }
 
-// Four rows a workgroup need many rows (us, a workgroup a row / four rows; 8 and 25 rounds): 2 bits, 2560 x 4096 21.8 / 23.0 and 35.4 / 31.9, 3000 x
-// 4096 24.5 / 23.4 and 38.1 / 32.2, 2560 x 1024 19.6 / 16.7 and 29.4 / 25.4; and short ones: with two waves a row a CU holds half as many
-// (1 / 2 / 4 bits, 3584 x 6400: 33 / 34 / 39 -> 40 / 39 / 44 and 42 / 51 / 59 -> 49 / 53 / 60).
-constexpr int64_t kWinLeastRows = 3000, kWinLeastShort = 2560, kWinMostK = 4096;
+// Four rows a workgroup need many rows, and more of them where rows are long and rounds few: what it saves is the rounds.  Measured (us), a
+// workgroup a row / four rows, 1 / 2 / 3 / 4 bits:
+//   2560 x 2048, no round 13.3 / 13.4, 13.7 / 13.6, 14.3 / 14.4, 15.8 / 15.9; one 14.2 / 14.1, 14.7 / 14.2, 15.3 / 15.1, 17.2 / 16.6; three
+//     15.9 / 15.0, 16.5 / 15.1, 17.3 / 16.3, 19.3 / 17.9
+//   3000 x 4096, no round 16.8 / 18.0, 17.4 / 18.3, 18.4 / 19.3, 20.1 / 20.8; one 17.8 / 19.0, 18.4 / 19.2, 19.4 / 20.2, 21.6 / 21.8; three
+//     19.6 / 19.9, 20.2 / 20.1, 21.5 / 21.4, 23.6 / 23.0; four 20.6 / 20.5, 21.0 / 20.6, 22.5 / 22.0, 24.7 / 23.6; 25 31.6 / 30.1,
+//     38.2 / 31.6, 41.4 / 34.6, 46.1 / 36.3 (2560 x 4096, 2 bits, 8 rounds: 21.8 / 23.0)
+//   7000 x 4096, no round 31.5 / 33.2, 32.7 / 33.6, 34.6 / 35.5, 37.8 / 38.8; 10240 x 4096 42.7 / 40.8, 44.4 / 41.4, 46.6 / 43.4, 51.1 / 47.2
+constexpr int64_t kWinMostK = 4096;
+static int64_t window_least_rows(int64_t K, int iters) { return K <= 2048 ? 2560 : iters >= 4 ? 3000 : 9216; }
 
 size_t quantize_blockscaled_workspace_bytes() { return sizeof(QuantScratch); }
 
@@ -1821,7 +1827,7 @@ static hipError_t quantize_rows_bits(const uint16_t* W, int64_t N, int64_t K, in
         hipLaunchKernelGGL((quantize_rows_kernel<BITS, false>), rows, block, 0, s, W, K, iters, packed, codebook);
         return hipGetLastError();
     }
-    if (K <= kWinMostK && N >= (K <= 2048 ? kWinLeastShort : kWinLeastRows)) {
+    if (K <= kWinMostK && N >= window_least_rows(K, iters)) {
         hipLaunchKernelGGL((quantize_rows_window_kernel<BITS>), dim3(static_cast<unsigned>((N + kWinRows - 1) / kWinRows)), dim3(kWinRows * 64), 0, s,
                            W, N, static_cast<int>(K), iters, packed, codebook);
         hipLaunchKernelGGL((quantize_rows_hist_kernel<BITS, 1, true>), rows, block, 0, s, W, K, iters, packed, codebook);

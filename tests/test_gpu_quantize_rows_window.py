@@ -1,7 +1,8 @@
-"""The row quantiser's kernel of four rows a workgroup (2560 rows and more, from 2049 elements on 3000, at most 4096 elements) at its edges, bit for bit against
-the fp64 oracle: row lengths around a thread's piece and a wave's share, row counts that leave a workgroup partly empty, and rows
-side by side that go its several ways: elements below its window (a few, sixteen, seventeen), boundaries among those, counters at
-and over 255, zeros of both signs, one value only, infinities' neighbours."""
+"""The row quantiser's kernel of four rows a workgroup (2560 rows and more, from 2049 elements on 3000, with fewer than four rounds 9216, at
+most 4096 elements) at its edges, bit for bit against the fp64 oracle: row lengths around a thread's piece and a wave's share, row
+counts that leave a workgroup partly empty, and rows side by side that go its several ways: elements below its window (a few, sixteen,
+seventeen), boundaries among those, counters at and over 255, zeros of both signs, one value only, infinities' neighbours.  Longer
+rows, and long ones with few rounds, are the other side of the rule: a workgroup a row."""
 import numpy as np
 import pytest
 
@@ -32,12 +33,23 @@ def check(gpu, W, bits, iters, rows):
     assert np.array_equal(pg[rows], oracle.pack(idx, bits))
 
 
+def check_size(gpu, N, K, bits, iters):
+    W = synth.make_dense_weights(120 + bits, K, N, K)
+    check(gpu, W, bits, iters, np.unique(np.r_[:9, np.linspace(0, N - 1, 20).astype(int), N - 9:N]))
+
+
 @pytest.mark.parametrize("bits", [1, 2, 3, 4])
 @pytest.mark.parametrize("N,K", [(2560, 1), (2561, 15), (2562, 16), (2563, 17), (2560, 33), (2561, 1023), (2562, 1041), (3003, 2049), (3003, 4095), (3000, 4096), (3001, 4097),
                                  (2562, 6001), (2563, 8191), (2560, 8192)])
 def test_sizes(gpu, N, K, bits):
-    W = synth.make_dense_weights(120 + bits, K, N, K)
-    check(gpu, W, bits, 12, np.unique(np.r_[:9, np.linspace(0, N - 1, 20).astype(int), N - 9:N]))
+    check_size(gpu, N, K, bits, 12)
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("iters", [0, 1, 3])
+@pytest.mark.parametrize("N,K", [(2561, 513), (2562, 529), (2563, 2047), (9215, 2049), (9217, 2049)])
+def test_few_rounds(gpu, N, K, iters, bits):
+    check_size(gpu, N, K, bits, iters)
 
 
 def special_rows(K, rng):
@@ -73,7 +85,7 @@ def special_rows(K, rng):
 
 
 @pytest.mark.parametrize("bits", [1, 2, 3, 4])
-@pytest.mark.parametrize("K", [301, 4096, 8000])
+@pytest.mark.parametrize("K", [301, 2035, 3001, 4096, 8000])
 @pytest.mark.parametrize("iters", [0, 1, 25])
 def test_rows_of_every_kind(gpu, K, bits, iters):
     rng = np.random.default_rng(K + bits)
