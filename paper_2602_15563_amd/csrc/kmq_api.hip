@@ -37,9 +37,14 @@ static bool per_column_faster(int M) {
 //     columns, batch 4: 512 rows 4.1 / 5.0, 2048 7.7 / 4.9
 //   block-scaled, batch 1: 4-bit 3648 columns: 1024 rows 3.8 / 7.1, 4096 7.2 / 7.6; 1-bit 11008 columns: 1024 5.9 / 6.2, 4096
 //     13.2 / 6.8
-//   block-scaled with a table kernel, batch 8: 4-bit 8192 columns: 256 rows 5.0 / 10.3, 1024 10.0 / 10.4, 4096 29.9 / 11.0
+//   block-scaled with a table kernel, batch 8: 4-bit 8192 columns: 256 rows 4.7 / 9.7, 1024 8.0 / 9.9, 4096 20.0 / 10.5
 // With more rows it is always faster from batch 2 (K in rounds; 2-bit 4096 x 11008, batch 16: 45.3 -> 12.3), at every batch
-// (block-scaled without a table kernel) and from batch 3 on (with one; 4-bit 8192 x 8192, batch 3: 23.9 -> 14.0).
+// (block-scaled without a table kernel) and from batch 3 on (with one; 4-bit 8192 x 8192, batch 3: 15.2 -> 13.4; but 3-bit 8192 x 8192, batch
+// 3: 11.5 -> 14.1, the worst of those).
+// The lines were drawn against table kernels of two columns a workgroup and a last tile fetched element by element; both are faster now, and
+// were timed again.  Block-scaled, 675 shapes (256..8192 rows, 2048..14336 columns, batch 2..16): the slower side by more than 10 % in 18, 0.9 %
+// over the faster one on average.  K in rounds, 840 (64..4096 rows, 1056..13856 columns): 32, 1.5 %; there `tail` is too high by now (2-bit 1024 x 1056,
+// batch 16: 7.5 taken, 4.5 the other).
 // Table kernels specialised on K keep per-row batches: their columns are the batch-1 results bit for bit.
 constexpr int64_t kAnyOneRound = 256 * 16;
 struct AnyCost { double start, per_k[3]; };               // us; us per 1000 columns at batches up to 4, 8, 16

@@ -9,8 +9,8 @@
 //
 // Bound by vector issue: 8 * MC dots (4 clocks each) for 8 lookups, whose LDS time (2.9 clocks each and a CU) and the reads of x
 // (2 * MC of 16 bytes per unit and RS rows) lie behind them.  2-bit 14336 x 4096, batch 16: 41.7 -> 27.4 us (two columns with their
-// slices in registers -> this), vector issue 88 % of the busy time; 4096 x 14336, batch 4: 14.1 -> 12.1, half of that time the one
-// workgroup a CU waits for x and its words; 4-bit 8192 x 6144, batch 16: 105.7 -> 45.3.
+// slices in registers -> this), vector issue 85 % of the busy time, LDS 43 %; 4096 x 14336, batch 4: 14.1 -> 12.1, vector issue 49 %: half of that
+// time the one workgroup a CU waits for x and its words; 4-bit 8192 x 6144, batch 16: 105.7 -> 45.3.
 #include <cstdlib>
 
 #include "kmq_device.h"

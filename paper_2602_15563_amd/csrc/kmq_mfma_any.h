@@ -618,8 +618,10 @@ static void canon_launch(const GemmArgs& a, hipStream_t s) {
 //     18.4; at batch 6 short rows keep one: 6976 x 3136 9.3 against 10.5);
 //   more: two row blocks and eight waves (3-bit scaled 15616 x 10880, batch 1: 21.2 against 21.7), but rows of up to 16 tiles,
 //     which eight waves do not share evenly, one block and four (4-bit 10496 x 2496, batch 9: 14.9 against 23.5).
-// Two or four tiles in flight per wave instead of one were no faster anywhere (1 to 10 % slower at batch 1, 10 to 20 % above):
-// the kernel is bound by decoding, and the registers cost it waves.
+// Neither pipe binds: vector issue is 32 % and LDS 8 % of the busy time at 3-bit 5001 x 4101, batch 3, and 40 % and 28 % at 1-bit scaled 8192 x 8192,
+// batch 8 (two waves a SIMD); the waves wait for memory.  Two or four tiles in flight per wave instead of one were no faster anywhere all the
+// same (1 to 10 % slower at batch 1, 10 to 20 % above).  Not among the shapes measured: a wave count fitted to the tiles (17 tiles on eight waves
+// are three for one and two for the others), sixteen waves for two row blocks, the last piece's words requested with the last whole tile's.
 template <int BITS, bool SC, bool TILED, int MR>
 static void canon_shape(const GemmArgs& a, hipStream_t s) {
     const int64_t tiles = (a.K + kCanonTile - 1) / kCanonTile, nrb = (a.N + 15) / 16;

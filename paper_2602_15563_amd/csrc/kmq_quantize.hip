@@ -518,7 +518,7 @@ __global__ __launch_bounds__(256, NI == 4 ? 6 : 8) void quantize_rows_hist_kerne
 // lies among them; rows with more, or with more than 255 of one value other than zero, are left to the kernel above.
 // The sums are the same integers, exact in fp64, so the results are the same bits.
 // 25 rounds, 14336 x 4096, 1 / 2 / 4 bits, a workgroup a row / this (us): 104 / 132 / 170 -> 78 / 89 / 109;
-// 100000 x 64, 2 bits, 10 rounds: 401 -> 160.  Vector issue: two thirds of the busy time.
+// 100000 x 64, 2 bits, 10 rounds: 401 -> 160.  Vector issue is 63 % of the busy time at 2 bits, LDS 37 % (61 % of that conflicts of the atomics).
 // Where every row is left over, the look at it comes on top: rows of more than 1024 elements are left once a part of their first 1024 has
 // shown it.  25 rounds, 2 / 4 bits, a workgroup a row / a look at the whole row / this (us): 4096 x 4096, elements spread evenly over 22
 // octaves 42 / 69 / 51 and 59 / 86 / 68; a grid of 15 values (4-bit integers times a scale) 48 / 80 / 61 and 50 / 82 / 63; 14336 x 4096, that
@@ -1058,8 +1058,8 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __re
 // Elements more than 31 octaves below their scale ("far", next to none in most trained tensors) are counted apart per sign, and
 // their sums taken from the tensor (below).
 //
-// 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits: 127 / 145 / 163 / 198 us (8519 / 9344 / 10727 / 13475 with every element
-// divided by its scale and compared with every boundary in fp64, each round); 1024 x 1024, 4 bits: 122 (3570).  At 8192 x 8192
+// 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits, one tensor again and again: 127 / 147 / 163 / 198 us (a new one each time, 4 bits: 205; 8519 / 9344 / 10727 / 13475 with every element
+// divided by its scale and compared with every boundary in fp64, each round); 1024 x 1024, 4 bits: 121 (3570).  At 8192 x 8192
 // and 4 bits: clear 5, scales 21 (6.5 TB/s), group 13, count 34 (blocks gathered 128 bytes at a time, LDS atomics, 16 for the adding up), prefix 9,
 // rounds 78 (3 us each: one CU's issue and its scattered line fetches), assign 45 us (vector issue).
 constexpr int kQuantMants = 128, kQuantBins = 2 * kHistMags, kQuantStride = kQuantBins + 1;
