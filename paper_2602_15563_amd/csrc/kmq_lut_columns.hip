@@ -23,6 +23,7 @@ namespace kmq {
 // NWR1: row waves of the batch-1 kernel of the same shape (1-bit: its sum of x is taken in that kernel's order).
 template <int BITS, int G, int LPR, int NWK, int NWR1, bool SC, int MC, int RSX>
 struct LutColumns {
+    static constexpr int COLUMNS = MC;
     static constexpr int EL = G * 32 / BITS, K = NWK * LPR * EL, RPL = kWave / LPR;
     static constexpr int RS = RSX / (LPR == 16 ? 2 : 1);                     // rows per lane group
     static constexpr int C16 = EL * 2 / 16, XSTR = C16 | 1;                 // 16-byte pieces of x per lane slice, and their stride in LDS
@@ -374,52 +375,119 @@ void gemm_lut_columns_kernel(const uint32_t* __restrict__ W, const uint16_t* __r
     }
 }
 
-template <int BITS, int G, int LPR, int NWK, int NWR1, bool SC, int MC, int RSX>
-static bool launch_columns_of(const GemmArgs& a, int least_waves, hipStream_t s) {
-    using S = LutColumns<BITS, G, LPR, NWK, NWR1, SC, MC, RSX>;
-    if constexpr (S::fits) {
-        const int64_t groups = (a.N + S::ROWS_WG - 1) / S::ROWS_WG, cgroups = (a.M + MC - 1) / MC;
-        if (groups * cgroups < 192 || groups * cgroups * (S::THREADS / 64) < least_waves * 256) return false;
-        const dim3 grid(static_cast<unsigned>((groups + 7) / 8 * 8 * cgroups));
-        hipLaunchKernelGGL((gemm_lut_columns_kernel<BITS, G, LPR, NWK, NWR1, SC, MC, RSX>), grid, dim3(S::THREADS), 0, s,
-                           a.W, a.codebook, a.X, a.Y, static_cast<int>(a.N), a.scales, a.M);
-        return true;
+// Which batches take several columns a workgroup, and how many.  The time of a call is a line in the number of workgroups on the busiest CU, whatever
+// the batch: so many us for the first of them, and for every further one.  The rows a wave and the columns make few large workgroups or many small
+// ones, so that a shape pays for a last workgroup that one CU in eight has (2-bit 1536 x 14336, batch 10: 288 workgroups of four columns 20.6, 960 of
+// two 12.6) or for columns that the batch does not have; the least of the five lines is taken.  Lines fitted to 10717 shapes (both formats, batch 2
+// to 16, 64..20480 rows; rms 2 to 6 % of a line's shapes).  Of the 8071 above the size asked for below, the pick is 0.3 % slower than the best of the five
+// on average and more than 10 % in 13.  Against the kernels of at most two columns that came before: 2525 other shapes, drawn, 18 % less time on
+// average, 12 of them more than 5 % slower, none more than 10 %.  (The most columns that give eight waves a CU, by preference: 3.9 % over the best
+// of the five on average, more than 10 % in 1157 of the 8071, and up to 59 % slower than at most two columns.)
+struct ColumnTimes {
+    int bits, G, LPR, NWK, NWR, RS;                          // the batch-1 shape
+    struct { float first, further; } us[5];                  // one column, two (two rows a wave), two, three, four (four rows a wave); zeros: never the least
+};
+constexpr ColumnTimes kColumnTimes[] = {
+    {1, 3, 16, 1, 4, 1, {{2.55f, 0.37f}, {3.06f, 0.38f}, {3.25f, 0.60f}, {3.21f, 0.86f}, {3.37f, 1.09f}}},   // 1 bit, K = 1536
+    {1, 4, 16, 1, 4, 1, {{2.54f, 0.44f}, {3.12f, 0.47f}, {3.50f, 0.73f}, {3.40f, 1.05f}, {3.56f, 1.33f}}},   // 1 bit, K = 2048
+    {1, 4, 16, 1, 2, 1, {{2.80f, 0.22f}, {3.23f, 0.45f}, {3.46f, 0.74f}, {3.43f, 1.05f}, {3.62f, 1.31f}}},   // 1 bit, K = 2048
+    {1, 3, 32, 1, 4, 2, {{2.88f, 0.53f}, {3.40f, 0.67f}, {3.71f, 1.12f}, {3.92f, 1.59f}, {3.90f, 2.16f}}},   // 1 bit, K = 3072
+    {1, 3, 32, 1, 3, 3, {{2.92f, 0.60f}, {3.32f, 0.66f}, {3.59f, 1.10f}, {3.77f, 1.59f}, {3.85f, 2.14f}}},   // 1 bit, K = 3072
+    {1, 3, 32, 1, 3, 2, {{2.90f, 0.41f}, {3.32f, 0.66f}, {3.59f, 1.10f}, {3.77f, 1.59f}, {3.85f, 2.14f}}},   // 1 bit, K = 3072
+    {1, 4, 32, 1, 4, 2, {{2.88f, 0.61f}, {3.48f, 0.81f}, {3.82f, 1.41f}, {3.85f, 2.04f}, {4.01f, 2.69f}}},   // 1 bit, K = 4096
+    {1, 3, 64, 1, 6, 2, {{2.30f, 1.24f}, {3.34f, 1.18f}, {3.87f, 2.01f}, {4.05f, 3.17f}, {4.08f, 4.34f}}},   // 1 bit, K = 6144
+    {1, 4, 64, 1, 4, 2, {{3.04f, 0.67f}, {3.48f, 1.01f}, {3.85f, 1.58f}, {4.06f, 4.04f}, {4.25f, 5.20f}}},   // 1 bit, K = 8192
+    {1, 4, 64, 1, 4, 3, {{3.33f, 0.85f}, {3.49f, 1.01f}, {4.10f, 1.48f}, {4.19f, 3.88f}, {4.19f, 5.13f}}},   // 1 bit, K = 8192
+    {2, 3, 32, 1, 4, 2, {{2.76f, 0.34f}, {2.95f, 0.43f}, {3.29f, 0.73f}, {3.37f, 1.00f}, {3.58f, 1.26f}}},   // 2 bits, K = 1536
+    {2, 4, 32, 1, 4, 2, {{2.87f, 0.40f}, {3.12f, 0.51f}, {3.53f, 0.92f}, {3.59f, 1.23f}, {3.83f, 1.55f}}},   // 2 bits, K = 2048
+    {2, 3, 64, 1, 4, 2, {{2.85f, 0.36f}, {3.14f, 0.48f}, {3.36f, 0.75f}, {3.50f, 1.01f}, {3.60f, 1.32f}}},   // 2 bits, K = 3072
+    {2, 4, 64, 1, 4, 2, {{3.00f, 0.40f}, {3.31f, 0.56f}, {3.72f, 0.92f}, {3.89f, 1.23f}, {4.09f, 1.58f}}},   // 2 bits, K = 4096
+    {2, 3, 64, 2, 3, 2, {{2.57f, 0.75f}, {3.18f, 0.61f}, {3.40f, 0.84f}, {3.35f, 2.29f}, {3.57f, 2.87f}}},   // 2 bits, K = 6144
+    {2, 4, 64, 2, 2, 4, {{3.41f, 0.82f}, {3.49f, 0.76f}, {3.80f, 1.05f}, {4.08f, 2.64f}, {4.27f, 3.28f}}},   // 2 bits, K = 8192
+    {2, 4, 64, 2, 2, 2, {{3.29f, 0.43f}, {3.21f, 0.77f}, {3.73f, 1.05f}, {4.06f, 2.61f}, {4.30f, 3.23f}}},   // 2 bits, K = 8192
+    {2, 4, 32, 7, 1, 4, {{3.03f, 1.92f}, {2.94f, 1.72f}, {3.22f, 2.49f}, {2.42f, 7.80f}, {2.24f, 9.54f}}},   // 2 bits, K = 14336
+    {2, 2, 64, 7, 1, 4, {{3.12f, 1.06f}, {2.37f, 1.48f}, {2.88f, 1.76f}, {2.37f, 5.39f}, {2.42f, 6.58f}}},   // 2 bits, K = 14336
+    {3, 3, 16, 3, 1, 2, {{3.03f, 0.34f}, {}, {3.20f, 0.38f}, {3.17f, 0.47f}, {3.23f, 0.54f}}},   // 3 bits, K = 1536
+    {3, 6, 32, 1, 4, 2, {{2.97f, 0.55f}, {3.22f, 0.66f}, {3.77f, 1.19f}, {3.85f, 1.49f}, {4.00f, 1.82f}}},   // 3 bits, K = 2048
+    {3, 3, 32, 3, 1, 4, {{3.35f, 0.46f}, {3.20f, 0.35f}, {3.40f, 0.60f}, {3.49f, 0.79f}, {3.60f, 1.02f}}},   // 3 bits, K = 3072
+    {3, 6, 64, 1, 4, 2, {{3.03f, 0.57f}, {3.31f, 0.68f}, {3.94f, 1.18f}, {4.07f, 1.48f}, {4.52f, 3.62f}}},   // 3 bits, K = 4096
+    {3, 3, 64, 3, 2, 4, {{2.89f, 1.12f}, {2.73f, 1.47f}, {3.34f, 2.20f}, {}, {}}},   // 3 bits, K = 6144
+    {3, 6, 64, 2, 2, 4, {{3.75f, 1.09f}, {3.75f, 1.38f}, {4.31f, 2.56f}, {4.52f, 3.12f}, {2.35f, 11.04f}}},   // 3 bits, K = 8192
+    {3, 6, 64, 2, 2, 2, {{3.23f, 0.60f}, {3.63f, 1.39f}, {4.16f, 2.56f}, {4.51f, 3.07f}, {2.67f, 10.67f}}},   // 3 bits, K = 8192
+    {3, 3, 64, 7, 1, 4, {{3.07f, 1.33f}, {2.52f, 1.49f}, {2.73f, 2.00f}, {2.13f, 5.79f}, {2.03f, 7.03f}}},   // 3 bits, K = 14336
+    {4, 3, 64, 1, 4, 2, {{2.74f, 0.32f}, {3.07f, 0.43f}, {3.36f, 0.62f}, {3.42f, 0.85f}, {3.67f, 1.07f}}},   // 4 bits, K = 1536
+    {4, 4, 64, 1, 4, 2, {{2.87f, 0.38f}, {3.28f, 0.51f}, {3.82f, 0.76f}, {3.91f, 1.02f}, {4.22f, 1.30f}}},   // 4 bits, K = 2048
+    {4, 3, 64, 2, 2, 2, {{2.88f, 0.34f}, {3.29f, 0.44f}, {3.47f, 0.65f}, {3.57f, 0.90f}, {3.72f, 1.17f}}},   // 4 bits, K = 3072
+    {4, 4, 64, 2, 2, 2, {{2.98f, 0.40f}, {3.47f, 0.54f}, {3.91f, 0.81f}, {4.03f, 1.10f}, {3.96f, 2.88f}}},   // 4 bits, K = 4096
+    {4, 4, 64, 3, 2, 2, {{2.57f, 0.84f}, {3.18f, 1.82f}, {3.67f, 2.60f}, {}, {}}},   // 4 bits, K = 6144
+    {4, 4, 64, 4, 1, 4, {{3.45f, 0.78f}, {3.69f, 1.18f}, {3.99f, 1.74f}, {3.83f, 2.51f}, {2.04f, 8.28f}}},   // 4 bits, K = 8192
+    {4, 4, 64, 4, 1, 2, {{3.19f, 0.42f}, {3.41f, 1.22f}, {3.99f, 1.68f}, {4.04f, 2.37f}, {2.46f, 7.83f}}},   // 4 bits, K = 8192
+    {4, 4, 64, 7, 1, 4, {{3.24f, 1.79f}, {3.52f, 1.80f}, {3.36f, 2.34f}, {2.58f, 7.03f}, {2.52f, 8.39f}}},   // 4 bits, K = 14336
+    {4, 4, 64, 7, 1, 2, {{2.73f, 1.03f}, {2.68f, 1.83f}, {3.33f, 2.29f}, {2.44f, 6.97f}, {2.45f, 8.30f}}},   // 4 bits, K = 14336
+    {3, 6, 32, 7, 1, 4, {{3.26f, 2.55f}, {2.96f, 2.01f}, {4.00f, 2.94f}, {1.87f, 10.54f}, {1.10f, 12.90f}}},   // 3 bits, K = 14336
+    {4, 4, 64, 4, 2, 4, {{2.82f, 1.85f}, {3.44f, 1.47f}, {3.90f, 2.16f}, {3.86f, 2.97f}, {1.21f, 10.07f}}},   // 4 bits, K = 8192
+};
+template <int BITS, int G, int LPR, int NWK, int NWR, int RS>
+constexpr int column_times() {
+    int i = 0;
+    for (const ColumnTimes& t : kColumnTimes) {
+        if (t.bits == BITS && t.G == G && t.LPR == LPR && t.NWK == NWK && t.NWR == NWR && t.RS == RS) return i;
+        ++i;
+    }
+    return -1;
+}
+
+template <int BITS, int G, int LPR, int NWK, int NWR1, int RS1, bool SC>
+static bool launch_columns(const GemmArgs& a, hipStream_t s) {
+    constexpr int T = column_times<BITS, G, LPR, NWK, NWR1, RS1>();
+    static_assert(T >= 0 || (BITS == 1 && SC), "no times for this shape");
+    if constexpr (T >= 0 && !(BITS == 1 && SC)) {
+        // (below that the batch is one column a workgroup's: the lines are those of launches that fill the chip)
+        if (a.N * a.K * a.M <= (int64_t(24) << 20)) return false;
+        // (the grid's row groups are padded to the eight XCDs, whose 32 CUs share theirs)
+        auto grid = [&](int rows, int columns) { return ((a.N + rows - 1) / rows + 7) / 8 * 8 * ((a.M + columns - 1) / columns); };
+        auto us = [&](int i, int64_t workgroups) { return kColumnTimes[T].us[i].first + kColumnTimes[T].us[i].further * static_cast<float>((workgroups + 255) / 256); };
+        float least = us(0, grid(NWR1 * (kWave / LPR) * RS1, 1));
+        int pick = 0;
+        auto offer = [&](auto mc, auto rsx, auto index) {
+            using S = LutColumns<BITS, G, LPR, NWK, NWR1, SC, decltype(mc)::value, decltype(rsx)::value>;
+            constexpr int i = decltype(index)::value;
+            if constexpr (S::fits && kColumnTimes[T].us[i].first > 0.f) {
+                const int64_t workgroups = grid(S::ROWS_WG, S::COLUMNS);
+                if (workgroups >= 192 && us(i, workgroups) < least) {
+                    least = us(i, workgroups);
+                    pick = i;
+                }
+            }
+        };
+        auto launch = [&](auto mc, auto rsx, auto index) {
+            using S = LutColumns<BITS, G, LPR, NWK, NWR1, SC, decltype(mc)::value, decltype(rsx)::value>;
+            if constexpr (S::fits && kColumnTimes[T].us[decltype(index)::value].first > 0.f) {
+                hipLaunchKernelGGL((gemm_lut_columns_kernel<BITS, G, LPR, NWK, NWR1, SC, decltype(mc)::value, decltype(rsx)::value>),
+                                   dim3(static_cast<unsigned>(grid(S::ROWS_WG, S::COLUMNS))), dim3(S::THREADS), 0, s,
+                                   a.W, a.codebook, a.X, a.Y, static_cast<int>(a.N), a.scales, a.M);
+            }
+        };
+        using std::integral_constant;
+        auto each = [&](auto&& f, int only) {
+            if (only < 0 || only == 1) f(integral_constant<int, 2>{}, integral_constant<int, 2>{}, integral_constant<int, 1>{});
+            if (only < 0 || only == 2) f(integral_constant<int, 2>{}, integral_constant<int, 4>{}, integral_constant<int, 2>{});
+            if (only < 0 || only == 3) f(integral_constant<int, 3>{}, integral_constant<int, 4>{}, integral_constant<int, 3>{});
+            if (only < 0 || only == 4) f(integral_constant<int, 4>{}, integral_constant<int, 4>{}, integral_constant<int, 4>{});
+        };
+        each(offer, -1);
+#ifdef KMQ_TUNING
+        if (const char* const v = std::getenv("KMQ_LUT_MC")) pick = v[0] - '0';      // 0..4, an index of us[]
+#endif
+        if (pick > 0) each(launch, pick);
+        return pick > 0;
     }
     return false;
 }
 
-// The most columns and rows a wave that still give the chip its work: at least 192 workgroups, and for four columns and four rows a
-// wave eight waves a CU (a lone group of three columns: four), else two columns and four rows with eight, else two and two with six
-// (1 bit: eight, and no group with a column that the batch does not have), else one column.  Measured (us), one column a workgroup / two
-// and two / two and four / four and four:
-//   2-bit 14336 x 4096, batch 4: 14.3 / 11.3 / 11.2 / 10.4, batch 16: 49.0 / 38.1 / 33.4 / 27.8; 4096 x 14336, batch 4: 20.4 / 18.6 /
-//   13.5 / 12.2; 2048 x 6144 (four waves a CU with four columns): 6.7 / 5.3 / 4.7 / 5.9; 2048 x 2048, batch 8: 4.0 / 3.7 / 4.1 / 4.8;
-//   3-bit 4096 x 14336, batch 4: 25.0 / 27.7 / 20.7 / 17.0; 4-bit 4096 x 4096: 9.0 / 7.8 / 7.0 / 6.6; 1-bit 8192 x 8192: 13.8 / 11.2 /
-//   10.4 / 9.2, 3072 x 8192, batch 2: 4.6 / 5.1 / 5.1 / -.
-template <int BITS, int G, int LPR, int NWK, int NWR1, bool SC>
-static bool launch_columns(const GemmArgs& a, hipStream_t s) {
-#ifdef KMQ_TUNING
-    if (const char* const v = std::getenv("KMQ_LUT_MC")) {
-        switch (v[0]) {
-            case '2': return launch_columns_of<BITS, G, LPR, NWK, NWR1, SC, 2, 2>(a, 0, s);
-            case '5': return launch_columns_of<BITS, G, LPR, NWK, NWR1, SC, 2, 4>(a, 0, s);
-            case '3': return launch_columns_of<BITS, G, LPR, NWK, NWR1, SC, 3, 4>(a, 0, s);
-            case '4': return launch_columns_of<BITS, G, LPR, NWK, NWR1, SC, 4, 4>(a, 0, s);
-            case '1': return false;
-        }
-    }
-#endif
-    if (a.N * a.K * a.M <= (int64_t(24) << 20)) return false;
-    const int cgroups = (a.M + 3) / 4, mc = (a.M + cgroups - 1) / cgroups;
-    if (mc == 4 && launch_columns_of<BITS, G, LPR, NWK, NWR1, SC, 4, 4>(a, 8, s)) return true;
-    if (mc == 3 && launch_columns_of<BITS, G, LPR, NWK, NWR1, SC, 3, 4>(a, a.M == 3 && BITS > 1 ? 4 : 8, s)) return true;
-    if (BITS == 1 && a.M % 2) return false;
-    return launch_columns_of<BITS, G, LPR, NWK, NWR1, SC, 2, 4>(a, 8, s) || launch_columns_of<BITS, G, LPR, NWK, NWR1, SC, 2, 2>(a, BITS == 1 ? 8 : 6, s);
-}
-
 static bool (*const kLutColumns[])(const GemmArgs&, hipStream_t) = {
-#define KMQ_ROW(BITS, G, LPR, NWK, NWR, RS, WPE) &launch_columns<BITS, G, LPR, NWK, NWR, false>,
-#define KMQ_SC(BITS, G, LPR, NWK, NWR, RS, WPE) &launch_columns<BITS, G, LPR, NWK, NWR, true>,
+#define KMQ_ROW(BITS, G, LPR, NWK, NWR, RS, WPE) &launch_columns<BITS, G, LPR, NWK, NWR, RS, false>,
+#define KMQ_SC(BITS, G, LPR, NWK, NWR, RS, WPE) &launch_columns<BITS, G, LPR, NWK, NWR, RS, true>,
     KMQ_LUT_SHAPES(KMQ_ROW, KMQ_SC)
 #undef KMQ_ROW
 #undef KMQ_SC

@@ -17,14 +17,16 @@ def gpu():
 
 
 @pytest.mark.parametrize("bits,K,N,M", [
-    (1, 1536, 8193, 2), (1, 1536, 8193, 5), (1, 2048, 8193, 2), (1, 2048, 8193, 5), (1, 2048, 4095, 4), (1, 2048, 4095, 8), (1, 2048, 4095, 14), (1, 2048, 8161, 5),
-    (1, 3072, 8193, 2), (1, 3072, 8193, 4), (1, 3072, 4095, 4), (1, 3072, 4095, 8), (1, 3072, 4095, 14), (1, 3072, 8161, 5), (1, 4096, 4095, 4), (1, 4096, 4095, 8),
-    (1, 6144, 4095, 2), (1, 6144, 4095, 4), (1, 8192, 4095, 2), (1, 8192, 4095, 4), (1, 8192, 8193, 6),
-    (2, 1536, 4095, 7), (2, 1536, 8193, 5), (2, 1536, 4095, 14), (2, 2048, 4095, 7), (2, 3072, 2801, 3), (2, 3072, 2801, 5), (2, 4096, 2801, 5),
-    (2, 6144, 2049, 3), (2, 8192, 301, 11), (2, 8192, 2049, 3), (2, 14336, 601, 3), (2, 14336, 801, 5), (2, 14336, 801, 7), (2, 14336, 1201, 2), (2, 14336, 1201, 3),
-    (3, 2048, 4097, 3), (3, 2048, 4095, 7), (3, 3072, 1201, 7), (3, 3072, 2049, 5), (3, 4096, 2801, 5), (3, 6144, 2049, 2), (3, 6144, 601, 7), (3, 6144, 1801, 3),
-    (3, 14336, 601, 3),
-    (4, 2048, 1801, 7), (4, 2048, 2801, 5), (4, 2048, 4095, 5), (4, 2048, 2801, 10), (4, 4096, 1501, 5), (4, 6144, 601, 7), (4, 8192, 1201, 3), (4, 14336, 601, 3)])
+    (1, 1536, 4121, 11), (1, 2048, 1265, 13), (1, 2048, 1769, 13), (1, 2048, 2909, 9), (1, 2048, 4095, 4), (1, 2048, 4095, 8), (1, 2048, 8161, 5),
+    (1, 3072, 4095, 4), (1, 3072, 4095, 8), (1, 3072, 8193, 2), (1, 3072, 10989, 5), (1, 3072, 10989, 7), (1, 3072, 12605, 11), (1, 4096, 7353, 7), (1, 6144, 2049, 11),
+    (1, 6144, 4095, 2), (1, 6144, 8565, 5), (1, 8192, 929, 11), (1, 8192, 2049, 8), (1, 8192, 2049, 11),
+    (2, 1536, 5737, 7), (2, 1536, 6949, 5), (2, 1536, 7353, 7), (2, 2048, 12605, 5), (2, 3072, 2049, 11), (2, 3072, 2801, 3), (2, 6144, 929, 5), (2, 6144, 1041, 7),
+    (2, 6144, 1545, 7), (2, 8192, 301, 11), (2, 8192, 817, 10), (2, 8192, 1545, 7), (2, 14336, 313, 13), (2, 14336, 801, 7), (2, 14336, 1201, 2),
+    (2, 14336, 1545, 3),
+    (3, 2048, 12605, 5), (3, 3072, 1201, 7), (3, 3072, 1377, 7), (3, 4096, 3717, 7), (3, 4096, 6545, 5), (3, 6144, 1801, 3), (3, 6144, 2049, 2), (3, 8192, 1041, 7),
+    (3, 8192, 2049, 11), (3, 8192, 2909, 7),
+    (4, 1536, 2049, 11), (4, 2048, 1801, 7), (4, 2048, 2049, 11), (4, 2048, 2909, 7), (4, 2048, 4095, 5), (4, 3072, 1545, 7), (4, 4096, 1501, 5),
+    (4, 4096, 1545, 7), (4, 6144, 1321, 5), (4, 8192, 705, 7), (4, 8192, 1545, 7)])
 def test_columns_equal_batch_1(gpu, bits, K, N, M):
     seed = 43 * bits + K + M
     idx, cb = synth.make_indices(seed, 0, N, K, bits), synth.make_codebook(seed, 0, N, bits, symmetric=(bits == 1))
@@ -39,13 +41,12 @@ def test_columns_equal_batch_1(gpu, bits, K, N, M):
 
 
 @pytest.mark.parametrize("bits,K,N,M", [
-    (2, 2048, 16385, 2), (2, 4096, 2049, 3), (2, 4096, 1801, 9), (2, 8192, 301, 11), (2, 8192, 2049, 3), (2, 8192, 2049, 5), (2, 8192, 3201, 3), (2, 8192, 1009, 13),
-    (2, 14336, 301, 6), (2, 14336, 601, 3), (2, 14336, 801, 5), (2, 14336, 801, 7), (2, 14336, 801, 16), (2, 14336, 1001, 9), (2, 14336, 1201, 2), (2, 14336, 1201, 3),
-    (2, 14336, 1801, 5), (2, 14336, 1201, 10),
-    (3, 2048, 1801, 7), (3, 2048, 16385, 2), (3, 4096, 2049, 3), (3, 4096, 8193, 2), (3, 8192, 301, 11), (3, 8192, 2049, 3), (3, 8192, 2049, 5),
-    (3, 14336, 1201, 3), (3, 14336, 1801, 5), (3, 14336, 801, 14), (3, 14336, 801, 15),
-    (4, 2048, 1801, 7), (4, 2048, 2801, 5), (4, 4096, 1501, 5), (4, 4096, 2049, 5), (4, 4096, 1009, 13), (4, 8192, 301, 11), (4, 8192, 1201, 3), (4, 8192, 1201, 5),
-    (4, 8192, 1801, 2), (4, 8192, 3601, 2), (4, 8192, 1801, 5), (4, 8192, 753, 13), (4, 14336, 601, 3), (4, 14336, 801, 5), (4, 14336, 801, 7), (4, 14336, 1801, 4)])
+    (2, 4096, 1801, 9), (2, 4096, 3717, 3), (2, 4096, 10585, 2), (2, 8192, 301, 11), (2, 8192, 1009, 13), (2, 8192, 2049, 5), (2, 8192, 3201, 3),
+    (2, 14336, 301, 6), (2, 14336, 313, 13), (2, 14336, 801, 7), (2, 14336, 1041, 11), (2, 14336, 1201, 2), (2, 14336, 1201, 10), (2, 14336, 1801, 5),
+    (3, 2048, 1801, 7), (3, 4096, 3313, 3), (3, 4096, 8193, 2), (3, 4096, 20479, 2), (3, 8192, 301, 11), (3, 8192, 1041, 7), (3, 8192, 10585, 2),
+    (3, 14336, 761, 3), (3, 14336, 1545, 7), (3, 14336, 1801, 5),
+    (4, 2048, 1801, 7), (4, 2048, 10585, 2), (4, 4096, 1009, 13), (4, 4096, 1501, 5), (4, 4096, 1713, 5), (4, 8192, 301, 11), (4, 8192, 705, 7), (4, 8192, 753, 13),
+    (4, 8192, 1801, 2), (4, 8192, 1801, 5), (4, 14336, 801, 5), (4, 14336, 801, 7)])
 def test_scaled_columns_equal_batch_1(gpu, bits, K, N, M):
     seed = 47 * bits + K + M
     p = oracle.pack(synth.make_indices(seed, 0, N, K, bits), bits)
