@@ -82,6 +82,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
     if (K % TC != 0 && wave == whole % NW) {
 #pragma unroll 1
         for (int h = 0; h < H; ++h) {
+            if (whole * TC + h * 64 >= K) break;             // (the same for every lane; looking up zeros up to column 256 all the same: 2048 x 64, batch 1: 5.0 us, now 3.2; 1030 x 320: 5.0, 3.4)
             const int k0 = whole * TC + h * 64 + q * 16, live = K - k0;
             u32x4_t wv = {0, 0, 0, 0}, xv[2] = {wv, wv};
             if (live >= 16) {
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
 // Where 16 rows a workgroup are the faster ones.  With few rows its workgroups leave CUs idle that a wave per row fills: a lone column
 // pays until there are more than 1024 of them (us, a wave per row / this: 256 x 4096 5.7 / 6.9, 512 x 8192 9.7 / 10.4, 1024 x 4096 6.9 / 7.1, 1500 x
 // 4096 8.5 / 7.2), two until 512 (256 x 4096 6.4 / 6.9; 512 x 8192 11.5 / 10.3); three on and rows that no 16-byte load divides never
-// (256 x 4096, batch 4: 7.8 / 6.9; 256 x 1025, batch 1: 6.3 / 5.8).  Fewer than 256 rows, too little to matter, stay where they were.
+// (256 x 4096, batch 4: 7.8 / 6.9; 256 x 1025, batch 1: 6.3 / 4.2).  Fewer than 256 rows, too little to matter, stay where they were.
 bool mfma_b8_takes(int64_t N, int64_t K, int M) {
     return N >= 256 && (M >= 3 || K % 8 != 0 || (M == 2 ? N >= 512 : N > 1024));
 }

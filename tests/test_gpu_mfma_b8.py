@@ -21,7 +21,7 @@ def _codebook(seed, N):
 
 
 @pytest.mark.parametrize("N", (1040, 1025, 1039))
-@pytest.mark.parametrize("K", (1, 15, 16, 17, 63, 65, 255, 256, 257, 1023, 1281, 2048 + 77, 4096, 4097))
+@pytest.mark.parametrize("K", (1, 15, 16, 17, 63, 64, 65, 128, 129, 191, 255, 256, 257, 320, 321, 1023, 1281, 2048 + 77, 4096, 4097))
 @pytest.mark.parametrize("M", (1, 5, 16))
 def test_edges(gpu, N, K, M):
     idx, cb, X = synth.make_indices(84, K, N, K, BITS), _codebook(84 + K, N), synth.make_x(84, K, M, K)
