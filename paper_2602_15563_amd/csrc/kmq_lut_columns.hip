@@ -460,12 +460,14 @@ static bool launch_columns(const GemmArgs& a, hipStream_t s) {
                 }
             }
         };
+        bool launched = false;
         auto launch = [&](auto mc, auto rsx, auto index) {
             using S = LutColumns<BITS, G, LPR, NWK, NWR1, SC, decltype(mc)::value, decltype(rsx)::value>;
             if constexpr (S::fits && kColumnTimes[T].us[decltype(index)::value].first > 0.f) {
                 hipLaunchKernelGGL((gemm_lut_columns_kernel<BITS, G, LPR, NWK, NWR1, SC, decltype(mc)::value, decltype(rsx)::value>),
                                    dim3(static_cast<unsigned>(grid(S::ROWS_WG, S::COLUMNS))), dim3(S::THREADS), 0, s,
                                    a.W, a.codebook, a.X, a.Y, static_cast<int>(a.N), a.scales, a.M);
+                launched = true;
             }
         };
         using std::integral_constant;
@@ -480,7 +482,7 @@ static bool launch_columns(const GemmArgs& a, hipStream_t s) {
         if (const char* const v = std::getenv("KMQ_LUT_MC")) pick = v[0] - '0';      // 0..4, an index of us[]
 #endif
         if (pick > 0) each(launch, pick);
-        return pick > 0;
+        return launched;
     }
     return false;
 }
