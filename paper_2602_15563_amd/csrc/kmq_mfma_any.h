@@ -613,23 +613,31 @@ static void canon_launch(const GemmArgs& a, hipStream_t s) {
                        a.W, a.codebook, a.X, a.Y, a.N, a.K, a.M, a.scales);
 }
 
-// Launch shape, measured (us) over both layouts and formats at batch 1..16:
+// Launch shape, measured (us) over both layouts and formats at batch 1..16 (420 drawn shapes, each with five shapes of launch):
 //   few row blocks (at most one a CU): eight waves, sixteen for long rows (2-bit 2773 x 14592 tiled, batch 1: 6.7 with sixteen, 7.5
-//     with eight, 8.0 with four; 3-bit 2048 x 4864: 4.2 with either); four for rows of at most four tiles;
+//     with eight, 8.0 with four), at batches up to 4 and at 4 bits already from 14 tiles on (17 at batches above 8; 3-bit 2419 x 6016, batch 3: 5.4 with
+//     eight, 4.8 with sixteen; 4-bit 4032 x 4224, batch 10: 9.6 and 8.6; but 1-bit 2368 x 7104, batch 15: 7.9 and 8.9); four for rows of at most
+//     four tiles;
 //   one to two a CU: the same, and from batch 5 on two row blocks a workgroup, so that X is read half as often and no CU has
 //     twice the work of another (3-bit scaled 7424 x 8064, batch 11: 13.4 against 15.6; 7650 x 14336, batch 6: 15.4 against
 //     18.4; at batch 6 short rows keep one: 6976 x 3136 9.3 against 10.5);
-//   more: two row blocks and eight waves (3-bit scaled 15616 x 10880, batch 1: 21.2 against 21.7), but rows of up to 16 tiles,
-//     which eight waves do not share evenly, one block and four (4-bit 10496 x 2496, batch 9: 14.9 against 23.5).
+//   more: two row blocks and eight waves where that leaves the busiest CU no more row blocks than one a workgroup would (3-bit scaled 15616 x
+//     10880, batch 1: 21.2 against 21.7; 2-bit 12480 x 6804, batch 16: 16.8 against 20.4); where the busiest CU's share is odd, and for rows of up to
+//     16 tiles, which eight waves do not share evenly, one block and four (but 2-bit 18112 x 5376, batch 11: 17.0 against 15.1; 4-bit 10496 x 2496, batch 9: 14.9 against 23.5; 4-bit
+//     scaled 8256 x 4480, batch 6, three blocks a CU instead of four: 12.5 against 18.4), or eight if that share is three and the batch at
+//     most 4 (3-bit 8635 x 5475, batch 1: 9.9, 10.1 with four, 12.3).
 // Neither pipe binds: vector issue is 32 % and LDS 8 % of the busy time at 3-bit 5001 x 4101, batch 3, and 40 % and 28 % at 1-bit scaled 8192 x 8192,
 // batch 8 (two waves a SIMD); the waves wait for memory.  Two or four tiles in flight per wave instead of one were no faster anywhere all the
 // same (1 to 10 % slower at batch 1, 10 to 20 % above).  Not among the shapes measured: a wave count fitted to the tiles (17 tiles on eight waves
-// are three for one and two for the others), sixteen waves for two row blocks, the last piece's words requested with the last whole tile's.
+// are three for one and two for the others).  Sixteen waves for two row blocks: 18 % slower on the average.  The last piece taken first, its operands asked for
+// at the start, or with the last whole tile's: 3 to 4 % slower at 3-bit 5001 x 4101, batch 3 (words one by one, ahead of everybody else's first tile).  Words through LDS,
+// so that four neighbouring lanes load 64 bytes of a row: 3 to 12 % slower.
 template <int BITS, bool SC, bool TILED, int MR>
 static void canon_shape(const GemmArgs& a, hipStream_t s) {
     const int64_t tiles = (a.K + kCanonTile - 1) / kCanonTile, nrb = (a.N + 15) / 16;
+    const int64_t share = (nrb + 255) / 256;              // row blocks of the busiest CU
     if (nrb <= 256) {
-        if (tiles >= 40) canon_launch<BITS, SC, TILED, MR, 1, 16>(a, s);
+        if (tiles >= 40 || (tiles >= 14 && MR == 1) || (BITS == 4 && tiles >= (MR == 4 ? 17 : 14))) canon_launch<BITS, SC, TILED, MR, 1, 16>(a, s);
         else if (tiles > 4) canon_launch<BITS, SC, TILED, MR, 1, 8>(a, s);
         else canon_launch<BITS, SC, TILED, MR, 1, 4>(a, s);
     } else if (nrb <= 512) {
@@ -637,7 +645,8 @@ static void canon_shape(const GemmArgs& a, hipStream_t s) {
         else if (tiles > 4) canon_launch<BITS, SC, TILED, MR, 1, 8>(a, s);
         else canon_launch<BITS, SC, TILED, MR, 1, 4>(a, s);
     } else {
-        if (tiles > 16) canon_launch<BITS, SC, TILED, MR, 2, 8>(a, s);
+        if (tiles > 16 && (share % 2 == 0 || (BITS == 2 && !SC && MR == 4))) canon_launch<BITS, SC, TILED, MR, 2, 8>(a, s);
+        else if (tiles > 16 && MR == 1 && share == 3) canon_launch<BITS, SC, TILED, MR, 1, 8>(a, s);
         else canon_launch<BITS, SC, TILED, MR, 1, 4>(a, s);
     }
 }
