@@ -21,6 +21,7 @@
 // Compiled with floating-point contraction off: the arithmetic is specified operation by
 // operation.
 #include <cstddef>
+#include <type_traits>
 
 #include "kmq_device.h"
 #include "kmq_launch.h"
@@ -1048,42 +1049,45 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __re
 //   scales   largest magnitude of every block; blocks counted per scale mantissa
 //   group    block numbers sorted by scale mantissa (kept in the output's index words until those are written)
 //   count    a workgroup takes a run of that list, counts its elements in LDS and adds the counts to the tensor's
-//   prefix   per scale mantissa: number and sum of the members below every value
-//   rounds   one workgroup, all rounds: per (boundary, scale mantissa) one look-up in the prefix arrays
+//   sort     the counters into the ascending order of their quotients, which is the same for every tensor; number and sum of the
+//            members below every sixteenth
+//   rounds   one workgroup, all rounds: per boundary its place in that order, and one look-up there
 //   assign   every element against its scale mantissa's boundaries, as 16-bit integers
-// A sum over members of one scale mantissa is a sum of weights (integers in the window's unit: exact) times the
-// reciprocal of the scale's mantissa.  A boundary b stands for the exact test fl(w / scale) > b: where b * scale comes
+// Quotients are added up as integers (a counter times its quotient's 57 leading bits), so that a cluster's sum, the difference of
+// what lies below two boundaries, does not depend on what else lies below.  A boundary b stands for the exact test fl(w / scale) > b: where b * scale comes
 // within a few units in the last place of a weight, the division itself decides.
 // Infinities and NaNs count as the magnitudes that their patterns continue (in range everywhere); the codebook says NaN then.
 // Elements more than 31 octaves below their scale ("far", next to none in most trained tensors) are counted apart per sign, and
 // their sums taken from the tensor (below).
 //
-// 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits, one tensor again and again: 127 / 147 / 163 / 198 us (a new one each time, 4 bits: 205; 8519 / 9344 / 10727 / 13475 with every element
-// divided by its scale and compared with every boundary in fp64, each round); 1024 x 1024, 4 bits: 121 (3570).  At 8192 x 8192
-// and 4 bits: clear 5, scales 21 (6.5 TB/s), group 13, count 34 (blocks gathered 128 bytes at a time, LDS atomics, 16 for the adding up), prefix 9,
-// rounds 78 (3 us each: one CU's issue and its scattered line fetches), assign 45 us (vector issue).
-constexpr int kQuantMants = 128, kQuantBins = 2 * kHistMags, kQuantStride = kQuantBins + 1;
+// 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits, a new tensor each time: 136 / 146 / 154 / 168 us (142 / 154 / 171 / 206 with a look-up per boundary and scale
+// mantissa in every round; 8519 / 9344 / 10727 / 13475 with every element divided by its scale and compared with every boundary in fp64, each round);
+// 1024 x 1024, 4 bits: 86 (120; 3570).  At 8192 x 8192 and 4 bits: clear 5, scales 21 (6.5 TB/s), group 13, count 32 (blocks gathered 128 bytes at a time,
+// LDS atomics, 14 for the adding up), sort 9, rounds 44 (1.5 us each, a chain of latencies of one wave a SIMD; 78 before), assign 45 us (vector issue).
+constexpr int kQuantMants = 128;
 constexpr double kFar = 4.656612873077393e-10;           // 2^-31: no far element reaches it
 
-// What lies below a bin: 40 bits of members (at most 2^38) above 88 bits of their sum, in units of 2^-31 / (128 + scale mantissa)
-// (at most 2^38 members of 2^39 units).  Integers, so that a cluster's sum, the difference of two of them, is exact however
-// much lies below it.
-struct BelowBin {
-    unsigned long long lo, hi;
+// The order of the quotients.  A weight's mantissa a and the scale's s (both 128..255) give a quotient f = a / s where a >= s, else 2a / s,
+// times a power of two: every octave of quotients holds each of the 16384 pairs once, in an order that f alone decides (two
+// different fractions are far more than an fp64 rounding apart; equal ones follow each other by s).  A place in it is
+// octave * 16384 + rank; pairs that the window does not hold (a >= s in octave 0, a < s in the last one) are counters that
+// stay zero.  One order per sign, from small magnitudes to large ones.
+constexpr int kOctaves = kHistOctaves + 1, kPairs = kQuantMants * 128, kPlaces = kOctaves * kPairs, kRun = 16, kParts = 4096;
+constexpr int kSortThreads = 256, kStretch = kSortThreads * kRun, kStretches = kPlaces / kStretch;      // places of a workgroup of the sorting step
+// Sums are integers in units of 2^-56 of the octave's lowest quotient: 57 bits of quotient, at most 2^38 members.
+struct Below {                                           // members of a stretch below a run of kRun places (or of a whole stretch): number and sum
+    unsigned long long n, lo, hi;
 };
 typedef __int128 int128_t;
-__device__ __forceinline__ BelowBin below_bin(long long count, int128_t sum) {
-    return BelowBin{static_cast<unsigned long long>(sum), static_cast<unsigned long long>(count) << 24 | (static_cast<unsigned long long>(sum >> 64) & 0xFFFFFFu)};
-}
-__device__ __forceinline__ double below_count(unsigned long long hi) { return static_cast<double>(hi >> 24); }
-__device__ __forceinline__ int128_t below_sum(unsigned long long lo, unsigned long long hi) {
-    return static_cast<int128_t>(static_cast<long long>(hi << 40) >> 40) << 64 | lo;
-}
-__device__ __forceinline__ double sum_to_f64(int128_t v) {   // |v| < 2^88: the high part is exact
-    const unsigned __int128 m = v < 0 ? -static_cast<unsigned __int128>(v) : static_cast<unsigned __int128>(v);
+typedef unsigned __int128 uint128_t;
+__device__ __forceinline__ double sum_to_f64(int128_t v) {
+    const uint128_t m = v < 0 ? -static_cast<uint128_t>(v) : static_cast<uint128_t>(v);
     const double d = static_cast<double>(static_cast<unsigned long long>(m >> 64)) * 18446744073709551616.0 + static_cast<double>(static_cast<unsigned long long>(m));
     return v < 0 ? -d : d;
 }
+// 2^63 / s, and from that the 57 bits of a pair's quotient
+__device__ __forceinline__ unsigned long long reciprocal(uint32_t s) { return ((1ull << 63) + s / 2) / s; }
+__device__ __forceinline__ unsigned long long quotient_bits(uint32_t a, uint32_t s, unsigned long long recip) { return ((a < s ? 2 * a : a) * recip) >> 7; }
 constexpr int kFarChunks = 512, kBlockCounters = 16;
 struct FarPart {
     double sum;
@@ -1096,27 +1100,70 @@ struct FarScratch {                                      // starts as zeros
     double bounds[16];                                   // of the present search: changed only when all its pieces are done
 };
 struct QuantScratch {                                    // layout of the caller's workspace; everything down to `members` starts as zeros
+    // (narrow: to its first half)
     FarScratch far;
     unsigned long long cursor[kQuantMants];              // blocks of a scale mantissa placed so far
     unsigned long long zeros, far_neg, far_pos;
     uint32_t exact_assign;                               // a stored boundary lies among the far elements
     uint32_t nonfinite;                                  // a weight is an infinity or a NaN
-    unsigned long long members[kQuantMants][kQuantBins];
     union {                                              // (until the rounds begin, when nobody asks for the blocks any more)
         FarPart far_part[kFarChunks][16];
         // blocks per scale mantissa, starting as zeros: a workgroup adds to one of sixteen (all to one: 33 us instead of 20 at 8192 x 8192)
         unsigned long long blocks[kBlockCounters][kQuantMants];
     };
-    BelowBin below[kQuantMants][kQuantStride];           // (side by side: a round's look-ups are scattered, a line each)
+    // per sign, scale mantissa and window position; narrow: both signs in one, the positive ones in the low half
+    unsigned long long members[2][kQuantMants][kHistMags];
+    Below total[2][kStretches];                          // per sign and stretch
+    Below base[2][kPlaces / kRun];
+    unsigned long long sorted[2][kPlaces];               // members per place; narrow: 32 bits each
+    uint16_t order[kPairs];                              // rank -> scale's mantissa << 7 | weight's mantissa
+    uint16_t part_start[kParts];                         // first rank of every part of an octave: of 1 + part / kParts or above (behind `order`: copied together)
     uint32_t above[kQuantMants][16];                     // per stored boundary: largest element key at or below it, in both halves
 };
 
-constexpr size_t kClearAll = (offsetof(QuantScratch, blocks) + sizeof(QuantScratch::blocks)) / 16, kClearSmall = offsetof(QuantScratch, members) / 16;
+constexpr size_t kClearAll = (offsetof(QuantScratch, members) + sizeof(QuantScratch::members)) / 16, kClearNarrow = (offsetof(QuantScratch, members) + sizeof(QuantScratch::members) / 2) / 16,
+                 kClearSmall = offsetof(QuantScratch, far_part) / 16;
+// Tensors below this size are "narrow": a counter holds both signs, places are 32 bits wide, and sums of a look's members, times the halves of a
+// quotient, 64.  (The copies of
+// a 4096 x 4096 tensor that make 2^28 elements take the wide path; 8192 x 8192, 4 bits, narrow instead of wide: count 36 -> 32 us.)
+constexpr int64_t kNarrowElements = int64_t(1) << 28;
 __global__ __launch_bounds__(256) void bs_clear_kernel(QuantScratch* q, size_t n16) {
     typedef u32x4_t __attribute__((aligned(8))) u32x4_a8_t;
     static_assert(alignof(QuantScratch) == 8 && offsetof(QuantScratch, far_part) % 16 == 0 && offsetof(QuantScratch, members) % 16 == 0, "cleared in 16-byte pieces");
     for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < n16; i += static_cast<size_t>(gridDim.x) * 256)
         reinterpret_cast<u32x4_a8_t*>(q)[i] = u32x4_t{0, 0, 0, 0};
+}
+
+// The order of the quotients, eight lanes a pair, and the parts' first ranks, eight lanes a part: pairs whose quotient lies below p / q
+// (1 <= p / q < 2; of equal ones those of a scale mantissa below s), for sixteen scale mantissas t from `first` on, from p * t / q, which is
+// carried from t to t + 1.
+__device__ __forceinline__ uint32_t pairs_before(uint32_t p, uint32_t q, int s, int first) {
+    int quo = static_cast<int>(p * first / q), rem = static_cast<int>(p * first % q), before = 0;
+#pragma unroll 4
+    for (int t = first; t < first + 16; ++t) {
+        const bool whole = rem == 0, even = (quo & 1) == 0;
+        const int below1 = quo - (whole ? 1 : 0), below2 = (quo >> 1) - (whole && even ? 1 : 0);      // largest a with a / t, with 2a / t under p / q
+        const int n1 = (below1 < 255 ? below1 : 255) - t + 1, n2 = (below2 < t - 1 ? below2 : t - 1) - 127;
+        before += (n1 > 0 ? n1 : 0) + (n2 > 0 ? n2 : 0);
+        if (t < s && whole) before += (quo >= t && quo <= 255 ? 1 : 0) + (even && quo >= 256 && quo < 2 * t ? 1 : 0);
+        ++quo;
+        rem += static_cast<int>(p - q);
+        if (rem >= static_cast<int>(q)) { rem -= static_cast<int>(q); ++quo; }
+    }
+    return lanes_sum<8>(static_cast<uint32_t>(before));
+}
+constexpr int kOrderGroups = (kPairs + kParts) * 8 / 256;      // workgroups of 256 lanes
+__device__ __forceinline__ void bs_order(QuantScratch* q, int group) {
+    const int i = (group * 256 + static_cast<int>(threadIdx.x)) >> 3, first = 128 + 16 * (threadIdx.x & 7);
+    if (i < kPairs) {                                     // (whole workgroups)
+        const int a = 128 + (i & 127), s = 128 + (i >> 7);
+        const uint32_t rank = pairs_before(a >= s ? a : 2 * a, s, s, first);
+        if ((threadIdx.x & 7) == 0) q->order[rank] = static_cast<uint16_t>(i);
+    } else {
+        const int part = i - kPairs;
+        const uint32_t rank = pairs_before(kParts + part, kParts, 0, first);
+        if ((threadIdx.x & 7) == 0) q->part_start[part] = static_cast<uint16_t>(rank < kPairs ? rank : kPairs - 1);      // (none at or above the last parts)
+    }
 }
 
 // Scales below 2^-95 put part of the window into bf16's subnormal range, where patterns are not spaced by exponents:
@@ -1151,14 +1198,20 @@ __device__ __forceinline__ uint32_t block_scale(const u32x4_t& v) {
 
 constexpr int kScaleTurn = 128;                          // blocks per workgroup and turn
 __global__ __launch_bounds__(256) void bs_scales_kernel(const uint16_t* __restrict__ W, int64_t nblocks,
-                                                        uint16_t* __restrict__ scales, QuantScratch* q) {
+                                                        uint16_t* __restrict__ scales, int orders, QuantScratch* q) {
+    // (the last workgroups make the order of the quotients: the others wait for memory meanwhile)
+    const int group = blockIdx.x, groups = gridDim.x - orders;
+    if (group >= groups) {
+        bs_order(q, group - groups);
+        return;
+    }
     __shared__ uint32_t cnt[kQuantMants];
     if (threadIdx.x < kQuantMants) cnt[threadIdx.x] = 0;
     __syncthreads();
     // eight lanes per block, kScaleTurn / 32 blocks in flight per lane
     constexpr int U = kScaleTurn / 32;
-    const int64_t step = static_cast<int64_t>(gridDim.x) * kScaleTurn;
-    for (int64_t b0 = static_cast<int64_t>(blockIdx.x) * kScaleTurn + (threadIdx.x >> 3); b0 < nblocks; b0 += step) {
+    const int64_t step = static_cast<int64_t>(groups) * kScaleTurn;
+    for (int64_t b0 = static_cast<int64_t>(group) * kScaleTurn + (threadIdx.x >> 3); b0 < nblocks; b0 += step) {
         u32x4_t v[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
@@ -1176,7 +1229,7 @@ __global__ __launch_bounds__(256) void bs_scales_kernel(const uint16_t* __restri
         }
     }
     __syncthreads();
-    if (threadIdx.x < kQuantMants && cnt[threadIdx.x]) atomicAdd(&q->blocks[blockIdx.x % kBlockCounters][threadIdx.x], static_cast<unsigned long long>(cnt[threadIdx.x]));
+    if (threadIdx.x < kQuantMants && cnt[threadIdx.x]) atomicAdd(&q->blocks[group % kBlockCounters][threadIdx.x], static_cast<unsigned long long>(cnt[threadIdx.x]));
 }
 
 // First list position of every scale mantissa's blocks (start[128]: their number); by the workgroup's first wave,
@@ -1228,9 +1281,9 @@ __global__ __launch_bounds__(kGroupThreads) void bs_group_kernel(const uint16_t*
 // Every workgroup counts the elements of its run of the block list, in LDS: cell 2 * magnitude key + sign.
 constexpr int kCountThreads = 1024, kCountCells = 2 * (kHistMags + 2);
 __global__ __launch_bounds__(kCountThreads) void bs_count_kernel(const uint16_t* __restrict__ W, const uint32_t* __restrict__ list,
-                                                                 int64_t nblocks, int64_t run, QuantScratch* q) {
+                                                                 int64_t nblocks, int64_t run, bool narrow, QuantScratch* q) {
     __shared__ long long start[kQuantMants + 1];
-    __shared__ uint32_t cell[kCountCells];
+    __shared__ alignas(8) uint32_t cell[kCountCells];
     const int tid = threadIdx.x;
     list_starts(q, start);
     for (int i = tid; i < kCountCells; i += kCountThreads) cell[i] = 0;
@@ -1270,71 +1323,111 @@ __global__ __launch_bounds__(kCountThreads) void bs_count_kernel(const uint16_t*
             }
         }
         __syncthreads();
-        for (int i = tid; i < kCountCells; i += kCountThreads) {
-            const int sign = i >= kCountCells / 2, key = i - sign * (kCountCells / 2);      // neighbouring threads, neighbouring counters
-            const unsigned long long c = cell[2 * key + sign];
-            if (c == 0) continue;
-            cell[2 * key + sign] = 0;
-            unsigned long long* const to = key >= 2 ? &q->members[mant][sign ? kHistMags - 1 - (key - 2) : kHistMags + (key - 2)]
-                                         : key == 1 ? (sign ? &q->far_neg : &q->far_pos) : &q->zeros;
-            atomicAdd(to, c);
+        for (int key = tid; key < kCountCells / 2; key += kCountThreads) {
+            u32x2_t* const at = reinterpret_cast<u32x2_t*>(cell) + key;      // positive ones, negative ones
+            const u32x2_t c = *at;
+            if ((c[0] | c[1]) == 0) continue;
+            *at = u32x2_t{0, 0};
+            const unsigned long long pos = c[0], neg = c[1];
+            if (key < 2) {
+                if (key == 0) {
+                    atomicAdd(&q->zeros, pos + neg);
+                } else {
+                    if (pos) atomicAdd(&q->far_pos, pos);
+                    if (neg) atomicAdd(&q->far_neg, neg);
+                }
+            } else if (narrow) {                          // one addition for both signs: 32 us instead of 36
+                atomicAdd(&q->members[0][mant][key - 2], neg << 32 | pos);
+            } else {
+                if (pos) atomicAdd(&q->members[0][mant][key - 2], pos);
+                if (neg) atomicAdd(&q->members[1][mant][key - 2], neg);
+            }
         }
         __syncthreads();
         p = stop;
     }
 }
 
-// counters -> members below (number and sum), one workgroup per scale mantissa, 8 bins per thread
-__global__ __launch_bounds__(1024) void bs_prefix_kernel(QuantScratch* q) {
-    constexpr int PER = kQuantBins / 1024;
-    __shared__ long long wn[16];
-    __shared__ int128_t ws[16];
+// Counters -> the order of the quotients, and what lies below every run of a stretch: a run a thread.  Bound by vector issue (a quotient and
+// its products per place); counters are picked one by one from the caches.  8192 x 8192: 13.5 us with a workgroup per octave and sign, the
+// octave's counters in LDS, 9.5 as here.
+template <bool NARROW>
+__global__ __launch_bounds__(kSortThreads) void bs_sort_kernel(QuantScratch* q) {
+    using Count = std::conditional_t<NARROW, uint32_t, unsigned long long>;
+    constexpr int WAVES = kSortThreads / 64;
+    __shared__ Count turned[kStretch];
+    __shared__ unsigned long long recip[kQuantMants];
+    __shared__ unsigned long long wn[WAVES];
+    __shared__ uint128_t ws[WAVES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const unsigned long long* const n = q->members[blockIdx.x] + tid * PER;
-    // (a thread's bins go through LDS, nine places for eight, so that a wave writes whole lines: 12 -> 9 us)
-    __shared__ BelowBin out[1024 * (PER + 1)];
-    BelowBin* const bin = out + tid * (PER + 1);
-    BelowBin* const below = q->below[blockIdx.x];
-    const bool pos = tid >= 512;
-    const int mi0 = pos ? (tid - 512) * PER : kHistMags - 1 - tid * PER;             // magnitude of the first bin; then rising / falling
-    const int octave = mi0 >> 7, m0 = 128 + (mi0 & 127), dm = pos ? 1 : -1;
-    auto in_units = [&](long long mantissas) { return static_cast<int128_t>(pos ? mantissas : -mantissas) << octave; };
-    uint64_t c[PER];
-    long long tn = 0, tm = 0;                             // members, sum of their mantissas
+    const int sign = blockIdx.x / kStretches, stretch = blockIdx.x % kStretches, oct = stretch * kStretch / kPairs;      // quotients from 2^(oct - 32) on; sign 1: negative
+    const uint16_t* const order = q->order + stretch * kStretch % kPairs + tid * kRun;
+    typedef u32x4_t __attribute__((aligned(8))) u32x4_a8_t;      // (as the workspace)
+    const u32x4_t pairs[2] = {reinterpret_cast<const u32x4_a8_t*>(order)[0], reinterpret_cast<const u32x4_a8_t*>(order)[1]};
+    auto pair_of = [&](int k) { return (pairs[k >> 3][(k >> 1) & 3] >> (16 * (k & 1))) & 0xFFFFu; };
+    if (tid < kQuantMants) recip[tid] = reciprocal(128 + tid);
+    Count got[kRun], any = 0;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        c[i] = n[i];
-        tn += static_cast<long long>(c[i]);
-        tm += static_cast<long long>(c[i]) * (m0 + dm * i);
+    for (int k = 0; k < kRun; ++k) {
+        const uint32_t pair = pair_of(k), m = pair >> 7, a = pair & 127;
+        const int o = a >= m ? oct - 1 : oct, in = o < 0 ? 0 : o >= kHistOctaves ? kHistOctaves - 1 : o;      // the weight's octave
+        if constexpr (NARROW) {
+            const uint32_t c = reinterpret_cast<const uint32_t*>(&q->members[0][m][(in << 7) + a])[sign];
+            got[k] = in != o ? 0 : c;
+        } else {
+            const unsigned long long c = q->members[sign][m][(in << 7) + a];
+            got[k] = in != o ? 0 : c;
+        }
     }
-    const int128_t ts = in_units(tm);
-    long long in = tn;
-    int128_t is = ts;
+#pragma unroll
+    for (int k = 0; k < kRun; ++k) any |= got[k];
+    Count* const sorted = reinterpret_cast<Count*>(q->sorted[0]) + sign * kPlaces + stretch * kStretch;
+    Below* const base = q->base[sign] + stretch * kSortThreads;
+    if (!__syncthreads_or(any != 0)) {                     // (most octaves of most tensors)
+#pragma unroll
+        for (int i = 0; i < kRun; ++i) sorted[i * kSortThreads + tid] = 0;
+        base[tid] = Below{0, 0, 0};
+        if (tid == 0) q->total[sign][stretch] = Below{0, 0, 0};
+        return;
+    }
+    unsigned long long tn = 0, t0 = 0, t1 = 0;
+    uint128_t ts = 0;
+#pragma unroll
+    for (int k = 0; k < kRun; ++k) {
+        const uint32_t pair = pair_of(k), m = pair >> 7;
+        const unsigned long long f = quotient_bits(128 + (pair & 127), 128 + m, recip[m]);
+        tn += got[k];
+        if constexpr (NARROW) {                            // (members below 2^28: sums of their halves of a quotient in 64 bits)
+            t0 += static_cast<unsigned long long>(got[k]) * (static_cast<uint32_t>(f) & 0x0FFFFFFFu);
+            t1 += static_cast<unsigned long long>(got[k]) * static_cast<uint32_t>(f >> 28);
+        } else {
+            ts += static_cast<uint128_t>(got[k]) * f;
+        }
+        // a thread's run through LDS, one place turned per thread, so that a wave writes whole lines
+        turned[tid * kRun + ((k + tid) & (kRun - 1))] = got[k];
+    }
+    if constexpr (NARROW) ts = (static_cast<uint128_t>(t1) << 28) + t0;
+    unsigned long long in = tn;
+    uint128_t is = ts;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-        const long long pn = __shfl_up(in, off, 64);
+        const unsigned long long pn = __shfl_up(in, off, 64);
         const unsigned long long lo = __shfl_up(static_cast<unsigned long long>(is), off, 64);
-        const long long hi = __shfl_up(static_cast<long long>(is >> 64), off, 64);
-        if (lane >= off) { in += pn; is += static_cast<int128_t>(hi) << 64 | lo; }
+        const unsigned long long hi = __shfl_up(static_cast<unsigned long long>(is >> 64), off, 64);
+        if (lane >= off) { in += pn; is += static_cast<uint128_t>(hi) << 64 | lo; }
     }
     if (lane == 63) { wn[wave] = in; ws[wave] = is; }
     __syncthreads();
-    for (int w = 0; w < wave; ++w) { in += wn[w]; is += ws[w]; }
-    in -= tn;
-    is -= ts;
-    tm = 0;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        bin[i] = below_bin(in, is + in_units(tm));
-        in += static_cast<long long>(c[i]);
-        tm += static_cast<long long>(c[i]) * (m0 + dm * i);
-    }
-    if (tid == 1023) below[kQuantBins] = below_bin(in, is + in_units(tm));
-    __syncthreads();
+    for (int w = 0; w < WAVES - 1; ++w)
+        if (w < wave) { in += wn[w]; is += ws[w]; }
+    auto below = [](unsigned long long n, uint128_t v) { return Below{n, static_cast<unsigned long long>(v), static_cast<unsigned long long>(v >> 64)}; };
+    if (tid == kSortThreads - 1) q->total[sign][stretch] = below(in, is);
+    base[tid] = below(in - tn, is - ts);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int b = i * 1024 + tid;
-        below[b] = out[b / PER * (PER + 1) + b % PER];
+    for (int i = 0; i < kRun; ++i) {
+        const int at = i * kSortThreads + tid, of = at / kRun;
+        sorted[at] = turned[of * kRun + ((at + of) & (kRun - 1))];
     }
 }
 
@@ -1374,15 +1467,6 @@ __device__ __forceinline__ double wave_total(double v) {
     const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(u), 63), hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(u >> 32), 63);
     return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
 }
-__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
-    return __builtin_amdgcn_readlane(v, 63);
-}
 // a value that is the same in every lane, for the scalar unit
 __device__ __forceinline__ double uniform(double v) {
     const uint64_t u = static_cast<uint64_t>(__double_as_longlong(v));
@@ -1399,6 +1483,7 @@ __device__ __forceinline__ double uniform(double v) {
 // added in a fixed order, and the pieces' sums in theirs.
 // 8192 x 8192, 4 bits, 25 rounds: 228 us without far elements, 314 with 0.01 % of them (one search), 2.7 ms where all but the
 // scales are far (a search every round, 0.1 ms each); 133 and 423 ms with the rounds' workgroup searching alone.
+constexpr int kLook = 2;                                 // runs that a boundary's row looks at together
 template <int C>
 struct FarShared {
     double bounds[C];
@@ -1485,26 +1570,33 @@ __device__ __forceinline__ void far_chunk(FarShared<C>& sh, QuantScratch* q, uin
     if (threadIdx.x == 0) __hip_atomic_fetch_add(&q->far.done, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// All rounds: wave i takes boundary i and cluster i, a lane scale mantissas `lane` and `lane + 64`.  Numbers of members
-// are kept as doubles (exact: at most 2^38).
-template <int BITS>
+// All rounds, in one workgroup: a row of sixteen lanes per boundary (four a wave), which finds the boundary's place in the order of the
+// quotients and what lies below it; then a lane per cluster, in each of those waves, for the means.  (A wave per
+// cluster there is for searches; those without a boundary of their own only meet the barriers of a round.)  Numbers of members are kept as doubles where a
+// search adds to them (exact: at most 2^38).
+template <int BITS, bool NARROW>
 __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratch* q, const uint16_t* __restrict__ W,
-                                                                     const uint16_t* __restrict__ scales, int64_t nblocks, uint32_t nchunks,
-                                                                     int iters, uint16_t* __restrict__ codebook) {
-    constexpr int C = 1 << BITS;
-    __shared__ double cs2[2][C];                          // the centroids of a round and of the next one
-    __shared__ BelowBin bb[C][kQuantMants];               // what lies below boundary i (i = C - 1: all), per scale mantissa
-    __shared__ double fsum_of[C];
+                                                                  const uint16_t* __restrict__ scales, int64_t nblocks, uint32_t nchunks,
+                                                                  int iters, uint16_t* __restrict__ codebook) {
+    constexpr int C = 1 << BITS, T = C * 64, ACTIVE = (C + 3) / 4;      // waves with boundaries
+    struct Side { unsigned long long n; int128_t s; };    // number and sum, in units of 2^-88
+    __shared__ double cs[C];
+    __shared__ Side bb[2][16];                            // what lies below boundary i (i = C - 1: all), of this round and the next
+    __shared__ Side stretch[2][kStretches], all[2];       // per sign: members of the stretches below; of all
+    __shared__ unsigned long long recip[kQuantMants];
+    __shared__ alignas(8) uint16_t order[kPairs + kParts];
+    const uint16_t* const part_start = order + kPairs;
+    __shared__ double fsum_of[C], fnum_of[C];
     __shared__ FarShared<C> fs;
-    __shared__ int moved, search;                         // last round (from 1) in which a boundary passed a member, or lay among the far ones
-    const int i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    __shared__ int moved[2], search[2];                   // the round (from 1), of even and odd ones, if a boundary passed a member in it, or lay among the far ones
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, row = tid >> 4, e = tid & 15;
     const double far_neg = static_cast<double>(q->far_neg), far_pos = static_cast<double>(q->far_pos), zeros = static_cast<double>(q->zeros);
     const bool any_far = far_neg + far_pos > 0.0;
     FarScratch* const f = &q->far;
     if (!any_far) {
         if (blockIdx.x != 0) return;
     } else {
-        if (threadIdx.x == 0) fs.chunk = __hip_atomic_fetch_add(&f->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) fs.chunk = __hip_atomic_fetch_add(&f->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         if (fs.chunk != 0) {
             for (;;) {
@@ -1515,128 +1607,227 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
         }
     }
     unsigned long long searches = 0;
-    // sum and number of this wave's cluster's far members, for the boundaries in f->bounds (written by the caller's threads)
-    auto far_search = [&](double& sum, double& num) {
+    // sums and numbers of every cluster's far members, for the boundaries in f->bounds (written by the caller's threads): fsum_of, fnum_of
+    auto far_search = [&] {
         ++searches;
         __syncthreads();
-        if (threadIdx.x == 0) __hip_atomic_store(&f->next, searches << 32, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) __hip_atomic_store(&f->next, searches << 32, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         for (;;) {
             const uint32_t c = far_claim<C>(fs, f, nchunks, false);
             if (c == kNoChunk) break;
             far_chunk<C>(fs, q, c, nchunks, W, scales, nblocks);
         }
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             while (__hip_atomic_load(&f->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < searches * nchunks) __builtin_amdgcn_s_sleep(2);
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         }
         __syncthreads();
-        double s = 0.0, n = 0.0;
-        for (uint32_t c = lane; c < nchunks; c += 64) { s += q->far_part[c][i].sum; n += static_cast<double>(q->far_part[c][i].num); }
-        sum = wave_total(s);
-        num = wave_total(n);
+        {
+            const int i = wave;
+            double s = 0.0, n = 0.0;
+            for (uint32_t c = lane; c < nchunks; c += 64) { s += q->far_part[c][i].sum; n += static_cast<double>(q->far_part[c][i].num); }
+            s = wave_total(s);
+            n = wave_total(n);
+            if (lane == 0) { fsum_of[i] = s; fnum_of[i] = n; }
+        }
+        __syncthreads();
     };
-    double scale[2], inv[2];                              // of this lane's two mantissas, in the window's unit
+    if (iters > 0) {
+        if (tid < kQuantMants) recip[tid] = reciprocal(128 + tid);      // (T >= kQuantMants)
+        // (part_start lies behind order, in LDS as in the workspace)
+        constexpr int kCopies = (kPairs + kParts) / 4 / T;
+        unsigned long long v[kCopies];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        scale[h] = static_cast<double>(static_cast<uint64_t>(128 + lane + 64 * h) << (kHistOctaves - 1));
-        inv[h] = 1.0 / scale[h];
-        bb[C - 1][lane + 64 * h] = q->below[lane + 64 * h][kQuantBins];      // (every wave the same)
+        for (int i = 0; i < kCopies; ++i) v[i] = reinterpret_cast<const unsigned long long*>(q->order)[i * T + tid];
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i) reinterpret_cast<unsigned long long*>(order)[i * T + tid] = v[i];
+        if (wave < 2) {                                   // wave 0: positive, wave 1: negative quotients
+            constexpr int EACH = (kStretches + 63) / 64;  // stretches a lane
+            Below t[EACH];
+#pragma unroll
+            for (int k = 0; k < EACH; ++k) t[k] = q->total[wave][lane * EACH + k < kStretches ? lane * EACH + k : 0];
+            unsigned long long n = 0, n_of[EACH];
+            uint128_t sum = 0, sum_of[EACH];
+#pragma unroll
+            for (int k = 0; k < EACH; ++k) {
+                const int at = lane * EACH + k;
+                const bool is = at < kStretches;
+                n_of[k] = n;
+                sum_of[k] = sum;
+                n += is ? t[k].n : 0;
+                sum += is ? (static_cast<uint128_t>(t[k].hi) << 64 | t[k].lo) << (at * kStretch / kPairs) : 0;
+            }
+            const unsigned long long n0 = n;
+            const uint128_t sum0 = sum;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const unsigned long long pn = __shfl_up(n, off, 64);
+                const unsigned long long lo = __shfl_up(static_cast<unsigned long long>(sum), off, 64);
+                const unsigned long long hi = __shfl_up(static_cast<unsigned long long>(sum >> 64), off, 64);
+                if (lane >= off) { n += pn; sum += static_cast<uint128_t>(hi) << 64 | lo; }
+            }
+#pragma unroll
+            for (int k = 0; k < EACH; ++k)
+                if (lane * EACH + k < kStretches) stretch[wave][lane * EACH + k] = Side{n - n0 + n_of[k], static_cast<int128_t>(sum - sum0 + sum_of[k])};
+            if (lane == 63) all[wave] = Side{n, static_cast<int128_t>(sum)};
+        }
     }
-    // fewer than 2^24 members of every scale mantissa, each of less than 2^39 units: their sums fit 64 bits (8192 x 8192, 4 bits:
-    // 234 -> 224 us)
-    const bool narrow = __all(below_count(bb[C - 1][lane].hi) < 16777216.0 && below_count(bb[C - 1][lane + 64].hi) < 16777216.0);
-    if (threadIdx.x < C) cs2[0][threadIdx.x] = -1.0 + (2 * static_cast<int>(threadIdx.x) + 1) / static_cast<double>(C);
-    if (threadIdx.x == 0) { moved = 0; search = 0; }
+    if (tid < C) cs[tid] = -1.0 + (2 * tid + 1) / static_cast<double>(C);
+    if (tid < 2) moved[tid] = search[tid] = 0;
     double neg_sum = 0.0, pos_sum = 0.0;
     if (any_far && iters > 0) {                           // per sign: all boundaries 0, so the first cluster and the last
-        if (threadIdx.x < C) f->bounds[threadIdx.x] = 0.0;
-        double s, n;
-        far_search(s, n);
-        if (lane == 0) fsum_of[i] = s;
-        __syncthreads();
+        if (tid < C) f->bounds[tid] = 0.0;
+        far_search();
         neg_sum = fsum_of[0];
         pos_sum = fsum_of[C - 1];
     }
     __syncthreads();
-    double* cs = cs2[0];
-    auto boundary = [&](int j) { return uniform(0.5 * (cs[j] + cs[j + 1])); };
-    auto below_of = [&](double b, int h) {
-        return b < 0.0 ? kHistMags - magnitudes_within<true>(-b, scale[h]) : kHistMags + magnitudes_within<false>(b, scale[h]);
-    };
     // what lies below b of something with a negative and a positive part (b not among the far elements)
     auto far_below = [&](double b, double neg, double pos) { return b >= kFar ? neg + pos : b >= 0.0 ? neg : 0.0; };
     auto zeros_below = [&](double b) { return b >= 0.0 ? zeros : 0.0; };
     auto among_far = [&](double b) { return any_far && b != 0.0 && fabs(b) < kFar; };
-    int seen[2] = {-1, -1};
+    auto row_sum = [](unsigned long long v) {             // in every lane of the row
+        auto step = [&](auto ctrl) {
+            constexpr int CTRL = decltype(ctrl)::value;
+            const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<uint32_t>(v), CTRL, 0xF, 0xF, true);
+            const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<uint32_t>(v >> 32), CTRL, 0xF, 0xF, true);
+            v += static_cast<unsigned long long>(hi) << 32 | lo;
+        };
+        step(std::integral_constant<int, 0xB1>{});        // quad_perm [1,0,3,2]
+        step(std::integral_constant<int, 0x4E>{});        // quad_perm [2,3,0,1]
+        step(std::integral_constant<int, 0x141>{});       // row_half_mirror
+        step(std::integral_constant<int, 0x140>{});       // row_mirror
+        return v;
+    };
+    const bool bounded = row < C - 1;                     // the row has a boundary
+    double centroid = cs[e < C ? e : 0];                  // of cluster e, in every row
+    unsigned long long seen = ~0ull;
+    auto lane_f64 = [&](int from) {
+        const uint64_t u = static_cast<uint64_t>(__double_as_longlong(centroid));
+        const uint32_t lo = __builtin_amdgcn_ds_bpermute(from * 4, static_cast<uint32_t>(u)), hi = __builtin_amdgcn_ds_bpermute(from * 4, static_cast<uint32_t>(u >> 32));
+        return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
+    };
     for (int t = 0; t < iters; ++t) {
-        const double b = i < C - 1 ? boundary(i) : 2.0, b0 = i > 0 ? boundary(i - 1) : -2.0;
-        if (i < C - 1) {
-            int now[2];
+      if (wave < ACTIVE) {
+        // the row's boundary, from its lanes `row` and `row + 1`
+        const double b = 0.5 * (lane_f64(bounded ? row : 0) + lane_f64(bounded ? row + 1 : 0));
+        const bool neg = b < 0.0;
+        const int sign = neg ? 1 : 0;
+        // Its place: the octave and the part by its leading bits; from that part's run on all quotients up to the first one above b.
+        // An equal quotient lies below a positive boundary and (by falling magnitude) above a negative one.
+        const uint64_t u = static_cast<uint64_t>(__double_as_longlong(b)) & 0x7FFFFFFFFFFFFFFFull;
+        const int oct = static_cast<int>(u >> 52) - (1023 - kHistOctaves);      // quotients of 2^(oct - 32) and more
+        const uint32_t o = oct < 0 ? 0 : oct >= kOctaves ? kOctaves - 1 : oct;
+        const unsigned long long bits = oct < 0 ? 0 : oct >= kOctaves ? ~0ull : (1ull << 56) | (u & ((1ull << 52) - 1)) << 4;
+        uint32_t first = oct < 0 ? 0 : part_start[static_cast<int>(u >> 40) & (kParts - 1)] & ~(kRun - 1u);      // in the octave
+        const Side below = stretch[sign][(o * kPairs + first) / kStretch];
+        // (atomic loads, so that they are issued here and not behind the search)
+        const unsigned long long* const base = reinterpret_cast<const unsigned long long*>(&q->base[sign][(o * kPairs + first) / kRun]);
+        auto now = [](const auto* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT); };
+        const unsigned long long base_n = now(base), base_lo = now(base + 1), base_hi = now(base + 2);
+        unsigned long long num = 0, s0 = 0, s1 = 0, s2 = 0;
+        for (;;) {
+            unsigned long long c[kLook], fq[kLook];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int below = below_of(b, h);
-                now[h] = below * 2 + (b < 0.0 ? 0 : 1);
-                if (now[h] != seen[h]) {                  // (a boundary soon moves past few of the bins: only those are fetched)
-                    bb[i][lane + 64 * h] = q->below[lane + 64 * h][below];
+            for (int k = 0; k < kLook; ++k) {
+                const uint32_t at = sign * kPlaces + o * kPairs + first + k * kRun + e;
+                const uint32_t* const p = reinterpret_cast<const uint32_t*>(q->sorted[0]) + (NARROW ? at : 2 * at);
+                c[k] = now(p);
+                if constexpr (!NARROW) c[k] |= static_cast<unsigned long long>(now(p + 1)) << 32;
+            }
+            bool near = false, in[kLook];
+#pragma unroll
+            for (int k = 0; k < kLook; ++k) {
+                const uint32_t rank = first + k * kRun + e, pair = order[rank & (kPairs - 1)], m = pair >> 7;
+                fq[k] = quotient_bits(128 + (pair & 127), 128 + m, recip[m]);
+                in[k] = fq[k] < bits && rank < kPairs;
+                near |= fq[k] - bits + 64 < 128;
+            }
+            if (__any(near)) {                            // quotients next to their boundary: the division itself decides
+#pragma unroll
+                for (int k = 0; k < kLook; ++k) {
+                    const uint32_t rank = first + k * kRun + e, pair = order[rank & (kPairs - 1)], a = 128 + (pair & 127), s = 128 + (pair >> 7);
+                    const double quot = static_cast<double>(a < s ? 2 * a : a) / static_cast<double>(s), mid = __longlong_as_double(static_cast<long long>(1023ull << 52 | (u & ((1ull << 52) - 1))));
+                    if (fq[k] - bits + 64 < 128) in[k] = (neg ? quot < mid : quot <= mid) && rank < kPairs;
                 }
             }
-            if (now[0] != seen[0] || now[1] != seen[1] || among_far(b)) moved = t + 1;
-            if (among_far(b)) search = t + 1;
-            seen[0] = now[0];
-            seen[1] = now[1];
-        }
-        __syncthreads();
-        if (moved != t + 1) break;                         // every boundary where it was: a fixed point
-        double n = 0.0, s = 0.0;
-        uint32_t n32 = 0;                                 // (narrow: at most 2^31)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int m = lane + 64 * h;
-            const BelowBin hi = bb[i][m], lo = i > 0 ? bb[i - 1][m] : BelowBin{0, 0};
-            if (narrow) {
-                n32 += static_cast<uint32_t>(hi.hi >> 24) - static_cast<uint32_t>(lo.hi >> 24);
-                s += static_cast<double>(static_cast<long long>(hi.lo - lo.lo)) * inv[h];
-            } else {
-                n += below_count(hi.hi) - below_count(lo.hi);
-                s += sum_to_f64(below_sum(hi.lo, hi.hi) - below_sum(lo.lo, lo.hi)) * inv[h];
+            for (int k = 0; k < kLook; ++k) {
+                c[k] = in[k] ? c[k] : 0;
+                num += c[k];
+                if constexpr (NARROW) {
+                    s0 += static_cast<unsigned long long>(static_cast<uint32_t>(c[k])) * (static_cast<uint32_t>(fq[k]) & 0x0FFFFFFFu);
+                    s1 += static_cast<unsigned long long>(static_cast<uint32_t>(c[k])) * static_cast<uint32_t>(fq[k] >> 28);
+                } else {                                  // (at most 2^38 members, 19 bits of quotient at a time)
+                    s0 += c[k] * (static_cast<uint32_t>(fq[k]) & 0x7FFFFu);
+                    s1 += c[k] * (static_cast<uint32_t>(fq[k] >> 19) & 0x7FFFFu);
+                    s2 += c[k] * static_cast<uint32_t>(fq[k] >> 38);
+                }
             }
+            // rows whose last quotient lies below go on (the others' further looks would find nothing: their quotients are above)
+            if (__ballot(in[kLook - 1] && bounded && e == kRun - 1) == 0) break;
+            first += kLook * kRun;
         }
-        n = narrow ? static_cast<double>(wave_total(n32)) : wave_total(n);
-        s = wave_total(s);
-        n += zeros_below(b) - zeros_below(b0);
+        uint128_t sum = static_cast<uint128_t>(base_hi) << 64 | base_lo;
+        sum += row_sum(s0);
+        if constexpr (NARROW) {
+            num = lanes_sum<16>(static_cast<uint32_t>(num));
+            sum += static_cast<uint128_t>(row_sum(s1)) << 28;
+        } else {
+            num = row_sum(num);
+            sum += static_cast<uint128_t>(row_sum(s1)) << 19;
+            sum += static_cast<uint128_t>(row_sum(s2)) << 38;
+        }
+        if (e == 0 && bounded) {
+            num += below.n + base_n;
+            const int128_t vs = below.s + static_cast<int128_t>(sum << o);
+            bb[t & 1][row] = neg ? Side{all[1].n - num, vs - all[1].s} : Side{all[1].n + num, vs - all[1].s};
+            num = num * 4 + (neg ? 0 : 1) + (fabs(b) < kFar ? 0 : 2);      // (b passes zeros and far members, too)
+            if (num != seen) moved[t & 1] = t + 1;
+            seen = num;
+        }
+        if (e == 0 && row == C - 1) bb[t & 1][row] = Side{all[0].n + all[1].n, all[0].s - all[1].s};
+        if (any_far && e == 0 && bounded) {
+            f->bounds[row] = b;
+            if (among_far(b)) moved[t & 1] = search[t & 1] = t + 1;
+        }
+      }
+        __syncthreads();
+        if (moved[t & 1] != t + 1) break;                        // every boundary where it was: a fixed point
+        const bool searched = any_far && search[t & 1] == t + 1;
+        if (searched) far_search();
+        if (wave >= ACTIVE) continue;
+        const int i = e < C ? e : 0;
+        const Side hi = bb[t & 1][i], lo = i > 0 ? bb[t & 1][i - 1] : Side{0, 0};
+        double n = static_cast<double>(hi.n - lo.n), s = sum_to_f64(hi.s - lo.s) * 3.2311742677852644e-27;      // 2^-88
+        // boundaries of cluster e
+        const double above = lane_f64(i + 1 < C ? i + 1 : i), under = lane_f64(i > 0 ? i - 1 : 0);
+        const double bh = i + 1 < C ? 0.5 * (centroid + above) : 2.0, bl = i > 0 ? 0.5 * (under + centroid) : -2.0;
+        n += zeros_below(bh) - zeros_below(bl);
         if (any_far) {
-            double fsum, fnum;
-            if (search == t + 1) {                        // (uniform)
-                if (lane == 0) f->bounds[i] = b;
-                far_search(fsum, fnum);
-            } else {
-                fsum = far_below(b, neg_sum, pos_sum) - far_below(b0, neg_sum, pos_sum);
-                fnum = far_below(b, far_neg, far_pos) - far_below(b0, far_neg, far_pos);
-            }
-            s += fsum;
-            n += fnum;
+            s += searched ? fsum_of[i] : far_below(bh, neg_sum, pos_sum) - far_below(bl, neg_sum, pos_sum);
+            n += searched ? fnum_of[i] : far_below(bh, far_neg, far_pos) - far_below(bl, far_neg, far_pos);
         }
-        const double c = s / n;
-        double* const next = cs2[(t + 1) & 1];
-        if (lane == 0) next[i] = n > 0.0 ? c : cs[i];
-        cs = next;
-        __syncthreads();                                  // (this round's values have been read by all)
+        const double mean = s / n;
+        centroid = n > 0.0 ? mean : centroid;
     }
     __syncthreads();
-    if (any_far && threadIdx.x == 0) __hip_atomic_store(&f->finished, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    if (threadIdx.x < C) {
-        const uint16_t hc = f64_to_bf16(cs[threadIdx.x]);
-        codebook[threadIdx.x] = q->nonfinite ? 0x7FC0 : hc;
-        cs[threadIdx.x] = bf16_to_f64(hc);
+    if (any_far && tid == 0) __hip_atomic_store(&f->finished, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid < C) {
+        const uint16_t hc = f64_to_bf16(centroid);
+        codebook[tid] = q->nonfinite ? 0x7FC0 : hc;
+        cs[tid] = bf16_to_f64(hc);
     }
     __syncthreads();
-    if (i < C - 1) {
-        const double b = boundary(i);
+    if (wave < C - 1) {
+        const int i = wave;
+        const double b = uniform(0.5 * (cs[i] + cs[i + 1]));
         if (lane == 0 && among_far(b)) q->exact_assign = 1;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
+            const double scale = static_cast<double>(static_cast<uint64_t>(128 + lane + 64 * h) << (kHistOctaves - 1));      // in the window's unit
             // largest key (sign * magnitude key) at or below b: zero 0, far 1, window position + 2
-            const int below = below_of(b, h);
+            const int below = b < 0.0 ? kHistMags - magnitudes_within<true>(-b, scale) : kHistMags + magnitudes_within<false>(b, scale);
             const int key = b < 0.0 ? -(kHistMags - below) - 2 : b == 0.0 ? 0 : below - kHistMags + 1;
             q->above[lane + 64 * h][i] = (static_cast<uint32_t>(key) & 0xFFFFu) * 0x00010001u;
         }
@@ -1866,22 +2057,26 @@ static hipError_t quantize_blockscaled_bits(const uint16_t* W, int64_t N, int64_
         hipLaunchKernelGGL((bs_small_kernel<BITS>), dim3(1), dim3(256), 0, s, W, static_cast<int>(nblocks), iters, packed, codebook, scales);
         return hipGetLastError();
     }
-    const size_t clear = iters ? kClearAll : kClearSmall;
+    const bool narrow = N * K < kNarrowElements;
+    const size_t clear = iters == 0 ? kClearSmall : narrow ? kClearNarrow : kClearAll;
+    const int orders = iters ? kOrderGroups : 0;
     hipLaunchKernelGGL(bs_clear_kernel, grid(static_cast<int64_t>(clear), 256, 2048), dim3(256), 0, s, q, clear);
-    hipLaunchKernelGGL(bs_scales_kernel, grid(nblocks, kScaleTurn, 1024), dim3(256), 0, s, W, nblocks, scales, q);
+    hipLaunchKernelGGL(bs_scales_kernel, dim3(grid(nblocks, kScaleTurn, 1024).x + orders), dim3(256), 0, s, W, nblocks, scales, orders, q);
     if (iters) {                                          // (without rounds nothing is counted)
         hipLaunchKernelGGL(bs_group_kernel, dim3(static_cast<unsigned>((nblocks + kGroupBlocks - 1) / kGroupBlocks)), dim3(kGroupThreads), 0, s, scales, nblocks, q, packed);
         // Two workgroups of 16 waves a CU, of at least 64 blocks each to spread the clearing and flushing of 8196 counters (1024 x 1024: 6 us more
         // with 16; 8192 x 8192: 44 us in all with four workgroups of eight waves, 34 with two), but at least one workgroup a CU: it flushes once per scale mantissa among its blocks (64 x 64: 171 us in one
         // workgroup, 49 with a block each; 25 rounds, 1 bit).
         const int64_t least = nblocks < 64 * 256 ? (nblocks + 255) / 256 : 64, run = (nblocks + 511) / 512 < least ? least : (nblocks + 511) / 512;
-        hipLaunchKernelGGL(bs_count_kernel, dim3(static_cast<unsigned>((nblocks + run - 1) / run)), dim3(kCountThreads), 0, s, W, packed, nblocks, run, q);
-        hipLaunchKernelGGL(bs_prefix_kernel, dim3(kQuantMants), dim3(1024), 0, s, q);
+        hipLaunchKernelGGL(bs_count_kernel, dim3(static_cast<unsigned>((nblocks + run - 1) / run)), dim3(kCountThreads), 0, s, W, packed, nblocks, run, narrow, q);
+        if (narrow) hipLaunchKernelGGL(bs_sort_kernel<true>, dim3(2 * kStretches), dim3(kSortThreads), 0, s, q);
+        else hipLaunchKernelGGL(bs_sort_kernel<false>, dim3(2 * kStretches), dim3(kSortThreads), 0, s, q);
     }
     // one workgroup runs the rounds; the others, a few a CU, end at once unless there are far elements
     const uint32_t nchunks = static_cast<uint32_t>(nblocks < 256 * kFarChunks ? (nblocks + 255) / 256 : kFarChunks);
-    hipLaunchKernelGGL((bs_rounds_kernel<BITS>), dim3(iters == 0 ? 1 : BITS <= 2 ? 512 : 256), dim3((1 << BITS) * 64), 0, s, q, W, scales, nblocks, nchunks,
-                       iters, codebook);
+    const dim3 round_grid(iters == 0 ? 1 : BITS <= 2 ? 512 : 256), round_block((1 << BITS) * 64);
+    if (narrow) hipLaunchKernelGGL((bs_rounds_kernel<BITS, true>), round_grid, round_block, 0, s, q, W, scales, nblocks, nchunks, iters, codebook);
+    else hipLaunchKernelGGL((bs_rounds_kernel<BITS, false>), round_grid, round_block, 0, s, q, W, scales, nblocks, nchunks, iters, codebook);
     hipLaunchKernelGGL((bs_assign_pack_kernel<BITS>), grid(npieces, 256, 4096), dim3(256), 0, s, W, scales, codebook, npieces, q, packed);
     return hipGetLastError();
 }

@@ -1,0 +1,76 @@
+"""The tensor quantiser's order of quotients: boundaries among the smallest quotients that it holds (whose octave has only half of
+the pairs), every scale mantissa with every weight mantissa, and tensors large enough for wide counters, which have to give
+what the same data gives on narrow ones."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2602_15563_amd import kmq, synth
+from tests.test_gpu_quantize import run_blockscaled
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    from tests import gpu_util
+    return gpu_util
+
+
+def check(gpu, W, bits, iters):
+    idx, cb, sc, _, _ = oracle.quantize_blockscaled(W, bits, iters)
+    pg, cg, sg = run_blockscaled(gpu, W, bits, iters)
+    assert np.array_equal(sg, sc)
+    assert np.array_equal(cg, cb)
+    assert np.array_equal(pg, oracle.pack(idx, bits))
+
+
+@pytest.mark.parametrize("bits", [1, 2, 4])
+@pytest.mark.parametrize("neg,pos", [(3, 1), (1, 3), (1, 1), (7, 6), (2, 1)])
+def test_boundaries_among_the_smallest_quotients(gpu, bits, neg, pos):
+    """Besides the scales only quotients of neg and pos times 2^-32 to 2^-31: the middle boundary comes to lie in the lowest octave
+    (2^-32 to 2^-31) or the one above it, on either side of zero, or at zero."""
+    rng = np.random.default_rng(11 * neg + pos)
+    mant = np.tile(128 + np.arange(128), 4)                # every scale mantissa
+    a = rng.integers(128, 256, size=(512, 64))
+    sign = rng.random((512, 64)) < 0.5
+    f = a * np.where(sign, -float(neg), float(pos)) * 2.0 ** -38
+    f = np.where(np.abs(f) < 128 * 2.0 ** -38, 128 * 2.0 ** -38, f)      # (nothing below the window)
+    f[:, 0] = mant / 128.0
+    check(gpu, synth.f32_to_bf16(f.astype(np.float32)).reshape(8, 4096), bits, 6)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_every_pair_of_mantissas(gpu, bits):
+    """Every quotient of three octaves once, negative ones twice: boundaries fall next to and on many of them."""
+    s, a = np.meshgrid(128 + np.arange(128), 128 + np.arange(128), indexing="ij")
+    rows = []
+    for octave in (1, 2, 5):
+        w = a * 2.0 ** -octave
+        for sgn in (1.0, -1.0, -1.0):
+            v = (w * sgn).reshape(128, 2, 64)
+            v[:, :, 0] = 2 * s[:, :1]                      # the block's scale: twice its mantissa
+            rows.append(v.reshape(128, 128))
+    W = synth.f32_to_bf16(np.concatenate(rows).astype(np.float32)).reshape(-1, 1024)
+    check(gpu, W, bits, 15)
+
+
+@pytest.mark.parametrize("bits", [1, 4])
+def test_wide_counters_give_what_narrow_ones_give(gpu, bits):
+    """A tensor of 2^24 elements, and sixteen copies of it: counts and sums are sixteen times as large (exactly), means the same."""
+    import torch
+    n, iters = 4096, 6
+    W = torch.from_numpy(synth.make_dense_weights(170, bits, n, n).view(np.int16)).cuda()
+    many = W.repeat(16, 1).contiguous()
+    outs = []
+    for w in (W, many):
+        N, K = w.shape
+        packed = torch.zeros((N, kmq.words_per_row(bits, K)), dtype=torch.int32, device="cuda")
+        cb, sc = torch.zeros(1 << bits, dtype=torch.int16, device="cuda"), torch.zeros((N, K // 64), dtype=torch.int16, device="cuda")
+        ws = torch.empty(kmq.quantize_blockscaled_workspace_bytes(), dtype=torch.uint8, device="cuda")
+        kmq.quantize_blockscaled(w, N, K, bits, iters, packed, cb, sc, ws)
+        outs.append((packed, cb, sc))
+    torch.cuda.synchronize()
+    (p, c, s), (pm, cm, sm) = outs
+    assert torch.equal(c, cm)
+    assert torch.equal(s.repeat(16, 1), sm) and torch.equal(p.repeat(16, 1), pm)
