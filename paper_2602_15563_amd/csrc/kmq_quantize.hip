@@ -1062,7 +1062,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __re
 //
 // 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits, a new tensor each time: 136 / 146 / 154 / 168 us (142 / 154 / 171 / 206 with a look-up per boundary and scale
 // mantissa in every round; 8519 / 9344 / 10727 / 13475 with every element divided by its scale and compared with every boundary in fp64, each round);
-// 1024 x 1024, 4 bits: 86 (120; 3570).  At 8192 x 8192 and 4 bits: clear 5, scales 21 (6.5 TB/s), group 13, count 32 (blocks gathered 128 bytes at a time,
+// 1024 x 1024, 4 bits: 81 (120; 3570).  At 8192 x 8192 and 4 bits: clear 5, scales 21 (6.5 TB/s), group 13, count 32 (blocks gathered 128 bytes at a time,
 // LDS atomics, 14 for the adding up), sort 9, rounds 44 (1.5 us each, a chain of latencies of one wave a SIMD; 78 before), assign 45 us (vector issue).
 constexpr int kQuantMants = 128;
 constexpr double kFar = 4.656612873077393e-10;           // 2^-31: no far element reaches it
@@ -1252,7 +1252,10 @@ __device__ __forceinline__ void list_starts(const QuantScratch* q, long long* st
     }
 }
 
-constexpr int kGroupThreads = 1024, kGroupBlocks = 8192;   // blocks per workgroup of the grouping step (few: every one adds to 128 shared cursors)
+// EACH blocks a thread: at most 128 workgroups where eight suffice for that (every one adds to 128 shared cursors; 8192 x 8192, 1 bit: 135.6 us in all
+// with eight, 136.7 with four, 139.0 with sixteen), of as few blocks as that leaves (1024 x 1024, 4 bits: 86.3 us with eight, 81.4 with one).
+constexpr int kGroupThreads = 1024;
+template <int EACH>
 __global__ __launch_bounds__(kGroupThreads) void bs_group_kernel(const uint16_t* __restrict__ scales, int64_t nblocks, QuantScratch* q,
                                                        uint32_t* __restrict__ list) {
     __shared__ long long start[kQuantMants + 1];
@@ -1261,10 +1264,10 @@ __global__ __launch_bounds__(kGroupThreads) void bs_group_kernel(const uint16_t*
     list_starts(q, start);
     if (threadIdx.x < kQuantMants) cnt[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t b0 = static_cast<int64_t>(blockIdx.x) * kGroupBlocks + threadIdx.x;
-    uint32_t mant[kGroupBlocks / kGroupThreads], rank[kGroupBlocks / kGroupThreads];
+    const int64_t b0 = static_cast<int64_t>(blockIdx.x) * (kGroupThreads * EACH) + threadIdx.x;
+    uint32_t mant[EACH], rank[EACH];
 #pragma unroll
-    for (int i = 0; i < kGroupBlocks / kGroupThreads; ++i)
+    for (int i = 0; i < EACH; ++i)
         if (b0 + i * kGroupThreads < nblocks) {
             mant[i] = scale_pattern(scales[b0 + i * kGroupThreads]) & 127u;
             rank[i] = atomicAdd(&cnt[mant[i]], 1u);
@@ -1274,7 +1277,7 @@ __global__ __launch_bounds__(kGroupThreads) void bs_group_kernel(const uint16_t*
         at[threadIdx.x] = start[threadIdx.x] + static_cast<long long>(atomicAdd(&q->cursor[threadIdx.x], static_cast<unsigned long long>(cnt[threadIdx.x])));
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kGroupBlocks / kGroupThreads; ++i)
+    for (int i = 0; i < EACH; ++i)
         if (b0 + i * kGroupThreads < nblocks) list[at[mant[i]] + rank[i]] = static_cast<uint32_t>(b0 + i * kGroupThreads);
 }
 
@@ -2063,7 +2066,15 @@ static hipError_t quantize_blockscaled_bits(const uint16_t* W, int64_t N, int64_
     hipLaunchKernelGGL(bs_clear_kernel, grid(static_cast<int64_t>(clear), 256, 2048), dim3(256), 0, s, q, clear);
     hipLaunchKernelGGL(bs_scales_kernel, dim3(grid(nblocks, kScaleTurn, 1024).x + orders), dim3(256), 0, s, W, nblocks, scales, orders, q);
     if (iters) {                                          // (without rounds nothing is counted)
-        hipLaunchKernelGGL(bs_group_kernel, dim3(static_cast<unsigned>((nblocks + kGroupBlocks - 1) / kGroupBlocks)), dim3(kGroupThreads), 0, s, scales, nblocks, q, packed);
+        auto group = [&](auto each) {
+            constexpr int EACH = decltype(each)::value;
+            hipLaunchKernelGGL(bs_group_kernel<EACH>, dim3(static_cast<unsigned>((nblocks + kGroupThreads * EACH - 1) / (kGroupThreads * EACH))), dim3(kGroupThreads), 0, s,
+                               scales, nblocks, q, packed);
+        };
+        if (nblocks <= 128 * kGroupThreads) group(std::integral_constant<int, 1>{});
+        else if (nblocks <= 256 * kGroupThreads) group(std::integral_constant<int, 2>{});
+        else if (nblocks <= 512 * kGroupThreads) group(std::integral_constant<int, 4>{});
+        else group(std::integral_constant<int, 8>{});
         // Two workgroups of 16 waves a CU, of at least 64 blocks each to spread the clearing and flushing of 8196 counters (1024 x 1024: 6 us more
         // with 16; 8192 x 8192: 44 us in all with four workgroups of eight waves, 34 with two), but at least one workgroup a CU: it flushes once per scale mantissa among its blocks (64 x 64: 171 us in one
         // workgroup, 49 with a block each; 25 rounds, 1 bit).
