@@ -323,7 +323,7 @@ kmq_status kmq_quantize_rows(const uint16_t* Wdense, int64_t N, int64_t K, int b
  * Weights are finite; if one is not, every entry of the codebook is a NaN (and so are products with it), the
  * indices are some, and its block's scale is the largest of the block's bit patterns without sign.
  *   workspace device memory of kmq_quantize_blockscaled_workspace_bytes() bytes, 8-byte aligned
- *             (25 MB: counters of the tensor's distinct values and their sums; contents undefined before and after)
+ *             (19 MB: counters of the tensor's distinct values and their sums; contents undefined before and after)
  * K % KMQ_BLOCK != 0 -> KMQ_ERR_SHAPE; workspace NULL or too small -> KMQ_ERR_WORKSPACE. */
 size_t kmq_quantize_blockscaled_workspace_bytes(void);
 kmq_status kmq_quantize_blockscaled(const uint16_t* Wdense, int64_t N, int64_t K, int bits, int iters,
