@@ -1787,7 +1787,7 @@ __global__ __launch_bounds__((1 << BITS) * 64) void bs_rounds_kernel(QuantScratc
             bb[t & 1][row] = neg ? Side{all[1].n - num, vs - all[1].s} : Side{all[1].n + num, vs - all[1].s};
             num = num * 4 + (neg ? 0 : 1) + (fabs(b) < kFar ? 0 : 2);      // (b passes zeros and far members, too)
             if (num != seen) moved[t & 1] = t + 1;
-            seen = num;
+            seen = among_far(b) ? ~0ull : num;            // (on its way to 0 it passes far members that are counted nowhere)
         }
         if (e == 0 && row == C - 1) bb[t & 1][row] = Side{all[0].n + all[1].n, all[0].s - all[1].s};
         if (any_far && e == 0 && bounded) {

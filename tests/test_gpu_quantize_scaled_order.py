@@ -101,3 +101,22 @@ def test_grouping_step_at_its_edges(gpu, blocks):
     else:                                                  # ... by less than a bf16 step, mostly: indices differ where a stored centroid does
         d = (c.int() - cm.int()).abs().max().item()
         assert d <= 1 and (d > 0 or torch.equal(pm, p[at]))
+
+
+@pytest.mark.parametrize("iters", [3, 5, 6])
+def test_a_boundary_that_goes_from_far_elements_to_zero(gpu, iters):
+    """2 bits, quotients whose sums are exact in any order.  The middle boundary is 0, then 2^-32, with 32 far elements of 2^-33 below it,
+    then 0 again, and the outer boundaries have moved past their last member by then: as many window members lie below every
+    boundary as in the round before, but the far elements have changed sides, so it is no fixed point."""
+    low = lambda n: [255 * 2.0 ** -12, 255 * 2.0 ** -20, n * 2.0 ** -28, 11 * 2.0 ** -32]
+    C = [0.5] * 4 + low(255)                                   # 8 elements, together 2.0625 - 5 * 2^-32
+    B = [-v for v in [1 / 16] * 28 + [1 / 32] * 8 + low(251)]      # 40 elements, together -2.0625 + 69 * 2^-32
+    f = C + B + [2.0 ** -33] * 32 + [-33 / 64] * 64
+    assert sum(C) == 2.0625 - 5 * 2.0 ** -32 and sum(B) == -2.0625 + 69 * 2.0 ** -32
+    n = 256 * 64
+    f = np.array(f + [-1.0] * (n // 2) + [1.0] * (n - n // 2 - len(f)))
+    f = np.random.default_rng(5).permutation(f).reshape(256, 64)
+    assert (np.abs(f).max(axis=1) == 1.0).all()
+    W = synth.f32_to_bf16(f.astype(np.float32)).reshape(4, 4096)
+    assert not np.array_equal(oracle.quantize_blockscaled(W, 2, 2)[1], oracle.quantize_blockscaled(W, 2, 3)[1])
+    check(gpu, W, 2, iters)
