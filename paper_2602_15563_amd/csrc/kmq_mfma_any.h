@@ -10,7 +10,7 @@
 // words; tiled: the layout's granules, every eighth column 32j + 8q -- decodes eight weights at a time into the second operand
 // of v_mfma_f32_16x16x32_bf16 (k = the lanes' eight columns, X first), and requests the words of its next tile as soon as the
 // present ones are decoded.  D holds batch columns 4q..4q+3 of row n, so what belongs to a row (scales, centroids) is needed by
-// the lane that loads it.  The waves' partial tiles are added through LDS, pairwise.  A last tile that K does not fill is one
+// the lane that loads it.  The partial tiles of the waves (of a wave's two chains) are added through LDS, pairwise.  A last tile that K does not fill is one
 // wave's; columns past K are zeros in both operands, so that an infinite centroid meets no zero.
 //
 // Decode.  The columns of a matrix step may be any eight, as long as both operands agree:
@@ -100,7 +100,8 @@ constexpr int canon_waves() {
 }
 
 // TILED: the matrix-core layout instead of the canonical one.  MR: groups of four batch rows that are staged (M <= 4 * MR).
-template <int BITS, bool SC, bool TILED, int MR, int RB, int NW>
+// CHAINS: sums a wave has, which take its tiles in turn.  With two of them a result is, bit for bit, that of twice the waves with one.
+template <int BITS, bool SC, bool TILED, int MR, int RB, int NW, int CHAINS>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(canon_waves<BITS, SC, TILED, MR, RB>()))) void gemm_canon_kernel(const uint32_t* __restrict__ W, const uint16_t* __restrict__ codebook,
                                                              const uint16_t* __restrict__ X, uint16_t* __restrict__ Y,
                                                              int64_t N, int64_t K, int M, const uint16_t* __restrict__ scales) {
@@ -116,13 +117,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(canon_w
     // columns, and the centroids in the epilogue, c0 * sum + (c1 - c0) * sum over the ones, as the table kernels do at batch 1.
     // Rows with a non-finite centroid, and all rows where K is no multiple of 32, multiply by the centroids themselves.
     constexpr bool SUMS = BITS == 1 && !SC && !TILED;
-    static_assert(RB <= 4, "partial tiles reuse the staging memory");
+    static_assert(RB * CHAINS <= 4 && CHAINS <= 2, "partial tiles reuse the staging memory");
     struct alignas(256) Smem {
         uint32_t ptab[TAB ? TAB : 1][TAB ? 16 : 1][64];   // 4-bit: centroid (in both halves) per entry and lane
         u32x2_t masks[16];                                // 1-bit: nibble -> four 16-bit masks
         u32x4_t xs[NW][R * 17];                           // per wave: R batch rows x 16 pieces of eight columns (+ 1 pad)
         uint32_t cc[SUMS ? RB * 16 : 1];                  // the rows' centroids
-        float sx[SUMS ? NW : 1][16];                      // per wave: sum of its columns of X, per batch column
+        float sx[SUMS ? NW * CHAINS : 1][16];             // per chain: sum of its columns of X, per batch column
     };
     __shared__ Smem sm;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -328,10 +329,22 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(canon_w
     }
     if constexpr (BITS == 1 || BITS == 4) __syncthreads();
 
-    f32x4_t acc[RB];
-    [[maybe_unused]] float accx[MR] = {};                 // sums of X, batch rows 4i + q
+    f32x4_t acc[CHAINS][RB];                              // [0]: the chain whose turn it is
+    [[maybe_unused]] float accx[CHAINS][MR] = {};         // sums of X, batch rows 4i + q
 #pragma unroll
-    for (int r = 0; r < RB; ++r) acc[r] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < CHAINS; ++c)
+#pragma unroll
+        for (int r = 0; r < RB; ++r) acc[c][r] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    int turn = 0;                                         // which chain [0] is
+    auto next_chain = [&] {
+        if constexpr (CHAINS == 2) {
+            turn ^= 1;
+#pragma unroll
+            for (int r = 0; r < RB; ++r) { const f32x4_t t = acc[0][r]; acc[0][r] = acc[1][r]; acc[1][r] = t; }
+#pragma unroll
+            for (int i = 0; i < MR; ++i) { const float t = accx[0][i]; accx[0][i] = accx[1][i]; accx[1][i] = t; }
+        }
+    };
     [[maybe_unused]] uint32_t areg[8];                    // 4-bit: look-up addresses, byte 0 = lane * 4, byte 1 = index
 #pragma unroll
     for (int e = 0; e < 8; ++e) areg[e] = static_cast<uint32_t>(lane) * 4u;
@@ -503,7 +516,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(canon_w
             }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[r][i] += tile_sum[i];
+        for (int i = 0; i < 4; ++i) acc[0][r][i] += tile_sum[i];
     };
     auto sum_x = [&] {                                    // this lane's pieces of a tile
 #pragma unroll
@@ -511,7 +524,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(canon_w
 #pragma unroll
             for (int hh = 0; hh < HALVES; ++hh)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) accx[i] = dot2_bf16(0x3F803F80u, xr[hh][i][j], accx[i]);
+                for (int j = 0; j < 4; ++j) accx[0][i] = dot2_bf16(0x3F803F80u, xr[hh][i][j], accx[0][i]);
     };
 
     // The pieces pass between lanes of one wave, whose LDS instructions run in order: the compiler has to keep that order.
@@ -552,51 +565,63 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(canon_w
         }
     };
     // the last tile is a copy of the code of its own: a branch around the loads would make every wait assume the fewest of them
-    for (; tile + NW < full; tile += NW) step(std::true_type{}, std::false_type{});
-    if (tile < full) step(std::false_type{}, std::false_type{});
+    for (; tile + NW < full; tile += NW) {
+        step(std::true_type{}, std::false_type{});
+        next_chain();
+    }
+    if (tile < full) {
+        step(std::false_type{}, std::false_type{});
+        next_chain();
+    }
     if (rest && wave == full % NW) {
 #pragma unroll
         for (int r = 0; r < RB; ++r) load_w_tail(r, full);
         step(std::false_type{}, std::true_type{});
+        next_chain();
     }
 
-    // ---- the waves' partial tiles: [batch column][row, padded to 17 per block], added pairwise
+    // ---- the chains' partial tiles: [chain, row block, batch column][row, padded to 17], added pairwise
     float* const part = reinterpret_cast<float*>(xs);
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        if (q < MR) {
+    for (int c = 0; c < CHAINS; ++c) {
+        const int chain = c ^ turn;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) part[(r * R + 4 * q + j) * 17 + n] = acc[r][j];
+        for (int r = 0; r < RB; ++r) {
+            if (q < MR) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) part[((chain * RB + r) * R + 4 * q + j) * 17 + n] = acc[c][r][j];
+            }
         }
-    }
-    if constexpr (SUMS) {
+        if constexpr (SUMS) {
 #pragma unroll
-        for (int i = 0; i < MR; ++i) {
-            const float t = group_sum<16>(accx[i]);
-            if (n == 15) sm.sx[wave][4 * i + q] = t;
+            for (int i = 0; i < MR; ++i) {
+                const float t = group_sum<16>(accx[c][i]);
+                if (n == 15) sm.sx[chain * NW + wave][4 * i + q] = t;
+            }
         }
     }
     __syncthreads();
-    auto over_waves = [](auto&& of) {
-        float v[NW];
+    auto over_chains = [](auto&& of) {                    // chain c of wave w as wave c * NW + w of more of them
+        constexpr int PARTS = NW * CHAINS;
+        float v[PARTS];
 #pragma unroll
-        for (int k = 0; k < NW; ++k) v[k] = of(k);
+        for (int k = 0; k < PARTS; ++k) v[k] = of(k);
 #pragma unroll
-        for (int w = 1; w < NW; w *= 2)
+        for (int w = 1; w < PARTS; w *= 2)
 #pragma unroll
-            for (int k = 0; k < NW; k += 2 * w) v[k] += v[k + w];
+            for (int k = 0; k < PARTS; k += 2 * w) v[k] += v[k + w];
         return v[0];
     };
     for (int o = threadIdx.x; o < RB * R * 16; o += NW * 64) {
         const int m = o / (RB * 16), nl = o % (RB * 16);  // consecutive threads: consecutive rows
         const int64_t row = row0 + nl;
         if (m < M && row < N) {
-            float s = over_waves([&](int k) { return reinterpret_cast<const float*>(sm.xs[k])[((nl >> 4) * R + m) * 17 + (nl & 15)]; });
+            float s = over_chains([&](int k) { return reinterpret_cast<const float*>(sm.xs[k % NW])[((k / NW * RB + (nl >> 4)) * R + m) * 17 + (nl & 15)]; });
             if constexpr (SUMS) {
                 const uint32_t cc = sm.cc[nl];
                 if (sums && finite(cc)) {
                     const float c0f = bf16_to_f32(cc & 0xFFFFu), d = bf16_to_f32(cc >> 16) - c0f;
-                    s = fmaf(d, s, c0f * over_waves([&](int k) { return sm.sx[k][m]; }));
+                    s = fmaf(d, s, c0f * over_chains([&](int k) { return sm.sx[k][m]; }));
                 }
             }
             Y[static_cast<int64_t>(m) * N + row] = f32_to_bf16(s);
@@ -606,10 +631,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(canon_w
 
 // ---- launch ------------------------------------------------------------------------------------
 
-template <int BITS, bool SC, bool TILED, int MR, int RB, int NW>
+template <int BITS, bool SC, bool TILED, int MR, int RB, int NW, int CHAINS = 1>
 static void canon_launch(const GemmArgs& a, hipStream_t s) {
     const int64_t nrb = (a.N + 15) / 16;
-    hipLaunchKernelGGL((gemm_canon_kernel<BITS, SC, TILED, MR, RB, NW>), dim3(static_cast<unsigned>((nrb + RB - 1) / RB)), dim3(NW * 64), 0, s,
+    hipLaunchKernelGGL((gemm_canon_kernel<BITS, SC, TILED, MR, RB, NW, CHAINS>), dim3(static_cast<unsigned>((nrb + RB - 1) / RB)), dim3(NW * 64), 0, s,
                        a.W, a.codebook, a.X, a.Y, a.N, a.K, a.M, a.scales);
 }
 
@@ -625,7 +650,8 @@ static void canon_launch(const GemmArgs& a, hipStream_t s) {
 //     10880, batch 1: 21.2 against 21.7; 2-bit 12480 x 6804, batch 16: 16.8 against 20.4); where the busiest CU's share is odd, and for rows of up to
 //     16 tiles, which eight waves do not share evenly, one block and four (but 2-bit 18112 x 5376, batch 11: 17.0 against 15.1; 4-bit 10496 x 2496, batch 9: 14.9 against 23.5; 4-bit
 //     scaled 8256 x 4480, batch 6, three blocks a CU instead of four: 12.5 against 18.4), or eight if that share is three and the batch at
-//     most 4 (3-bit 8635 x 5475, batch 1: 9.9, 10.1 with four, 12.3).
+//     most 4 (3-bit 8635 x 5475, batch 1: 9.9, 10.1 with four, 12.3).  Four waves have two chains each there, so that a sum is of eight as
+//     it is with eight waves (one chain each: 2 % less time on the average, but 5 to 18 % more rounding in the 32-bit sums).
 // Neither pipe binds: vector issue is 32 % and LDS 8 % of the busy time at 3-bit 5001 x 4101, batch 3, and 40 % and 28 % at 1-bit scaled 8192 x 8192,
 // batch 8 (two waves a SIMD); the waves wait for memory.  Two or four tiles in flight per wave instead of one were no faster anywhere all the
 // same (1 to 10 % slower at batch 1, 10 to 20 % above).  Not among the shapes measured: a wave count fitted to the tiles (17 tiles on eight waves
@@ -647,6 +673,7 @@ static void canon_shape(const GemmArgs& a, hipStream_t s) {
     } else {
         if (tiles > 16 && (share % 2 == 0 || (BITS == 2 && !SC && MR == 4))) canon_launch<BITS, SC, TILED, MR, 2, 8>(a, s);
         else if (tiles > 16 && MR == 1 && share == 3) canon_launch<BITS, SC, TILED, MR, 1, 8>(a, s);
+        else if (tiles > 16) canon_launch<BITS, SC, TILED, MR, 1, 4, 2>(a, s);
         else canon_launch<BITS, SC, TILED, MR, 1, 4>(a, s);
     }
 }
