@@ -638,6 +638,23 @@ static void canon_launch(const GemmArgs& a, hipStream_t s) {
                        a.W, a.codebook, a.X, a.Y, a.N, a.K, a.M, a.scales);
 }
 
+// Largest odd share of row blocks at which one a workgroup is no slower than two, by the mean of its shapes (time of one / of two at shares 3, 5,
+// 7 to 9, 11 to 15, above 31): any at batches up to 4 (per row, 2 bits .91 .94 .96 .99 1.02; block-scaled, 4 bits .96 .88 .97 .96 .99) and
+// where two blocks are short of registers (block-scaled, 4 bits, batch 5 to 8 .73 .78 .80 .79 .70; batch 9 to 16 .75 .78 .82 .80 .85).  Between: per row, 2
+// bits, batch 5 to 8 .97 1.00 1.05 1.07 1.24, 3 bits .91 .95 .97 1.05 1.06, 1 bit 1.03 1.03 1.07 1.11 1.13.
+// Rows of more than 40 tiles: 7 at most (47 of 700 shapes of 8192 to 16384 columns more than 3 % slower than with two blocks otherwise, 15 so).
+template <int BITS, bool SC, bool TILED, int MR>
+static int64_t most_one_block(int64_t K) {
+    const int64_t any = K > 10240 ? 7 : int64_t(1) << 40;
+    if (MR == 1 || (SC && (MR == 4 || BITS == 4))) return any;
+    int64_t most;
+    if (SC) most = BITS == 1 ? 31 : 5;
+    else if (MR == 2) most = BITS == 1 ? 0 : BITS == 3 ? 7 : 3;
+    else if (BITS == 1) most = K % 32 == 0 ? 31 : 0;      // (rows of whole words have no products)
+    else most = BITS == 2 ? (TILED ? 0 : 3) : BITS == 3 ? 9 : any;
+    return most < any ? most : any;
+}
+
 // Launch shape, measured (us) over both layouts and formats at batch 1..16 (420 drawn shapes, each with five shapes of launch):
 //   few row blocks (at most one a CU): eight waves, sixteen for long rows (2-bit 2773 x 14592 tiled, batch 1: 6.7 with sixteen, 7.5
 //     with eight, 8.0 with four), at batches up to 4 and at 4 bits already from 14 tiles on (17 at batches above 8; 3-bit 2419 x 6016, batch 3: 5.4 with
@@ -646,12 +663,15 @@ static void canon_launch(const GemmArgs& a, hipStream_t s) {
 //   one to two a CU: the same, and from batch 5 on two row blocks a workgroup, so that X is read half as often and no CU has
 //     twice the work of another (3-bit scaled 7424 x 8064, batch 11: 13.4 against 15.6; 7650 x 14336, batch 6: 15.4 against
 //     18.4; at batch 6 short rows keep one: 6976 x 3136 9.3 against 10.5);
-//   more: two row blocks and eight waves where that leaves the busiest CU no more row blocks than one a workgroup would (3-bit scaled 15616 x
-//     10880, batch 1: 21.2 against 21.7; 2-bit 12480 x 6804, batch 16: 16.8 against 20.4); where the busiest CU's share is odd, and for rows of up to
-//     16 tiles, which eight waves do not share evenly, one block and four (but 2-bit 18112 x 5376, batch 11: 17.0 against 15.1; 4-bit 10496 x 2496, batch 9: 14.9 against 23.5; 4-bit
-//     scaled 8256 x 4480, batch 6, three blocks a CU instead of four: 12.5 against 18.4), or eight if that share is three and the batch at
-//     most 4 (3-bit 8635 x 5475, batch 1: 9.9, 10.1 with four, 12.3).  Four waves have two chains each there, so that a sum is of eight as
-//     it is with eight waves (one chain each: 2 % less time on the average, but 5 to 18 % more rounding in the 32-bit sums).
+//   more, rows of up to 16 tiles, which eight waves do not share evenly: one block and four (4-bit 10496 x 2496, batch 9: 14.9 against 23.5);
+//   more, longer rows: two row blocks and eight waves (3-bit scaled 15616 x 10880, batch 1: 21.2 against 21.7), but one block a workgroup where the
+//     busiest CU's share of them is odd, so that two would give it one more (4-bit scaled 8256 x 4480, batch 6, three instead of four: 12.5 against
+//     18.4).  Against that one block reads X twice as often, which counts for more the larger the share and the batch and the fewer the bits:
+//     most_one_block().  One block has four waves with two chains each, so that a sum is of eight as it is with eight waves (one
+//     chain each: 2 % less time, 5 to 18 % more rounding in the 32-bit sums); at a share of three and batches up to 4 eight waves where they are
+//     faster (`eight`: 283 shapes, 7 % less time than with four; 125 of the other instances: 4 % more).
+//     1957 drawn shapes of odd shares from 3 to 73: 9 % less time than with two blocks everywhere (12 % at 3 and 5, 4 % from 11 on), 45 of
+//     them 3 to 10 % more; 1.7 % over the fastest of the three shapes of launch on the average.
 // Neither pipe binds: vector issue is 32 % and LDS 8 % of the busy time at 3-bit 5001 x 4101, batch 3, and 40 % and 28 % at 1-bit scaled 8192 x 8192,
 // batch 8 (two waves a SIMD); the waves wait for memory.  Two or four tiles in flight per wave instead of one were no faster anywhere all the
 // same (1 to 10 % slower at batch 1, 10 to 20 % above).  Not among the shapes measured: a wave count fitted to the tiles (17 tiles on eight waves
@@ -662,6 +682,7 @@ template <int BITS, bool SC, bool TILED, int MR>
 static void canon_shape(const GemmArgs& a, hipStream_t s) {
     const int64_t tiles = (a.K + kCanonTile - 1) / kCanonTile, nrb = (a.N + 15) / 16;
     const int64_t share = (nrb + 255) / 256;              // row blocks of the busiest CU
+    constexpr bool eight = TILED ? !SC && (BITS == 2 || BITS == 3) : !SC || BITS <= 2;
     if (nrb <= 256) {
         if (tiles >= 40 || (tiles >= 14 && MR == 1) || (BITS == 4 && tiles >= (MR == 4 ? 17 : 14))) canon_launch<BITS, SC, TILED, MR, 1, 16>(a, s);
         else if (tiles > 4) canon_launch<BITS, SC, TILED, MR, 1, 8>(a, s);
@@ -671,10 +692,10 @@ static void canon_shape(const GemmArgs& a, hipStream_t s) {
         else if (tiles > 4) canon_launch<BITS, SC, TILED, MR, 1, 8>(a, s);
         else canon_launch<BITS, SC, TILED, MR, 1, 4>(a, s);
     } else {
-        if (tiles > 16 && (share % 2 == 0 || (BITS == 2 && !SC && MR == 4))) canon_launch<BITS, SC, TILED, MR, 2, 8>(a, s);
-        else if (tiles > 16 && MR == 1 && share == 3) canon_launch<BITS, SC, TILED, MR, 1, 8>(a, s);
-        else if (tiles > 16) canon_launch<BITS, SC, TILED, MR, 1, 4, 2>(a, s);
-        else canon_launch<BITS, SC, TILED, MR, 1, 4>(a, s);
+        if (tiles <= 16) canon_launch<BITS, SC, TILED, MR, 1, 4>(a, s);
+        else if (share % 2 == 0 || share > most_one_block<BITS, SC, TILED, MR>(a.K)) canon_launch<BITS, SC, TILED, MR, 2, 8>(a, s);
+        else if (MR == 1 && share == 3 && eight) canon_launch<BITS, SC, TILED, MR, 1, 8>(a, s);
+        else canon_launch<BITS, SC, TILED, MR, 1, 4, 2>(a, s);
     }
 }
 
