@@ -89,7 +89,7 @@ __device__ __forceinline__ void canon_index_to_byte1(uint32_t& a, uint32_t src, 
         asm("v_and_b32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:DWORD" : "+v"(a) : "v"(src), "v"(mask));
 }
 
-// Waves a SIMD that the registers have to leave room for: what an instance keeps without spilling.  Left alone the compiler spends
+// Waves a SIMD that the registers have to leave room for: what an instance keeps without spilling (sixteen waves a workgroup: four in any case).  Left alone the compiler spends
 // up to a third more of them, and a SIMD loses a wave or two (1-bit 18624 x 2843, batch 1: 10.3 us against 7.4).
 template <int BITS, bool SC, bool TILED, int MR, int RB>
 constexpr int canon_waves() {
@@ -659,7 +659,8 @@ static int64_t most_one_block(int64_t K) {
 //   few row blocks (at most one a CU): eight waves, sixteen for long rows (2-bit 2773 x 14592 tiled, batch 1: 6.7 with sixteen, 7.5
 //     with eight, 8.0 with four), at batches up to 4 and at 4 bits already from 14 tiles on (17 at batches above 8; 3-bit 2419 x 6016, batch 3: 5.4 with
 //     eight, 4.8 with sixteen; 4-bit 4032 x 4224, batch 10: 9.6 and 8.6; but 1-bit 2368 x 7104, batch 15: 7.9 and 8.9); four for rows of at most
-//     four tiles;
+//     four tiles.  Sixteen waves leave 128 registers, which 1-bit and 4-bit block-scaled tiled instances of batch 9 to 16 do not fit in: eight with two
+//     chains each, the same sums (84 shapes: 1-bit 6 % less time, block-scaled 24 and 5 %; 1-bit block-scaled 3680 x 13824, batch 13: 16.0 -> 11.1);
 //   one to two a CU: the same, and from batch 5 on two row blocks a workgroup, so that X is read half as often and no CU has
 //     twice the work of another (3-bit scaled 7424 x 8064, batch 11: 13.4 against 15.6; 7650 x 14336, batch 6: 15.4 against
 //     18.4; at batch 6 short rows keep one: 6976 x 3136 9.3 against 10.5);
@@ -682,9 +683,13 @@ template <int BITS, bool SC, bool TILED, int MR>
 static void canon_shape(const GemmArgs& a, hipStream_t s) {
     const int64_t tiles = (a.K + kCanonTile - 1) / kCanonTile, nrb = (a.N + 15) / 16;
     const int64_t share = (nrb + 255) / 256;              // row blocks of the busiest CU
+    constexpr bool spills = TILED && MR == 4 && (BITS == 1 || (BITS == 4 && SC));      // with sixteen waves
     constexpr bool eight = TILED ? !SC && (BITS == 2 || BITS == 3) : !SC || BITS <= 2;
     if (nrb <= 256) {
-        if (tiles >= 40 || (tiles >= 14 && MR == 1) || (BITS == 4 && tiles >= (MR == 4 ? 17 : 14))) canon_launch<BITS, SC, TILED, MR, 1, 16>(a, s);
+        if (tiles >= 40 || (tiles >= 14 && MR == 1) || (BITS == 4 && tiles >= (MR == 4 ? 17 : 14))) {
+            if constexpr (spills) canon_launch<BITS, SC, TILED, MR, 1, 8, 2>(a, s);
+            else canon_launch<BITS, SC, TILED, MR, 1, 16>(a, s);
+        }
         else if (tiles > 4) canon_launch<BITS, SC, TILED, MR, 1, 8>(a, s);
         else canon_launch<BITS, SC, TILED, MR, 1, 4>(a, s);
     } else if (nrb <= 512) {

@@ -65,3 +65,18 @@ def test_block_scaled_rows_do_not_depend_on_how_many_there_are(gpu, bits, N, K, 
     gpu.check_blockscaled_against_oracle(tall, p, cb, sc, X, K, bits, row_ranges=[(0, 32), (N - 32, N)], label=f"b{bits} {N}x{K} M{M}", strict=False)
     alone = gpu.run_gemm_blockscaled(gpu.dev(p[:few]), gpu.dev(cb), gpu.dev(sc[:few]), X, few, K, bits)
     assert np.array_equal(tall[:, :few], alone)
+
+
+@pytest.mark.parametrize("bits,N,K,M", [(1, 300, 10752, 9), (1, 33, 13824, 16), (1, 4090, 15872, 12), (4, 300, 4736, 16), (4, 47, 5504, 9), (4, 33, 16256, 13)])
+def test_block_scaled_tiles_of_two_chains(gpu, bits, N, K, M):
+    """Few row blocks, instances that eight waves of two chains serve: numbers of tiles below, at and above the sixteen chains' turns."""
+    import torch
+    seed = 17 * bits + N + K + M
+    idx, cb = synth.make_indices(seed, 0, N, K, bits), synth.make_shared_codebook(seed, 0, bits)
+    sc, X = synth.make_scales(seed, 0, N, K), synth.make_x(seed, 0, M, K)
+    p = oracle.pack(idx, bits)
+    assert kmq.kernel_name_blockscaled(N, K, bits, M, kmq.LAYOUT_TILED) == f"mfma_any_sc_b{bits}"
+    Y = torch.full((M, N), 0x7FC1, dtype=torch.int16, device="cuda")
+    kmq.gemm_smallbatch_blockscaled(gpu.dev(kmq.repack(p, K, bits, kmq.LAYOUT_TILED)), gpu.dev(cb), gpu.dev(sc), gpu.dev(X), Y, N, K, M, bits, kmq.LAYOUT_TILED)
+    torch.cuda.synchronize()
+    gpu.check_blockscaled_against_oracle(gpu.host_u16(Y), p, cb, sc, X, K, bits, row_ranges=gpu.sample_ranges(N, seed, nblocks=3), label=f"b{bits} {N}x{K} M{M}")
