@@ -41,22 +41,23 @@ static bool per_column_faster(int M) {
 // With more rows it is always faster from batch 2 (K in rounds; 2-bit 4096 x 11008, batch 16: 45.3 -> 12.3), at every batch
 // (block-scaled without a table kernel) and from batch 3 on (with one; 4-bit 8192 x 8192, batch 3: 15.2 -> 13.4; but 3-bit 8192 x 8192, batch
 // 3: 11.5 -> 14.1, the worst of those).
-// The lines of this kernel against the rounds were drawn again (per column and for a last tile 0.85 and 0.4 of what they were; 1 bit: half a microsecond less to start with) when its words came by
-// whole lines and a last piece as one load: 200 drawn shapes of 256 to
-// 4096 rows whose route that changes take 27 % less time on the average (2-bit 873 x 2496, batch 15: 7.2 -> 4.9; 4-bit 960 x 4544, batch 6: 10.6 -> 5.9), four of them
-// 3 to 5 % more and one 13 % (4-bit 960 x 16256, batch 3: 9.1 -> 10.3).  Lower ones still lose more than they gain (0.8
-// and 0.25: 30 of 200 slower).  The block-scaled lines stay: on the table kernels' side of them a column
-// is its batch-1 result bit for bit.
+// The lines were drawn against table kernels of two columns a workgroup and a last tile fetched element by element; both are faster now, and
+// were timed again.  Block-scaled, 675 shapes (256..8192 rows, 2048..14336 columns, batch 2..16): the slower side by more than 10 % in 18, 0.9 %
+// over the faster one on average.  K in rounds, 840 (64..4096 rows, 1056..13856 columns): 32, 1.5 %.
+// By time alone the lines against the rounds would be lower since the words come by whole lines and a last piece as one load (costs of 0.85 per column, 0.4 for a
+// last tile: 500 drawn shapes of 64 to 4096 rows whose route that changes, 24 % less time, 7 of them 4 to 16 % more).  They are not, for two reasons: up to them a
+// column is its batch-1 result bit for bit, and the 32-bit sums of the rounds are rounded less (rows that cancel, 1500 such shapes, root mean square of this
+// kernel over theirs: 2 and 3 bits 1.03, from 40 tiles on 1.01, 4 bits 1.07).
 // Table kernels specialised on K keep per-row batches: their columns are the batch-1 results bit for bit.
 constexpr int64_t kAnyOneRound = 256 * 16;
 struct AnyCost { double start, per_k[3]; };               // us; us per 1000 columns at batches up to 4, 8, 16
 static double any_length_us(int64_t K, int bits, int M, bool scaled) {
-    static const AnyCost cost[2][4] = {{{2.5, {0.30, 0.45, 0.72}}, {2.8, {0.22, 0.38, 0.64}}, {2.8, {0.38, 0.49, 0.72}}, {3.6, {0.45, 0.58, 0.81}}},
+    static const AnyCost cost[2][4] = {{{3.0, {0.30, 0.45, 0.72}}, {2.8, {0.26, 0.45, 0.75}}, {2.8, {0.45, 0.58, 0.85}}, {3.6, {0.53, 0.68, 0.95}}},
                                        {{2.7, {0.38, 0.45, 0.62}}, {2.9, {0.45, 0.53, 0.68}}, {2.6, {0.65, 0.73, 0.90}}, {4.1, {0.70, 0.77, 0.90}}}};
-    static const double tail[2][3] = {{0.32, 0.52, 1.0}, {0.8, 1.3, 2.5}};        // a last tile that K does not fill (the second: 1 bit and block-scaled)
+    static const double tail[3] = {0.8, 1.3, 2.5};        // a last tile that K does not fill
     const int g = M <= 4 ? 0 : M <= 8 ? 1 : 2;
     const AnyCost& c = cost[scaled ? 1 : 0][bits - 1];
-    return c.start + c.per_k[g] * 1e-3 * static_cast<double>(K) + (K % 256 ? tail[scaled || bits == 1 ? 1 : 0][g] : 0.0);
+    return c.start + c.per_k[g] * 1e-3 * static_cast<double>(K) + (K % 256 ? tail[g] : 0.0);
 }
 static double from_floor(double floor, double start, double each, double work) {
     const double t = start + each * work;
@@ -65,10 +66,10 @@ static double from_floor(double floor, double start, double each, double work) {
 static double millions(int64_t N, int64_t K, int M) { return 1e-6 * static_cast<double>(N) * static_cast<double>(K) * M; }
 // against the table kernel that walks K in rounds
 static bool any_beats_rounds(int64_t N, int64_t K, int bits, int M) {
-    static const double each[4] = {0.10, 0.105, 0.12, 0.19}, floor[4] = {3.5, 3.7, 4.1, 4.0};
+    static const double each[4] = {0.10, 0.105, 0.12, 0.19};
     const int64_t k = K > 2048 ? K : 2048;                // (shorter rows cost it as much; large matrices get a better launch shape)
     const double work = millions(N, k, M) * (N * K > (int64_t(24) << 20) ? 0.75 : 1.0);
-    return M >= 2 && (N > kAnyOneRound || any_length_us(K, bits, M, false) < from_floor(floor[bits - 1], 2.5, each[bits - 1], work));
+    return M >= 2 && (N > kAnyOneRound || any_length_us(K, bits, M, false) < from_floor(bits == 3 ? 4.3 : 4.0, 2.5, each[bits - 1], work));
 }
 // against the specialised table kernels, block-scaled
 static bool any_beats_scaled_table(int64_t N, int64_t K, int bits, int M) {
