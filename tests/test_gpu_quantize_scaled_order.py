@@ -1,6 +1,6 @@
 """The tensor quantiser's order of quotients: boundaries among the smallest quotients that it holds (whose octave has only half of
-the pairs), every scale mantissa with every weight mantissa, and tensors large enough for wide counters, which have to give
-what the same data gives on narrow ones."""
+the pairs), every scale mantissa with every weight mantissa, tensors large enough for wide counters, which have to give
+what the same data gives on narrow ones, the step that sorts blocks at its edges, and a boundary that leaves the far elements."""
 import numpy as np
 import pytest
 
@@ -78,33 +78,36 @@ def test_wide_counters_give_what_narrow_ones_give(gpu, bits):
 
 @pytest.mark.parametrize("blocks", [128 * 1024, 128 * 1024 + 1, 256 * 1024, 256 * 1024 + 1, 512 * 1024 + 1])
 def test_grouping_step_at_its_edges(gpu, blocks):
-    """One, two, four and eight blocks a thread of the step that sorts blocks by scale mantissa, the last workgroup full or with one block:
-    copies of one block row have that row's codebook and indices, however many there are."""
+    """One, two, four and eight blocks a thread of the step that sorts blocks by scale mantissa, the last workgroup full or with one block.
+    Quotients are 1 and -1 except in one block of each workgroup (its first, its last or one between), whose 63 quotients of 15/32 or 1/32 with either
+    sign are all that the two middle clusters have: a block that is lost, or counted twice, moves their means by two bf16 steps or more."""
     import torch
-    row = torch.from_numpy(synth.make_dense_weights(180, 2, 1, 64 * 1024).view(np.int16)).cuda().reshape(1024, 64)
-    copies, rest = divmod(blocks, 1024)
-    W = torch.cat([row.repeat(copies, 1), row[:rest]]) if rest else row.repeat(copies, 1)
-    outs = []
-    for w, check_rows in ((row, 1024), (W, blocks)):
-        N, K, bits = w.shape[0], 64, 2
-        packed = torch.zeros((N, 4), dtype=torch.int32, device="cuda")
-        cb, sc = torch.zeros(4, dtype=torch.int16, device="cuda"), torch.zeros((N, 1), dtype=torch.int16, device="cuda")
-        ws = torch.empty(kmq.quantize_blockscaled_workspace_bytes(), dtype=torch.uint8, device="cuda")
-        kmq.quantize_blockscaled(w.contiguous(), N, K, bits, 6, packed, cb, sc, ws)
-        outs.append((packed, cb, sc))
+    bits, rng = 2, np.random.default_rng(blocks)
+    each = 1024 * (1 if blocks <= 128 * 1024 else 2 if blocks <= 256 * 1024 else 4 if blocks <= 512 * 1024 else 8)
+    scale = (128 + rng.integers(0, 128, blocks)) / 128.0
+    quot = np.where(rng.integers(0, 2, (blocks, 64), dtype=np.int8) == 1, np.float32(1), np.float32(-1))
+    groups = range((blocks + each - 1) // each)
+    for g in groups:
+        first, last = g * each, min((g + 1) * each, blocks) - 1
+        at = (first, last, (first + last) // 2)[g % 3]
+        quot[at, 1:] = (-1.0 if g & 1 else 1.0) * (15 / 32 if g & 2 else 1 / 32)
+        scale[at] = 1.0
+    count = {(neg, big): sum((g & 1 == neg) and (g & 2 == 2 * big) for g in groups) for neg in (0, 1) for big in (0, 1)}
+    mean = [(count[n, 0] / 32 + count[n, 1] * 15 / 32) / (count[n, 0] + count[n, 1]) for n in (0, 1)]
+    idx = (quot > -0.625).astype(np.uint8) + (quot > 0) + (quot > 0.625)
+    want = synth.f32_to_bf16(np.array([-1, -mean[1], mean[0], 1], np.float32))
+    W = gpu.dev(synth.f32_to_bf16(quot * scale[:, None].astype(np.float32)))
+    packed = torch.ones((blocks, 4), dtype=torch.int32, device="cuda")      # (the step's list lies there: an entry that is not written is block 1)
+    cb, sc = torch.zeros(4, dtype=torch.int16, device="cuda"), torch.zeros((blocks, 1), dtype=torch.int16, device="cuda")
+    ws = torch.empty(kmq.quantize_blockscaled_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    kmq.quantize_blockscaled(W, blocks, 64, bits, 6, packed, cb, sc, ws)
     torch.cuda.synchronize()
-    (p, c, s), (pm, cm, sm) = outs
-    at = torch.arange(blocks, device="cuda") % 1024
-    assert torch.equal(sm, s[at])
-    if rest == 0:                                          # (one block more moves the means)
-        assert torch.equal(c, cm) and torch.equal(pm, p[at])
-    else:                                                  # ... by less than a bf16 step, mostly: indices differ where a stored centroid does
-        d = (c.int() - cm.int()).abs().max().item()
-        assert d <= 1 and (d > 0 or torch.equal(pm, p[at]))
+    assert np.array_equal(gpu.host_u16(sc)[:, 0], synth.f32_to_bf16(scale.astype(np.float32)))
+    assert np.array_equal(gpu.host_u16(cb), want)
+    assert np.array_equal(packed.cpu().numpy().view(np.uint32), oracle.pack(idx, bits))
 
 
-@pytest.mark.parametrize("iters", [3, 5, 6])
-def test_a_boundary_that_goes_from_far_elements_to_zero(gpu, iters):
+def far_then_zero():
     """2 bits, quotients whose sums are exact in any order.  The middle boundary is 0, then 2^-32, with 32 far elements of 2^-33 below it,
     then 0 again, and the outer boundaries have moved past their last member by then: as many window members lie below every
     boundary as in the round before, but the far elements have changed sides, so it is no fixed point."""
@@ -119,4 +122,27 @@ def test_a_boundary_that_goes_from_far_elements_to_zero(gpu, iters):
     assert (np.abs(f).max(axis=1) == 1.0).all()
     W = synth.f32_to_bf16(f.astype(np.float32)).reshape(4, 4096)
     assert not np.array_equal(oracle.quantize_blockscaled(W, 2, 2)[1], oracle.quantize_blockscaled(W, 2, 3)[1])
-    check(gpu, W, 2, iters)
+    return W
+
+
+@pytest.mark.parametrize("iters", [3, 5, 6])
+def test_a_boundary_that_goes_from_far_elements_to_zero(gpu, iters):
+    check(gpu, far_then_zero(), 2, iters)
+
+
+@pytest.mark.parametrize("iters", [2, 3, 6])
+def test_wide_counters_with_far_elements(gpu, iters):
+    """2^28 elements, copies of the tensor above: searches among far elements in two of the rounds, and every sum exactly as many times as large."""
+    import torch
+    W, copies = far_then_zero(), 1 << 14
+    idx, want, scales, _, _ = oracle.quantize_blockscaled(W, 2, iters)
+    w = gpu.dev(W).repeat(copies, 1)
+    N, K = w.shape
+    packed = torch.zeros((N, kmq.words_per_row(2, K)), dtype=torch.int32, device="cuda")
+    cb, sc = torch.zeros(4, dtype=torch.int16, device="cuda"), torch.zeros((N, K // 64), dtype=torch.int16, device="cuda")
+    ws = torch.empty(kmq.quantize_blockscaled_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    kmq.quantize_blockscaled(w, N, K, 2, iters, packed, cb, sc, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(gpu.host_u16(cb), want)
+    assert torch.equal(sc, gpu.dev(scales).reshape(W.shape[0], -1).repeat(copies, 1))
+    assert torch.equal(packed, gpu.dev(oracle.pack(idx, 2)).reshape(W.shape[0], -1).repeat(copies, 1))
