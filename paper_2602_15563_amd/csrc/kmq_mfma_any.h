@@ -43,9 +43,9 @@ typedef u32x2_t __attribute__((aligned(2))) cu32x2_a2_t;
 typedef __attribute__((address_space(3))) const uint32_t clds_cu32_t;
 
 // Words w[0..WPL-1] of a lane, 4-byte aligned.  Not non-temporal, and neither are scales: one instruction takes 32 to 64 bytes from each of
-// 16 rows, and other instructions and waves take the rest of those 128-byte lines a little later (us, non-temporal / as here: 3-bit
-// 5001 x 4101, batch 3 7.75 / 6.71; 1-bit scaled 8192 x 8192, batch 8 9.8 / 8.5; 90 drawn canonical and tiled products 9 % less on the
-// average, none more than 1 % slower).  Tiled granules come in whole lines and stay non-temporal.
+// 16 rows, and other instructions and waves take the rest of those 128-byte lines a little later; with the hint they were asked for from the L2 again (requests of
+// the first-level caches, non-temporal / as here: 3-bit 5001 x 4101, batch 3 328000 / 120000; 1-bit scaled 8192 x 8192, batch 8 786000 / 352000; misses of the L2 the
+// same).  us, 16 and 8 matrices in turn: 8.1 / 7.2 and 10.0 / 8.4; 90 drawn canonical and tiled products 9 % less on the average, none more than 1 % slower.  Tiled granules come in whole lines and stay non-temporal.
 template <int WPL>
 __device__ __forceinline__ void canon_words(const uint32_t* p, uint32_t (&w)[WPL]) {
     typedef u32x4_t __attribute__((aligned(4))) u32x4_a4_t;
@@ -655,12 +655,13 @@ static int64_t most_one_block(int64_t K) {
     return most < any ? most : any;
 }
 
-// Launch shape, measured (us) over both layouts and formats at batch 1..16 (420 drawn shapes, each with five shapes of launch):
+// Launch shape, measured (us) over both layouts and formats at batch 1..16, drawn shapes, each with every shape of launch that is named:
 //   few row blocks (at most one a CU): eight waves, sixteen for long rows (2-bit 2773 x 14592 tiled, batch 1: 6.7 with sixteen, 7.5
 //     with eight, 8.0 with four), at batches up to 4 and at 4 bits already from 14 tiles on (17 at batches above 8; 3-bit 2419 x 6016, batch 3: 5.4 with
 //     eight, 4.8 with sixteen; 4-bit 4032 x 4224, batch 10: 9.6 and 8.6; but 1-bit 2368 x 7104, batch 15: 7.9 and 8.9); four for rows of at most
-//     four tiles.  Sixteen waves leave 128 registers, which 1-bit and 4-bit block-scaled tiled instances of batch 9 to 16 do not fit in: eight with two
-//     chains each, the same sums (84 shapes: 1-bit 6 % less time, block-scaled 24 and 5 %; 1-bit block-scaled 3680 x 13824, batch 13: 16.0 -> 11.1);
+//     four tiles.  500 shapes of 1300 columns and more: 1.5 % over the fastest on the average; the 106 that sixteen waves take from 14 tiles on 6 % less
+//     time, four of them 2 to 5 % more.  Sixteen waves leave 128 registers, which 1-bit and 4-bit block-scaled tiled instances of batch 9 to 16 do not fit in: eight with two
+//     chains each, the same sums (84 shapes: 1-bit per row 6 % less time, block-scaled 24 and 5 %; 1-bit block-scaled 3680 x 13824, batch 13: 16.0 -> 11.1);
 //   one to two a CU: the same, and from batch 5 on two row blocks a workgroup, so that X is read half as often and no CU has
 //     twice the work of another (3-bit scaled 7424 x 8064, batch 11: 13.4 against 15.6; 7650 x 14336, batch 6: 15.4 against
 //     18.4; at batch 6 short rows keep one: 6976 x 3136 9.3 against 10.5);
@@ -673,9 +674,9 @@ static int64_t most_one_block(int64_t K) {
 //     faster (`eight`: 283 shapes, 7 % less time than with four; 125 of the other instances: 4 % more).
 //     1957 drawn shapes of odd shares from 3 to 73: 9 % less time than with two blocks everywhere (12 % at 3 and 5, 4 % from 11 on), 45 of
 //     them 3 to 10 % more; 1.7 % over the fastest of the three shapes of launch on the average.
-// Neither pipe binds: vector issue is 32 % and LDS 8 % of the busy time at 3-bit 5001 x 4101, batch 3, and 40 % and 28 % at 1-bit scaled 8192 x 8192,
+// Neither pipe binds: vector issue is 37 % and LDS 9 % of the busy time at 3-bit 5001 x 4101, batch 3, and 47 % and 33 % at 1-bit scaled 8192 x 8192,
 // batch 8 (two waves a SIMD); the waves wait for memory.  Two or four tiles in flight per wave instead of one were no faster anywhere all the
-// same (1 to 10 % slower at batch 1, 10 to 20 % above).  Not among the shapes measured: a wave count fitted to the tiles (17 tiles on eight waves
+// same (1 to 10 % slower at batch 1, 10 to 20 % above; with the loads past the end clamped instead of branched around 10 to 40 %).  Not among the shapes measured: a wave count fitted to the tiles (17 tiles on eight waves
 // are three for one and two for the others).  Sixteen waves for two row blocks: 18 % slower on the average.  The last piece taken first, its operands asked for
 // at the start, or with the last whole tile's: 3 to 4 % slower at 3-bit 5001 x 4101, batch 3 (words one by one, ahead of everybody else's first tile).  Words through LDS,
 // so that four neighbouring lanes load 64 bytes of a row: 3 to 12 % slower.
@@ -684,6 +685,7 @@ static void canon_shape(const GemmArgs& a, hipStream_t s) {
     const int64_t tiles = (a.K + kCanonTile - 1) / kCanonTile, nrb = (a.N + 15) / 16;
     const int64_t share = (nrb + 255) / 256;              // row blocks of the busiest CU
     constexpr bool spills = TILED && MR == 4 && (BITS == 1 || (BITS == 4 && SC));      // with sixteen waves
+    constexpr bool one = SC || !((MR == 2 && BITS == 1) || (MR == 4 && BITS == 2 && TILED));      // where most_one_block() is not 0 throughout
     constexpr bool eight = TILED ? !SC && (BITS == 2 || BITS == 3) : !SC || BITS <= 2;
     if (nrb <= 256) {
         if (tiles >= 40 || (tiles >= 14 && MR == 1) || (BITS == 4 && tiles >= (MR == 4 ? 17 : 14))) {
@@ -700,7 +702,7 @@ static void canon_shape(const GemmArgs& a, hipStream_t s) {
         if (tiles <= 16) canon_launch<BITS, SC, TILED, MR, 1, 4>(a, s);
         else if (share % 2 == 0 || share > most_one_block<BITS, SC, TILED, MR>(a.K)) canon_launch<BITS, SC, TILED, MR, 2, 8>(a, s);
         else if (MR == 1 && share == 3 && eight) canon_launch<BITS, SC, TILED, MR, 1, 8>(a, s);
-        else canon_launch<BITS, SC, TILED, MR, 1, 4, 2>(a, s);
+        else if constexpr (one) canon_launch<BITS, SC, TILED, MR, 1, 4, 2>(a, s);
     }
 }
 
