@@ -39,11 +39,11 @@ static bool per_column_faster(int M) {
 //     13.2 / 6.8
 //   block-scaled with a table kernel, batch 8: 4-bit 8192 columns: 256 rows 4.7 / 9.7, 1024 8.0 / 9.9, 4096 20.0 / 10.5
 // With more rows it is always faster from batch 2 (K in rounds; 2-bit 4096 x 11008, batch 16: 45.3 -> 12.3), at every batch
-// (block-scaled without a table kernel) and from batch 3 on (with one; 4-bit 8192 x 8192, batch 3: 15.2 -> 13.4; but 3-bit 8192 x 8192, batch
-// 3: 11.5 -> 14.1, the worst of those).
-// The lines were drawn against table kernels of two columns a workgroup and a last tile fetched element by element; both are faster now, and
-// were timed again.  Block-scaled, 675 shapes (256..8192 rows, 2048..14336 columns, batch 2..16): the slower side by more than 10 % in 18, 0.9 %
-// over the faster one on average.  K in rounds, 840 (64..4096 rows, 1056..13856 columns): 32, 1.5 %.
+// (block-scaled without a table kernel) and from batch 3 on (with one; 143 drawn shapes of 4097 to 8192 rows, 2048 to 14336 columns: 6 % less time at
+// the least; 2-bit 4928 x 8192, batch 3: 9.9 -> 8.1).
+// The lines were drawn against table kernels of two columns a workgroup, and with this kernel's last tile fetched element by element and its lines of words asked for
+// more than once.  Block-scaled with a table kernel, 700 shapes (256..8192 rows, batch 2..16): the slower side by more than 10 % in 43, 1.7 % over the faster one on
+// average; all but one of the 43 are table kernels (2-bit 896 x 14336, batch 14: 15.9 taken, 9.5 the other), where a column is its batch-1 result bit for bit.
 // By time alone the lines against the rounds would be lower since the words come by whole lines and a last piece as one load (costs of 0.85 per column, 0.4 for a
 // last tile: 500 drawn shapes of 64 to 4096 rows whose route that changes, 24 % less time, 7 of them 4 to 16 % more).  They are not, for two reasons: up to them a
 // column is its batch-1 result bit for bit, and the 32-bit sums of the rounds are rounded less (rows that cancel, 1500 such shapes, root mean square of this

@@ -1062,8 +1062,8 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __re
 //
 // 8192 x 8192, 25 rounds, 1 / 2 / 3 / 4 bits, a new tensor each time: 136 / 146 / 154 / 168 us (142 / 154 / 171 / 206 with a look-up per boundary and scale
 // mantissa in every round; 8519 / 9344 / 10727 / 13475 with every element divided by its scale and compared with every boundary in fp64, each round);
-// 1024 x 1024, 4 bits: 81 (120; 3570).  At 8192 x 8192 and 4 bits: clear 5, scales 21 (6.5 TB/s), group 13, count 32 (blocks gathered 128 bytes at a time,
-// LDS atomics, 14 for the adding up), sort 9, rounds 44 (1.5 us each, a chain of latencies of one wave a SIMD; 78 before), assign 45 us (vector issue).
+// 1024 x 1024, 4 bits: 81 (120; 3570).  At 8192 x 8192 and 4 bits: clear 3, scales 22 (6.1 TB/s), group 13, count 30 (blocks gathered 128 bytes at a time,
+// LDS atomics, 14 for the adding up), sort 10, rounds 44 (1.5 us each, a chain of latencies of one wave a SIMD; 78 before), assign 45 us (vector issue).
 constexpr int kQuantMants = 128;
 constexpr double kFar = 4.656612873077393e-10;           // 2^-31: no far element reaches it
 
@@ -1073,6 +1073,7 @@ constexpr double kFar = 4.656612873077393e-10;           // 2^-31: no far elemen
 // octave * 16384 + rank; pairs that the window does not hold (a >= s in octave 0, a < s in the last one) are counters that
 // stay zero.  One order per sign, from small magnitudes to large ones.
 constexpr int kOctaves = kHistOctaves + 1, kPairs = kQuantMants * 128, kPlaces = kOctaves * kPairs, kRun = 16, kParts = 4096;
+constexpr int kLook = 2;                                 // runs that a boundary's row looks at together
 constexpr int kSortThreads = 256, kStretch = kSortThreads * kRun, kStretches = kPlaces / kStretch;      // places of a workgroup of the sorting step
 // Sums are integers in units of 2^-56 of the octave's lowest quotient: 57 bits of quotient, at most 2^38 members.
 struct Below {                                           // members of a stretch below a run of kRun places (or of a whole stretch): number and sum
@@ -1351,8 +1352,8 @@ __global__ __launch_bounds__(kCountThreads) void bs_count_kernel(const uint16_t*
     }
 }
 
-// Counters -> the order of the quotients, and what lies below every run of a stretch: a run a thread.  Bound by vector issue (a quotient and
-// its products per place); counters are picked one by one from the caches.  8192 x 8192: 13.5 us with a workgroup per octave and sign, the
+// Counters -> the order of the quotients, and what lies below every run of a stretch: a run a thread.  Bound by latency: counters are picked
+// one by one from the caches, by one workgroup a CU (vector issue 16 %, LDS 6 % of the busy time).  8192 x 8192: 13.5 us with a workgroup per octave and sign, the
 // octave's counters in LDS, 9.5 as here.
 template <bool NARROW>
 __global__ __launch_bounds__(kSortThreads) void bs_sort_kernel(QuantScratch* q) {
@@ -1484,9 +1485,8 @@ __device__ __forceinline__ double uniform(double v) {
 // and the leader then waits for the claimed ones to be done.  Whoever is waited for is running: nothing depends on how many
 // workgroups are resident or in which order they start, and the helpers end when the leader says so.  A piece's sums are
 // added in a fixed order, and the pieces' sums in theirs.
-// 8192 x 8192, 4 bits, 25 rounds: 228 us without far elements, 314 with 0.01 % of them (one search), 2.7 ms where all but the
-// scales are far (a search every round, 0.1 ms each); 133 and 423 ms with the rounds' workgroup searching alone.
-constexpr int kLook = 2;                                 // runs that a boundary's row looks at together
+// 8192 x 8192, 4 bits, 8 / 25 rounds: 153 / 172 us without far elements, 227 / 254 with 0.01 % of them (one search), 2.7 / 8.0 ms where all but the
+// scales are far (a search every round, 0.3 ms each; before the grid helped the rounds' workgroup, 25 rounds took 133 ms with 0.01 %).
 template <int C>
 struct FarShared {
     double bounds[C];
